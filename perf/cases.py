@@ -1,0 +1,311 @@
+"""What the performance of this repository is measured on: batches of one pipeline stage through its public entry points.
+
+A case is a plain dict.  `kind` says what one pass is:
+
+  stage      one batch: zero_grad, a forward and a backward for every microbatch (message-driven on `streams` library
+             streams, or direct calls on one stream if `streams` is 0), all weight gradients formed
+  model      the same with the pipeline's two ends attached: token ids in, embedding, layers, final LayerNorm, LM head,
+             loss, and everything back to the embedding table's gradient
+  step       a batch, then the offloaded Adam step under a dynamic loss scale (a whole training step of the stage)
+  optimizer  the offloaded, bucketed Adam step alone
+
+Weights are N(0, 0.02) with LayerNorm gains around 1 and small biases, activations and upstream gradients N(0, 1), the
+optimizer state that of a run in progress: what a stage in the middle of training holds and receives.
+"""
+import ctypes
+import math
+
+import numpy as np
+import torch
+
+from paper_2110_13005_amd import binding as B
+from paper_2110_13005_amd.inputs import StageShape
+from paper_2110_13005_amd.stage import Stage
+
+VOCAB = 51200            # of the head and the token table (bench.py's)
+HYPER = dict(lr=1e-6, beta1=0.9, beta2=0.95, eps=1e-8, weight_decay=0.01, step=100)
+
+
+def _case(name, kind="stage", layers=1, hidden=0, heads=1, ffn=0, seq=0, microbatch=1, batch=1, limit=0, streams=2,
+          accum="bf16", group=0, split=0, stride=0, elem="bf16", params=0, bucket=0):
+    c = dict(kind=kind, elem=elem)
+    if kind == "optimizer":
+        c.update(params=params, bucket=bucket)
+    else:
+        c.update(layers=layers, hidden=hidden, heads=heads, ffn=ffn or 4 * hidden, seq=seq, microbatch=microbatch,
+                 batch=batch, limit=limit or batch, streams=streams, accum=accum, group=group, split=split, stride=stride)
+        if kind == "model":
+            c.update(vocab=VOCAB)
+        if kind == "step":
+            c.update(bucket=bucket)
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # the smallest workload the repository names: a debugging / unit-test sized stage, launches and latency
+        _case("tiny", layers=2, hidden=256, heads=4, seq=128, microbatch=2, batch=4, accum="fp32"),
+        # a small odd-sized stage driven by direct calls on the caller's stream (ragged tokens, ffn not 4h)
+        _case("ragged_direct", layers=3, hidden=384, heads=3, ffn=1000, seq=200, microbatch=2, batch=3, streams=0, accum="fp32"),
+        # a stage of a model of a few hundred million parameters, head dim 64, one sequence per microbatch
+        _case("small_d64", layers=4, hidden=1024, heads=16, seq=1024, batch=8, accum="fp32"),
+        # a stage of a model of one to two billion parameters, head dim 128
+        _case("mid_d128", layers=2, hidden=2048, heads=16, seq=2048, batch=8, group=3),
+        # long sequences: half of the work is attention
+        _case("long_seq", layers=1, hidden=2048, heads=16, seq=8192, batch=2),
+        # activation checkpointing, as memory-bound users of larger stages run it
+        _case("mid_checkpointed", layers=4, hidden=3072, heads=24, seq=2048, batch=4, stride=2),
+        # two layers of the paper's own 12B model: head dim 188, sequence 512, microbatch 8, hidden no multiple of 64
+        _case("table1_12b", layers=2, hidden=4512, heads=24, seq=512, microbatch=8, batch=6, group=3),
+        # the benchmark's default workload
+        _case("stage_12b", layers=4, hidden=5120, heads=40, seq=2048, batch=8, group=3),
+        # the widest shape of the benchmark, with the split projection input its gradients need
+        _case("stage_100b", layers=2, hidden=10240, heads=80, seq=2048, batch=4, group=3, split=2),
+        # a small whole model on one GPU: embedding and LM head around two layers, vocabulary 51200
+        _case("model_small", kind="model", layers=2, hidden=1024, heads=16, seq=512, microbatch=4, batch=4),
+        # a whole training step in half precision under a loss scale
+        _case("step_fp16", kind="step", layers=2, hidden=1024, heads=16, seq=512, microbatch=2, batch=4, elem="fp16",
+              bucket=1 << 23),
+        # the offloaded optimizer step: 64 M parameters in buckets of 16 M
+        _case("optimizer", kind="optimizer", params=1 << 26, bucket=1 << 24),
+    ]
+
+
+def _log_uniform(rng, lo, hi):
+    return math.exp(rng.uniform(math.log(lo), math.log(hi)))
+
+
+def draw(rng):
+    kind = rng.choice(["stage"] * 7 + ["model", "step", "optimizer"])
+    if kind == "optimizer":
+        n = int(_log_uniform(rng, 1 << 20, 1 << 26))
+        return _case(None, kind=kind, params=n, bucket=1 << rng.randint(18, 24), elem=rng.choice(["bf16", "bf16", "fp16"]))
+    hi = 6144 if kind == "stage" else 1536
+    while True:
+        d = rng.choice([64, 64, 128, 128, 128, 4 * rng.randint(8, 48)])
+        heads = max(1, round(_log_uniform(rng, 256, hi) / d))
+        hidden = heads * d
+        if hidden % 8 or not 256 <= hidden <= hi:
+            continue
+        tokens = _log_uniform(rng, 128, 4096)
+        microbatch = rng.choice([1, 1, 2, 4])
+        seq = max(16, round(tokens / microbatch / 8) * 8 if rng.random() < 0.5 else 64 * round(tokens / microbatch / 64))
+        layers, batch = rng.randint(1, 4), rng.randint(1, 8)
+        ffn = 4 * hidden if rng.random() < 0.8 else 8 * rng.randint(hidden // 4, hidden // 2)
+        stride = rng.choice([0, 0, 0, 0, 1, layers]) if kind == "stage" else 0
+        c = _case(None, kind=kind, layers=layers, hidden=hidden, heads=heads, ffn=ffn, seq=seq, microbatch=microbatch,
+                  batch=batch, limit=rng.randint(1, batch), streams=rng.choice([2, 2, 2, 3, 1] if kind != "stage" else [2, 2, 2, 3, 1, 0]),
+                  accum=rng.choice(["bf16", "fp32"]), group=rng.choice([0, 1, 3]), stride=stride,
+                  split=rng.choice([0, 0, 0, 0, 1, 2]), elem=rng.choice(["bf16", "bf16", "bf16", "fp16"]), bucket=1 << 22)
+        if _flops(c) <= 4e13:
+            return c
+
+
+# ------------------------------------------------------------------------------------------------------------- work
+def _n_params(c):
+    h, f = c["hidden"], c["ffn"]
+    return c["layers"] * (4 * h * h + 2 * h * f + 9 * h + f)
+
+
+def _flops(c):
+    h, f, s, b = c["hidden"], c["ffn"], c["seq"], c["microbatch"]
+    layer = 2 * b * s * (4 * h * h + 2 * h * f) + 2 * b * s * s * h            # causal pairs only
+    fl = 3 * c["layers"] * c["batch"] * layer
+    if c.get("stride"):                                                        # backward regenerates the activations
+        per_mb = c["layers"] * layer - (c["layers"] // c["stride"]) * 2 * b * s * h * f
+        fl += c["batch"] * per_mb
+    if c["kind"] == "model":
+        fl += 3 * c["batch"] * 2 * b * s * h * c["vocab"]
+    return fl
+
+
+def work(case):
+    c = case
+    if c["kind"] == "optimizer":
+        return {"bytes": 28 * c["params"], "flops": 12 * c["params"]}
+    act = c["microbatch"] * c["seq"] * c["hidden"] * 2
+    n = _n_params(c)
+    if c["kind"] == "model":
+        n += (2 * c["vocab"] + c["seq"] + 2) * c["hidden"]
+        moved = 4 * n
+    else:
+        moved = 4 * n + 4 * c["batch"] * act
+    if c["kind"] == "step":
+        moved += 28 * n
+    return {"bytes": moved, "flops": _flops(c)}
+
+
+def tolerance(case):
+    # With the sums in another order (other GEMM kernels and tile widths) the outputs move by up to 6e-4 in bf16 and
+    # 4e-4 in half precision, single elements by 0.15 and 0.006; against the fp64 oracle the path is off by 5e-3 at
+    # h = 256, 1.3e-2 at h = 5120 and 2.7e-2 at h = 10240 (the logits, and with them the amplification of a rounding,
+    # grow with h).  The optimizer is 32-bit arithmetic element by element; its 16-bit parameters may differ in ties.
+    if case["kind"] == "optimizer":
+        return {"rel": 1e-5, "max": 1e-2}
+    if case["elem"] == "fp16":
+        return {"rel": 3e-3}
+    return {"rel": 1e-2 if case["hidden"] < 4096 else 2e-2}
+
+
+# ------------------------------------------------------------------------------------------------------------ state
+class _Owner:
+    """Closes what it holds when the last reference to it (the state's, or that of an output view) goes."""
+
+    def __init__(self):
+        self.closers = []
+
+    def __del__(self):
+        for f in reversed(self.closers):
+            f()
+
+
+class _Memory:
+    """Device memory of the library as something torch can view; keeps its owner alive."""
+
+    def __init__(self, owner, ptr, n_bytes):
+        self.owner = owner
+        self.__cuda_array_interface__ = {"shape": (n_bytes,), "typestr": "|u1", "data": (ptr, False), "version": 3}
+
+
+def _view(owner, ptr, n, dtype):
+    return torch.as_tensor(_Memory(owner, ptr, 2 * n), device="cuda").view(dtype)
+
+
+class _Pinned:
+    def __init__(self, owner, ptr, n):
+        self.owner = owner
+        self.__array_interface__ = {"shape": (n,), "typestr": "<f4", "data": (ptr, False), "version": 3}
+
+
+def _pinned(owner, n):
+    ptr = B.axonn_pinned_alloc(4 * n)
+    owner.closers.append(lambda: B.axonn_pinned_free(ptr))
+    return torch.from_numpy(np.asarray(_Pinned(owner, ptr, n)))
+
+
+def _normal_into(dst, g, std, mean=0.0):
+    """dst (flat) <- N(mean, std), drawn on the GPU in pieces."""
+    for o in range(0, dst.numel(), 1 << 26):
+        n = min(1 << 26, dst.numel() - o)
+        dst[o:o + n].copy_(torch.randn(n, generator=g, device="cuda") * std + mean)
+
+
+def _moments(owner, n, g):
+    """fp32 master weights (to be filled in), first and second moment of a run in progress, in pinned host memory."""
+    host = [_pinned(owner, n) for _ in range(3)]
+    _normal_into(host[1], g, 1e-4)
+    _normal_into(host[2], g, 1e-6)
+    host[2].abs_()
+    return host
+
+
+def prepare(case, seed):
+    c = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    was = B.ELEM
+    B.select_elem(c["elem"])
+    try:
+        return _prepare(c, g, B.torch_elem_dtype())
+    finally:
+        B.select_elem(was)
+
+
+def _prepare(c, g, dtype):
+    owner = _Owner()
+    stream = torch.cuda.Stream()
+    if c["kind"] == "optimizer":
+        n = c["params"]
+        host = _moments(owner, n, g)
+        p16 = torch.empty(n, device="cuda", dtype=dtype)
+        g16 = torch.empty(n, device="cuda", dtype=dtype)
+        _normal_into(p16, g, 0.02)
+        _normal_into(g16, g, 1e-3)
+        host[0].copy_(p16)
+        opt = B.axonn_offload_adam_create(0, n, c["bucket"], p16, g16, *host)
+        owner.closers.append(lambda: B.axonn_offload_adam_destroy(opt))
+        torch.cuda.synchronize()
+        return dict(case=c, owner=owner, stream=stream, opt=opt, out=(p16, *host), g16=g16)
+    sh = StageShape(c["layers"], c["hidden"], c["heads"], c["seq"], c["microbatch"], c["batch"], c["ffn"])
+    M = c["batch"]
+    st = Stage(sh, pipeline_limit=c["limit"], grad_accum_fp32=int(c["accum"] == "fp32"), wgrad_group=c["group"],
+               qkv_input_split=c["split"], ckpt_stride=c["stride"])
+    owner.closers.append(st.close)
+    for name, (off, dims) in st.layout.items():
+        _normal_into(st.params[off:off + math.prod(dims)], g, 0.02, 1.0 if name.endswith("_g") else 0.0)
+    state = dict(case=c, owner=owner, stream=stream, st=st,
+                 grads=_view(owner, B.axonn_stage_grads(st.handle), st.n_params, dtype))
+    bs = (c["microbatch"], c["seq"])
+    if c["kind"] == "model":
+        embed = B.axonn_embed_create(0, c["vocab"], c["hidden"], c["seq"], c["microbatch"])
+        head = B.axonn_head_create(0, c["vocab"], c["hidden"], sh.tokens, M, 1e-5)
+        # the stage goes first: it borrows the two
+        owner.closers[:0] = [lambda: B.axonn_head_destroy(head), lambda: B.axonn_embed_destroy(embed)]
+        for key, handle, fn, lo in (("embed", embed, B.axonn_embed_buffers, 0), ("head", head, B.axonn_head_buffers, 2 * c["hidden"])):
+            p, gr, n = fn(handle)
+            _normal_into(_view(owner, p, n, dtype)[lo:], g, 0.02)
+            state[key + "_grads"] = _view(owner, gr, n, dtype)
+        B.axonn_stage_attach_ends(st.handle, embed, head)
+        state["tokens"], state["targets"] = (
+            [torch.randint(0, c["vocab"], bs, generator=g, device="cuda", dtype=torch.int32) for _ in range(M)] for _ in range(2))
+        state["loss"] = torch.zeros(M, device="cuda")
+    else:
+        def batch():
+            return [torch.randn(*bs, c["hidden"], generator=g, device="cuda").to(dtype) for _ in range(M)]
+        state["x"], state["dy"] = batch(), batch()
+        state["y"], state["dx"] = ([torch.empty_like(x) for x in state["x"]] for _ in range(2))
+    if c["kind"] == "step":
+        host = _moments(owner, st.n_params, g)
+        host[0].copy_(st.params)
+        B.axonn_stage_optimizer_attach(st.handle, *host, st.n_params, c["bucket"])
+        state["host"] = host
+        state["params"] = _view(owner, B.axonn_stage_params(st.handle), st.n_params, dtype)
+        # the upstream gradients already carry the loss scale
+        state["scaler"] = B.axonn_loss_scaler(1024.0, 2.0, 0.5, 1 << 30, 0)
+    torch.cuda.synchronize()
+    return state
+
+
+# --------------------------------------------------------------------------------------------------------------- run
+def _order(limit, M):
+    """Message order of a middle stage: `limit` forwards, then one backward / one forward, then the rest."""
+    order = [(0, i) for i in range(min(limit, M))]
+    for i in range(M):
+        order.append((1, i))
+        if limit + i < M:
+            order.append((0, limit + i))
+    return order
+
+
+def _batch(state):
+    c, st, stream, M = state["case"], state["st"], state["stream"], state["case"]["batch"]
+    st.zero_grad(stream)
+    if c["kind"] == "model":
+        for i in range(M):
+            st.post(0, i, state["tokens"][i], None, targets=state["targets"][i], loss=state["loss"][i:i + 1])
+    else:
+        x, y, dy, dx = state["x"], state["y"], state["dy"], state["dx"]
+        for kind, i in _order(c["limit"], M):
+            if c["streams"] == 0:
+                st.forward(i, x[i], y[i], stream) if kind == 0 else st.backward(i, dy[i], dx[i], stream)
+            else:
+                st.post(kind, i, x[i] if kind == 0 else dy[i], y[i] if kind == 0 else dx[i])
+    if c["streams"]:
+        st.run(c["streams"], stream)
+        st.join(stream)
+
+
+def run(state):
+    c = state["case"]
+    if c["kind"] == "optimizer":
+        B.axonn_offload_adam_step(state["opt"], *HYPER.values(), 1.0, state["stream"])
+        return state["out"]
+    _batch(state)
+    if c["kind"] == "model":
+        return state["loss"], state["grads"], state["embed_grads"], state["head_grads"]
+    if c["kind"] == "step":
+        B.axonn_stage_optimizer_step_scaled(state["st"].handle, *HYPER.values(), 1.0 / c["batch"], state["scaler"], 0, state["stream"])
+        return state["y"], state["dx"], state["grads"], state["params"], state["host"]
+    return state["y"], state["dx"], state["grads"]
