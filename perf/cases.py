@@ -245,8 +245,8 @@ def _prepare(c, g, dtype):
         owner.closers[:0] = [lambda: B.axonn_head_destroy(head), lambda: B.axonn_embed_destroy(embed)]
         for key, handle, fn, lo in (("embed", embed, B.axonn_embed_buffers, 0), ("head", head, B.axonn_head_buffers, 2 * c["hidden"])):
             p, gr, n = fn(handle)
-            _normal_into(_view(owner, p, n, dtype)[lo:], g, 0.02)
-            state[key + "_grads"] = _view(owner, gr, n, dtype)
+            state[key + "_params"], state[key + "_grads"] = _view(owner, p, n, dtype), _view(owner, gr, n, dtype)
+            _normal_into(state[key + "_params"][lo:], g, 0.02)
         B.axonn_stage_attach_ends(st.handle, embed, head)
         state["tokens"], state["targets"] = (
             [torch.randint(0, c["vocab"], bs, generator=g, device="cuda", dtype=torch.int32) for _ in range(M)] for _ in range(2))
@@ -309,3 +309,83 @@ def run(state):
         B.axonn_stage_optimizer_step_scaled(state["st"].handle, *HYPER.values(), 1.0 / c["batch"], state["scaler"], 0, state["stream"])
         return state["y"], state["dx"], state["grads"], state["params"], state["host"]
     return state["y"], state["dx"], state["grads"]
+
+
+# ------------------------------------------------------------------------------------------------------------- exact
+def _exact_layer(x, p, heads):
+    """One pre-LayerNorm GPT layer in 64 bits, x: [b, s, h]."""
+    F = torch.nn.functional
+    b, s, h = x.shape
+    d = h // heads
+    qkv = F.layer_norm(x, (h,), p["ln1_g"], p["ln1_b"], 1e-5) @ p["w_qkv"] + p["b_qkv"]
+    future = torch.ones(s, s, dtype=torch.bool, device=x.device).triu(1)
+    rows = []
+    for i in range(b):
+        cols = []
+        for j in range(heads):
+            q, k, v = (qkv[i, :, t * h + j * d:t * h + (j + 1) * d] for t in range(3))
+            scores = (q @ k.t()) / math.sqrt(d)
+            cols.append(torch.softmax(scores.masked_fill(future, -math.inf), dim=-1) @ v)
+        rows.append(torch.cat(cols, dim=-1))
+    y = x + torch.stack(rows) @ p["w_o"] + p["b_o"]
+    w = F.layer_norm(y, (h,), p["ln2_g"], p["ln2_b"], 1e-5)
+    return y + F.gelu(w @ p["w_fc1"] + p["b_fc1"]) @ p["w_fc2"] + p["b_fc2"]
+
+
+def _exact_adam(theta, m, v, g):
+    t = HYPER
+    m = t["beta1"] * m + (1 - t["beta1"]) * g
+    v = t["beta2"] * v + (1 - t["beta2"]) * g * g
+    mhat, vhat = m / (1 - t["beta1"] ** t["step"]), v / (1 - t["beta2"] ** t["step"])
+    theta = theta - t["lr"] * (mhat / (vhat.sqrt() + t["eps"]) + t["weight_decay"] * theta)
+    return theta, theta, m, v                                                  # 16-bit and fp32 copies of one value
+
+
+def exact(case, seed):
+    c = case
+    state = prepare(c, seed)
+    if c["kind"] == "optimizer":
+        return _exact_adam(*(t.cuda().double() for t in state["out"][1:]), state["g16"].double())
+    st = state["st"]
+    layers = [{} for _ in range(c["layers"])]
+    for name, (off, dims) in st.layout.items():
+        l, short = name.split(".")
+        layers[int(l[5:])][short] = st.params[off:off + math.prod(dims)].view(*dims).double().requires_grad_()
+
+    def through(x):
+        for p in layers:
+            x = _exact_layer(x, p, c["heads"])
+        return x
+
+    def gradients():
+        flat = torch.zeros(st.n_params, device="cuda", dtype=torch.float64)
+        for name, (off, dims) in st.layout.items():
+            l, short = name.split(".")
+            flat[off:off + math.prod(dims)] = layers[int(l[5:])][short].grad.flatten()
+        return flat
+
+    M, h, s = c["batch"], c["hidden"], c["seq"]
+    if c["kind"] == "model":
+        V = c["vocab"]
+        embed, head = (state[k + "_params"].double().requires_grad_() for k in ("embed", "head"))
+        wte, wpe = embed[:V * h].view(V, h), embed[V * h:].view(-1, h)
+        losses = []
+        for tok, tgt in zip(state["tokens"], state["targets"]):
+            a = torch.nn.functional.layer_norm(through(wte[tok.long()] + wpe[:s]), (h,), head[:h], head[h:2 * h], 1e-5)
+            logits = a.reshape(-1, h) @ head[2 * h:].view(h, V)
+            loss = torch.nn.functional.cross_entropy(logits, tgt.long().view(-1)) / M
+            loss.backward()
+            losses.append(loss.detach())
+        return torch.stack(losses), gradients(), embed.grad, head.grad
+    ys, dxs = [], []
+    for x, dy in zip(state["x"], state["dy"]):
+        x = x.double().requires_grad_()
+        y = through(x)
+        y.backward(dy.double())
+        ys.append(y.detach())
+        dxs.append(x.grad)
+    grads = gradients()
+    if c["kind"] == "step":
+        new = _exact_adam(*(t.cuda().double() for t in state["host"]), grads / (c["batch"] * 1024.0))
+        return ys, dxs, grads, new[0], list(new[1:])
+    return ys, dxs, grads
