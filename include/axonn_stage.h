@@ -400,9 +400,9 @@ int axonn_gemm_bf16(int32_t a_kcontig, int32_t b_kcontig, int32_t epilogue,
  * tokens of the microbatches, of x^T dy and of dy): axonn_gemm_bf16 with (a_kcontig, b_kcontig) =
  * (0, 0) and epilogue 4 or 5, so C[M,N] (+)= sum_k A[k*lda + m] * B[k*ldb + n], and beside it
  *   colsum[n] = (accumulate ? colsum[n] : 0) + sum_k B[k*ldb + n],   n < N,
- * in C's element type (float32 for epilogue 4, bf16 for 5; sums in fp32, one rounding).  Problems of
- * at least 128 tiles of 256 x 256 form the sums inside the GEMM kernel, from the tiles of B it
- * multiplies (B is read once); smaller ones run axonn_colsum's kernels behind the GEMM.
+ * in C's element type (float32 for epilogue 4, bf16 for 5; sums in fp32, one rounding).  The sums are
+ * formed inside the GEMM kernel, from the tiles of B it multiplies (B is read once); only for operands
+ * of 2 GiB and more axonn_colsum's kernels run behind the GEMM.
  * workspace_f32: ceil(K/64)*N floats, needed either way.  Sizes as for axonn_gemm_bf16. */
 int axonn_gemm_wgrad_colsum(int32_t epilogue, int64_t M, int64_t N, int64_t K,
                             const void* A, int64_t lda, const void* B, int64_t ldb,
@@ -481,7 +481,7 @@ int axonn_profile_collect(double* total_ms, int64_t* launches, int32_t n_categor
  *                                  8 weight gradients with an fp32 result (built-in: 7); it applies where K is a
  *                                  multiple of 64
  *   AXONN_TUNE_GEMM_BIG_MIN_TILES  number of 256 x 256 tiles from which the large-problem kernels are used
- *                                  (built-in: 128)
+ *                                  (built-in: 256, below that where they are modelled to be faster)
  *   AXONN_TUNE_GEMM_TILE_N         block width of the large-problem kernels: 160, 192 or 256 (0 or -1: chosen per
  *                                  problem) */
 typedef enum {

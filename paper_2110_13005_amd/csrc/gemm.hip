@@ -1061,6 +1061,290 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
   if (CS) { if (cs_on) colsum_store<EPI, TN>(cs, g, n0 + wn * (16 * TN), lane); }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Ring kernel: problems that do not fill the chip with 256 x 256 tiles.  32*TM x 32*TN block tile, KG groups of 2 x 2
+// waves that share the k range of every stage (group j takes its share of the stage's 32-wide k slices), so that a
+// small tile still puts two waves on every SIMD without more LDS reads per MFMA; the groups' results are added
+// through LDS at the end.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
+// the traffic into and out of LDS (32 KB copied in, 64 KB of fragments read per 512 MFMA clocks).
+//   * Tiles are copied into LDS by the memory pipeline, into a ring of NS stages of 64*NSUB k each: NS - 1 stages are
+//     in flight or being read, so a short k range is fetched in one memory latency, and a long one has two or three
+//     steps for every copy to arrive.  One barrier per step.
+//   * Two sets of fragment registers: the MFMAs of a step run while the fragments of the next one are read.
+//   * Any K (a multiple of 8), any segment length: a copy whose k lies beyond the segment reads zeros, chosen per lane.
+//   * What the epilogue reads (bias, residual, stored derivative, accumulating C) is requested before the k loop.
+// Stage layout: a k-contiguous operand in blocks of 64 k, 128 bytes per row, chunk q of row r in slot q ^ ((r >> 1) & 7);
+// a k-strided one as k rows of ROWS elements, the 32-byte pieces of row k permuted by ring_swizzle(k), so that the
+// eight k rows that one transposing read touches (k0 .. k0+3 and k0+8 .. k0+11) fall into different banks.
+// 256 tiles of 128 x 128 take 0.47 us per 64-wide k-step (2048 x 2048 x 8192: 67 us, 1030 TFLOP/s); with the copies issued
+// behind the barrier instead of between the MFMAs it is the same, with one set of fragment registers 0.52.
+template <int ROWS>
+__device__ __forceinline__ int ring_swizzle(int k) {
+  return ROWS % 128 == 0 ? (k & 3) | ((k >> 1) & 4) : ((k >> 1) & 1) | ((k >> 2) & 2);
+}
+// Copy instruction i of a stage of one operand: what lane `lane` fetches.  k: its k within the stage; returns the
+// lane's byte offset from the segment base in k-tile 0, or kOutOfRange outside the matrix.
+template <bool KC, int ROWS>
+__device__ __forceinline__ uint32_t ring_source(int i, int lane, int row0, int rows, uint32_t ld, int& k) {
+  if (KC) {
+    const int sub = i / (ROWS / 8), r = (i % (ROWS / 8)) * 8 + (lane >> 3);
+    k = sub * 64 + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+    return row0 + r < rows ? ((uint32_t)(row0 + r) * ld + k) * 2u : kOutOfRange;
+  }
+  constexpr int CPR = ROWS / 8;                        // chunks per k row
+  const int chunk = i * 64 + lane;
+  k = chunk / CPR;
+  const int s = chunk % CPR, ch = (((s >> 1) ^ ring_swizzle<ROWS>(k)) << 1) | (s & 1);
+  return row0 + ch * 8 < rows ? ((uint32_t)k * ld + row0 + ch * 8) * 2u : kOutOfRange;
+}
+// Fragment of rows r0 .. r0+15 (r0 a multiple of 16) and k slice `slice` of a stage of one operand at `base`.
+template <bool KC, int ROWS>
+__device__ __forceinline__ elemx8 ring_fragment(const char* base, int r0, int slice, int lane) {
+  const int ft = lane & 15, fg = lane >> 4;
+  if (KC)
+    return *reinterpret_cast<const elemx8*>(base + (slice >> 1) * (ROWS * 128) + (r0 + ft) * 128 +
+                                            (((((slice & 1) << 2) + fg) ^ ((ft >> 1) & 7)) << 4));
+  const int k = 8 * fg + (ft >> 2);
+  const char* p = base + (slice * 32 + k) * (ROWS * 2) + (((r0 >> 4) ^ ring_swizzle<ROWS>(k)) << 5) + ((ft & 3) << 3);
+  union { elemx8 v; short4v h[2]; } u;
+  u.h[0] = lds_read_tr16(reinterpret_cast<const elem_t*>(p));
+  u.h[1] = lds_read_tr16(reinterpret_cast<const elem_t*>(p + 4 * ROWS * 2));
+  return u.v;
+}
+
+template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS>
+__global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
+  constexpr int BM = 32 * TM, BN = 32 * TN, BK = 64 * NSUB, W = 4 * KG, NT = 64 * W;
+  constexpr int SA = BM * BK * 2, SB = BN * BK * 2, STAGE = SA + SB;
+  constexpr int NDA = SA / 1024 / W, NDB = SB / 1024 / W, ND = NDA + NDB;    // copy instructions per wave and stage
+  constexpr int SLICES = 2 * NSUB / KG;
+  static_assert(BM * BN / 4 % NT == 0 && NDA * W * 1024 == SA && NDB * W * 1024 == SB && SLICES * KG == 2 * NSUB && NS >= 3, "tile split");
+  static_assert((NS - 1) * ND < 64, "vmcnt range");
+  constexpr int LD = BN + 4;                           // staging rows of the epilogue, in floats
+  // partial results kept apart until the rows leave, or, where LDS does not hold both, added in place first
+  constexpr bool APART = KG * (BM * LD + BN) * 4 <= 160 * 1024;
+  static_assert(APART || KG == 2, "partial results");
+  constexpr int NPART = APART ? KG : 1;
+  constexpr int EPI_BYTES = (NPART * BM * LD + KG * BN) * 4;
+  constexpr int LDS_BYTES = NS * STAGE > EPI_BYTES ? NS * STAGE : EPI_BYTES;
+  __shared__ __align__(1024) char smem[LDS_BYTES];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
+  int tm, tn;
+  tile_of_block(g.tiles_m, g.tiles_n, tm, tn);
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
+  uint32_t va[NDA], vb[NDB];
+  int ka[NDA], kb[NDB];
+#pragma unroll
+  for (int c = 0; c < NDA; ++c) va[c] = ring_source<A_KC, BM>(c * W + wave, lane, m0, g.M, lda, ka[c]);
+#pragma unroll
+  for (int c = 0; c < NDB; ++c) vb[c] = ring_source<B_KC, BN>(c * W + wave, lane, n0, g.N, ldb, kb[c]);
+  const uint32_t sa = A_KC ? BK * 2u : BK * lda * 2u, sb = B_KC ? BK * 2u : BK * ldb * 2u;
+  const uint32_t nra = (uint32_t)(A_KC ? g.M : g.K) * lda * 2u, nrb = (uint32_t)(B_KC ? g.N : g.K) * ldb * 2u;
+  const int K = g.K, tps = (K + BK - 1) / BK, nk = tps * g.n_seg;
+  int ld_seg = 0, ld_kin = 0;                          // segment and k-tile within it of the NEXT tile to fetch
+  u32x4 rsa = rsrc_words(g.A_seg[0], nra), rsb = rsrc_words(g.B_seg[0], nrb);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(AXONN_LDS char*)smem + (uint32_t)wave * 1024u;
+
+  // Copy instruction c (A's, then B's) of the next k-tile into the stage at byte offset `at`: k beyond the segment and
+  // tiles beyond the last one read zeros.
+  auto copy = [&](int c, uint32_t at) {
+    if (c < NDA)
+      dma_chunk16(rsa, ld_kin * BK + ka[c < NDA ? c : 0] < K ? va[c < NDA ? c : 0] : kOutOfRange, (uint32_t)ld_kin * sa,
+                  lds0 + at + c * (W * 1024));
+    else
+      dma_chunk16(rsb, ld_kin * BK + kb[c >= NDA ? c - NDA : 0] < K ? vb[c >= NDA ? c - NDA : 0] : kOutOfRange,
+                  (uint32_t)ld_kin * sb, lds0 + at + SA + (c - NDA) * (W * 1024));
+  };
+  auto copy_done = [&]() {                             // on to the next k-tile
+    if (++ld_kin == tps) {
+      ld_kin = 0;
+      ++ld_seg;
+      const bool live = ld_seg < g.n_seg;
+      const int sidx = live ? ld_seg : 0;
+      rsa = rsrc_words(g.A_seg[sidx], live ? nra : 0u);
+      rsb = rsrc_words(g.B_seg[sidx], live ? nrb : 0u);
+    }
+  };
+
+#pragma unroll
+  for (int t = 0; t < NS - 1; ++t) {
+#pragma unroll
+    for (int c = 0; c < ND; ++c) copy(c, t * STAGE);
+    copy_done();
+  }
+
+  // bias and what the epilogue reads at this thread's output positions are fetched beside the k loop
+  constexpr int NP = BM * BN / 4 / NT, CW = BN / 4;    // positions per thread (4 columns each), positions per row
+  constexpr int NBV = NT % CW == 0 ? 1 : NP;           // one column for all positions of a thread, or one each
+  const bool reads = epi_reads_operand<EPI>(g);
+  const int64_t ld_side = epi_ld_side<EPI>(g);
+  float bv[NBV][4];
+  EpiOperand opnd[NP];
+  auto load_operands = [&]() {
+#pragma unroll
+    for (int p = 0; p < NBV; ++p) {
+      const int n = n0 + 4 * ((tid + p * NT) % CW);
+      if (n < g.N) load_bias4<EPI>(bv[p], g, n);
+    }
+    if (!reads) return;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int m = m0 + (tid + p * NT) / CW, n = n0 + 4 * ((tid + p * NT) % CW);
+      if (n < g.N && m < g.M) opnd[p] = epi_load_operand<EPI>(g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
+    }
+  };
+  constexpr bool EARLY = NP <= 8;                      // registers to hold them through the k loop
+  if (EARLY) load_operands();
+
+  floatx4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  constexpr bool CS = epilogue_sums_columns(A_KC, B_KC, EPI);
+  const bool cs_on = CS && g.colsum != nullptr && wm == 0 &&              // the same for all lanes of a wave
+                     tm == (int)((int64_t)tn * g.tiles_m / g.tiles_n);
+  float cs[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) cs[j] = 0.f;
+
+  uint32_t cur = 0, nxt = (NS - 1) * STAGE;            // stage to read next; stage to refill
+  elemx8 fa[2][SLICES][TM], fb[2][SLICES][TN];
+  // Stage `cur` into fragment set F.  The wave's own copies of it have arrived behind the wait, everybody's behind
+  // the barrier, and nobody reads the stage of the step before any more: it may be refilled from here on.
+  auto read = [&](auto set) {
+    constexpr int F = decltype(set)::value;
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NS - 2) * ND) : "memory");
+    lds_barrier();
+#pragma unroll
+    for (int s = 0; s < SLICES; ++s) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, grp * SLICES + s, lane);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, grp * SLICES + s, lane);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // The MFMAs of set F, and between them (COPY) the copies of the next k-tile into the stage read last but one.
+  auto multiply = [&](auto set, auto with_copies) {
+    constexpr int F = decltype(set)::value;
+    constexpr bool COPY = decltype(with_copies)::value;
+    constexpr int NM = SLICES * TM * TN;
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+      const int s = q / (TM * TN), i = q / TN % TM, j = q % TN;
+      acc[i][j] = mfma16(fb[F][s][j], fa[F][s][i], acc[i][j]);
+      if (COPY) {
+        const int c = item_at(q, ND, 0, NM);
+        if (c >= 0) {
+          copy(c, nxt);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    if (COPY) copy_done();
+    nxt = cur;
+    cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+    if (CS && cs_on) {
+#pragma unroll
+      for (int s = 0; s < SLICES; ++s)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) colsum_pair(cs[j], fb[F][s][j], e);
+    }
+  };
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
+  read(Set0{});
+#pragma unroll
+  for (int c = 0; c < ND; ++c) copy(c, nxt);
+  copy_done();
+  nxt = cur;
+  cur += STAGE;
+  int left = nk - 1;                                   // stages not read yet
+  for (; left >= 2; left -= 2) {
+    read(Set1{});
+    multiply(Set0{}, std::true_type{});
+    read(Set0{});
+    multiply(Set1{}, std::true_type{});
+  }
+  if (left) read(Set1{});
+  multiply(Set0{}, std::false_type{});
+  if (left) multiply(Set1{}, std::false_type{});
+  dma_wait_all();                                      // copies of tiles past the end still write (zeros) to LDS
+  lds_barrier();                                       // and every wave is done with the tiles
+
+  // The groups' partial results meet in LDS, and the result leaves in whole rows: lane owns 4 columns.
+  float* const stage = reinterpret_cast<float*>(smem);
+  float* const sums = stage + NPART * BM * LD;
+  float* const mine = stage + (APART ? grp * (BM * LD) : 0) + (wm * 16 * TM + (lane & 15)) * LD + wn * 16 * TN + 4 * (lane >> 4);
+  if (!EARLY) load_operands();
+  if (!APART) {
+    if (grp == 1) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4*>(mine + 16 * i * LD + 16 * j) = acc[i][j];
+    }
+    lds_barrier();
+    if (grp == 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          floatx4* p = reinterpret_cast<floatx4*>(mine + 16 * i * LD + 16 * j);
+          *p = *p + acc[i][j];
+        }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4*>(mine + 16 * i * LD + 16 * j) = acc[i][j];
+  }
+  if (CS && cs_on) {
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      float v = cs[j];
+      v += __shfl_xor(v, 16);
+      v += __shfl_xor(v, 32);
+      if (lane < 16) sums[grp * BN + (wn * TN + j) * 16 + lane] = v;
+    }
+  }
+  lds_barrier();
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = (tid + p * NT) / CW, ec = 4 * ((tid + p * NT) % CW), m = m0 + r, n = n0 + ec;
+    if (n < g.N && m < g.M) {
+      floatx4 x = *reinterpret_cast<const floatx4*>(stage + r * LD + ec);
+#pragma unroll
+      for (int q = 1; q < NPART; ++q) x += *reinterpret_cast<const floatx4*>(stage + q * (BM * LD) + r * LD + ec);
+      float v[4] = {x[0], x[1], x[2], x[3]};
+      epi_finish<EPI>(v, bv[NBV == 1 ? 0 : p], opnd[p], g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
+    }
+  }
+  if (CS && g.colsum != nullptr && tm == (int)((int64_t)tn * g.tiles_m / g.tiles_n) && tid < BN && n0 + tid < g.N) {
+    float v = sums[tid];
+#pragma unroll
+    for (int q = 1; q < KG; ++q) v += sums[q * BN + tid];
+    if (EPI == EPI_ACC_F32) {
+      float* o = reinterpret_cast<float*>(g.colsum) + n0 + tid;
+      *o = g.accumulate ? *o + v : v;
+    } else {
+      elem_t* o = reinterpret_cast<elem_t*>(g.colsum) + n0 + tid;
+      *o = (elem_t)(g.accumulate ? (float)*o + v : v);
+    }
+  }
+}
+
 // Only the (layout, epilogue) pairs the layer uses are instantiated: forward maps take the
 // bias epilogues, input gradients the plain / GeLU' ones, weight gradients the accumulating ones.
 constexpr bool epilogue_allowed(bool a_kc, bool b_kc, int e) {
@@ -1165,18 +1449,40 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   return hipGetLastError();          // both kernels form the column sums of a weight gradient themselves
 }
 
+template <bool A_KC, bool B_KC, int TM, int TN, int KG, int NSUB, int NS>
+static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s) {
+  g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
+  g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
+  const dim3 grid(g.tiles_m * g.tiles_n), block(256 * KG);
+#define AXONN_GEMM_CASE(E)                                                                      \
+  case E:                                                                                       \
+    if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
+      hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, E, TM, TN, KG, NSUB, NS>), grid, block, 0, s, g); \
+      break;                                                                                    \
+    } else {                                                                                    \
+      return hipErrorInvalidValue;                                                              \
+    }
+  switch (epi) {
+    AXONN_GEMM_CASE(EPI_BIAS)
+    AXONN_GEMM_CASE(EPI_BIAS_RES)
+    AXONN_GEMM_CASE(EPI_BIAS_GELU)
+    AXONN_GEMM_CASE(EPI_DGELU)
+    AXONN_GEMM_CASE(EPI_ACC_F32)
+    AXONN_GEMM_CASE(EPI_ACC_BF16)
+    default: return hipErrorInvalidValue;
+  }
+#undef AXONN_GEMM_CASE
+  return hipGetLastError();
+}
+
 // The large-problem kernel addresses an operand with 32-bit byte offsets from the segment base.
 static bool fits_32bit_offsets(int64_t rows, int64_t ld) {
   return ld > 0 && (rows + 1024) * ld * 2 < (int64_t(1) << 31);
 }
 
-// Number of 256 x 256 tiles from which the large-problem kernel is used: half the CUs, unless
-// axonn_tuning(AXONN_TUNE_GEMM_BIG_MIN_TILES, n) says otherwise (the tests send small ragged problems through
-// the large-problem kernels with it).
-static int64_t big_tile_threshold() {
-  const int64_t v = g_tune_big_min_tiles.load();
-  return v >= 0 ? v : 128;
-}
+// Number of 256 x 256 tiles from which the large-problem kernels are used if axonn_tuning(
+// AXONN_TUNE_GEMM_BIG_MIN_TILES, n) fixes it (the tests send small ragged problems through them with it), else -1.
+static int64_t big_tile_threshold() { return g_tune_big_min_tiles.load(); }
 
 // Block width of the large-problem kernel for an M x N x (nk k-steps) problem: when other kernels share the chip
 // (they fill the CUs a partly filled round leaves idle), the widest and most efficient one; when the launch has
@@ -1203,22 +1509,69 @@ static int choose_tn(int64_t M, int64_t N, int64_t nk, bool concurrent) {
   return best;
 }
 
+// Tile of the ring kernel for a problem that 256 x 256 tiles would not fill the chip with.
+enum RingTile { RING_64x64, RING_128x64, RING_128x128, RING_128x192, RING_128x256, RING_TILES };
+struct TileCost { int bm, bn; double fixed, step_few, step_full; };
+// Microseconds: what a round of up to 256 tiles (one workgroup per CU) costs beside its k-steps, and a 64-wide k-step
+// with few and with 256 tiles in flight.  From single launches with K = 1024 and K = 4096 of outputs of 256 x 256 to
+// 2048 x 12288 (the difference gives the step, the rest the fixed part).
+constexpr TileCost kRingCost[RING_TILES] = {{64, 64, 3.2, 0.20, 0.21}, {128, 64, 4.0, 0.28, 0.30},
+                                            {128, 128, 5.0, 0.40, 0.47}, {128, 192, 7.5, 0.54, 0.68},
+                                            {128, 256, 8.0, 0.65, 0.73}};
+constexpr TileCost kBigCost[3] = {{256, 160, 10.0, 0.75, 1.05}, {256, 192, 10.0, 0.80, 1.10}, {256, 256, 10.0, 1.0, 1.4}};
+
+// Modelled time of a problem with one tile size: whole rounds and a last one whose steps are faster the emptier it is.
+static double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
+  const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  const double last = (double)(tiles % 256) / 256;
+  return (double)(tiles / 256) * (c.fixed + nk * c.step_full) +
+         (last > 0 ? c.fixed + nk * (c.step_few + (c.step_full - c.step_few) * last) : 0.0);
+}
+
+// Which ring tile an M x N x (nk k-steps) problem takes; -1: a large-problem kernel.  Those stay where their 256 x 256
+// tiles fill the chip, and where the model prefers one of their widths.  Measured (bf16, single launches, the kernels
+// before / now): 256 x 256 x 1024 17.0 / 5.7 us, 1024 x 1024 x 4096 52.6 / 16.1, 2048 x 1024 x 4096 52.6 / 23.8, 2048 x 2048 x
+// 8192 103 / 67, 2048 x 3072 x 12288 226 / 137 (a kernel of 128 x 128 tiles staged through registers, which had no case
+// left), 2048 x 4096 x 1024 with GeLU 35.6 / 28.5 (half a round of 256 x 256 tiles).
+// The rule does not look at whether the launch shares the chip: a ring kernel adds its two halves of k in another order
+// than the large-problem kernels, and a batch's results should not depend on the number of streams it runs on.
+// Measured, the choice would be the same: leaving half-filled rounds to the large-problem kernels beside other streams,
+// or weighing in the CUs that a round leaves idle, changed whole batches by less than 1 % or made them slower.
+static int choose_ring_tile(int64_t M, int64_t N, int64_t nk) {
+  const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  const int64_t forced = big_tile_threshold();
+  if (big_tiles >= (forced >= 0 ? forced : 256)) return -1;
+  int best = RING_64x64;
+  double best_cost = tile_cost(kRingCost[0], M, N, nk);
+  for (int t = 1; t < RING_TILES; ++t) {
+    const double cost = tile_cost(kRingCost[t], M, N, nk);
+    if (cost < best_cost) { best = t; best_cost = cost; }
+  }
+  if (forced < 0)
+    for (const TileCost& c : kBigCost)
+      if (tile_cost(c, M, N, nk) < best_cost) return -1;
+  return best;
+}
+
 template <bool A_KC, bool B_KC>
 static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
-  // Large tile when the problem fills the chip with it, smaller tile otherwise.
-  const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256);
-  if (big_tiles >= big_tile_threshold()) {
-    if (fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) && fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb)) {
-      const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
-      switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
-        case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);
-        case 6: return launch_big<A_KC, B_KC, 6>(epi, g, s);
-        default: return launch_big<A_KC, B_KC, 8>(epi, g, s);
-      }
-    }
+  if (!fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) || !fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb))
     return launch_cfg<256, 256, 64, 2, 4, A_KC, B_KC>(epi, g, s);
+  const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
+  const int tile = choose_ring_tile(g.M, g.N, nk);
+  switch (tile) {
+    case RING_64x64: return launch_ring<A_KC, B_KC, 2, 2, 2, 2, 4>(epi, g, s);
+    case RING_128x64: return launch_ring<A_KC, B_KC, 4, 2, 2, 2, 3>(epi, g, s);
+    case RING_128x128: return launch_ring<A_KC, B_KC, 4, 4, 2, 1, 4>(epi, g, s);
+    case RING_128x192: return launch_ring<A_KC, B_KC, 4, 6, 2, 1, 3>(epi, g, s);
+    case RING_128x256: return launch_ring<A_KC, B_KC, 4, 8, 2, 1, 3>(epi, g, s);
+    default: break;
   }
-  return launch_cfg<128, 128, 64, 2, 2, A_KC, B_KC>(epi, g, s);
+  switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
+    case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);
+    case 6: return launch_big<A_KC, B_KC, 6>(epi, g, s);
+    default: return launch_big<A_KC, B_KC, 8>(epi, g, s);
+  }
 }
 
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, const GemmArgs& g, hipStream_t s) {

@@ -115,8 +115,8 @@ def test_gemm_wgrad_layout_accumulate(M, N, K):
 
 @pytest.mark.parametrize("M,N,K", GEMM_SHAPES)
 def test_gemm_wgrad_with_bias_gradient(M, N, K):
-    """dW = x^T dy and db = the column sums of dy from one call (the large-problem kernels form db from the tiles of
-    dy they multiply, the others run the column-sum kernels behind the GEMM): stored, then accumulated, in fp32 and
+    """dW = x^T dy and db = the column sums of dy from one call (formed from the tiles of dy that the kernel
+    multiplies): stored, then accumulated, in fp32 and
     in 16-bit accumulators; dy with a leading dimension beyond N, whose padding must stay out of the sums."""
     import torch
     rng = np.random.default_rng(M + N * 7 + K)
@@ -146,6 +146,27 @@ def test_gemm_wgrad_with_bias_gradient(M, N, K):
     parity(host(c16), first + ref, TOL, C_ONE, label="gemm_wgrad_with_bias_gradient")
     parity(host(db16)[:N], first_db + ref_db, TOL, C_ONE, label="gemm_wgrad_with_bias_gradient")
     assert (host(db16)[N:] == 3.0).all()
+
+
+# One problem per tile size of the ring kernel (below the threshold of the large-problem kernels the launcher picks the
+# one with the lowest modelled time): ragged rows and columns, a k tail, k ranges shorter than the ring and longer.
+RING_SHAPES = [
+    (72, 136, 40),       # 64 x 64: one k-tile with a tail, the rest of the ring beyond the end
+    (1000, 1016, 456),   # 64 x 64: 8 k-tiles, the last one short
+    (2040, 1016, 520),   # 128 x 64
+    (2008, 2040, 328),   # 128 x 128: an even number of k-steps, 1032 an odd one
+    (1032, 3080, 1032),  # 128 x 128 and the columns of a ninth half-empty tile row
+    (2040, 3064, 200),   # 128 x 192: partial results added in place
+    (2040, 4088, 264),   # 128 x 256
+]
+
+
+@pytest.mark.parametrize("M,N,K", RING_SHAPES)
+def test_gemm_ring_tiles(M, N, K):
+    test_gemm_forward_layout_bias_res_gelu(M, N, K)
+    test_gemm_dgrad_layout_plain_and_dgelu(M, N, K)
+    test_gemm_wgrad_layout_accumulate(M, N, K)
+    test_gemm_wgrad_with_bias_gradient(M, N, K)
 
 
 def test_gemm_big_tile_strided_operands():
