@@ -266,5 +266,9 @@ hipError_t launch_xent(int T, int V, void* logits, const int* targets, int n_mic
 hipError_t launch_adam(uint64_t n, float* theta, float* m, float* v, const void* g16,
                        void* p16, double lr, double b1, double b2, double eps, double wd,
                        int64_t step, double grad_scale, hipStream_t s);
+// The same with theta, m and v in host memory that the GPU can address (device addresses of it, 16-byte aligned).
+hipError_t launch_adam_host(uint64_t n, float* theta, float* m, float* v, const void* g16,
+                            void* p16, double lr, double b1, double b2, double eps, double wd,
+                            int64_t step, double grad_scale, hipStream_t s);
 
 }  // namespace axonn

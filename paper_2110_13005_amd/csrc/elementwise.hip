@@ -3,6 +3,7 @@
 // kernel.  All of them move 16-byte vectors per lane along the contiguous dimension and
 // reduce with wavefront shuffles; none of them uses atomics, so results are reproducible.
 #include "common.h"
+#include <algorithm>
 
 namespace axonn {
 
@@ -387,6 +388,44 @@ hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void*
   return hipGetLastError();
 }
 
+// Adam straight on the host arrays: theta, m and v are read and written over the host link by the kernel itself, in both
+// directions at once, without staging buffers, copies or a pipeline to fill.  The link is the bound (12 bytes per
+// parameter each way).  Few workgroups on purpose: with 64 the requests in flight just cover the link's round trip;
+// more of them only queue reads in front of the writes.  2^26 parameters: 64 workgroups 16.3 ms (49.5 GB/s each way),
+// 256 17.7, 4096 17.8; through buckets of 2^24 with copies on both sides 20-31 ms.  2^20: 0.37 ms against 0.60.
+// Four elements per lane and array: a wave's access is 1 KB of consecutive bytes.
+constexpr int ADAM_HOST_BLOCKS = 64;
+__global__ __launch_bounds__(256) void adam_host_kernel(uint64_t n4, uint64_t n, float* __restrict__ theta,
+                                                        float* __restrict__ m, float* __restrict__ v,
+                                                        const elem_t* __restrict__ g16,
+                                                        elem_t* __restrict__ p16, AdamConsts c) {
+  const uint64_t stride = (uint64_t)gridDim.x * 256;
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += stride) {
+    const uint64_t o = i * 4;
+    floatx4 t = *reinterpret_cast<const floatx4*>(theta + o);
+    floatx4 mm = *reinterpret_cast<const floatx4*>(m + o);
+    floatx4 vv = *reinterpret_cast<const floatx4*>(v + o);
+    const elemx4 gv = *reinterpret_cast<const elemx4*>(g16 + o);
+    elemx4 pv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float a = t[e], b = mm[e], d = vv[e];
+      adam_elem(a, b, d, (float)gv[e], c);
+      t[e] = a; mm[e] = b; vv[e] = d; pv[e] = round_stored(a);
+    }
+    *reinterpret_cast<floatx4*>(theta + o) = t;
+    *reinterpret_cast<floatx4*>(m + o) = mm;
+    *reinterpret_cast<floatx4*>(v + o) = vv;
+    *reinterpret_cast<elemx4*>(p16 + o) = pv;
+  }
+  if (blockIdx.x == 0 && threadIdx.x < n - n4 * 4) {
+    const uint64_t i = n4 * 4 + threadIdx.x;
+    float a = theta[i], b = m[i], d = v[i];
+    adam_elem(a, b, d, (float)g16[i], c);
+    theta[i] = a; m[i] = b; v[i] = d; p16[i] = round_stored(a);
+  }
+}
+
 static unsigned grid_for(uint64_t work_items) {
   uint64_t b = (work_items + 255) / 256;
   if (b < 1) b = 1;
@@ -452,9 +491,7 @@ hipError_t launch_fill_elem(uint64_t n, void* dst, float value, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_adam(uint64_t n, float* theta, float* m, float* v, const void* g16, void* p16,
-                       double lr, double b1, double b2, double eps, double wd, int64_t step,
-                       double grad_scale, hipStream_t s) {
+static AdamConsts adam_consts(double lr, double b1, double b2, double eps, double wd, int64_t step, double grad_scale) {
   AdamConsts c;
   c.lr = (float)lr; c.b1 = (float)b1; c.b2 = (float)b2; c.eps = (float)eps; c.wd = (float)wd;
   c.grad_scale = (float)grad_scale;
@@ -463,7 +500,22 @@ hipError_t launch_adam(uint64_t n, float* theta, float* m, float* v, const void*
   c.omb1 = (float)(1.0 - b1); c.omb2 = (float)(1.0 - b2);
   c.inv_bc1 = (float)(1.0 / (1.0 - pow(b1, (double)step)));
   c.inv_bc2 = (float)(1.0 / (1.0 - pow(b2, (double)step)));
+  return c;
+}
+hipError_t launch_adam(uint64_t n, float* theta, float* m, float* v, const void* g16, void* p16,
+                       double lr, double b1, double b2, double eps, double wd, int64_t step,
+                       double grad_scale, hipStream_t s) {
+  const AdamConsts c = adam_consts(lr, b1, b2, eps, wd, step, grad_scale);
   hipLaunchKernelGGL(adam_kernel, dim3(grid_for(n / 8)), dim3(256), 0, s, n / 8, n, theta, m, v,
+                     (const elem_t*)g16, (elem_t*)p16, c);
+  return hipGetLastError();
+}
+hipError_t launch_adam_host(uint64_t n, float* theta, float* m, float* v, const void* g16, void* p16,
+                            double lr, double b1, double b2, double eps, double wd, int64_t step,
+                            double grad_scale, hipStream_t s) {
+  const AdamConsts c = adam_consts(lr, b1, b2, eps, wd, step, grad_scale);
+  const unsigned grid = (unsigned)std::min<uint64_t>(ADAM_HOST_BLOCKS, (n / 4 + 255) / 256 + (n < 4 ? 1 : 0));
+  hipLaunchKernelGGL(adam_host_kernel, dim3(grid), dim3(256), 0, s, n / 4, n, theta, m, v,
                      (const elem_t*)g16, (elem_t*)p16, c);
   return hipGetLastError();
 }

@@ -350,6 +350,39 @@ def test_offloaded_adam_matches_oracle(n, bucket, fresh, wd, step, gs):
             B.axonn_pinned_free(p)
 
 
+@pytest.mark.parametrize("n,bucket", [(3, 8), (1027, 1 << 8), (262_147, 1 << 16)])
+def test_offloaded_adam_in_place_and_through_buckets_agree(n, bucket):
+    """Pinned 16-byte-aligned state is updated in place over the link; pinned state at an odd element and pageable state go
+    through the device buckets.  The same elementwise arithmetic: the same bits, and nothing written past the end."""
+    import torch
+    th, m, v, g16 = make_adam_inputs(n, seed=n)
+    G = dev_bf16(g16)
+    got = []
+    for kind in ("aligned", "odd", "pageable"):
+        ptrs, bufs = zip(*[_pinned_array(n + 2) for _ in range(3)])
+        arrs = [np.full(n + 2, 7.0, np.float32) for _ in range(3)] if kind == "pageable" else [b for b in bufs]
+        lo = 1 if kind == "odd" else 0
+        for a, src in zip(arrs, (th, m, v)):
+            a[:] = 7.0
+            a[lo:lo + n] = src
+        P16 = torch.zeros(n, dtype=B.torch_elem_dtype(), device="cuda")
+        opt = B.axonn_offload_adam_create(0, n, bucket, P16, G, *[a.ctypes.data + 4 * lo for a in arrs])
+        try:
+            for step in (1, 2):
+                B.axonn_offload_adam_step(opt, 1e-3, 0.9, 0.95, 1e-8, 0.01, step, 0.5)
+            assert all((a[lo + n:] == 7.0).all() and (a[:lo] == 7.0).all() for a in arrs)
+            got.append([a[lo:lo + n].copy() for a in arrs] + [host(P16)])
+        finally:
+            B.axonn_offload_adam_destroy(opt)
+            for p in ptrs:
+                B.axonn_pinned_free(p)
+    rt = oracle.adam_step(*oracle.adam_step(th, m, v, g16, 1e-3, 0.9, 0.95, 1e-8, 0.01, 1, 0.5, half=B.ELEM)[:3], g16,
+                          1e-3, 0.9, 0.95, 1e-8, 0.01, 2, 0.5, half=B.ELEM)[0]
+    assert rel_fro(got[0][0], rt) <= ADAM_TOL
+    for other in got[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(got[0], other))
+
+
 def test_stage_batch_then_optimizer_step():
     """Alg. 1's per-GPU body: all microbatches forward/backward, then "run the optimizer" on the
     stage's own bf16 parameter / gradient buffers with grad_scale = 1/M."""
