@@ -242,6 +242,14 @@ hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const vo
                                 const float* stats, const void* gamma, const void* res_grad,
                                 void* dx, void* dgamma, void* dbeta, int acc_mode, bool dst_fp32,
                                 float* ws, hipStream_t s);
+// dx and the parameter-gradient sums of one call, added to (`first`: stored in) `partial`: layernorm_bwd_slices(T, h)
+// slices of 2 * h floats.  launch_layernorm_param_grads stores what the slices have collected in the gradient vectors.
+int layernorm_bwd_slices(int64_t T, int64_t h);
+hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, const void* x, const float* stats,
+                                        const void* gamma, const void* res_grad, void* dx, float* partial, bool first,
+                                        hipStream_t s);
+hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
+                                        bool dst_fp32, hipStream_t s);
 hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void* out, int acc_mode,
                          bool dst_fp32, float* ws, hipStream_t s);
 hipError_t launch_f32_to_elem(uint64_t n, const float* src, void* dst, hipStream_t s);

@@ -137,6 +137,151 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_bwd_dx_kernel(
   }
 }
 
+// The same dx together with this workgroup's share of the parameter gradients: dgamma = sum_t dout * xhat, dbeta = sum_t
+// dout over the rows the workgroup walks, kept in registers and added at the end to its slice of `partial`
+// ([workgroup][dbeta, dgamma][h], stored instead of added if `first`): x and dout are read once for all three results.
+// The slices of one LayerNorm collect a whole batch; one colsum_final_kernel launch then adds them up.
+// A row belongs to WPR waves (8 * MAXC elements per lane), 4 / WPR rows of a workgroup at a time; the next rows are
+// requested before the sums of the current ones are reduced.  HBM-bound at large T * h, bound by the chain load -
+// reduce - store of a few rows at small ones.  1024 x 1024: 7.2 us against 5.0 + 5.1 + 4.6 for the three launches it
+// replaced in a stage (dx, partial sums, final sums); 256 x 256: 4.0 against 4.3 + 5.1 + 2.2.
+template <int WPR, int MAXC>
+__global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void layernorm_bwd_kernel(
+    int T, int h, const elem_t* __restrict__ dout, const elem_t* __restrict__ x, const float* __restrict__ stats,
+    const elem_t* __restrict__ gamma, const elem_t* __restrict__ res, elem_t* __restrict__ dx,
+    float* __restrict__ partial, int first) {
+  constexpr int GROUPS = WPR > 4 ? 1 : 4 / WPR;       // rows in flight per workgroup
+  constexpr int RED = GROUPS > 1 ? (GROUPS - 1) * 2 * WPR * 64 * MAXC * 8 : 1;
+  __shared__ float2 red[2][GROUPS * WPR];
+  __shared__ __align__(16) float merge[RED];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = wave / WPR;
+  const int pos = tid - grp * (WPR * 64);             // thread within its row
+  const int nch = h >> 3, step = gridDim.x * GROUPS;
+  constexpr bool AHEAD = MAXC <= 2;                   // registers for the next row beside the current one
+  struct Row { elemx8 x[MAXC], d[MAXC], r[MAXC]; float mean, rstd; };
+  elemx8 gv[MAXC];
+  float a_g[MAXC][8], a_b[MAXC][8];
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) {
+    gv[c] = elemx8{};
+    if (c * (WPR * 64) + pos < nch) gv[c] = *reinterpret_cast<const elemx8*>(gamma + (c * (WPR * 64) + pos) * 8);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) a_g[c][e] = a_b[c][e] = 0.f;
+  }
+  auto load = [&](Row& w, int row) {                  // rows and columns that do not exist: zeros
+    const bool live = row < T;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c) {
+      const int ch = c * (WPR * 64) + pos;
+      w.x[c] = w.d[c] = w.r[c] = elemx8{};
+      if (live && ch < nch) {
+        const int64_t o = (int64_t)row * h + ch * 8;
+        w.x[c] = *reinterpret_cast<const elemx8*>(x + o);
+        w.d[c] = *reinterpret_cast<const elemx8*>(dout + o);
+        if (res) w.r[c] = *reinterpret_cast<const elemx8*>(res + o);
+      }
+    }
+    w.mean = live ? stats[2 * (int64_t)row] : 0.f;
+    w.rstd = live ? stats[2 * (int64_t)row + 1] : 0.f;
+  };
+  int row = blockIdx.x * GROUPS + grp;
+  Row w, next;
+  if (AHEAD) load(next, row);
+  // the same number of rounds for all rows of the workgroup: rows past the end hold zeros and store nothing
+  const int rounds = (T - (int)blockIdx.x * GROUPS + step - 1) / step;
+  for (int it = 0; it < rounds; ++it, row += step) {
+    if (AHEAD) {
+      w = next;
+      if (it + 1 < rounds) load(next, row + step);
+    } else {
+      load(w, row);
+    }
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int c = 0; c < MAXC; ++c)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {                    // d is 0 where a column does not exist
+        const float d = (float)w.d[c][e], dxh = d * (float)gv[c][e];
+        const float xh = ((float)w.x[c][e] - w.mean) * w.rstd;
+        s1 += dxh;
+        s2 += dxh * xh;
+        a_b[c][e] += d;
+        a_g[c][e] += d * xh;
+      }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if (WPR > 1) {
+      if (lane == 0) red[it & 1][wave] = make_float2(s1, s2);
+      __syncthreads();
+      s1 = s2 = 0.f;
+#pragma unroll
+      for (int q = 0; q < WPR; ++q) {
+        s1 += red[it & 1][grp * WPR + q].x;
+        s2 += red[it & 1][grp * WPR + q].y;
+      }
+    }
+    const float m1 = s1 / (float)h, m2 = s2 / (float)h;
+    if (row < T) {
+#pragma unroll
+      for (int c = 0; c < MAXC; ++c) {
+        const int ch = c * (WPR * 64) + pos;
+        if (ch < nch) {
+          elemx8 o;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float dxh = (float)w.d[c][e] * (float)gv[c][e];
+            const float xh = ((float)w.x[c][e] - w.mean) * w.rstd;
+            float r = w.rstd * (dxh - m1 - xh * m2);
+            if (res) r += (float)w.r[c][e];
+            o[e] = (elem_t)r;
+          }
+          *reinterpret_cast<elemx8*>(dx + (int64_t)row * h + ch * 8) = o;
+        }
+      }
+    }
+  }
+  // rows of a workgroup that ran side by side: groups 1.. hand their sums to group 0, in a fixed order
+  if (GROUPS > 1) {
+    constexpr int STRIDE = WPR * 64;
+    if (grp > 0) {
+#pragma unroll
+      for (int c = 0; c < MAXC; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          merge[(((grp - 1) * 2 + 0) * MAXC * 8 + c * 8 + e) * STRIDE + pos] = a_b[c][e];
+          merge[(((grp - 1) * 2 + 1) * MAXC * 8 + c * 8 + e) * STRIDE + pos] = a_g[c][e];
+        }
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int q = 0; q < GROUPS - 1; ++q)
+#pragma unroll
+      for (int c = 0; c < MAXC; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          a_b[c][e] += merge[((q * 2 + 0) * MAXC * 8 + c * 8 + e) * STRIDE + pos];
+          a_g[c][e] += merge[((q * 2 + 1) * MAXC * 8 + c * 8 + e) * STRIDE + pos];
+        }
+  }
+  float* p = partial + (int64_t)blockIdx.x * 2 * h;
+#pragma unroll
+  for (int c = 0; c < MAXC; ++c) {
+    const int ch = c * (WPR * 64) + pos;
+    if (ch >= nch) continue;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      floatx4* pb = reinterpret_cast<floatx4*>(p + ch * 8 + 4 * q);
+      floatx4* pg = reinterpret_cast<floatx4*>(p + h + ch * 8 + 4 * q);
+      floatx4 b = {a_b[c][4 * q], a_b[c][4 * q + 1], a_b[c][4 * q + 2], a_b[c][4 * q + 3]};
+      floatx4 gsum = {a_g[c][4 * q], a_g[c][4 * q + 1], a_g[c][4 * q + 2], a_g[c][4 * q + 3]};
+      if (!first) { b += *pb; gsum += *pg; }
+      *pb = b;
+      *pg = gsum;
+    }
+  }
+}
+
 // Column partial sums over a block of 64 rows.  Each wave owns 512 columns (8 per lane) of
 // a 16-row quarter of the block; quarters are combined through LDS.  MODE 0: sum y.
 // MODE 1: sum y and sum y * xhat with xhat = (x - mean) * rstd (LayerNorm gain gradient).
@@ -354,6 +499,39 @@ hipError_t launch_layernorm_fwd(int64_t T, int64_t h, const void* x, const void*
   return hipGetLastError();
 }
 
+// Workgroups of layernorm_bwd_kernel, i.e. slices of its partial sums: a row per wave (group), at most one workgroup per
+// CU (128, 256, 512 and 1024 measured in whole batches of h = 1024 to 10240: 256 and 512 the same, 128 and 1024 up to 1 %
+// slower; 256 needs half the memory).
+static int ln_waves_per_row(int64_t h) { return h <= 1024 ? 1 : h <= 2048 ? 2 : h <= 8192 ? 4 : 8; }
+int layernorm_bwd_slices(int64_t T, int64_t h) {
+  const int64_t rows = std::max(1, 4 / ln_waves_per_row(h));
+  return (int)std::min<int64_t>(256, (T + rows - 1) / rows);
+}
+hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, const void* x, const float* stats,
+                                        const void* gamma, const void* res_grad, void* dx, float* partial, bool first,
+                                        hipStream_t s) {
+  const dim3 grid(layernorm_bwd_slices(T, h));
+#define AXONN_LN(WPR, MAXC)                                                                               \
+  hipLaunchKernelGGL((layernorm_bwd_kernel<WPR, MAXC>), grid, dim3(WPR > 4 ? 64 * WPR : 256), 0, s, (int)T, (int)h, \
+                     (const elem_t*)dout, (const elem_t*)x, stats, (const elem_t*)gamma, (const elem_t*)res_grad, (elem_t*)dx, \
+                     partial, first ? 1 : 0)
+  if (h <= 512) AXONN_LN(1, 1);
+  else if (h <= 1024) AXONN_LN(1, 2);
+  else if (h <= 2048) AXONN_LN(2, 2);
+  else if (h <= 4096) AXONN_LN(4, 2);
+  else if (h <= 6144) AXONN_LN(4, 3);
+  else if (h <= 8192) AXONN_LN(4, 4);
+  else if (h <= 16384) AXONN_LN(8, 4);
+  else return hipErrorInvalidValue;
+#undef AXONN_LN
+  return hipGetLastError();
+}
+hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
+                                        bool dst_fp32, hipStream_t s) {
+  hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, layernorm_bwd_slices(T, h),
+                     (int)h, partial, dbeta, dgamma, 1, dst_fp32 ? 1 : 0);
+  return hipGetLastError();
+}
 hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const void* x,
                                 const float* stats, const void* gamma, const void* res_grad,
                                 void* dx, void* dgamma, void* dbeta, int acc_mode, bool dst_fp32,

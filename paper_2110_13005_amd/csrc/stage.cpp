@@ -176,7 +176,7 @@ struct axonn_head {
   char* ws_base = nullptr;
   uint64_t ws_bytes = 0;
   elem_t *a = nullptr, *logits = nullptr, *da = nullptr;
-  float *stats = nullptr, *token_loss = nullptr, *red_ws = nullptr;
+  float *stats = nullptr, *token_loss = nullptr, *ln_part = nullptr;
   int count = 0;       // microbatches since zero_grad
 };
 
@@ -195,7 +195,7 @@ struct axonn_stage {
   char* ws_base = nullptr;
   uint64_t ws_bytes = 0;
   elem_t *dw = nullptr, *dattn = nullptr, *du = nullptr;
-  float *delta = nullptr, *red_ws = nullptr, *wgrad_red_ws = nullptr;
+  float *delta = nullptr, *ln_part = nullptr, *wgrad_red_ws = nullptr;
   // activation checkpointing: shared activation sets (empty when cfg.ckpt_stride == 0)
   std::vector<ActSet> fwd_sets, regen_sets;
   unsigned fwd_set_rr = 0, regen_rr = 0;
@@ -267,14 +267,19 @@ int ln_fwd(int64_t T, int64_t h, const void* x, const void* g, const void* b, fl
   ProfScope ps(PC_LN_FWD, s);
   return check_launch(launch_layernorm_fwd(T, h, x, g, b, eps, out, out_lo, stats, s), "layernorm_fwd");
 }
-// The LayerNorm parameter gradients and the bias gradients (column sums) go straight into the
-// gradient accumulators: stored if acc == 0, added otherwise.
-int ln_bwd(axonn_stage* st, int layer, int which_g, int which_b, int64_t T, int64_t h, const void* dout,
-           const void* x, const float* stats, const void* g, const void* res, void* dx, int acc, hipStream_t s) {
+// LayerNorm backward of layer `layer` (which: 0 the first, 1 the second).  The parameter gradients of a batch collect in
+// the LayerNorm's slices of st->ln_part (acc == 0: the batch's first microbatch) and are stored in the gradient
+// accumulators behind the batch's last one.
+int ln_bwd(axonn_stage* st, int layer, int which, int64_t T, int64_t h, const void* dout, const void* x,
+           const float* stats, const void* res, void* dx, int acc, hipStream_t s) {
   ProfScope ps(PC_LN_BWD, s);
-  return check_launch(launch_layernorm_bwd(T, h, dout, x, stats, g, res, dx, grad_ptr(st, layer, which_g),
-                                           grad_ptr(st, layer, which_b), acc ? 2 : 1,
-                                           st->cfg.grad_accum_fp32 != 0, st->red_ws, s), "layernorm_bwd");
+  const int which_g = which ? P_LN2G : P_LN1G, which_b = which ? P_LN2B : P_LN1B;
+  float* const part = st->ln_part + (uint64_t)(2 * layer + which) * 2 * h * layernorm_bwd_slices(T, h);
+  AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, dout, x, stats, param_ptr(st, layer, which_g), res, dx, part,
+                                                   acc == 0, s), "layernorm_bwd"));
+  if (st->bwd_count + 1 < st->cfg.n_microbatches) return AXONN_OK;
+  return check_launch(launch_layernorm_param_grads(T, h, part, grad_ptr(st, layer, which_g), grad_ptr(st, layer, which_b),
+                                                   st->cfg.grad_accum_fp32 != 0, s), "layernorm parameter gradients");
 }
 int attn_fwd(int b, int sq, int a, int d, const void* qkv, void* o, float* lse, hipStream_t s) {
   ProfScope ps(PC_ATTN_FWD, s);
@@ -373,8 +378,7 @@ int backward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* d_out, i
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, f, a.dpre, f, param_ptr(st, l, P_WFC1), f, st->dw, h,
               nullptr, nullptr, 0, nullptr, 0, 0, s));
   // w = LN2(y); residual: dy = d_in + dLN2
-  AX_TRY(ln_bwd(st, l, P_LN2G, P_LN2B, T, h, st->dw, a.y, a.stats2, param_ptr(st, l, P_LN2G), d_in, a.dy_mid,
-                acc, s));
+  AX_TRY(ln_bwd(st, l, 1, T, h, st->dw, a.y, a.stats2, d_in, a.dy_mid, acc, s));
   // y = x + o Wo + bo
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, h, a.dy_mid, h, param_ptr(st, l, P_WO), h, st->dattn, h,
               nullptr, nullptr, 0, nullptr, 0, 0, s));
@@ -385,8 +389,7 @@ int backward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* d_out, i
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, 3 * h, a.dqkv, 3 * h, param_ptr(st, l, P_WQKV), 3 * h, st->du, h,
               nullptr, nullptr, 0, nullptr, 0, 0, s));
   // u = LN1(x); residual: dx = dy + dLN1
-  AX_TRY(ln_bwd(st, l, P_LN1G, P_LN1B, T, h, st->du, a.x, a.stats1, param_ptr(st, l, P_LN1G), a.dy_mid, d_out,
-                acc, s));
+  AX_TRY(ln_bwd(st, l, 0, T, h, st->du, a.x, a.stats1, a.dy_mid, d_out, acc, s));
   return AXONN_OK;
 }
 
@@ -775,8 +778,10 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s));
   {
     ProfScope ps(PC_LN_BWD, s);
-    AX_TRY(check_launch(launch_layernorm_bwd(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->grads, hd->grads + h,
-                                             acc ? 2 : 1, false, hd->red_ws, s), "layernorm_bwd (head)"));
+    AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part, !acc, s),
+                        "layernorm_bwd (head)"));
+    AX_TRY(check_launch(launch_layernorm_param_grads(T, h, hd->ln_part, hd->grads, hd->grads + h, false, s),
+                        "layernorm parameter gradients (head)"));
   }
   hd->count++;
   return AXONN_OK;
@@ -916,16 +921,16 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   }
   // backward workspace
   const int64_t wide = std::max<int64_t>(f, 3 * h);
-  // partial column sums: of the LayerNorm parameter gradients (gradient chain), and of the bias gradients where
-  // a weight-gradient kernel does not form them itself (weight-gradient stream): one area each
-  const uint64_t e_red = align_up((uint64_t)2 * ((T + 63) / 64) * h * 4, 256);
+  // partial sums of the LayerNorm parameter gradients, which collect over a batch (two LayerNorms per layer; gradient
+  // chain), and of the bias gradients where a weight-gradient kernel does not form them itself (weight-gradient stream)
+  const uint64_t e_red = align_up((uint64_t)2 * cfg->n_layers * 2 * layernorm_bwd_slices(T, h) * h * 4, 256);
   const uint64_t e_wred = align_up((uint64_t)2 * ((T + 63) / 64) * wide * 4, 256);
   st->ws_bytes = 3 * e_th + e_lse + e_red + e_wred;
   CREATE_TRY(hipMalloc((void**)&st->ws_base, st->ws_bytes));
   {
     char* p = st->ws_base;
     st->dw = (elem_t*)p; p += e_th; st->dattn = (elem_t*)p; p += e_th; st->du = (elem_t*)p; p += e_th;
-    st->delta = (float*)p; p += e_lse; st->red_ws = (float*)p; p += e_red;
+    st->delta = (float*)p; p += e_lse; st->ln_part = (float*)p; p += e_red;
     st->wgrad_red_ws = (float*)p; p += e_wred;
   }
   CREATE_TRY(hipEventCreateWithFlags(&st->last_bwd, hipEventDisableTiming));
@@ -1589,7 +1594,7 @@ int axonn_head_create(int32_t device, int32_t vocab, int32_t hidden, int32_t tok
   const uint64_t T = hd->T, h = hd->h, V = hd->vocab;
   hd->n_params = 2 * h + h * V;
   const uint64_t e_th = align_up(T * h * 2, 256), e_tv = align_up(T * V * 2, 256), e_st = align_up(T * 2 * 4, 256),
-                 e_tl = align_up(T * 4, 256), e_red = align_up(2 * ((T + 63) / 64) * h * 4, 256);
+                 e_tl = align_up(T * 4, 256), e_red = align_up((uint64_t)2 * layernorm_bwd_slices(T, h) * h * 4, 256);
   hd->ws_bytes = 2 * e_th + e_tv + e_st + e_tl + e_red;
   hipError_t err = hipMalloc((void**)&hd->params, hd->n_params * sizeof(elem_t));
   if (err == hipSuccess) err = hipMalloc((void**)&hd->grads, hd->n_params * sizeof(elem_t));
@@ -1607,7 +1612,7 @@ int axonn_head_create(int32_t device, int32_t vocab, int32_t hidden, int32_t tok
   }
   char* p = hd->ws_base;
   hd->a = (elem_t*)p; p += e_th; hd->da = (elem_t*)p; p += e_th; hd->logits = (elem_t*)p; p += e_tv;
-  hd->stats = (float*)p; p += e_st; hd->token_loss = (float*)p; p += e_tl; hd->red_ws = (float*)p; p += e_red;
+  hd->stats = (float*)p; p += e_st; hd->token_loss = (float*)p; p += e_tl; hd->ln_part = (float*)p; p += e_red;
   *out = hd;
   return AXONN_OK;
 }

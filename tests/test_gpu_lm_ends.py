@@ -79,6 +79,35 @@ def test_head_loss_and_backward(T, h, V, M):
         hd.close()
 
 
+@pytest.mark.parametrize("T,h", [(8, 8), (2056, 512), (1032, 520), (1048, 1024), (520, 1032), (1032, 2048), (264, 2056),
+                                 (264, 4104), (264, 6152), (72, 8200), (264, 16384)])
+def test_head_layernorm_backward_at_every_row_width(T, h):
+    """The LayerNorm backward kernel splits a row over 1, 2, 4 or 8 waves and holds 1 to 4 chunks per lane, several rows
+    per workgroup or several rounds of rows: dx and the parameter gradients of two microbatches at the edges of that."""
+    import torch
+    rng = np.random.default_rng(T + h)
+    V, M = 16, 2
+    g = snap_elem((1 + 0.1 * rng.standard_normal(h)).astype(np.float32)); bt = snap_elem((0.1 * rng.standard_normal(h)).astype(np.float32))
+    W = snap_elem((rng.standard_normal((h, V)) / np.sqrt(h)).astype(np.float32))
+    hd = HeadHandle(V, h, T, M, g, bt, W)
+    try:
+        tot = None
+        for it in range(M):
+            x = snap_elem(rng.standard_normal((1, T, h), dtype=np.float32)); tg = rng.integers(0, V, (1, T))
+            loss = torch.zeros(1, device="cuda"); dx = torch.zeros(T, h, dtype=B.torch_elem_dtype(), device="cuda")
+            B.axonn_head_forward_backward(hd.h, dev_bf16(x), dev_i32(tg), loss, dx)
+            torch.cuda.synchronize()
+            rl, c = OE.head_loss_forward(x, g, bt, W, tg, EPS, M)
+            rdx, rg = OE.head_loss_backward(c, g, W, tg, M)
+            assert rel_fro(host(dx).reshape(rdx.shape), rdx) <= GRAD_TOL
+            tot = rg if tot is None else {k: tot[k] + rg[k] for k in rg}
+            got = hd.grads_numpy()
+            for k in ("lnf_g", "lnf_b"):
+                assert rel_fro(got[k], tot[k]) <= GRAD_TOL, (k, it)
+    finally:
+        hd.close()
+
+
 @pytest.mark.parametrize("n_streams,ckpt", [(1, 0), (2, 0), (3, 2)])
 def test_whole_model_on_one_stage_message_driven(n_streams, ckpt):
     """A stage that is both the first and the last one: token messages in, losses out, every gradient against the
