@@ -35,39 +35,58 @@ __global__ __launch_bounds__(ENDS_THREADS) void embed_fwd_kernel(
 // One workgroup per token t; it works only if t is the first occurrence of its id, and then adds the
 // rows of all occurrences in token order (fp32), so every table row has exactly one writer.  Rows
 // whose id does not occur are not touched (the caller clears the table before a batch's first pass).
+// The workgroup compares 256 tokens at a time and walks the matches as bit masks: with every thread comparing all
+// tokens one after the other the search took longer than the rows (2048 tokens of h = 1024: 111 -> 18 us).
 __global__ __launch_bounds__(ENDS_THREADS) void embed_bwd_wte_kernel(
     int T, int h, int vocab, const int* __restrict__ tokens, const elem_t* __restrict__ dx,
     elem_t* __restrict__ dwte, int accumulate) {
-  __shared__ int first_flag;
-  const int t = blockIdx.x, tid = threadIdx.x;
+  constexpr int WAVES = ENDS_THREADS / 64, BLOCKS = 4, WINDOW = BLOCKS * ENDS_THREADS;   // tokens per round of masks
+  __shared__ unsigned long long match[BLOCKS * WAVES];
+  const int t = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int id = clamp_id(tokens[t], vocab);
-  if (tid == 0) first_flag = 1;
-  __syncthreads();
-  for (int u = tid; u < t; u += ENDS_THREADS)
-    if (clamp_id(tokens[u], vocab) == id) first_flag = 0;   // benign race: every writer stores 0
-  __syncthreads();
-  if (!first_flag) return;
+  int earlier = 0;
+  for (int u = tid; u < t; u += ENDS_THREADS) earlier |= clamp_id(tokens[u], vocab) == id;
+  if (__syncthreads_or(earlier)) return;
   elem_t* g = dwte + (int64_t)id * h;
-  for (int c = tid * 8; c < h; c += ENDS_THREADS * 8) {
+  for (int c0 = 0; c0 < h; c0 += ENDS_THREADS * 8) {
+    const int c = c0 + tid * 8;
+    const bool live = c < h;
     float acc[8];
-    if (accumulate) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    if (live && accumulate) {
       const elemx8 old = *reinterpret_cast<const elemx8*>(g + c);
 #pragma unroll
       for (int i = 0; i < 8; ++i) acc[i] = (float)old[i];
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
     }
-    for (int u = t; u < T; ++u) {
-      if (clamp_id(tokens[u], vocab) != id) continue;   // uniform over the workgroup
-      const elemx8 v = *reinterpret_cast<const elemx8*>(dx + (int64_t)u * h + c);
+    for (int w0 = t; w0 < T; w0 += WINDOW) {
+      __syncthreads();                                // the masks of the previous window are done with
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[i] += (float)v[i];
+      for (int k = 0; k < BLOCKS; ++k) {
+        const int u = w0 + k * ENDS_THREADS + tid;
+        const unsigned long long m = __ballot(u < T && clamp_id(tokens[min(u, T - 1)], vocab) == id);
+        if (lane == 0) match[k * WAVES + wave] = m;
+      }
+      __syncthreads();
+      for (int k = 0; k < BLOCKS * WAVES; ++k) {
+        unsigned long long m = match[k];
+        while (m) {                                   // the same for every thread of the workgroup
+          const int u = w0 + k * 64 + __ffsll(m) - 1;
+          m &= m - 1;
+          if (live) {
+            const elemx8 v = *reinterpret_cast<const elemx8*>(dx + (int64_t)u * h + c);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) acc[i] += (float)v[i];
+          }
+        }
+      }
     }
-    elemx8 r;
+    if (live) {
+      elemx8 r;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = (elem_t)acc[i];
-    *reinterpret_cast<elemx8*>(g + c) = r;
+      for (int i = 0; i < 8; ++i) r[i] = (elem_t)acc[i];
+      *reinterpret_cast<elemx8*>(g + c) = r;
+    }
   }
 }
 

@@ -211,3 +211,23 @@ def test_first_stage_and_last_stage_separately():
                 assert rel_fro(host(DX[i]).reshape(dx.shape), dx) <= GRAD_TOL
     finally:
         hd.close()
+
+
+@pytest.mark.parametrize("T,h,V", [(8, 8, 1), (1032, 64, 3), (2056, 8, 3000), (264, 2056, 40), (1288, 4104, 7)])
+def test_embedding_table_gradient_repeats_across_windows(T, h, V):
+    """Occurrences of an id further apart than one round of match masks (1024 tokens), every token the same id, rows wider
+    than one pass of a workgroup: sums in token order in fp32, accumulated over two passes, unused rows untouched."""
+    import torch
+    rng = np.random.default_rng(T + h + V)
+    e = EmbedHandle(V, h, T, 1, np.zeros((V, h), np.float32), np.zeros((T, h), np.float32))
+    try:
+        tot = 0.0
+        for _ in range(2):
+            tokens = rng.integers(0, V, (1, T))
+            dx = snap_elem(rng.standard_normal((1, T, h), dtype=np.float32))
+            B.axonn_embed_backward(e.h, dev_i32(tokens), dev_bf16(dx))
+            torch.cuda.synchronize()
+            tot = tot + OE.embedding_backward(dx, tokens, V, T)[0]
+            assert rel_fro(e.grads_numpy()[0], tot) <= 6e-3     # two 16-bit roundings of an fp32 sum
+    finally:
+        e.close()
