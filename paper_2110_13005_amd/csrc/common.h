@@ -225,7 +225,13 @@ struct GemmArgs {
   // ceil(K/64) * N floats of workspace.
   void* colsum;
   float* colsum_ws;
+  // Input gradients without an epilogue operand only: workspace of split_floats floats with which a contraction that is
+  // long for its output may be split over workgroups (null or too small: not split).
+  float* split_ws;
+  int64_t split_floats;
 };
+// Workspace of that kind that the launcher can use for an M x N x K problem (0: it would not split it).
+int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K);
 
 // All return hipError_t of the launch (hipGetLastError) and validate nothing: callers check.
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epilogue, const GemmArgs& g, hipStream_t s);

@@ -15,6 +15,7 @@
 // lane of the result owns one row m and runs of 4 consecutive columns n: epilogue loads and
 // stores are 8-byte (bf16) or 16-byte (fp32) vectors along the contiguous dimension of C.
 #include "common.h"
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 
@@ -1145,9 +1146,12 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
   for (int c = 0; c < NDB; ++c) vb[c] = ring_source<B_KC, BN>(c * W + wave, lane, n0, g.N, ldb, kb[c]);
   const uint32_t sa = A_KC ? BK * 2u : BK * lda * 2u, sb = B_KC ? BK * 2u : BK * ldb * 2u;
   const uint32_t nra = (uint32_t)(A_KC ? g.M : g.K) * lda * 2u, nrb = (uint32_t)(B_KC ? g.N : g.K) * ldb * 2u;
-  const int K = g.K, tps = (K + BK - 1) / BK, nk = tps * g.n_seg;
-  int ld_seg = 0, ld_kin = 0;                          // segment and k-tile within it of the NEXT tile to fetch
-  u32x4 rsa = rsrc_words(g.A_seg[0], nra), rsb = rsrc_words(g.B_seg[0], nrb);
+  // a split launch (gridDim.y parts): part y multiplies its share of the k-tiles and leaves fp32 sums in g.split_ws
+  const int K = g.K, tps = (K + BK - 1) / BK, parts = gridDim.y, part = blockIdx.y;
+  const int k_first = (int)((int64_t)tps * g.n_seg * part / parts);
+  const int nk = (int)((int64_t)tps * g.n_seg * (part + 1) / parts) - k_first;
+  int ld_seg = k_first / tps, ld_kin = k_first % tps;  // segment and k-tile within it of the NEXT tile to fetch
+  u32x4 rsa = rsrc_words(g.A_seg[ld_seg], nra), rsb = rsrc_words(g.B_seg[ld_seg], nrb);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(AXONN_LDS char*)smem + (uint32_t)wave * 1024u;
 
   // Copy instruction c (A's, then B's) of the next k-tile into the stage at byte offset `at`: k beyond the segment and
@@ -1181,7 +1185,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
   // bias and what the epilogue reads at this thread's output positions are fetched beside the k loop
   constexpr int NP = BM * BN / 4 / NT, CW = BN / 4;    // positions per thread (4 columns each), positions per row
   constexpr int NBV = NT % CW == 0 ? 1 : NP;           // one column for all positions of a thread, or one each
-  const bool reads = epi_reads_operand<EPI>(g);
+  const bool reads = epi_reads_operand<EPI>(g) && parts == 1;
   const int64_t ld_side = epi_ld_side<EPI>(g);
   float bv[NBV][4];
   EpiOperand opnd[NP];
@@ -1327,6 +1331,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
       floatx4 x = *reinterpret_cast<const floatx4*>(stage + r * LD + ec);
 #pragma unroll
       for (int q = 1; q < NPART; ++q) x += *reinterpret_cast<const floatx4*>(stage + q * (BM * LD) + r * LD + ec);
+      if (parts > 1) {
+        *reinterpret_cast<floatx4*>(g.split_ws + ((int64_t)part * g.M + m) * g.N + n) = x;
+        continue;
+      }
       float v[4] = {x[0], x[1], x[2], x[3]};
       epi_finish<EPI>(v, bv[NBV == 1 ? 0 : p], opnd[p], g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
     }
@@ -1342,6 +1350,20 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
       elem_t* o = reinterpret_cast<elem_t*>(g.colsum) + n0 + tid;
       *o = (elem_t)(g.accumulate ? (float)*o + v : v);
     }
+  }
+}
+
+// The sums of a split launch's parts, added in their order, through the epilogue: 4 columns per thread.
+template <int EPI>
+__global__ __launch_bounds__(256) void gemm_split_sum_kernel(const GemmArgs g, int parts) {
+  const int64_t n4 = g.N / 4, total = (int64_t)g.M * n4, stride = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+    const int m = (int)(i / n4), n = 4 * (int)(i % n4);
+    floatx4 x = reinterpret_cast<const floatx4*>(g.split_ws)[i];
+    for (int p = 1; p < parts; ++p) x += reinterpret_cast<const floatx4*>(g.split_ws)[(int64_t)p * total + i];
+    float v[4] = {x[0], x[1], x[2], x[3]}, bv[4];
+    load_bias4<EPI>(bv, g, n);
+    epilogue_run<EPI>(v, bv, g, m, n);
   }
 }
 
@@ -1450,10 +1472,10 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
 }
 
 template <bool A_KC, bool B_KC, int TM, int TN, int KG, int NSUB, int NS>
-static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s) {
+static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s, int parts = 1) {
   g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
   g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
-  const dim3 grid(g.tiles_m * g.tiles_n), block(256 * KG);
+  const dim3 grid(g.tiles_m * g.tiles_n, parts), block(256 * KG);
 #define AXONN_GEMM_CASE(E)                                                                      \
   case E:                                                                                       \
     if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
@@ -1554,19 +1576,59 @@ static int choose_ring_tile(int64_t M, int64_t N, int64_t nk) {
 }
 
 template <bool A_KC, bool B_KC>
+static hipError_t launch_ring_tile(int tile, int epi, const GemmArgs& g, hipStream_t s, int parts) {
+  switch (tile) {
+    case RING_64x64: return launch_ring<A_KC, B_KC, 2, 2, 2, 2, 4>(epi, g, s, parts);
+    case RING_128x64: return launch_ring<A_KC, B_KC, 4, 2, 2, 2, 3>(epi, g, s, parts);
+    case RING_128x128: return launch_ring<A_KC, B_KC, 4, 4, 2, 1, 4>(epi, g, s, parts);
+    case RING_128x192: return launch_ring<A_KC, B_KC, 4, 6, 2, 1, 3>(epi, g, s, parts);
+    default: return launch_ring<A_KC, B_KC, 4, 8, 2, 1, 3>(epi, g, s, parts);
+  }
+}
+
+// Split of a long contraction with a small output, for callers that can hand over a workspace (g.split_ws): tile and
+// number of parts (1: not split) with the lowest modelled time.  The parts cost a write and a read of their fp32 sums
+// (4 TB/s) and a launch (5 us).  The LM head's input gradient, 2048 x 1024 x 51200 in four parts of 128 x 256 tiles: 345 -> 205 us.
+struct RingSplit { int tile, parts; };
+static RingSplit choose_split(int64_t M, int64_t N, int64_t K) {
+  const int64_t nk = (K + 63) / 64;
+  RingSplit best = {choose_ring_tile(M, N, nk), 1};
+  if (best.tile < 0) return best;
+  double best_cost = tile_cost(kRingCost[best.tile], M, N, nk);
+  for (int parts = 2; parts <= 16 && nk / parts >= 16; parts *= 2)
+    for (int t = 0; t < RING_TILES; ++t) {
+      const TileCost& c = kRingCost[t];
+      const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * parts;
+      const double cost = tile_cost({1, 1, c.fixed, c.step_few, c.step_full}, tiles, 1, (nk + parts - 1) / parts) +
+                          5.0 + 8.0 * parts * M * N / 4e6;
+      if (cost < best_cost) { best = {t, parts}; best_cost = cost; }
+    }
+  return best;
+}
+int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K) {
+  const RingSplit r = choose_split(M, N, K);
+  return r.parts > 1 ? r.parts * M * N : 0;
+}
+
+template <bool A_KC, bool B_KC>
 static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
   if (!fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) || !fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb))
     return launch_cfg<256, 256, 64, 2, 4, A_KC, B_KC>(epi, g, s);
   const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
-  const int tile = choose_ring_tile(g.M, g.N, nk);
-  switch (tile) {
-    case RING_64x64: return launch_ring<A_KC, B_KC, 2, 2, 2, 2, 4>(epi, g, s);
-    case RING_128x64: return launch_ring<A_KC, B_KC, 4, 2, 2, 2, 3>(epi, g, s);
-    case RING_128x128: return launch_ring<A_KC, B_KC, 4, 4, 2, 1, 4>(epi, g, s);
-    case RING_128x192: return launch_ring<A_KC, B_KC, 4, 6, 2, 1, 3>(epi, g, s);
-    case RING_128x256: return launch_ring<A_KC, B_KC, 4, 8, 2, 1, 3>(epi, g, s);
-    default: break;
+  if constexpr (A_KC && B_KC) {
+    if (g.split_ws && g.n_seg == 1 && epi == EPI_BIAS) {
+      const RingSplit r = choose_split(g.M, g.N, g.K);
+      if (r.parts > 1 && r.parts * (int64_t)g.M * g.N <= g.split_floats) {
+        const hipError_t e = launch_ring_tile<A_KC, B_KC>(r.tile, epi, g, s, r.parts);
+        if (e != hipSuccess) return e;
+        const unsigned blocks = (unsigned)std::min<int64_t>(2048, ((int64_t)g.M * g.N / 4 + 255) / 256);
+        hipLaunchKernelGGL(gemm_split_sum_kernel<EPI_BIAS>, dim3(blocks), dim3(256), 0, s, g, r.parts);
+        return hipGetLastError();
+      }
+    }
   }
+  const int tile = choose_ring_tile(g.M, g.N, nk);
+  if (tile >= 0) return launch_ring_tile<A_KC, B_KC>(tile, epi, g, s, 1);
   switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
     case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);
     case 6: return launch_big<A_KC, B_KC, 6>(epi, g, s);

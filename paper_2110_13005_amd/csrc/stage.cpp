@@ -176,7 +176,8 @@ struct axonn_head {
   char* ws_base = nullptr;
   uint64_t ws_bytes = 0;
   elem_t *a = nullptr, *logits = nullptr, *da = nullptr;
-  float *stats = nullptr, *token_loss = nullptr, *ln_part = nullptr;
+  float *stats = nullptr, *token_loss = nullptr, *ln_part = nullptr, *split_ws = nullptr;
+  int64_t split_floats = 0;   // size of split_ws, the input gradient's (its contraction runs over the vocabulary)
   int count = 0;       // microbatches since zero_grad
 };
 
@@ -249,7 +250,7 @@ static thread_local int t_concurrent = 0;
 
 int gemm(bool a_kc, bool b_kc, int epi, int M, int N, int K, const void* A, int64_t lda,
          const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* res,
-         int64_t ld_res, void* aux, int64_t ld_aux, int accumulate, hipStream_t s) {
+         int64_t ld_res, void* aux, int64_t ld_aux, int accumulate, hipStream_t s, float* split_ws = nullptr, int64_t split_floats = 0) {
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.A_seg[0] = (const elem_t*)A; g.B_seg[0] = (const elem_t*)B; g.C = C; g.n_seg = 1;
@@ -257,6 +258,7 @@ int gemm(bool a_kc, bool b_kc, int epi, int M, int N, int K, const void* A, int6
   g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ld_res = ld_res; g.ld_aux = ld_aux;
   g.M = M; g.N = N; g.K = K; g.accumulate = accumulate; g.tiles_m = g.tiles_n = 0;
   g.concurrent = t_concurrent;
+  g.split_ws = split_ws; g.split_floats = split_floats;
   ProfScope ps(a_kc ? (b_kc ? PC_GEMM_DGRAD : PC_GEMM_FWD) : PC_GEMM_WGRAD, s);
   return check_launch(launch_gemm(a_kc, b_kc, epi, g, s), "gemm");
 }
@@ -775,7 +777,8 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
     const elem_t* B[1] = {hd->logits};
     AX_TRY(gemm_seg(EPI_ACC_BF16, h, V, T, A, h, B, V, 1, hd->grads + 2 * (uint64_t)h, V, nullptr, nullptr, acc, s));
   }
-  AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s));
+  AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s,
+              hd->split_ws, hd->split_floats));
   {
     ProfScope ps(PC_LN_BWD, s);
     AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part, !acc, s),
@@ -1595,7 +1598,8 @@ int axonn_head_create(int32_t device, int32_t vocab, int32_t hidden, int32_t tok
   hd->n_params = 2 * h + h * V;
   const uint64_t e_th = align_up(T * h * 2, 256), e_tv = align_up(T * V * 2, 256), e_st = align_up(T * 2 * 4, 256),
                  e_tl = align_up(T * 4, 256), e_red = align_up((uint64_t)2 * layernorm_bwd_slices(T, h) * h * 4, 256);
-  hd->ws_bytes = 2 * e_th + e_tv + e_st + e_tl + e_red;
+  hd->split_floats = gemm_split_ws_floats(T, h, V);
+  hd->ws_bytes = 2 * e_th + e_tv + e_st + e_tl + e_red + (uint64_t)hd->split_floats * 4;
   hipError_t err = hipMalloc((void**)&hd->params, hd->n_params * sizeof(elem_t));
   if (err == hipSuccess) err = hipMalloc((void**)&hd->grads, hd->n_params * sizeof(elem_t));
   if (err == hipSuccess) err = hipMalloc((void**)&hd->ws_base, hd->ws_bytes);
@@ -1613,6 +1617,7 @@ int axonn_head_create(int32_t device, int32_t vocab, int32_t hidden, int32_t tok
   char* p = hd->ws_base;
   hd->a = (elem_t*)p; p += e_th; hd->da = (elem_t*)p; p += e_th; hd->logits = (elem_t*)p; p += e_tv;
   hd->stats = (float*)p; p += e_st; hd->token_loss = (float*)p; p += e_tl; hd->ln_part = (float*)p; p += e_red;
+  hd->split_ws = hd->split_floats ? (float*)p : nullptr;
   *out = hd;
   return AXONN_OK;
 }

@@ -231,3 +231,29 @@ def test_embedding_table_gradient_repeats_across_windows(T, h, V):
             assert rel_fro(e.grads_numpy()[0], tot) <= 6e-3     # two 16-bit roundings of an fp32 sum
     finally:
         e.close()
+
+
+@pytest.mark.parametrize("T,h,V", [(136, 72, 4104), (1032, 264, 10248), (2056, 520, 20488), (256, 1024, 2048)])
+def test_head_input_gradient_split_over_the_vocabulary(T, h, V):
+    """The head's input gradient is long for its output (its contraction runs over the vocabulary): the parts' fp32 sums and
+    their order, ragged tiles, part boundaries that are no multiple of a stage; twice, and the same bits both times."""
+    import torch
+    rng = np.random.default_rng(T + V)
+    g, bt = np.ones(h, np.float32), np.zeros(h, np.float32)
+    W = snap_elem((0.05 * rng.standard_normal((h, V))).astype(np.float32))
+    hd = HeadHandle(V, h, T, 1, g, bt, W)
+    try:
+        x = snap_elem(rng.standard_normal((1, T, h), dtype=np.float32)); tg = rng.integers(0, V, (1, T))
+        c = OE.head_loss_forward(x, g, bt, W, tg, EPS, 1)[1]
+        rdx = OE.head_loss_backward(c, g, W, tg, 1)[0]
+        got = []
+        for _ in range(2):
+            loss = torch.zeros(1, device="cuda"); dx = torch.zeros(T, h, dtype=B.torch_elem_dtype(), device="cuda")
+            B.axonn_head_zero_grad(hd.h)
+            B.axonn_head_forward_backward(hd.h, dev_bf16(x), dev_i32(tg), loss, dx)
+            torch.cuda.synchronize()
+            got.append(host(dx))
+        assert rel_fro(got[0].reshape(rdx.shape), rdx) <= GRAD_TOL
+        assert np.array_equal(got[0], got[1])
+    finally:
+        hd.close()
