@@ -124,9 +124,8 @@ __device__ __forceinline__ elemx8 global_frag(const elem_t* base, int64_t ld, in
 // own, so XCD x gets ids x, x+8, ...: those are mapped to a contiguous range of (batch, head) pairs, so
 // that the K/V (or Q/dO) rows of a head are fetched into one L2 instead of all eight; inside the range
 // the tiles of rank 0 (the longest-running ones under causal masking) of every head come first.
-__device__ __forceinline__ void attn_block(int n_bh, int& rank, int& bh) {
-  const int id = blockIdx.x;
-  if ((gridDim.x & 7) == 0 && (n_bh & 7) == 0) {
+__device__ __forceinline__ void attn_block(int id, int n_blocks, int n_bh, int& rank, int& bh) {
+  if ((n_blocks & 7) == 0 && (n_bh & 7) == 0) {
     const int per_xcd = n_bh >> 3, j = id >> 3;        // j-th block of XCD id % 8
     rank = j / per_xcd;
     bh = (id & 7) * per_xcd + j % per_xcd;
@@ -201,7 +200,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   elem_t* sV = smem + BKV * LDK;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int rank, bh;
-  attn_block(n_bh, rank, bh);
+  attn_block(blockIdx.x, gridDim.x, n_bh, rank, bh);
   const int qt = (s + 127) / 128 - 1 - rank;  // longest rows first
   const int bi = bh / a, hd = bh % a;
   const int d = EXACT ? D : d_arg;
@@ -396,7 +395,7 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
   }
 }
 
-// dK / dV: grid (ceil(s/128), b*a); wave w owns keys k0 + 32w .. +31 and walks the query tiles at or below the
+// dK / dV: one workgroup per tile of 128 keys and (batch, head); wave w owns keys k0 + 32w .. +31 and walks the query tiles at or below the
 // diagonal.  The Q / dO tiles alternate between two LDS buffers: the next tile is fetched into registers at the top
 // of a step and stored to the other buffer at the end, so one barrier per tile is enough.
 //
@@ -411,21 +410,30 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
 // are written.  The tile on the diagonal takes the same path with the mask applied to every element (a block above
 // the diagonal comes out as zeros; the wave with the lowest keys needs all four blocks anyway).
 // At D = 192 the registers do not hold two blocks: tiles of 64 queries, block by block.
+template <int D>
+struct DkdvLds {
+  static constexpr int BQ = D <= 128 ? 128 : 64, LDQ = BothWaysStride<D>::LD, NBUF = 2;
+  __align__(16) elem_t q[NBUF][BQ * LDQ];
+  __align__(16) elem_t dout[NBUF][BQ * LDQ];
+  __align__(16) float lse[NBUF][BQ];
+  __align__(16) float delta[NBUF][BQ];
+};
 template <int D, bool EXACT>
-__global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
-    int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
-    const float* __restrict__ lse, const float* __restrict__ delta, elem_t* __restrict__ dqkv) {
+__device__ __forceinline__ void attn_bwd_dkdv(
+    DkdvLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv,
+    const elem_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
+    elem_t* __restrict__ dqkv) {
   constexpr bool PAIR = D <= 128;
-  constexpr int BQ = PAIR ? 128 : 64, LDQ = BothWaysStride<D>::LD, DT = D / 32, KK = D / 16;
-  constexpr int NBUF = 2;
-  __shared__ __align__(16) elem_t sQ_[NBUF][BQ * LDQ];
-  __shared__ __align__(16) elem_t sdO_[NBUF][BQ * LDQ];
-  __shared__ __align__(16) float s_lse_[NBUF][BQ];
-  __shared__ __align__(16) float s_delta_[NBUF][BQ];
+  constexpr int BQ = DkdvLds<D>::BQ, LDQ = DkdvLds<D>::LDQ, DT = D / 32, KK = D / 16;
+  constexpr int NBUF = DkdvLds<D>::NBUF;
+  auto& sQ_ = lds.q;
+  auto& sdO_ = lds.dout;
+  auto& s_lse_ = lds.lse;
+  auto& s_delta_ = lds.delta;
   static_assert(NBUF * BQ * LDQ >= 128 * LDQ, "the workgroup's 128 keys fit the tile buffers");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int rank, bh;
-  attn_block(n_bh, rank, bh);                  // key tile `rank` walks n_tiles - rank query tiles: longest first
+  attn_block(id, n_blocks, n_bh, rank, bh);    // key tile `rank` walks n_tiles - rank query tiles: longest first
   const int bi = bh / a, hd = bh % a;
   const int d = EXACT ? D : d_arg;
   const int h = a * d;
@@ -729,19 +737,27 @@ __global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
 // The exact-size kernels also form delta (above) for their 128 queries, from the rows of dO they stage anyway and
 // the same rows of O, and leave it in `delta` for the dK / dV kernel, which then has to run behind this one: no
 // launch of its own for it, and dO is read once less.  The general kernels read `delta` and ignore `o`.
-template <int D, bool EXACT>
-__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
-    int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
-    const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
+template <int D>
+struct DqLds {
+  static constexpr int BKV = 64, LDK = BothWaysStride<D>::LD;
+  __align__(16) elem_t tiles[2 * BKV * LDK];          // K and V tile; at the ends the staged Q, dO and dQ rows
+  float delta[128];
+};
+// FORM_DELTA: delta is formed here, kept, and written out for a dK / dV launch behind this one; else it is read.
+template <int D, bool EXACT, bool FORM_DELTA>
+__device__ __forceinline__ void attn_bwd_dq(
+    DqLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv,
+    const elem_t* __restrict__ o, const elem_t* __restrict__ dout, const float* __restrict__ lse, float* delta,
     elem_t* __restrict__ dqkv) {
-  constexpr int BKV = 64, LDK = BothWaysStride<D>::LD, DT = D / 32, KK = D / 16;
-  __shared__ __align__(16) elem_t smem[2 * BKV * LDK];          // K and V tile; at the ends the staged Q, dO and dQ rows
+  static_assert(EXACT || !FORM_DELTA, "the general kernels read delta");
+  constexpr int BKV = DqLds<D>::BKV, LDK = DqLds<D>::LDK, DT = D / 32, KK = D / 16;
+  elem_t* const smem = lds.tiles;
   static_assert(2 * BKV * LDK >= 128 * (D + 8), "the workgroup's 128 rows fit the tile buffers");
   elem_t* sK = smem;
   elem_t* sV = smem + BKV * LDK;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
   int rank, bh;
-  attn_block(n_bh, rank, bh);
+  attn_block(id, n_blocks, n_bh, rank, bh);
   const int qt = (s + 127) / 128 - 1 - rank;
   const int bi = bh / a, hd = bh % a;
   const int d = EXACT ? D : d_arg;
@@ -755,7 +771,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
   const float scale = rsqrtf((float)d), scale_log2 = kLog2e * scale;
   const float lse_q = (qi < s) ? lse[((int64_t)bi * a + hd) * s + qi] * kLog2e : 0.f;
   float delta_q;
-  __shared__ float s_delta[128];
+  float* const s_delta = lds.delta;
 
   elemx8 qf[KK], dof[KK];
   if (EXACT) {
@@ -768,7 +784,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     r_q.load_buffer(make_rsrc(qb, (uint32_t)(((int64_t)(s - 1) * ld + D) * 2)), Rows::offset0((uint32_t)ld * 2u, tid),
                     (uint32_t)ld * 2u, q0);
     r_do.load_buffer(make_rsrc(dob, o_bytes), o_off0, (uint32_t)h * 2u, q0);
-    r_o.load_buffer(make_rsrc(o + (int64_t)bi * s * h + hd * d, o_bytes), o_off0, (uint32_t)h * 2u, q0);
+    if (FORM_DELTA) r_o.load_buffer(make_rsrc(o + (int64_t)bi * s * h + hd * d, o_bytes), o_off0, (uint32_t)h * 2u, q0);
     r_q.template store<D + 8>(smem, tid);
     __syncthreads();
 #pragma unroll
@@ -776,7 +792,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     __syncthreads();
     r_do.template store<D + 8>(smem, tid);
 #pragma unroll
-    for (int j = 0; j < Rows::NCH; ++j) {
+    for (int j = 0; FORM_DELTA && j < Rows::NCH; ++j) {
       const elemx8 ov = __builtin_bit_cast(elemx8, r_o.r[j]), dv = __builtin_bit_cast(elemx8, r_do.r[j]);
       float p = 0.f;
 #pragma unroll
@@ -792,7 +808,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     __syncthreads();
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) dof[kk] = frag_kcontig(smem + (32 * wave) * (D + 8) + kk * 16, D + 8, lane);
-    delta_q = s_delta[32 * wave + (lane & 31)];
+    delta_q = FORM_DELTA ? s_delta[32 * wave + (lane & 31)] : (qi < s) ? delta[((int64_t)bi * a + hd) * s + qi] : 0.f;
   } else {
     delta_q = (qi < s) ? delta[((int64_t)bi * a + hd) * s + qi] : 0.f;
 #pragma unroll
@@ -886,6 +902,35 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
   }
 }
 
+// ------------------------------------------------------------------- backward kernels
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
+    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
+    const float* __restrict__ lse, const float* __restrict__ delta, elem_t* __restrict__ dqkv) {
+  __shared__ DkdvLds<D> lds;
+  attn_bwd_dkdv<D, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
+}
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
+    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
+    const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
+    elem_t* __restrict__ dqkv) {
+  __shared__ DqLds<D> lds;
+  attn_bwd_dq<D, EXACT, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv);
+}
+// Both at once, for problems whose tiles do not fill the chip: the first half of the workgroups forms dK and dV, the second
+// dQ; delta is there already.  Each half alone is a chain of up to s / 128 (s / 64) tiles per workgroup on a part of the
+// CUs; side by side they take the longer of the two times.
+template <int D, bool EXACT>
+__global__ __launch_bounds__(256) void attn_bwd_both_kernel(
+    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
+    const float* __restrict__ lse, float* delta, elem_t* __restrict__ dqkv) {
+  __shared__ union { DkdvLds<D> dkdv; DqLds<D> dq; } lds;
+  const int n = gridDim.x >> 1, id = blockIdx.x;
+  if (id < n) attn_bwd_dkdv<D, EXACT>(lds.dkdv, id, n, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
+  else attn_bwd_dq<D, EXACT, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv);
+}
+
 // ------------------------------------------------------------------------- launchers
 // d = 64 or 128: the kernels compiled for exactly that head dimension.  Any other multiple of 4 up to 192:
 // the next compiled size with the columns beyond d masked.
@@ -901,6 +946,12 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     else hipLaunchKernelGGL((KERNEL<192, false>), grid, dim3(256), 0, st, __VA_ARGS__);               \
   } while (0)
 
+// dK / dV and dQ as one launch while the workgroups of both find a CU each (the dK / dV one leaves no room for a second in
+// registers and LDS).  delta then has a launch of its own, which the dQ kernel otherwise spares.  Measured, backward of 16
+// heads of 64 x 1024 (128 tiles): 44.3 -> 31.3 us with it; 3 heads of 128 x 200, 2 sequences: 26.0 -> 17.6; 4 heads of 64 x 128,
+// 2 sequences: 14.0 -> 10.2.
+constexpr int kBothMaxTiles = 128;
+
 static bool head_dim_supported(int d) { return d >= 4 && d <= 192 && d % 4 == 0; }
 
 hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, void* o, float* lse,
@@ -915,10 +966,12 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
                                 const float* lse, const void* dout, void* dqkv, float* delta,
                                 hipStream_t st) {
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(((s + 127) / 128) * b * a));
+  const int n_tiles = ((s + 127) / 128) * b * a;
+  const bool both = n_tiles <= kBothMaxTiles;
   // the exact-size dQ kernel (the dispatch's condition for it) forms delta itself and runs first
-  const bool dq_forms_delta = (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
+  const bool dq_forms_delta = !both && (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
   hipError_t e;
+  dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
     AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
     e = hipGetLastError();
@@ -931,6 +984,11 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
                      (const elem_t*)o, (const elem_t*)dout, delta);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
+  if (both) {
+    grid = dim3(2u * (unsigned)n_tiles);
+    AXONN_ATTN_DISPATCH(attn_bwd_both_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
+    return hipGetLastError();
+  }
   AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -358,6 +358,13 @@ def test_attention_fwd_bwd(b, s, a, d):
     assert np.array_equal(host(o).reshape(b, s, h)[:, 0], v0.astype(np.float64))
 
 
+@pytest.mark.parametrize("b,s,a,d", [(2, 200, 32, 64), (2, 200, 33, 64), (1, 264, 44, 128), (3, 130, 22, 44), (1, 130, 66, 188)])
+def test_attention_around_the_one_launch_backward(b, s, a, d):
+    """Up to 128 tiles of 128 rows the backward runs as one launch for dQ, dK and dV, beyond as two: 128 tiles, and 130 to 132
+    with exact and masked head dimensions."""
+    test_attention_fwd_bwd(b, s, a, d)
+
+
 def test_attention_large_scores_stay_finite():
     """Scores of order +-100: the running-max subtraction must keep exp in range."""
     import torch
