@@ -723,7 +723,7 @@ __global__ __launch_bounds__(256) void gemm_big_kernel(const GemmArgs g) {
 // gemm_dma_kernel: the tiling of gemm_big_kernel (256 x 32*TN x 64 block, 2 x 2 waves, one wave per
 // SIMD, 128 x 16*TN wave tile of 16x16x32 MFMAs) with the tiles copied global -> LDS by the memory
 // pipeline itself (`buffer_load_dwordx4 ... lds`): no staging registers, no LDS store instructions, no
-// vector ALU work for addresses inside the loop.  For problems whose K is a multiple of 64.
+// vector ALU work for addresses inside the loop.
 //
 // One such instruction writes the 64 chunks of 16 bytes its lanes fetch to 1 KB of consecutive LDS
 // bytes in lane order (M0 holds the start), so the LDS tiles cannot be padded; instead the lanes
@@ -814,7 +814,11 @@ constexpr int frag_item(bool a_early, int tn, int phase, int k) {
   return k < tn ? k + 1 : k + 4;      // b0 .. b(tn-1), then a4 .. a7
 }
 
-template <bool A_KC, bool B_KC, int EPI, int TN>
+// TAIL: K is not a multiple of 64.  The chunks of a segment's last k-tile that lie beyond it are fetched from out of range
+// (zeros): their lanes' offsets are switched over in front of that tile's copies and back behind them.  (A lane whose
+// row is outside the matrix then fetches the operand's first elements instead of zeros, for a result nobody stores.)
+// Two layers of h = 4512 (70.5 k-tiles), whole batches: 64.3 ms with the register-staged kernel for them, 63.6 with this.
+template <bool A_KC, bool B_KC, int EPI, int TN, bool TAIL>
 __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
   constexpr int BM = 256, BN = 32 * TN, BK = 64, TM = 8;
   constexpr int NCA = 8, NCB = B_KC ? TN : 8;     // copy instructions per wave and tile
@@ -902,11 +906,23 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
     fb_off[0] = (uint32_t)(2 * SA + (4 * fg + (ft >> 2)) * KS_BLOCK + (wn * 16 * TN + 4 * (ft & 3)) * 2);
   }
 
-  const int tps = g.K / BK;               // k-tiles per segment (K is a multiple of BK)
+  const int tps = TAIL ? (g.K + BK - 1) / BK : g.K / BK;     // k-tiles per segment
   const int nk = tps * g.n_seg;
   int ld_seg = 0, ld_kin = 0;             // segment and k-tile within it of the NEXT tile to fetch
   u32x4 rsa = rsrc_words(g.A_seg[0], nra), rsb = rsrc_words(g.B_seg[0], nrb);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(AXONN_LDS char*)smem;
+
+  const int k_tail = g.K % BK;            // TAIL: length of a segment's last k-tile
+  bool in_tail = false;
+  auto switch_tail = [&]() {
+    in_tail = !in_tail;
+    const int q8 = ((lane & 7) ^ (((wave & 1) << 2) + (lane >> 4))) * 8, kl = wave + 4 * (lane >> 5);
+#pragma unroll
+    for (int c = 0; c < NCA; ++c) va[c] ^= (A_KC ? q8 : 8 * c + kl) >= k_tail ? kOutOfRange : 0u;
+#pragma unroll
+    for (int c = 0; c < NCB; ++c) vb[c] ^= (B_KC ? q8 : 8 * c + kl) >= k_tail ? kOutOfRange : 0u;
+  };
+  if (TAIL && tps == 1) switch_tail();
 
   // Copy instruction d (A chunks first, then B chunks) of the next tile into stage `buf`.
 #define AXONN_DMA(buf, d)                                                                      \
@@ -937,7 +953,8 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
     const int sidx = live ? ld_seg : 0;                                                        \
     rsa = rsrc_words(g.A_seg[sidx], live ? nra : 0u);                                          \
     rsb = rsrc_words(g.B_seg[sidx], live ? nrb : 0u);                                          \
-  }
+  }                                                                                            \
+  if (TAIL && (ld_kin == tps - 1) != in_tail) switch_tail();
 #define AXONN_FRAG(F, buf, kk, f)                                                              \
   if ((f) == 0 || (f) > TN) {                                                                  \
     const int i = (f) == 0 ? 0 : (f) - TN;                                                     \
@@ -1435,7 +1452,7 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   g.tiles_m = (g.M + 255) / 256;
   g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
   const dim3 grid(g.tiles_m * g.tiles_n), block(256);
-  // The kernel with copies by the memory pipeline needs whole k tiles.  It is the faster one for every layout
+  // The kernel with copies by the memory pipeline is the faster one for every layout
   // with a 16-bit result (single launches of the 12B-shape problems: forward +11 %, input gradients +4 %, weight
   // gradients +8 % over the register-staged kernel; whole batches of the 12B / 24B / 100B stage shapes 3.4 / 3.3 /
   // 4.3 % faster than with the previous choice); with an fp32 read-modify-write result the register-staged
@@ -1446,12 +1463,14 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   const int64_t mask_set = g_tune_copy_mask.load();
   const int64_t dma_mask = mask_set >= 0 ? mask_set : 7;
   const int dma_bit = A_KC ? (B_KC ? 0 : 1) : (epi == EPI_ACC_F32 ? 3 : 2);
-  const bool use_dma = ((dma_mask >> dma_bit) & 1) && g.K % 64 == 0;
+  const bool use_dma = (dma_mask >> dma_bit) & 1;
 #define AXONN_GEMM_CASE(E)                                                                      \
   case E:                                                                                       \
     if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
-      if (use_dma)                                                                              \
-        hipLaunchKernelGGL((gemm_dma_kernel<A_KC, B_KC, E, TN>), grid, block, 0, s, g);         \
+      if (use_dma && g.K % 64 == 0)                                                             \
+        hipLaunchKernelGGL((gemm_dma_kernel<A_KC, B_KC, E, TN, false>), grid, block, 0, s, g);  \
+      else if (use_dma)                                                                         \
+        hipLaunchKernelGGL((gemm_dma_kernel<A_KC, B_KC, E, TN, true>), grid, block, 0, s, g);   \
       else                                                                                      \
         hipLaunchKernelGGL((gemm_big_kernel<A_KC, B_KC, E, TN>), grid, block, 0, s, g);         \
       break;                                                                                    \

@@ -192,8 +192,8 @@ def test_gemm_big_tile_strided_operands():
 def test_gemm_both_large_kernels_all_layouts_and_results(mask, min_tiles):
     """The large-problem kernel whose tiles are copied by the memory pipeline serves three of the four (layout, result
     type) classes by default and the register-staged one the fourth; axonn_tuning fixes the choice, so every GEMM
-    case of this file runs again through the copying kernel wherever it applies (K a multiple of 64: mask 15) and
-    through the register-staged kernel everywhere (mask 0), with the threshold lowered so that the small ragged
+    case of this file runs again through the copying kernel (mask 15; its variant with a short last k-tile where K
+    is no multiple of 64) and through the register-staged kernel everywhere (mask 0), with the threshold lowered so that the small ragged
     shapes reach the large-problem kernels too (all three block widths)."""
     try:
         B.axonn_tuning(B.TUNE_GEMM_COPY_MASK, mask)
