@@ -132,11 +132,14 @@ int axonn_stage_forward(axonn_stage_t* st, int32_t mb_id, const void* x_dev_bf16
                         void* y_dev_bf16, void* hip_stream);
 /* Backward(msg) of Alg. 2: given dL/dy for microbatch mb_id, writes dL/dx to
  * dx_dev_bf16 [b,s,h] (dy is copied, so the caller may recycle its receive buffer), adds
- * the bias and LayerNorm gradients into the accumulators and leaves the microbatch's
- * weight gradients pending (see wgrad_group); the microbatch no longer counts as in
+ * the LayerNorm gradients to the batch's fp32 sums and leaves the microbatch's weight and
+ * bias gradients pending (see wgrad_group); the microbatch no longer counts as in
  * flight.  AXONN_ESTATE if mb_id has no forward in flight.  After the n_microbatches-th
  * backward since the last zero_grad all pending weight gradients are formed and the bf16
- * gradient buffer is final on that stream; before that its contents are unspecified. */
+ * gradient buffer is final on that stream.  Before that its contents are unspecified, except
+ * with grad_accum_fp32 = 0 after a backward that leaves no weight gradients pending
+ * (ckpt_stride > 0, or one that closes a group): it then holds the gradients of the
+ * microbatches so far, and the optimizer calls below accept such a shortened batch. */
 int axonn_stage_backward(axonn_stage_t* st, int32_t mb_id, const void* dy_dev_bf16,
                          void* dx_dev_bf16, void* hip_stream);
 

@@ -256,6 +256,10 @@ hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, 
                                         hipStream_t s);
 hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
                                         bool dst_fp32, hipStream_t s);
+// The same for both LayerNorms of n_layers layers (their slices lie behind one another) in one launch, into a 16-bit
+// gradient buffer: dgamma is the first layer's first one, each shift gradient follows its gain gradient.
+hipError_t launch_layernorm_param_grads_all(int64_t T, int64_t h, int n_layers, const float* partial, void* dgamma,
+                                            int64_t layer_stride, int64_t second_offset, hipStream_t s);
 hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void* out, int acc_mode,
                          bool dst_fp32, float* ws, hipStream_t s);
 hipError_t launch_f32_to_elem(uint64_t n, const float* src, void* dst, hipStream_t s);

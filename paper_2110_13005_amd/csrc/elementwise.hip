@@ -360,20 +360,25 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(
 // fp32 (acc_mode 0), or stored into / added to gradient vectors of the accumulation type
 // (acc_mode 1 / 2; dst_fp32 says whether that type is fp32 or bf16).
 template <typename T>
-__device__ __forceinline__ void put_sum(T* dst, int n, float v, int acc_mode) {
+__device__ __forceinline__ void put_sum(T* dst, int64_t n, float v, int acc_mode) {
   dst[n] = (T)((acc_mode == 2 ? (float)dst[n] : 0.f) + v);
 }
 // A block owns 64 columns; its four wavefronts each sum every fourth row block (loads independent of one
 // another, so they are all in flight at once), and the four sums are combined through LDS in a fixed order.
+// gridDim.y problems of one size: their partial sums lie behind one another, the results of an even and the odd one
+// after it `odd_stride` elements apart and such pairs `pair_stride`.
 template <int KSUM>
 __global__ __launch_bounds__(256) void colsum_final_kernel(int nrb, int N,
                                                            const float* __restrict__ partial,
                                                            void* __restrict__ out0,
                                                            void* __restrict__ out1,
-                                                           int acc_mode, int dst_fp32) {
+                                                           int acc_mode, int dst_fp32,
+                                                           int64_t pair_stride, int64_t odd_stride) {
   __shared__ float red[3][KSUM][64];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const int n = blockIdx.x * 64 + lane;
+  const int64_t o = (blockIdx.y >> 1) * pair_stride + (blockIdx.y & 1) * odd_stride + n;
+  partial += (int64_t)blockIdx.y * nrb * KSUM * N;
   float s0 = 0.f, s1 = 0.f;
   if (n < N) {
 #pragma unroll 8
@@ -391,11 +396,11 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(int nrb, int N,
   s0 = ((s0 + red[0][0][lane]) + red[1][0][lane]) + red[2][0][lane];
   if (KSUM == 2) s1 = ((s1 + red[0][KSUM - 1][lane]) + red[1][KSUM - 1][lane]) + red[2][KSUM - 1][lane];
   if (acc_mode == 0 || dst_fp32) {
-    put_sum(reinterpret_cast<float*>(out0), n, s0, acc_mode);
-    if (KSUM == 2) put_sum(reinterpret_cast<float*>(out1), n, s1, acc_mode);
+    put_sum(reinterpret_cast<float*>(out0), o, s0, acc_mode);
+    if (KSUM == 2) put_sum(reinterpret_cast<float*>(out1), o, s1, acc_mode);
   } else {
-    put_sum(reinterpret_cast<elem_t*>(out0), n, s0, acc_mode);
-    if (KSUM == 2) put_sum(reinterpret_cast<elem_t*>(out1), n, s1, acc_mode);
+    put_sum(reinterpret_cast<elem_t*>(out0), o, s0, acc_mode);
+    if (KSUM == 2) put_sum(reinterpret_cast<elem_t*>(out1), o, s1, acc_mode);
   }
 }
 
@@ -529,7 +534,13 @@ hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, 
 hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
                                         bool dst_fp32, hipStream_t s) {
   hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, layernorm_bwd_slices(T, h),
-                     (int)h, partial, dbeta, dgamma, 1, dst_fp32 ? 1 : 0);
+                     (int)h, partial, dbeta, dgamma, 1, dst_fp32 ? 1 : 0, 0, 0);
+  return hipGetLastError();
+}
+hipError_t launch_layernorm_param_grads_all(int64_t T, int64_t h, int n_layers, const float* partial, void* dgamma,
+                                            int64_t layer_stride, int64_t second_offset, hipStream_t s) {
+  hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64), (unsigned)(2 * n_layers)), dim3(256), 0, s,
+                     layernorm_bwd_slices(T, h), (int)h, partial, (elem_t*)dgamma + h, dgamma, 1, 0, layer_stride, second_offset);
   return hipGetLastError();
 }
 hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const void* x,
@@ -548,7 +559,7 @@ hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const vo
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, nrb,
-                     (int)h, (const float*)ws, dbeta, dgamma, acc_mode, dst_fp32 ? 1 : 0);
+                     (int)h, (const float*)ws, dbeta, dgamma, acc_mode, dst_fp32 ? 1 : 0, 0, 0);
   return hipGetLastError();
 }
 #undef AXONN_LN_DISPATCH
@@ -562,7 +573,7 @@ hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void*
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(colsum_final_kernel<1>, dim3((unsigned)((N + 63) / 64)), dim3(256), 0, s, nrb,
-                     (int)N, (const float*)ws, out, (void*)nullptr, acc_mode, dst_fp32 ? 1 : 0);
+                     (int)N, (const float*)ws, out, (void*)nullptr, acc_mode, dst_fp32 ? 1 : 0, 0, 0);
   return hipGetLastError();
 }
 

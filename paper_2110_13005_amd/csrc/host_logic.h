@@ -95,6 +95,11 @@ inline int wgrad_action(bool last_of_batch, int group, int n_awaiting) {
   if (last_of_batch) return WGRAD_FLUSH_FINAL;
   return (group > 0 && n_awaiting >= group) ? WGRAD_FLUSH : WGRAD_NONE;
 }
+// Are the gradients of every backward so far complete once the next one's work is queued (`n_awaiting` slots wait
+// before it)?  With checkpointing its weight gradients go with the chain; otherwise if a group closes.
+inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting) {
+  return ckpt || wgrad_action(last_of_batch, group, n_awaiting + 1) != WGRAD_NONE;
+}
 
 // ------------------------------------------------------------------------------ messages
 // A message is admissible if its work may start now: a forward needs a pipeline place and must not be in

@@ -271,7 +271,7 @@ int ln_fwd(int64_t T, int64_t h, const void* x, const void* g, const void* b, fl
 }
 // LayerNorm backward of layer `layer` (which: 0 the first, 1 the second).  The parameter gradients of a batch collect in
 // the LayerNorm's slices of st->ln_part (acc == 0: the batch's first microbatch) and are stored in the gradient
-// accumulators behind the batch's last one.
+// accumulators behind the batch's last one (and by store_ln_grads).
 int ln_bwd(axonn_stage* st, int layer, int which, int64_t T, int64_t h, const void* dout, const void* x,
            const float* stats, const void* res, void* dx, int acc, hipStream_t s) {
   ProfScope ps(PC_LN_BWD, s);
@@ -282,6 +282,15 @@ int ln_bwd(axonn_stage* st, int layer, int which, int64_t T, int64_t h, const vo
   if (st->bwd_count + 1 < st->cfg.n_microbatches) return AXONN_OK;
   return check_launch(launch_layernorm_param_grads(T, h, part, grad_ptr(st, layer, which_g), grad_ptr(st, layer, which_b),
                                                    st->cfg.grad_accum_fp32 != 0, s), "layernorm parameter gradients");
+}
+// Stores what all LayerNorms have collected so far in the 16-bit gradient buffer.
+int store_ln_grads(axonn_stage* st, hipStream_t s) {
+  ProfScope ps(PC_LN_BWD, s);
+  const uint64_t ln1 = st->tensors[P_LN1G].offset, ln2 = st->tensors[P_LN2G].offset;
+  const uint64_t layer = st->cfg.n_layers > 1 ? st->tensors[kTensorsPerLayer + P_LN1G].offset - ln1 : 0;
+  return check_launch(launch_layernorm_param_grads_all(st->T, st->h, st->cfg.n_layers, st->ln_part, st->grads + ln1,
+                                                       (int64_t)layer, (int64_t)(ln2 - ln1), s),
+                      "layernorm parameter gradients");
 }
 int attn_fwd(int b, int sq, int a, int d, const void* qkv, void* o, float* lse, hipStream_t s) {
   ProfScope ps(PC_ATTN_FWD, s);
@@ -603,6 +612,11 @@ int do_backward(axonn_stage* st, int mb_id, const void* dy, void* dx, hipStream_
   const bool last = st->bwd_count + 1 == st->cfg.n_microbatches;
   if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, dy, dx, acc, last, s, ws));
   else AX_TRY(backward_layers(st, *slot, dy, dx, acc, last, s));
+  // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
+  // the microbatches so far, the LayerNorms' too.
+  if (st->bwd_count + 1 < st->cfg.n_microbatches && !st->cfg.grad_accum_fp32 &&
+      host::gradients_complete(ckpt, last, st->cfg.wgrad_group, slots_in_state(st, SLOT_AWAIT_WGRAD)))
+    AX_TRY(store_ln_grads(st, s));
   st->bwd_count++;
   HIP_TRY(hipEventRecord(slot->dgrad_done, s));
   HIP_TRY(hipEventRecord(st->last_bwd, s));

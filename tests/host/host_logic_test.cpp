@@ -251,6 +251,9 @@ void test_wgrad_groups() {
   CHECK(tight.wgrad_passes.size() >= 3);
   CHECK(wgrad_action(false, 0, 100) == WGRAD_NONE && wgrad_action(false, 2, 1) == WGRAD_NONE);
   CHECK(wgrad_action(false, 2, 2) == WGRAD_FLUSH && wgrad_action(true, 0, 1) == WGRAD_FLUSH_FINAL);
+  CHECK(gradients_complete(true, false, 0, 0) && gradients_complete(false, true, 0, 3));
+  CHECK(gradients_complete(false, false, 1, 0) && gradients_complete(false, false, 2, 1));
+  CHECK(!gradients_complete(false, false, 0, 3) && !gradients_complete(false, false, 2, 0));
 }
 
 void test_bucket_plan(unsigned seed) {

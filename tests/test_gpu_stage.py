@@ -408,3 +408,33 @@ def test_stage_batch_then_optimizer_step():
         assert np.array_equal(host(st.params), oracle.half_round(arrs[0], B.ELEM).astype(np.float64))
     for p in ptrs:
         B.axonn_pinned_free(p)
+
+
+@pytest.mark.parametrize("done,opts", [(2, dict(wgrad_group=1)), (2, dict(wgrad_group=2)), (1, dict(ckpt_stride=1)),
+                                       (3, dict(ckpt_stride=2)), (1, dict(wgrad_group=1, pipeline_limit=1))])
+def test_batch_cut_short_where_no_weight_gradients_are_pending(done, opts):
+    """A batch of fewer microbatches than n_microbatches, after a full one: every gradient in the 16-bit buffer, the
+    LayerNorms' among them, is that of the short batch, and the optimizer step takes exactly those."""
+    import torch
+    sh = StageShape(2, 192, 3, 96, 2, 4)
+    layers, xs, dys = make_stage_inputs(sh, seed=4, perturb=True)
+    pairs = [m for i in range(4) for m in ((0, i), (1, i))]
+    with Stage(sh, grad_accum_fp32=0, **opts) as st:
+        st.load_params(layers)
+        run_direct(st, xs, dys, pairs)
+        outs, dxs, grads = run_direct(st, xs[::-1][:done], dys[::-1][:done], pairs[:2 * done])
+        check_batch(outs, dxs, grads, oracle.stage_batch(xs[::-1][:done], dys[::-1][:done], layers, sh.n_heads, EPS))
+        n = st.n_params
+        ptrs, arrs = zip(*[_pinned_array(n) for _ in range(3)])
+        try:
+            theta0 = st.params.float().cpu().numpy()
+            arrs[0][:] = theta0; arrs[1][:] = 0; arrs[2][:] = 0
+            B.axonn_stage_optimizer_attach(st.handle, *ptrs, n, 1 << 18)
+            assert B.axonn_stage_count_nonfinite_grads(st.handle, None) == 0
+            B.axonn_stage_optimizer_step(st.handle, 1e-3, 0.9, 0.999, 1e-8, 0.01, 1, 1.0 / done)
+            g16 = np.concatenate([grads[int(k.split(".")[0][5:])][k.split(".")[1]].ravel() for k in st.layout])
+            rt = oracle.adam_step(theta0, 0 * theta0, 0 * theta0, g16, 1e-3, 0.9, 0.999, 1e-8, 0.01, 1, 1.0 / done, half=B.ELEM)[0]
+            assert rel_fro(arrs[0], rt) <= ADAM_TOL
+        finally:
+            for p in ptrs:
+                B.axonn_pinned_free(p)

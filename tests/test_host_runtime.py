@@ -42,6 +42,6 @@ def test_stage_runtime_takes_its_decisions_from_the_tested_header():
     """stage.cpp must call the functions the CPU tests exercise, not private copies of them."""
     src = open(os.path.join(os.path.dirname(HERE), "paper_2110_13005_amd", "csrc", "stage.cpp")).read()
     for fn in ("host::choose_message", "host::admit_forward", "host::commit_forward", "host::admit_backward",
-               "host::commit_backward", "host::wgrad_action", "host::release_awaiting", "host::check_post",
-               "host::stream_index", "host::WaitClock", "host::bucket_plan", "host::chunk_span", "host::lowest_layer"):
+               "host::commit_backward", "host::wgrad_action", "host::gradients_complete", "host::release_awaiting",
+               "host::check_post", "host::stream_index", "host::WaitClock", "host::bucket_plan", "host::chunk_span", "host::lowest_layer"):
         assert fn in src, fn
