@@ -195,8 +195,8 @@ int axonn_stage_dispatch_log(const axonn_stage_t* st, int32_t* out, int32_t capa
  * Offloaded, bucketed Adam (Sec. 5.2): only theta16 and grad16 live on the GPU; the fp32
  * master weights theta and the two Adam moments live in pinned host memory.  A plain step
  * is one kernel that reads and writes the host arrays over the link.  A step overlapped with
- * the backward tail, and host memory that the GPU cannot address (not pinned, or not 16-byte
- * aligned), fetch bucket after bucket (bucket_elems parameters) into reusable device buffers,
+ * the backward tail, and host memory that the GPU cannot address (an array that is not pinned,
+ * not 16-byte aligned or not inside one allocation), fetch bucket after bucket (bucket_elems parameters) into reusable device buffers,
  * update it and write it back; H2D copy, update kernel and D2H copy of consecutive buckets
  * overlap on three streams.
  * Per element (Sec. 2.1 mixed precision; Kingma & Ba; decoupled decay):
@@ -219,8 +219,8 @@ int axonn_offload_adam_destroy(axonn_offload_adam_t* opt);
 /* One full step (all buckets).  The work starts after everything already in hip_stream;
  * the call returns when the step is complete and the host arrays hold the new state (it
  * synchronizes hip_stream).  step t >= 1.  If a HIP call fails in the middle of the step, the step's streams are drained
- * before the error is returned (nothing is in flight any more); the buckets processed up to then are updated, the
- * others untouched, and the message says how many. */
+ * before the error is returned (nothing is in flight any more).  Of a step in buckets, those processed up to then are
+ * updated, the others untouched, and the message says how many; of a step in place it is unknown which elements are. */
 int axonn_offload_adam_step(axonn_offload_adam_t* opt, double lr, double beta1, double beta2,
                             double eps, double weight_decay, int64_t step, double grad_scale,
                             void* hip_stream);

@@ -165,6 +165,14 @@ struct WaitClock {
   }
 };
 
+// ------------------------------------------------------------------------------ optimizer state in place
+// May a kernel work on `bytes` of host memory at device address `dev` (0: the memory has none)?  Only if all of them lie
+// in the one allocation [alloc, alloc + alloc_bytes) that holds the first: the two ends may belong to different
+// allocations with memory between them that the GPU cannot reach.  The kernel needs 16-byte alignment.
+inline bool addressable_in_place(uint64_t dev, uint64_t bytes, uint64_t alloc, uint64_t alloc_bytes) {
+  return dev != 0 && dev % 16 == 0 && dev >= alloc && dev - alloc <= alloc_bytes && bytes <= alloc_bytes - (dev - alloc);
+}
+
 // ------------------------------------------------------------------------------ optimizer buckets
 inline uint64_t bucket_count(uint64_t n, uint64_t bucket) { return bucket ? (n + bucket - 1) / bucket : 0; }
 

@@ -1294,21 +1294,21 @@ int fetch_bucket(axonn_offload_adam* o, int set, uint64_t off, size_t bytes, hip
   return AXONN_OK;
 }
 
-// Device address of n floats of host memory that the GPU can read and write in place (pinned, 16-byte aligned, one
-// mapping from the first to the last byte), or null.
-float* gpu_view_of_host(float* host, uint64_t n) {
-  hipPointerAttribute_t first, last;
-  memset(&first, 0, sizeof first);
-  memset(&last, 0, sizeof last);
-  char* const end = (char*)(host + n) - 1;
-  if (hipPointerGetAttributes(&first, host) != hipSuccess || hipPointerGetAttributes(&last, end) != hipSuccess) {
+// Device address of n floats of host memory that the GPU can read and write in place (pinned, 16-byte aligned, all of
+// them in one allocation), or null.
+float* gpu_view_of_host(float* host_ptr, uint64_t n) {
+  hipPointerAttribute_t at;
+  memset(&at, 0, sizeof at);
+  hipDeviceptr_t base = nullptr;
+  size_t bytes = 0;
+  if (hipPointerGetAttributes(&at, host_ptr) != hipSuccess || at.type != hipMemoryTypeHost || !at.devicePointer ||
+      hipMemGetAddressRange(&base, &bytes, (hipDeviceptr_t)at.devicePointer) != hipSuccess) {
     (void)hipGetLastError();                     // memory the runtime does not know: the copies take it
     return nullptr;
   }
-  if (first.type != hipMemoryTypeHost || last.type != hipMemoryTypeHost || !first.devicePointer || !last.devicePointer ||
-      (char*)last.devicePointer - (char*)first.devicePointer != end - (char*)host || (uintptr_t)first.devicePointer % 16)
-    return nullptr;
-  return (float*)first.devicePointer;
+  const bool ok = host::addressable_in_place((uint64_t)(uintptr_t)at.devicePointer, n * sizeof(float),
+                                             (uint64_t)(uintptr_t)base, (uint64_t)bytes);
+  return ok ? (float*)at.devicePointer : nullptr;
 }
 
 // One pass over all buckets.  Without `gate`: in ascending order, after everything queued on the caller's
@@ -1320,7 +1320,7 @@ float* gpu_view_of_host(float* host, uint64_t n) {
 int adam_pass_body(axonn_offload_adam* o, double lr, double beta1, double beta2, double eps, double weight_decay,
                    int64_t step, double grad_scale, hipStream_t user, int chunk_buckets,
                    const std::function<hipEvent_t(uint64_t, uint64_t)>* gate, hipStream_t early,
-                   uint64_t* buckets_queued) {
+                   uint64_t* buckets_queued, bool* in_place) {
   constexpr int S = axonn_offload_adam::kSets;
   if (!gate) {
     // Whole pass behind the caller's stream: one kernel that works on the host arrays in place, faster than the
@@ -1332,7 +1332,7 @@ int adam_pass_body(axonn_offload_adam* o, double lr, double beta1, double beta2,
       ProfScope ps(PC_ADAM, user);
       AX_TRY(check_launch(launch_adam_host(o->n, th, m, v, o->g16, o->p16, lr, beta1, beta2, eps, weight_decay, step,
                                            grad_scale, user), "adam"));
-      *buckets_queued = host::bucket_count(o->n, o->bucket);
+      *in_place = true;
       HIP_TRY(hipStreamSynchronize(user));
       return AXONN_OK;
     }
@@ -1390,8 +1390,9 @@ int adam_pass(axonn_offload_adam* o, double lr, double beta1, double beta2, doub
     return fail(AXONN_EINVAL, "adam_step: betas must be in [0,1)");
   HIP_TRY(hipSetDevice(o->device));
   uint64_t queued = 0;
+  bool in_place = false;
   const int rc = adam_pass_body(o, lr, beta1, beta2, eps, weight_decay, step, grad_scale, user, chunk_buckets, gate,
-                                early, &queued);
+                                early, &queued, &in_place);
   if (rc != AXONN_OK) {
     // An error in the middle of the pass: whatever was queued may still be copying into the caller's host arrays
     // or writing parameters.  Wait for it, so that nothing is in flight when the error reaches the caller; the
@@ -1402,6 +1403,11 @@ int adam_pass(axonn_offload_adam* o, double lr, double beta1, double beta2, doub
     (void)hipStreamSynchronize(o->s_d2h);
     if (early) (void)hipStreamSynchronize(early);
     for (bool& r : o->d2h_recorded) r = false;
+    if (in_place) {
+      (void)hipStreamSynchronize(user);
+      return fail(rc, "%s (optimizer step on the host arrays in place: which elements of them and of the 16-bit "
+                  "parameters are updated is unknown)", first.c_str());
+    }
     return fail(rc, "%s (optimizer pass stopped after %llu of %llu buckets in %s order; those are updated in host "
                 "memory and in the 16-bit parameters, the others are untouched)", first.c_str(),
                 (unsigned long long)queued, (unsigned long long)host::bucket_count(o->n, o->bucket),

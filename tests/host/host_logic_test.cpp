@@ -306,6 +306,18 @@ void test_bucket_plan(unsigned seed) {
   CHECK(bucket_plan(1600000000ull, 1ull << 26, 3, 0, true).count == 56496128ull);
 }
 
+void test_addressable_in_place() {
+  const uint64_t a = 1ull << 32, n = 1 << 20;
+  CHECK(addressable_in_place(a, n, a, n) && addressable_in_place(a + 16, n - 16, a, n) && addressable_in_place(a, 12, a, n));
+  CHECK(!addressable_in_place(a + 4, 64, a, n));                // alignment
+  CHECK(!addressable_in_place(0, n, 0, n));                     // no device address
+  CHECK(!addressable_in_place(a, n + 1, a, n) && !addressable_in_place(a + 16, n, a, n));   // reaches past the allocation
+  // the last byte lies in a second pinned allocation at a + 2 n: what is between the two has no mapping
+  CHECK(!addressable_in_place(a + n - 4096, n + 8192, a, n));
+  CHECK(!addressable_in_place(a - 16, 64, a, n) && !addressable_in_place(a + n + 16, 64, a, n) && !addressable_in_place(a, n, 0, 0));
+  CHECK(!addressable_in_place(a + 16, ~0ull - 8, a, n));        // no wrap-around
+}
+
 void test_two_stages_two_threads() {
   // handles are independent: two host threads each drive a stage of their own (no shared state in the logic)
   auto work = [](unsigned seed) { test_pipeline_limit_and_order(seed); test_bucket_plan(seed); };
@@ -324,6 +336,7 @@ int main() {
   test_wait_limit_is_per_wait();
   test_wgrad_groups();
   test_bucket_plan(2);
+  test_addressable_in_place();
   test_two_stages_two_threads();
   std::puts("host logic: all checks passed");
   return 0;

@@ -367,12 +367,16 @@ def test_offloaded_adam_in_place_and_through_buckets_agree(n, bucket):
             a[lo:lo + n] = src
         P16 = torch.zeros(n, dtype=B.torch_elem_dtype(), device="cuda")
         opt = B.axonn_offload_adam_create(0, n, bucket, P16, G, *[a.ctypes.data + 4 * lo for a in arrs])
+        B.axonn_profile_enable(True)
         try:
             for step in (1, 2):
                 B.axonn_offload_adam_step(opt, 1e-3, 0.9, 0.95, 1e-8, 0.01, step, 0.5)
+            # one launch per step in place, one per bucket otherwise
+            assert B.axonn_profile_collect()["adam"][1] == 2 * (1 if kind == "aligned" else -(-n // bucket))
             assert all((a[lo + n:] == 7.0).all() and (a[:lo] == 7.0).all() for a in arrs)
             got.append([a[lo:lo + n].copy() for a in arrs] + [host(P16)])
         finally:
+            B.axonn_profile_enable(False)
             B.axonn_offload_adam_destroy(opt)
             for p in ptrs:
                 B.axonn_pinned_free(p)

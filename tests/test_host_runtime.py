@@ -43,5 +43,6 @@ def test_stage_runtime_takes_its_decisions_from_the_tested_header():
     src = open(os.path.join(os.path.dirname(HERE), "paper_2110_13005_amd", "csrc", "stage.cpp")).read()
     for fn in ("host::choose_message", "host::admit_forward", "host::commit_forward", "host::admit_backward",
                "host::commit_backward", "host::wgrad_action", "host::gradients_complete", "host::release_awaiting",
-               "host::check_post", "host::stream_index", "host::WaitClock", "host::bucket_plan", "host::chunk_span", "host::lowest_layer"):
+               "host::check_post", "host::stream_index", "host::WaitClock",
+               "host::addressable_in_place", "host::bucket_plan", "host::chunk_span", "host::lowest_layer"):
         assert fn in src, fn
