@@ -405,7 +405,8 @@ int axonn_gemm_bf16(int32_t a_kcontig, int32_t b_kcontig, int32_t epilogue,
  *   colsum[n] = (accumulate ? colsum[n] : 0) + sum_k B[k*ldb + n],   n < N,
  * in C's element type (float32 for epilogue 4, bf16 for 5; sums in fp32, one rounding).  The sums are
  * formed inside the GEMM kernel, from the tiles of B it multiplies (B is read once); only for operands
- * of 2 GiB and more axonn_colsum's kernels run behind the GEMM.
+ * of 2 GiB and more, and for small problems with operands that are not 16-byte aligned, axonn_colsum's kernels run
+ * behind the GEMM.
  * workspace_f32: ceil(K/64)*N floats, needed either way.  Sizes as for axonn_gemm_bf16. */
 int axonn_gemm_wgrad_colsum(int32_t epilogue, int64_t M, int64_t N, int64_t K,
                             const void* A, int64_t lda, const void* B, int64_t ldb,

@@ -1516,7 +1516,7 @@ static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s, int parts = 1)
   return hipGetLastError();
 }
 
-// The large-problem kernel addresses an operand with 32-bit byte offsets from the segment base.
+// The kernels that copy tiles with buffer instructions address an operand with 32-bit byte offsets from the segment base.
 static bool fits_32bit_offsets(int64_t rows, int64_t ld) {
   return ld > 0 && (rows + 1024) * ld * 2 < (int64_t(1) << 31);
 }
@@ -1629,10 +1629,23 @@ int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K) {
   return r.parts > 1 ? r.parts * M * N : 0;
 }
 
+static bool aligned16(const GemmArgs& g) {
+  uintptr_t bits = 0;
+  for (int i = 0; i < g.n_seg; ++i) bits |= (uintptr_t)g.A_seg[i] | (uintptr_t)g.B_seg[i];
+  return bits % 16 == 0;
+}
+
 template <bool A_KC, bool B_KC>
 static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
-  if (!fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) || !fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb))
-    return launch_cfg<256, 256, 64, 2, 4, A_KC, B_KC>(epi, g, s);
+  // Operands beyond 32-bit offsets go through the kernel of plain pointers, and so do small problems whose operands do
+  // not start at a multiple of 16 bytes: the ring kernel's copies into LDS are not used on them.  Tiles of 128 x 128 below
+  // half a chip of 256 x 256 ones: weight gradient 1024 x 4096 over 270336 tokens 4.02 ms, with 256 x 256 tiles 7.19.
+  const bool fits = fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) && fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb);
+  if (!fits || !aligned16(g)) {
+    const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), forced = big_tile_threshold();
+    if (big_tiles < (forced >= 0 ? forced : 128)) return launch_cfg<128, 128, 64, 2, 2, A_KC, B_KC>(epi, g, s);
+    if (!fits) return launch_cfg<256, 256, 64, 2, 4, A_KC, B_KC>(epi, g, s);
+  }
   const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
   if constexpr (A_KC && B_KC) {
     if (g.split_ws && g.n_seg == 1 && epi == EPI_BIAS) {
@@ -1646,7 +1659,7 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
       }
     }
   }
-  const int tile = choose_ring_tile(g.M, g.N, nk);
+  const int tile = aligned16(g) ? choose_ring_tile(g.M, g.N, nk) : -1;
   if (tile >= 0) return launch_ring_tile<A_KC, B_KC>(tile, epi, g, s, 1);
   switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
     case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);

@@ -219,6 +219,56 @@ def test_gemm_both_large_kernels_all_layouts_and_results(mask, min_tiles):
         B.axonn_tuning(7, 0)
 
 
+def _wide(rows, width, ld, offset=0):
+    """rows x width random elements with leading dimension ld, `offset` elements into a buffer that is NaN elsewhere near
+    them -> (values, tensor that starts at the first element)."""
+    import torch
+    buf = torch.zeros(rows * ld + offset, dtype=B.torch_elem_dtype(), device="cuda")
+    view = buf[offset:].view(rows, ld)
+    view[:, width:min(ld, width + 256)] = float("nan")
+    vals = _rng_bf16(np.random.default_rng(rows + width), (rows, width))
+    view[:, :width] = dev_bf16(vals)
+    return vals.astype(np.float64), buf[offset:]
+
+
+@pytest.mark.parametrize("min_tiles", [-1, 1])
+@pytest.mark.parametrize("M,N,K", [(8, 8, 8), (136, 264, 200), (264, 136, 72)])
+@pytest.mark.parametrize("wide", ["A", "B", "misaligned"])
+def test_gemm_operands_of_the_pointer_kernel(M, N, K, wide, min_tiles):
+    """Operands that 32-bit byte offsets do not span (a leading dimension of 2^20) and, for small problems, operands that
+    do not start at a multiple of 16 bytes: tiles of 128 x 128, or of 256 x 256 above the threshold, all layouts, the
+    column sums in launches of their own where an operand is too large."""
+    import torch
+    off = 4 if wide == "misaligned" else 0
+    lda_of = lambda w: 1 << 20 if wide == "A" else w + 8
+    ldb_of = lambda w: 1 << 20 if wide == "B" else w + 8
+    ws = torch.empty(((K + 63) // 64) * N, dtype=torch.float32, device="cuda")
+    try:
+        B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, min_tiles if not off else -1)
+        for a_kc, b_kc, epi in ((1, 0, B.EPI_BIAS), (1, 1, B.EPI_BIAS), (0, 0, B.EPI_ACC_F32), (0, 0, B.EPI_ACC_BF16)):
+            ash, bsh = ((M, K) if a_kc else (K, M)), ((N, K) if b_kc else (K, N))
+            lda, ldb = lda_of(ash[1]), ldb_of(bsh[1])
+            am, a = _wide(*ash, lda, off)
+            bm, b = _wide(*bsh, ldb, off)
+            ref = (am if a_kc else am.T) @ (bm.T if b_kc else bm)
+            if a_kc:
+                out = torch.zeros(M, N, dtype=B.torch_elem_dtype(), device="cuda")
+                B.axonn_gemm_bf16(a_kc, b_kc, epi, M, N, K, a, lda, b, ldb, out, N)
+                parity(host(out), ref, TOL, C_ONE, label="gemm_operands_of_the_pointer_kernel")
+                continue
+            f32 = epi == B.EPI_ACC_F32
+            out = torch.full((M, N), 7.0, dtype=torch.float32 if f32 else B.torch_elem_dtype(), device="cuda")
+            db = torch.full((N + 8,), 3.0, dtype=out.dtype, device="cuda")
+            for acc in (0, 1):
+                B.axonn_gemm_wgrad_colsum(epi, M, N, K, a, lda, b, ldb, out, N, db, ws, accumulate=acc)
+            # stored, then added to what was stored: each step one 16-bit rounding, or fp32 sums
+            assert rel_fro(host(out), 2 * ref) < (1e-5 if f32 else TOL)
+            assert rel_fro(host(db)[:N], 2 * bm.sum(axis=0)) < (1e-5 if f32 else TOL)
+            assert (host(db)[N:] == 3.0).all()
+    finally:
+        B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, -1)
+
+
 def test_gemm_strided_operands_and_run_to_run_determinism():
     """Leading dimensions larger than the logical width (the qkv weight-gradient uses slices)."""
     import torch
