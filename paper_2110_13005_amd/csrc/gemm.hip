@@ -15,6 +15,7 @@
 // lane of the result owns one row m and runs of 4 consecutive columns n: epilogue loads and
 // stores are 8-byte (bf16) or 16-byte (fp32) vectors along the contiguous dimension of C.
 #include "common.h"
+#include "host_logic.h"
 #include <algorithm>
 #include <atomic>
 #include <type_traits>
@@ -42,10 +43,15 @@ __device__ __forceinline__ void lds_barrier() {
 // the eight XCDs together work on few bands at a time (bands across the longer side -- 80 x 20 tiles, the
 // weight gradient of the second MLP matrix -- put a different band, with 8 panels of the wide operand, on
 // every XCD: 192 MB of panels in flight, beyond what the 256 MB last-level cache holds beside the rest).
+// A number of tiles that is no multiple of 8 is remapped only if ANY_COUNT.  The ring kernel, whose smaller tiles fetch
+// more per MFMA, needs it (230 tiles of 128 x 256, 640 x 11776 x 9632 input gradient: 174 -> 141 us); with tiles of 256 x 256
+// it is as often 4 % slower (4624 x 10448 x 1440 with GeLU, 779 tiles: 194 -> 201 us) as faster.
+template <bool ANY_COUNT = false>
 __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
   int pid = blockIdx.x;
   const int nblk = gridDim.x;
-  if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
+  if (ANY_COUNT) pid = (int)host::xcd_contiguous(blockIdx.x, gridDim.x);
+  else if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
   constexpr int BAND = 8;
   const bool wide = tiles_m <= tiles_n;                    // bands of tile rows, walked column by column
   const int t_band = wide ? tiles_m : tiles_n, t_walk = wide ? tiles_n : tiles_m;
@@ -1151,7 +1157,7 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
   int tm, tn;
-  tile_of_block(g.tiles_m, g.tiles_n, tm, tn);
+  tile_of_block<true>(g.tiles_m, g.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
   const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;

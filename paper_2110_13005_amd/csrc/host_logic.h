@@ -2,8 +2,8 @@
 // takes next, the bookkeeping of the activation stash slots (Sec. 3.3: at most pipeline_limit microbatches in
 // flight), when the deferred weight gradients of a group of microbatches are formed, how long the loop waits
 // for a message, and the bucket plan of the offloaded optimizer (Sec. 5.2) with the chunks of the step that
-// overlaps the backward tail (Sec. 5.3).  stage.cpp calls these with its HIP streams and events around them; the
-// CPU tests compile this header alone (with the address, undefined-behaviour and thread sanitizers) and drive it
+// overlaps the backward tail (Sec. 5.3); and the order of a GEMM's workgroups.  stage.cpp calls these with its HIP
+// streams and events around them, the kernels the last; the CPU tests compile this header alone (with the address, undefined-behaviour and thread sanitizers) and drive it
 // with simulated events.
 #pragma once
 #include <stdint.h>
@@ -203,6 +203,14 @@ inline int lowest_layer(const uint64_t* layer_begin, int n_layers, uint64_t lo) 
   int l = 0;
   while (l + 1 < n_layers && layer_begin[l + 1] <= lo) ++l;
   return l;
+}
+
+// ------------------------------------------------------------------------------ order of a launch's workgroups
+// Workgroups are dealt round-robin to the 8 XCDs: ids x, x + 8, ... run on XCD x.  The position of workgroup `id` in an
+// order in which every XCD's workgroups are consecutive, for any number of workgroups.
+constexpr uint32_t xcd_contiguous(uint32_t id, uint32_t n_workgroups) {
+  const uint32_t xcd = id % 8, left = n_workgroups % 8;  // the first `left` XCDs have one workgroup more
+  return xcd * (n_workgroups / 8) + (xcd < left ? xcd : left) + id / 8;
 }
 
 }  // namespace host

@@ -318,6 +318,18 @@ void test_addressable_in_place() {
   CHECK(!addressable_in_place(a + 16, ~0ull - 8, a, n));        // no wrap-around
 }
 
+void test_workgroup_order() {
+  for (int n = 1; n <= 600; ++n) {
+    std::vector<int> xcd_at(n, -1);
+    for (int id = 0; id < n; ++id) {
+      const int p = (int)xcd_contiguous(id, n);
+      CHECK(p >= 0 && p < n && xcd_at[p] < 0);            // every position once
+      xcd_at[p] = id % 8;
+    }
+    for (int p = 1; p < n; ++p) CHECK(xcd_at[p] >= xcd_at[p - 1]);   // one run per XCD
+  }
+}
+
 void test_two_stages_two_threads() {
   // handles are independent: two host threads each drive a stage of their own (no shared state in the logic)
   auto work = [](unsigned seed) { test_pipeline_limit_and_order(seed); test_bucket_plan(seed); };
@@ -337,6 +349,7 @@ int main() {
   test_wgrad_groups();
   test_bucket_plan(2);
   test_addressable_in_place();
+  test_workgroup_order();
   test_two_stages_two_threads();
   std::puts("host logic: all checks passed");
   return 0;
