@@ -3,6 +3,9 @@ header declares; argument validation that needs no device returns the documented
 import ctypes
 import os
 import re
+import shutil
+import struct
+import subprocess
 
 import pytest
 
@@ -102,3 +105,38 @@ def test_argument_validation_without_device():
     with pytest.raises(B.AxonnError) as e:
         B.axonn_attention_fwd(1, 128, 4, 200, 1, 1, 1)
     assert e.value.status == B.AXONN_EUNSUPPORTED
+
+
+def _kernel_scratch(lib_path, tmp_path):
+    """{mangled kernel name: bytes of scratch memory per lane} of a built library, from its own code objects' notes."""
+    readelf = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
+    if not os.path.exists(readelf):
+        pytest.skip("no llvm-readelf")
+    blob = open(lib_path, "rb").read()
+    magic, out = b"__CLANG_OFFLOAD_BUNDLE__", {}
+    at = blob.find(magic)
+    while at >= 0:
+        (n,), p = struct.unpack_from("<Q", blob, at + len(magic)), at + len(magic) + 8
+        for _ in range(n):
+            off, size, name_len = struct.unpack_from("<QQQ", blob, p)
+            triple = blob[p + 24:p + 24 + name_len]
+            p += 24 + name_len
+            if b"gfx950" in triple and size:
+                obj = tmp_path / "code_object"
+                obj.write_bytes(blob[at + off:at + off + size])
+                notes = subprocess.run([readelf, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+                names = re.findall(r"^ +\.name: +(_Z\S+)$", notes, flags=re.M)
+                scratch = re.findall(r"^ +\.private_segment_fixed_size: +(\d+)$", notes, flags=re.M)
+                assert len(names) == len(scratch)
+                out.update(zip(names, map(int, scratch)))
+        at = blob.find(magic, at + 1)
+    return out
+
+
+@pytest.mark.parametrize("elem", ["bf16", "fp16"])
+def test_gemm_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
+    """A register spilled inside a k loop waits for every copy in flight at each reload."""
+    from paper_2110_13005_amd import build as BLD
+    scratch = {k: v for k, v in _kernel_scratch(BLD.VARIANTS[elem][0], tmp_path).items() if "gemm_" in k}
+    assert len(scratch) > 50
+    assert not {k: v for k, v in scratch.items() if v}
