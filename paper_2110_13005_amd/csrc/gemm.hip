@@ -1573,82 +1573,19 @@ static int choose_tn(int64_t M, int64_t N, int64_t nk, bool concurrent) {
   return best;
 }
 
-// Tile of the ring kernel for a problem that 256 x 256 tiles would not fill the chip with.
-enum RingTile { RING_64x64, RING_128x64, RING_128x128, RING_128x192, RING_128x256, RING_TILES };
-struct TileCost { int bm, bn; double fixed, step_few, step_full; };
-// Microseconds: what a round of up to 256 tiles (one workgroup per CU) costs beside its k-steps, and a 64-wide k-step
-// with few and with 256 tiles in flight.  From single launches with K = 1024 and K = 4096 of outputs of 256 x 256 to
-// 2048 x 12288 (the difference gives the step, the rest the fixed part).
-constexpr TileCost kRingCost[RING_TILES] = {{64, 64, 3.2, 0.20, 0.21}, {128, 64, 4.0, 0.28, 0.30},
-                                            {128, 128, 5.0, 0.40, 0.47}, {128, 192, 7.5, 0.54, 0.68},
-                                            {128, 256, 8.0, 0.65, 0.73}};
-constexpr TileCost kBigCost[3] = {{256, 160, 10.0, 0.75, 1.05}, {256, 192, 10.0, 0.80, 1.10}, {256, 256, 10.0, 1.0, 1.4}};
-
-// Modelled time of a problem with one tile size: whole rounds and a last one whose steps are faster the emptier it is.
-static double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
-  const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
-  const double last = (double)(tiles % 256) / 256;
-  return (double)(tiles / 256) * (c.fixed + nk * c.step_full) +
-         (last > 0 ? c.fixed + nk * (c.step_few + (c.step_full - c.step_few) * last) : 0.0);
-}
-
-// Which ring tile an M x N x (nk k-steps) problem takes; -1: a large-problem kernel.  Those stay where their 256 x 256
-// tiles fill the chip, and where the model prefers one of their widths.  Measured (bf16, single launches, the kernels
-// before / now): 256 x 256 x 1024 17.0 / 5.7 us, 1024 x 1024 x 4096 52.6 / 16.1, 2048 x 1024 x 4096 52.6 / 23.8, 2048 x 2048 x
-// 8192 103 / 67, 2048 x 3072 x 12288 226 / 137 (a kernel of 128 x 128 tiles staged through registers, which had no case
-// left), 2048 x 4096 x 1024 with GeLU 35.6 / 28.5 (half a round of 256 x 256 tiles).
-// The rule does not look at whether the launch shares the chip: a ring kernel adds its two halves of k in another order
-// than the large-problem kernels, and a batch's results should not depend on the number of streams it runs on.
-// Measured, the choice would be the same: leaving half-filled rounds to the large-problem kernels beside other streams,
-// or weighing in the CUs that a round leaves idle, changed whole batches by less than 1 % or made them slower.
-static int choose_ring_tile(int64_t M, int64_t N, int64_t nk) {
-  const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  const int64_t forced = big_tile_threshold();
-  if (big_tiles >= (forced >= 0 ? forced : 256)) return -1;
-  int best = RING_64x64;
-  double best_cost = tile_cost(kRingCost[0], M, N, nk);
-  for (int t = 1; t < RING_TILES; ++t) {
-    const double cost = tile_cost(kRingCost[t], M, N, nk);
-    if (cost < best_cost) { best = t; best_cost = cost; }
-  }
-  if (forced < 0)
-    for (const TileCost& c : kBigCost)
-      if (tile_cost(c, M, N, nk) < best_cost) return -1;
-  return best;
-}
-
 template <bool A_KC, bool B_KC>
 static hipError_t launch_ring_tile(int tile, int epi, const GemmArgs& g, hipStream_t s, int parts) {
   switch (tile) {
-    case RING_64x64: return launch_ring<A_KC, B_KC, 2, 2, 2, 2, 4>(epi, g, s, parts);
-    case RING_128x64: return launch_ring<A_KC, B_KC, 4, 2, 2, 2, 3>(epi, g, s, parts);
-    case RING_128x128: return launch_ring<A_KC, B_KC, 4, 4, 2, 1, 4>(epi, g, s, parts);
-    case RING_128x192: return launch_ring<A_KC, B_KC, 4, 6, 2, 1, 3>(epi, g, s, parts);
+    case host::RING_64x64: return launch_ring<A_KC, B_KC, 2, 2, 2, 2, 4>(epi, g, s, parts);
+    case host::RING_128x64: return launch_ring<A_KC, B_KC, 4, 2, 2, 2, 3>(epi, g, s, parts);
+    case host::RING_128x128: return launch_ring<A_KC, B_KC, 4, 4, 2, 1, 4>(epi, g, s, parts);
+    case host::RING_128x192: return launch_ring<A_KC, B_KC, 4, 6, 2, 1, 3>(epi, g, s, parts);
     default: return launch_ring<A_KC, B_KC, 4, 8, 2, 1, 3>(epi, g, s, parts);
   }
 }
 
-// Split of a long contraction with a small output, for callers that can hand over a workspace (g.split_ws): tile and
-// number of parts (1: not split) with the lowest modelled time.  The parts cost a write and a read of their fp32 sums
-// (4 TB/s) and a launch (5 us).  The LM head's input gradient, 2048 x 1024 x 51200 in four parts of 128 x 256 tiles: 345 -> 205 us.
-struct RingSplit { int tile, parts; };
-static RingSplit choose_split(int64_t M, int64_t N, int64_t K) {
-  const int64_t nk = (K + 63) / 64;
-  RingSplit best = {choose_ring_tile(M, N, nk), 1};
-  if (best.tile < 0) return best;
-  double best_cost = tile_cost(kRingCost[best.tile], M, N, nk);
-  for (int parts = 2; parts <= 16 && nk / parts >= 16; parts *= 2)
-    for (int t = 0; t < RING_TILES; ++t) {
-      const TileCost& c = kRingCost[t];
-      const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * parts;
-      const double cost = tile_cost({1, 1, c.fixed, c.step_few, c.step_full}, tiles, 1, (nk + parts - 1) / parts) +
-                          5.0 + 8.0 * parts * M * N / 4e6;
-      if (cost < best_cost) { best = {t, parts}; best_cost = cost; }
-    }
-  return best;
-}
 int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K) {
-  const RingSplit r = choose_split(M, N, K);
+  const host::RingSplit r = host::choose_split(M, N, K, big_tile_threshold());
   return r.parts > 1 ? r.parts * M * N : 0;
 }
 
@@ -1672,7 +1609,7 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
   const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
   if constexpr (A_KC && B_KC) {
     if (g.split_ws && g.n_seg == 1 && epi == EPI_BIAS) {
-      const RingSplit r = choose_split(g.M, g.N, g.K);
+      const host::RingSplit r = host::choose_split(g.M, g.N, g.K, big_tile_threshold());
       if (r.parts > 1 && r.parts * (int64_t)g.M * g.N <= g.split_floats) {
         const hipError_t e = launch_ring_tile<A_KC, B_KC>(r.tile, epi, g, s, r.parts);
         if (e != hipSuccess) return e;
@@ -1682,7 +1619,7 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
       }
     }
   }
-  const int tile = aligned16(g) ? choose_ring_tile(g.M, g.N, nk) : -1;
+  const int tile = aligned16(g) ? host::choose_ring_tile(g.M, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) : -1;
   if (tile >= 0) return launch_ring_tile<A_KC, B_KC>(tile, epi, g, s, 1);
   switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
     case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);

@@ -2,9 +2,9 @@
 // takes next, the bookkeeping of the activation stash slots (Sec. 3.3: at most pipeline_limit microbatches in
 // flight), when the deferred weight gradients of a group of microbatches are formed, how long the loop waits
 // for a message, and the bucket plan of the offloaded optimizer (Sec. 5.2) with the chunks of the step that
-// overlaps the backward tail (Sec. 5.3); and the order of a GEMM's workgroups.  stage.cpp calls these with its HIP
-// streams and events around them, the kernels the last; the CPU tests compile this header alone (with the address, undefined-behaviour and thread sanitizers) and drive it
-// with simulated events.
+// overlaps the backward tail (Sec. 5.3); and the tile a GEMM launch takes with the order of its workgroups (gemm.hip).
+// stage.cpp calls these with its HIP streams and events around them; the CPU tests compile this header alone (with the
+// address, undefined-behaviour and thread sanitizers) and drive it with simulated events.
 #pragma once
 #include <stdint.h>
 
@@ -211,6 +211,79 @@ inline int lowest_layer(const uint64_t* layer_begin, int n_layers, uint64_t lo) 
 constexpr uint32_t xcd_contiguous(uint32_t id, uint32_t n_workgroups) {
   const uint32_t xcd = id % 8, left = n_workgroups % 8;  // the first `left` XCDs have one workgroup more
   return xcd * (n_workgroups / 8) + (xcd < left ? xcd : left) + id / 8;
+}
+
+// ------------------------------------------------------------------------------ tiles of the GEMM launcher
+// Tile of the ring kernel for a problem that 256 x 256 tiles would not fill the chip with.
+enum RingTile { RING_64x64, RING_128x64, RING_128x128, RING_128x192, RING_128x256, RING_TILES };
+struct TileCost { int bm, bn; double fixed, step_few, step_full; };
+// Microseconds: what a round of up to 256 tiles (one workgroup per CU) costs beside its k-steps, and a 64-wide k-step
+// with few and with 256 tiles in flight.  From single launches with K = 1024 and K = 4096 of outputs of 256 x 256 to
+// 2048 x 12288 (the difference gives the step, the rest the fixed part).
+constexpr TileCost kRingCost[RING_TILES] = {{64, 64, 3.2, 0.20, 0.21}, {128, 64, 4.0, 0.28, 0.30},
+                                            {128, 128, 5.0, 0.40, 0.47}, {128, 192, 7.5, 0.54, 0.68},
+                                            {128, 256, 8.0, 0.65, 0.73}};
+// The large-problem kernels.  Weights for the comparison with the ring tiles and no rates: their scale is the one that
+// picks the faster kernel on 230 random shapes of 64 to 255 tiles of 256 x 256 (0.1 % slower than the better of the two on
+// average, weight gradients with an fp32 result, whose large-problem kernel is the register-staged one, 4.5 %).
+constexpr double kBigFp32 = 1.4;
+constexpr TileCost kBigCost[3] = {{256, 160, 12.0, 0.57, 0.80}, {256, 192, 12.0, 0.61, 0.84}, {256, 256, 12.0, 0.76, 1.06}};
+
+// Modelled time of a problem with one tile size: whole rounds and a last one whose steps are faster the emptier it is.
+inline double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
+  const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  const double last = (double)(tiles % 256) / 256, steps = (double)nk;
+  return (double)(tiles / 256) * (c.fixed + steps * c.step_full) +
+         (last > 0 ? c.fixed + steps * (c.step_few + (c.step_full - c.step_few) * last) : 0.0);
+}
+
+// Which ring tile an M x N x (nk k-steps) problem takes; -1: a large-problem kernel.  Those stay where their 256 x 256
+// tiles fill the chip, and where the model prefers one of their widths.  Measured (bf16, single launches, the kernels
+// before / now): 256 x 256 x 1024 17.0 / 5.7 us, 1024 x 1024 x 4096 52.6 / 16.1, 2048 x 1024 x 4096 52.6 / 23.8, 2048 x 2048 x
+// 8192 103 / 67, 2048 x 3072 x 12288 226 / 137 (a kernel of 128 x 128 tiles staged through registers), 2048 x 4096 x 1024
+// with GeLU 35.6 / 28.5 (half a round of 256 x 256 tiles).
+// From 128 tiles on, which the large-problem kernels run well, the ring tile has to be modelled 8 % faster: without that,
+// and with weights of 10, 0.75 / 0.80 / 1.0 and 1.05 / 1.10 / 1.4, 21 of 910 launches of such shapes were more than 4 % slower
+// than on the large-problem kernels, up to 2816 x 2944 x 10112 168 us against 137; now 5 are, by at most 5 %.
+// `forced` (-1: none): number of 256 x 256 tiles from which the large-problem kernels are used whatever the model says.
+// The rule does not look at whether the launch shares the chip: a ring kernel adds its two halves of k in another order
+// than the large-problem kernels, and a batch's results should not depend on the number of streams it runs on.
+// Measured, the choice would be the same: leaving half-filled rounds to the large-problem kernels beside other streams,
+// or weighing in the CUs that a round leaves idle, changed whole batches by less than 1 % or made them slower.
+inline int choose_ring_tile(int64_t M, int64_t N, int64_t nk, int64_t forced, bool fp32_result) {
+  const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  if (big_tiles >= (forced >= 0 ? forced : 256)) return -1;
+  int best = RING_64x64;
+  double best_cost = tile_cost(kRingCost[0], M, N, nk);
+  for (int t = 1; t < RING_TILES; ++t) {
+    const double cost = tile_cost(kRingCost[t], M, N, nk);
+    if (cost < best_cost) { best = t; best_cost = cost; }
+  }
+  const double limit = best_cost * (big_tiles >= 128 ? 1.08 : 1.0) / (fp32_result ? kBigFp32 : 1.0);
+  if (forced < 0)
+    for (const TileCost& c : kBigCost)
+      if (tile_cost(c, M, N, nk) < limit) return -1;
+  return best;
+}
+
+// Split of a long contraction with a small output over workgroups, for callers that can hand over a workspace: tile and
+// number of parts (1: not split) with the lowest modelled time.  The parts cost a write and a read of their fp32 sums
+// (4 TB/s) and a launch (5 us).  The LM head's input gradient, 2048 x 1024 x 51200 in four parts of 128 x 256 tiles: 345 -> 205 us.
+struct RingSplit { int tile, parts; };
+inline RingSplit choose_split(int64_t M, int64_t N, int64_t K, int64_t forced) {
+  const int64_t nk = (K + 63) / 64;
+  RingSplit best = {choose_ring_tile(M, N, nk, forced, false), 1};
+  if (best.tile < 0) return best;
+  double best_cost = tile_cost(kRingCost[best.tile], M, N, nk);
+  for (int parts = 2; parts <= 16 && nk / parts >= 16; parts *= 2)
+    for (int t = 0; t < RING_TILES; ++t) {
+      const TileCost& c = kRingCost[t];
+      const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn) * parts;
+      const double cost = tile_cost({1, 1, c.fixed, c.step_few, c.step_full}, tiles, 1, (nk + parts - 1) / parts) +
+                          5.0 + 8.0 * (double)parts * (double)M * (double)N / 4e6;
+      if (cost < best_cost) { best = {t, parts}; best_cost = cost; }
+    }
+  return best;
 }
 
 }  // namespace host

@@ -330,6 +330,27 @@ void test_workgroup_order() {
   }
 }
 
+void test_gemm_tiles() {
+  // the large-problem kernels: from 256 tiles of 256 x 256, from a threshold given, and where they are the faster ones
+  CHECK(choose_ring_tile(4096, 4096, 16, -1, false) == -1 && choose_ring_tile(512, 512, 16, 4, false) == -1);
+  CHECK(choose_ring_tile(4080, 4000, 2, 1000, false) >= 0);
+  CHECK(choose_ring_tile(2816, 2944, 158, -1, false) == -1);     // 132 tiles, two full rounds of 128 x 128: 137 us against 168
+  CHECK(choose_ring_tile(5632, 1408, 24, -1, false) == -1);
+  CHECK(choose_ring_tile(2768, 2944, 11, -1, true) >= 0);        // with an fp32 result 29.9 us against 40.5
+  CHECK(choose_ring_tile(3968, 3712, 188, -1, true) == -1);
+  // the ring kernel where a round of its tiles covers the problem: 28.5 us against 35.6, 137 against 226
+  CHECK(choose_ring_tile(2048, 4096, 16, -1, false) == RING_128x256 && choose_ring_tile(2048, 3072, 192, -1, false) >= 0);
+  CHECK(choose_ring_tile(256, 256, 16, -1, false) == RING_64x64);
+  // a split is bounded (16 parts of 16 k-steps at least) and none where the problem fills the chip
+  std::mt19937 rng(3);
+  for (int rep = 0; rep < 2000; ++rep) {
+    const int64_t M = 8 * (1 + rng() % 1024), N = 8 * (1 + rng() % 1024), K = 8 * (1 + rng() % 8192);
+    const RingSplit r = choose_split(M, N, K, -1);
+    CHECK(r.parts >= 1 && r.parts <= 16 && (r.parts == 1 || ((K + 63) / 64) / r.parts >= 16));
+    CHECK(r.parts == 1 || (r.tile >= 0 && ((M + 255) / 256) * ((N + 255) / 256) < 256));
+  }
+}
+
 void test_two_stages_two_threads() {
   // handles are independent: two host threads each drive a stage of their own (no shared state in the logic)
   auto work = [](unsigned seed) { test_pipeline_limit_and_order(seed); test_bucket_plan(seed); };
@@ -340,7 +361,14 @@ void test_two_stages_two_threads() {
 
 }  // namespace
 
-int main() {
+// With the arguments "tile M N K": the GEMM launcher's choice for a problem of one segment (ring tile or -1, and the
+// parts of a split over k where a workspace is at hand).
+int main(int argc, char** argv) {
+  if (argc == 5 && std::string(argv[1]) == "tile") {
+    const long M = std::atol(argv[2]), N = std::atol(argv[3]), K = std::atol(argv[4]);
+    std::printf("%d %d\n", choose_ring_tile(M, N, (K + 63) / 64, -1, false), choose_split(M, N, K, -1).parts);
+    return 0;
+  }
   test_pipeline_limit_and_order(1);
   test_arrival_order_decides();
   test_duplicates_and_surplus();
@@ -350,6 +378,7 @@ int main() {
   test_bucket_plan(2);
   test_addressable_in_place();
   test_workgroup_order();
+  test_gemm_tiles();
   test_two_stages_two_threads();
   std::puts("host logic: all checks passed");
   return 0;

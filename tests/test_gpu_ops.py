@@ -34,18 +34,20 @@ def _rng_bf16(rng, shape, std=1.0):
 
 # ------------------------------------------------------------------------- GEMM
 GEMM_SHAPES = [
-    (256, 256, 64),      # one big tile, one k-step
-    (512, 768, 256),     # several 256-tiles -> big-tile kernel? (2x3=6 tiles -> small-tile path)
-    (2048, 4096, 512),   # 128 big tiles: big-tile kernel
+    # ring kernel, tiles of 64 x 64 but for the third (the large-problem kernels run all of these in
+    # test_gemm_both_large_kernels_all_layouts_and_results)
+    (256, 256, 64),      # one k-step
+    (512, 768, 256),     # several tiles
+    (2048, 4096, 512),   # tiles of 128 x 256, an even number of them per XCD
     (200, 136, 72),      # ragged in every dimension (multiples of 8 only)
     (8, 8, 8),           # degenerate minimum
     (264, 2056, 1032),   # ragged tails on a multi-tile problem
-    # big-tile kernel, ragged rows and columns, k tail, odd number of k-tiles; the launcher picks
+    # large-problem kernels, ragged rows and columns, k tail, odd number of k-tiles; the launcher picks
     # block widths 160, 192 and 256 for these three
     (2056, 4104, 264),
     (2056, 4512, 264),
     (2056, 5464, 264),
-    (4096, 2048, 448),   # big-tile kernel: odd number of k-tiles, no tail
+    (4096, 2048, 448),   # ring kernel, 128 x 256: odd number of k-tiles, no tail
     # whole k-tiles (the kernel that copies tiles without staging registers), ragged rows and columns,
     # block widths 160, 192 and 256
     (2056, 4104, 320),
@@ -148,17 +150,19 @@ def test_gemm_wgrad_with_bias_gradient(M, N, K):
     assert (host(db16)[N:] == 3.0).all()
 
 
-# One problem per tile size of the ring kernel (below the threshold of the large-problem kernels the launcher picks the
-# one with the lowest modelled time): ragged rows and columns, a k tail, k ranges shorter than the ring and longer.
-RING_SHAPES = [
-    (72, 136, 40),       # 64 x 64: one k-tile with a tail, the rest of the ring beyond the end
-    (1000, 1016, 456),   # 64 x 64: 8 k-tiles, the last one short
-    (2040, 1016, 520),   # 128 x 64
-    (2008, 2040, 328),   # 128 x 128: an even number of k-steps, 1032 an odd one
-    (1032, 3080, 1032),  # 128 x 128 and the columns of a ninth half-empty tile row
-    (2040, 3064, 200),   # 128 x 192: partial results added in place
-    (2040, 4088, 264),   # 128 x 256
-]
+# Problems for every tile size of the ring kernel (below the threshold of the large-problem kernels the launcher picks the
+# one with the lowest modelled time; test_host_runtime.py checks that it still picks these): ragged rows and columns, a k
+# tail, k ranges shorter than the ring and longer.
+RING_TILES = {
+    (72, 136, 40): "64x64",        # one k-tile with a tail, the rest of the ring beyond the end
+    (1000, 1016, 456): "64x64",    # 8 k-tiles, the last one short
+    (2040, 1016, 520): "128x64",
+    (2008, 2040, 328): "128x128",  # an even number of k-steps, 1032 an odd one
+    (1032, 3080, 1032): "128x128", # and the columns of a ninth half-empty tile row
+    (2040, 3064, 200): "128x192",  # partial results added in place
+    (2040, 4088, 264): "128x256",
+}
+RING_SHAPES = list(RING_TILES)
 
 
 @pytest.mark.parametrize("M,N,K", RING_SHAPES)
@@ -170,12 +174,13 @@ def test_gemm_ring_tiles(M, N, K):
 
 
 def test_gemm_big_tile_strided_operands():
-    """The big-tile kernel with leading dimensions larger than the logical widths and a k tail: what lies
-    beyond K in a row of a k-contiguous operand must not enter the sum."""
+    """Leading dimensions larger than the logical widths and a k tail, on the ring kernel (128 x 256) and, for the third
+    problem and wherever axonn_tuning asks for them, the large-problem kernels: what lies beyond K in a row of a
+    k-contiguous operand must not enter the sum."""
     import torch
     rng = np.random.default_rng(6)
     for (M, N, K), (a_kc, b_kc, epi) in itertools.product(
-            ((2048, 4096, 200), (2048, 4096, 192)),
+            ((2048, 4096, 200), (2048, 4096, 192), (4096, 4104, 200)),
             ((1, 0, B.EPI_BIAS), (1, 1, B.EPI_BIAS), (0, 0, B.EPI_ACC_BF16))):
         ash, bsh = ((M, K) if a_kc else (K, M)), ((N, K) if b_kc else (K, N))
         lda, ldb, ldc = ash[1] + 72, bsh[1] + 136, N + 8

@@ -46,3 +46,26 @@ def test_stage_runtime_takes_its_decisions_from_the_tested_header():
                "host::check_post", "host::stream_index", "host::WaitClock",
                "host::addressable_in_place", "host::bucket_plan", "host::chunk_span", "host::lowest_layer"):
         assert fn in src, fn
+
+
+def test_gemm_test_shapes_reach_the_tiles_they_name(tmp_path):
+    """The GPU tests of the ring kernel's tiles and of the head's split input gradient rely on the launcher's cost model
+    for the kernel that their shapes run on."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    exe = str(tmp_path / "tiles")
+    subprocess.run([gxx, "-std=c++17", "-O1", SRC, "-o", exe, "-pthread"], check=True, timeout=300)
+
+    def choice(M, N, K):
+        tile, parts = map(int, subprocess.run([exe, "tile", str(M), str(N), str(K)], capture_output=True, text=True,
+                                              check=True).stdout.split())
+        return ("64x64", "128x64", "128x128", "128x192", "128x256", "large")[tile], parts
+
+    from test_gpu_lm_ends import SPLIT_PARTS
+    from test_gpu_ops import RING_TILES
+    assert {s: choice(*s)[0] for s in RING_TILES} == RING_TILES
+    assert set(RING_TILES.values()) == {"64x64", "128x64", "128x128", "128x192", "128x256"}
+    assert {s: choice(*s)[1] for s in SPLIT_PARTS} == SPLIT_PARTS
+    gemm = open(os.path.join(os.path.dirname(HERE), "paper_2110_13005_amd", "csrc", "gemm.hip")).read()
+    assert all(fn in gemm for fn in ("host::choose_ring_tile", "host::choose_split", "host::xcd_contiguous"))
