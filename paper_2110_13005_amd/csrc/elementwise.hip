@@ -198,9 +198,11 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void layernorm_bwd_kernel
     }
     float s1 = 0.f, s2 = 0.f;
 #pragma unroll
-    for (int c = 0; c < MAXC; ++c)
+    for (int c = 0; c < MAXC; ++c) {
+      // a column that does not exist stays out of the sums (of a row of large equal values, -mean * rstd overflows)
+      if (c * (WPR * 64) + pos >= nch) continue;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {                    // d is 0 where a column does not exist
+      for (int e = 0; e < 8; ++e) {
         const float d = (float)w.d[c][e], dxh = d * (float)gv[c][e];
         const float xh = ((float)w.x[c][e] - w.mean) * w.rstd;
         s1 += dxh;
@@ -208,6 +210,7 @@ __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void layernorm_bwd_kernel
         a_b[c][e] += d;
         a_g[c][e] += d * xh;
       }
+    }
     s1 = wave_sum(s1);
     s2 = wave_sum(s2);
     if (WPR > 1) {

@@ -108,6 +108,25 @@ def test_head_layernorm_backward_at_every_row_width(T, h):
         hd.close()
 
 
+@pytest.mark.parametrize("T,h", [(8, 8), (16, 520), (8, 2056)])
+def test_head_layernorm_backward_of_large_equal_rows(T, h):
+    """Rows of one large value (2^120 in bfloat16): xhat is exactly zero and every gradient finite, although -mean * rstd
+    would overflow."""
+    import torch
+    V, rng = 16, np.random.default_rng(h)
+    big = 2.0 ** 120 if B.ELEM == "bf16" and h == 8 else 2.0 ** 110 if B.ELEM == "bf16" else 2.0 ** 14
+    hd = HeadHandle(V, h, T, 1, np.ones(h, np.float32), np.zeros(h, np.float32), snap_elem(rng.standard_normal((h, V)).astype(np.float32)))
+    try:
+        x = np.full((1, T, h), big, np.float32)
+        loss = torch.zeros(1, device="cuda"); dx = torch.zeros(T, h, dtype=B.torch_elem_dtype(), device="cuda")
+        B.axonn_head_forward_backward(hd.h, dev_bf16(x), dev_i32(rng.integers(0, V, (1, T))), loss, dx)
+        torch.cuda.synchronize()
+        assert np.isfinite(host(dx)).all() and np.isfinite(hd.grads_numpy()["lnf_g"]).all()
+        assert not hd.grads_numpy()["lnf_g"].any() and np.abs(host(dx)).max() > 0      # xhat = 0: no gain gradient
+    finally:
+        hd.close()
+
+
 @pytest.mark.parametrize("n_streams,ckpt", [(1, 0), (2, 0), (3, 2)])
 def test_whole_model_on_one_stage_message_driven(n_streams, ckpt):
     """A stage that is both the first and the last one: token messages in, losses out, every gradient against the
