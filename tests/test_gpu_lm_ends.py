@@ -80,7 +80,7 @@ def test_head_loss_and_backward(T, h, V, M):
 
 
 @pytest.mark.parametrize("T,h", [(8, 8), (2056, 512), (1032, 520), (1048, 1024), (520, 1032), (1032, 2048), (264, 2056),
-                                 (264, 4104), (264, 6152), (72, 8200), (264, 16384)])
+                                 (264, 4104), (264, 6152), (72, 8200), (264, 16384), (520, 8192), (264, 12288), (264, 12296)])
 def test_head_layernorm_backward_at_every_row_width(T, h):
     """The LayerNorm backward kernel splits a row over 1, 2, 4 or 8 waves and holds 1 to 4 chunks per lane, several rows
     per workgroup or several rounds of rows: dx and the parameter gradients of two microbatches at the edges of that."""

@@ -134,9 +134,10 @@ def _kernel_scratch(lib_path, tmp_path):
 
 
 @pytest.mark.parametrize("elem", ["bf16", "fp16"])
-def test_gemm_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
-    """A register spilled inside a k loop waits for every copy in flight at each reload."""
+def test_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
+    """A register spilled inside a GEMM's k loop or the LayerNorm backward's row loop waits for every load in flight at
+    each reload."""
     from paper_2110_13005_amd import build as BLD
-    scratch = {k: v for k, v in _kernel_scratch(BLD.VARIANTS[elem][0], tmp_path).items() if "gemm_" in k}
+    scratch = {k: v for k, v in _kernel_scratch(BLD.VARIANTS[elem][0], tmp_path).items() if "gemm_" in k or "layernorm_" in k}
     assert len(scratch) > 50
     assert not {k: v for k, v in scratch.items() if v}
