@@ -144,9 +144,10 @@ __global__ __launch_bounds__(LN_THREADS) void layernorm_bwd_dx_kernel(
 // A row belongs to WPR waves (8 * MAXC elements per lane), 4 / WPR rows of a workgroup at a time; the next rows are
 // requested before the sums of the current ones are reduced.  HBM-bound at large T * h, bound by the chain load - reduce -
 // store of a few rows at small ones.  The kernel alone, against the three launches it replaced in a stage (dx, partial
-// sums, final sums), us: 1024 x 1024 5.7 / 12.3, 2048 x 4096 18.5 / 24.3, 2048 x 5120 21.7 / 29.2, 2048 x 10240 38.4 / 52.5,
-// 2048 x 16384 62.9 / 85.8, 512 x 16384 26.3 / 29.8; the final sums, once per batch, 4 to 5.  4 waves of 3 chunks: 32.6 at
-// 2048 x 5120; without the next row in registers 43.5 at 2048 x 10240, 71.9 at 2048 x 16384.
+// sums, final sums), us: 1024 x 1024 5.7 / 12.3, 2048 x 4096 18.5 / 24.3, 2048 x 5120 22.6 / 29.2, 2048 x 10240 38.4 / 52.5,
+// 2048 x 16384 62.9 / 85.8, 512 x 16384 26.3 / 29.8; the final sums, once per batch, 4 to 5.  Without the next row in
+// registers 32.6 at 2048 x 5120, 43.5 at 2048 x 10240, 71.9 at 2048 x 16384.  8 waves of 2 chunks instead of 4 of 3: 21.7 at
+// 2048 x 5120, but batches on two streams 0.4 to 0.9 % slower (a workgroup then finds less room beside a GEMM's).
 template <int WPR, int MAXC>
 __global__ __launch_bounds__(WPR > 4 ? 64 * WPR : 256) void layernorm_bwd_kernel(
     int T, int h, const elem_t* __restrict__ dout, const elem_t* __restrict__ x, const float* __restrict__ stats,
@@ -507,7 +508,7 @@ hipError_t launch_layernorm_fwd(int64_t T, int64_t h, const void* x, const void*
 // Workgroups of layernorm_bwd_kernel, i.e. slices of its partial sums: a row per wave (group), at most one workgroup per
 // CU (128, 256, 512 and 1024 measured in whole batches of h = 1024 to 10240: 256 and 512 the same, 128 and 1024 up to 1 %
 // slower; 256 needs half the memory).
-static int ln_waves_per_row(int64_t h) { return h <= 1024 ? 1 : h <= 2048 ? 2 : h <= 4096 ? 4 : 8; }
+static int ln_waves_per_row(int64_t h) { return h <= 1024 ? 1 : h <= 2048 ? 2 : h <= 8192 ? 4 : 8; }
 int layernorm_bwd_slices(int64_t T, int64_t h) {
   const int64_t rows = std::max(1, 4 / ln_waves_per_row(h));
   return (int)std::min<int64_t>(256, (T + rows - 1) / rows);
@@ -524,7 +525,8 @@ hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, 
   else if (h <= 1024) AXONN_LN(1, 2);
   else if (h <= 2048) AXONN_LN(2, 2);
   else if (h <= 4096) AXONN_LN(4, 2);
-  else if (h <= 8192) AXONN_LN(8, 2);
+  else if (h <= 6144) AXONN_LN(4, 3);
+  else if (h <= 8192) AXONN_LN(4, 4);
   else if (h <= 12288) AXONN_LN(8, 3);
   else if (h <= 16384) AXONN_LN(8, 4);
   else return hipErrorInvalidValue;
