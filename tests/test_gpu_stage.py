@@ -7,11 +7,12 @@ import numpy as np
 import pytest
 
 import oracle
+from oracle import transformer as OT
 from paper_2110_13005_amd import binding as B
 from paper_2110_13005_amd.inputs import CONFIGS, StageShape, make_stage_inputs, make_adam_inputs
 from paper_2110_13005_amd.stage import Stage
-from helpers import (rel_fro, dev_bf16, dev_f32, host, run_direct, check_batch, schedules, FWD_TOL, GRAD_TOL,
-                     ADAM_TOL, EPS)
+from helpers import (rel_fro, dev_bf16, dev_f32, host, parity, round_elem, run_direct, check_batch, schedules, FWD_TOL,
+                     GRAD_TOL, ADAM_TOL, EPS)
 
 pytestmark = pytest.mark.gpu
 
@@ -442,3 +443,34 @@ def test_batch_cut_short_where_no_weight_gradients_are_pending(done, opts):
         finally:
             for p in ptrs:
                 B.axonn_pinned_free(p)
+
+
+@pytest.mark.parametrize("T,h", [(2056, 256), (1032, 512), (1048, 520), (1032, 1024), (520, 1032), (528, 2048), (264, 2056),
+                                 (264, 4096), (264, 4104), (264, 6144), (264, 6152), (264, 8192), (264, 8200), (264, 12288),
+                                 (264, 12296), (72, 16384)])
+def test_layernorm_backward_of_a_layer_at_every_row_width(T, h):
+    """The LayerNorm backward a stage runs, on its own: with an identity and a diagonal of powers of two as the MLP's maps, a
+    GeLU far in its linear part and nothing else in the layer, dout is dz times the diagonal and the stage's input
+    gradient is LayerNorm 2's, residual gradient dz included, all exact but for the kernel's own rounding.  Widths at the
+    edges of its variants (1 to 8 waves per row, 1 to 4 chunks per lane), several rounds of rows, two microbatches."""
+    import torch
+    rng = np.random.default_rng(T + h)
+    sh = StageShape(1, h, h // 8, T, 1, 2, h)
+    diag = np.float32([1, -2, 0.5, -0.25, 4])[rng.integers(0, 5, h)]
+    gamma = round_elem(1 + 0.2 * rng.standard_normal(h)).astype(np.float32)
+    with Stage(sh, grad_accum_fp32=0) as st:
+        st.tensor("layer0.w_fc1").fill_diagonal_(1.0)
+        st.tensor("layer0.w_fc2").copy_(torch.diag(dev_f32(diag)))
+        st.tensor("layer0.b_fc1").fill_(64.0)
+        st.tensor("layer0.ln2_g").copy_(dev_f32(gamma))
+        torch.cuda.synchronize()
+        xs, dys = ([round_elem(m + rng.standard_normal((1, T, h))).astype(np.float32) for _ in range(2)] for m in (0.5, 0.0))
+        _, dxs, grads = run_direct(st, xs, dys)
+    tot_g = tot_b = 0.0
+    for x, dy, dx in zip(xs, dys, dxs):
+        _, xhat, rstd = OT.layernorm_fwd(x.astype(np.float64), gamma.astype(np.float64), np.zeros(h), EPS)
+        ref, dg, db = OT.layernorm_bwd(dy.astype(np.float64) * diag, xhat, rstd, gamma.astype(np.float64))
+        parity(dx.reshape(ref.shape), ref + dy, 5e-3, 1.0, label="layernorm_backward_of_a_layer")      # one rounding
+        tot_g, tot_b = tot_g + dg, tot_b + db
+    parity(grads[0]["ln2_g"], tot_g, 5e-3, 1.0, axis=None, label="layernorm_backward_of_a_layer")
+    parity(grads[0]["ln2_b"], tot_b, 5e-3, 1.0, axis=None, label="layernorm_backward_of_a_layer")
