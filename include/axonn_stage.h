@@ -120,7 +120,8 @@ int axonn_stage_grads(axonn_stage_t* st, void** dev_bf16);
 int axonn_stage_zero_grad(axonn_stage_t* st, void* hip_stream);
 /* Device bytes the stage holds, by category (Sec. 5.2 accounting): [0] bf16 params,
  * [1] bf16 grads, [2] fp32 grad shadow (0 unless grad_accum_fp32), [3] activation stash,
- * [4] backward workspace (with ckpt_stride: including the shared activation buffers),
+ * [4] backward workspace (with ckpt_stride: including the shared activation buffers; up to 8 KiB
+ * per layer and hidden unit of it are the partial sums of the LayerNorm parameter gradients),
  * [5] optimizer bucket buffers (0 until attached). */
 int axonn_stage_device_bytes(const axonn_stage_t* st, uint64_t bytes[6]);
 

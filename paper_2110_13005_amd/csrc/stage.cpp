@@ -941,7 +941,7 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   // partial sums of the LayerNorm parameter gradients, which collect over a batch (two LayerNorms per layer; gradient
   // chain), and of the bias gradients where a weight-gradient kernel does not form them itself (weight-gradient stream)
   const uint64_t e_red = align_up((uint64_t)2 * cfg->n_layers * 2 * layernorm_bwd_slices(T, h) * h * 4, 256);
-  const uint64_t e_wred = align_up((uint64_t)2 * ((T + 63) / 64) * wide * 4, 256);
+  const uint64_t e_wred = align_up((uint64_t)((T + 63) / 64) * wide * 4, 256);
   st->ws_bytes = 3 * e_th + e_lse + e_red + e_wred;
   CREATE_TRY(hipMalloc((void**)&st->ws_base, st->ws_bytes));
   {
