@@ -187,7 +187,7 @@ def other_workload(args, config, batches, dev):
 
 def host_link_probe(n_bytes=1 << 28, reps=6):
     """Bare rates of the machine's host link for 256 MiB buckets of pinned memory (the library's probe: hipMemcpyAsync
-    as the optimizer pipeline issues it): host to device alone, device to host alone, and per direction with both
+    as the optimizer's bucket pipeline issues it): host to device alone, device to host alone, and per direction with both
     running at once on two streams."""
     from paper_2110_13005_amd import binding as B
     h2d, d2h, both = B.axonn_host_link_probe(0, n_bytes, reps)
@@ -339,8 +339,7 @@ def main():
     }
     if not args.no_optimizer:
         om = float(np.mean(opt_ms))
-        out["optimizer"] = {"ms": om, "params": n, "host_link_GBps_each_way": 12.0 * n / (om * 1e-3) / 1e9,
-                            "buckets": (n + args.bucket_elems - 1) // args.bucket_elems}
+        out["optimizer"] = {"ms": om, "params": n, "host_link_GBps_each_way": 12.0 * n / (om * 1e-3) / 1e9}
         if args.overlap_chunk > 0:
             # the same steps with the optimizer step overlapped with the backward tail (not part of `value`)
             k_steps = max(2, min(args.steps, 5))
@@ -353,7 +352,7 @@ def main():
             torch.cuda.synchronize()
             wall_o = time.perf_counter() - t1
             out["optimizer_overlapped"] = {
-                "chunk_buckets": args.overlap_chunk, "steps": k_steps, "ms_per_step": wall_o / k_steps * 1e3,
+                "chunk_buckets": args.overlap_chunk, "buckets": (n + args.bucket_elems - 1) // args.bucket_elems, "steps": k_steps, "ms_per_step": wall_o / k_steps * 1e3,
                 "ms_per_step_plain": wall / args.steps * 1e3,
                 "tokens_per_s_whole_step": tokens / (wall_o / k_steps)}
 
@@ -405,10 +404,11 @@ def main():
         if "layernorm_fwd" in kern:      # read x, write the normalised row + 8 B of statistics per row
             kern["layernorm_fwd"]["GBps"] = (4.0 * T * h + 8.0 * T) / (kern["layernorm_fwd"]["avg_ms"] * 1e-3) / 1e9
         if "layernorm_bwd" in kern:
-            # read dout, x and the residual gradient, write dx, read the statistics: the work as defined; the three
-            # launches of a call (dx; column partial sums; their reduction) read dout and x a second time
+            # read dout, x and the residual gradient, write dx, read the statistics: the work as defined; the kernel
+            # also reads and writes its 256 slices of the parameter sums (the time includes their reduction behind the
+            # batch's last microbatch)
             kern["layernorm_bwd"]["GBps"] = (8.0 * T * h + 8.0 * T) / (kern["layernorm_bwd"]["avg_ms"] * 1e-3) / 1e9
-            kern["layernorm_bwd"]["GBps_as_launched"] = 12.0 * T * h / (kern["layernorm_bwd"]["avg_ms"] * 1e-3) / 1e9
+            kern["layernorm_bwd"]["GBps_as_launched"] = (8.0 * T * h + 16.0 * 256 * h) / (kern["layernorm_bwd"]["avg_ms"] * 1e-3) / 1e9
         # (the bias gradients have no launches of their own: the weight-gradient GEMMs form them)
         if "adam" in kern:               # theta, m, v read and written (fp32), gradient read and parameter written (bf16)
             kern["adam"]["GBps"] = 28.0 * n / (kern["adam"]["total_ms"] * 1e-3) / 1e9
@@ -452,7 +452,7 @@ def main():
             o = out["optimizer"]
             # the step moves 12 B per parameter in each direction at once; the denominator is what the box
             # delivers in one direction alone (two bare copy streams with nothing between them serialise on the copy
-            # engine: `both_GBps_each_way`; the step's drain copies run as kernels beside the engine's fetches)
+            # engine: `both_GBps_each_way`; the step is a kernel that reads and writes over the link itself)
             o["frac_of_link_measured"] = o["host_link_GBps_each_way"] / min(hl["h2d_alone_GBps"], hl["d2h_alone_GBps"])
             o["frac_of_link_raw"] = o["host_link_GBps_each_way"] / hl["pcie_gen5_x16_raw_GBps"]
     # the other stage shapes of the benchmark definition, forward+backward only, a few batches each

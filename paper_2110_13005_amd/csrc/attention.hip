@@ -367,7 +367,8 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 // ============================================================================ backward
 // delta[b][a][i] = sum_d dO[i][d] * O[i][d]
 // For any head dimension d that is a multiple of 4: 16 lanes per (row, head), 4 elements per lane and step.
-// (Launched in front of the general kernels only: the exact-size dQ kernel forms delta itself.)
+// (Launched in front of the general kernels and of the one-launch backward of either kind; the exact-size dQ kernel in a
+// launch of its own forms delta itself.)
 __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs, int s, int a, int d,
                                                                  const elem_t* __restrict__ o,
                                                                  const elem_t* __restrict__ dout,

@@ -583,7 +583,7 @@ hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void*
 // directions at once, without staging buffers, copies or a pipeline to fill.  The link is the bound (12 bytes per
 // parameter each way).  Few workgroups on purpose: with 64 the requests in flight just cover the link's round trip;
 // more of them only queue reads in front of the writes.  2^26 parameters: 64 workgroups 16.3 ms (49.5 GB/s each way),
-// 256 17.7, 4096 17.8; through buckets of 2^24 with copies on both sides 20-31 ms.  2^20: 0.37 ms against 0.60.
+// 256 17.7, 4096 17.8; through buckets of 2^24 with copies on both sides 20-31 ms.  2^20: 0.34 ms against 0.52 to 0.60.
 // Four elements per lane and array: a wave's access is 1 KB of consecutive bytes.
 constexpr int ADAM_HOST_BLOCKS = 64;
 __global__ __launch_bounds__(256) void adam_host_kernel(uint64_t n4, uint64_t n, float* __restrict__ theta,

@@ -1096,7 +1096,8 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
 //     steps for every copy to arrive.  One barrier per step.
 //   * Two sets of fragment registers: the MFMAs of a step run while the fragments of the next one are read.
 //   * Any K (a multiple of 8), any segment length: a copy whose k lies beyond the segment reads zeros, chosen per lane.
-//   * What the epilogue reads (bias, residual, stored derivative, accumulating C) is requested before the k loop.
+//   * What the epilogue reads (bias, residual, stored derivative, accumulating C) is requested before the k loop, with
+//     tiles of 128 x 192 and 128 x 256, which leave no registers for it, behind the loop.
 // Stage layout: a k-contiguous operand in blocks of 64 k, 128 bytes per row, chunk q of row r in slot q ^ ((r >> 1) & 7);
 // a k-strided one as k rows of ROWS elements, the 32-byte pieces of row k permuted by ring_swizzle(k), so that the
 // eight k rows that one transposing read touches (k0 .. k0+3 and k0+8 .. k0+11) fall into different banks.

@@ -243,7 +243,7 @@ inline double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
 // 8192 103 / 67, 2048 x 3072 x 12288 226 / 137 (a kernel of 128 x 128 tiles staged through registers), 2048 x 4096 x 1024
 // with GeLU 35.6 / 28.5 (half a round of 256 x 256 tiles).
 // From 128 tiles on, which the large-problem kernels run well, the ring tile has to be modelled 8 % faster: without that,
-// and with weights of 10, 0.75 / 0.80 / 1.0 and 1.05 / 1.10 / 1.4, 21 of 910 launches of such shapes were more than 4 % slower
+// and with weights of 10, 0.75 / 0.80 / 1.0 and 1.05 / 1.10 / 1.4, 21 of 1050 launches of such shapes were more than 4 % slower
 // than on the large-problem kernels, up to 2816 x 2944 x 10112 168 us against 137; now 5 are, by at most 5 %.
 // `forced` (-1: none): number of 256 x 256 tiles from which the large-problem kernels are used whatever the model says.
 // The rule does not look at whether the launch shares the chip: a ring kernel adds its two halves of k in another order

@@ -35,8 +35,8 @@ __global__ __launch_bounds__(ENDS_THREADS) void embed_fwd_kernel(
 // One workgroup per token t; it works only if t is the first occurrence of its id, and then adds the
 // rows of all occurrences in token order (fp32), so every table row has exactly one writer.  Rows
 // whose id does not occur are not touched (the caller clears the table before a batch's first pass).
-// The workgroup compares 256 tokens at a time and walks the matches as bit masks: with every thread comparing all
-// tokens one after the other the search took longer than the rows (2048 tokens of h = 1024: 111 -> 18 us).
+// The workgroup compares 1024 tokens at a time, four per thread, and walks the matches as bit masks: with every thread
+// comparing all tokens one after the other the search took longer than the rows (2048 tokens of h = 1024: 111 -> 18 us).
 __global__ __launch_bounds__(ENDS_THREADS) void embed_bwd_wte_kernel(
     int T, int h, int vocab, const int* __restrict__ tokens, const elem_t* __restrict__ dx,
     elem_t* __restrict__ dwte, int accumulate) {

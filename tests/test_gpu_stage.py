@@ -68,9 +68,9 @@ def test_ragged_and_degenerate_shapes(sh):
 @pytest.mark.parametrize("mask", [15, 0])
 def test_parity_through_the_large_problem_gemm_kernels(mask):
     """The weight-gradient kernels of large problems also add up the bias gradients, from the tiles they multiply.
-    With the launcher's threshold lowered the small shapes go through them too (the copying kernels where the token
-    count is a multiple of 64, mask 15; the register-staged ones everywhere, mask 0), element by element against
-    the oracle."""
+    With the launcher's threshold lowered the small shapes go through them too (the copying kernels, mask 15, in their
+    variant with a short last k-tile where the token count is no multiple of 64; the register-staged ones, mask 0),
+    element by element against the oracle."""
     try:
         B.axonn_tuning(B.TUNE_GEMM_COPY_MASK, mask)
         B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, 1)
