@@ -366,9 +366,40 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 
 // ============================================================================ backward
 // delta[b][a][i] = sum_d dO[i][d] * O[i][d]
+// Launched in front of the general kernels and of the one-launch backward; the exact-size dQ kernel in a launch of its own
+// forms delta itself.  For the exact head dimensions: D / 8 lanes per (row, head), 8 elements each, added in the order of
+// that dQ kernel, so that a gradient does not depend on which of the two forms it.
+__device__ __forceinline__ float delta_of_8(elemx8 ov, elemx8 dv) {
+  float p = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    float x = (float)ov[e];
+#ifdef AXONN_ELEM_FP16
+    asm("" : "+v"(x));   // else one of the two kernels gets two-element dot products, whose sums are rounded differently
+#endif
+    p = fmaf(x, (float)dv[e], p);
+  }
+  return p;
+}
+template <int D>
+__global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_pairs, int s, int a, const elem_t* __restrict__ o,
+                                                         const elem_t* __restrict__ dout, float* __restrict__ delta) {
+  constexpr int LPR = D / 8;
+  const int64_t pair = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;   // (row, head)
+  const int j = threadIdx.x % LPR;
+  float p = 0.f;
+  if (pair < n_pairs)                                                             // rows are a * D long
+    p = delta_of_8(*reinterpret_cast<const elemx8*>(o + pair * D + 8 * j), *reinterpret_cast<const elemx8*>(dout + pair * D + 8 * j));
+#pragma unroll
+  for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
+  if (pair < n_pairs && j == 0) {
+    const int64_t row = pair / a;
+    const int hd = (int)(pair % a);
+    const int64_t bi = row / s, i = row % s;
+    delta[(bi * a + hd) * s + i] = p;
+  }
+}
 // For any head dimension d that is a multiple of 4: 16 lanes per (row, head), 4 elements per lane and step.
-// (Launched in front of the general kernels and of the one-launch backward of either kind; the exact-size dQ kernel in a
-// launch of its own forms delta itself.)
 __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs, int s, int a, int d,
                                                                  const elem_t* __restrict__ o,
                                                                  const elem_t* __restrict__ dout,
@@ -794,10 +825,7 @@ __device__ __forceinline__ void attn_bwd_dq(
     r_do.template store<D + 8>(smem, tid);
 #pragma unroll
     for (int j = 0; FORM_DELTA && j < Rows::NCH; ++j) {
-      const elemx8 ov = __builtin_bit_cast(elemx8, r_o.r[j]), dv = __builtin_bit_cast(elemx8, r_do.r[j]);
-      float p = 0.f;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) p += (float)ov[e] * (float)dv[e];
+      float p = delta_of_8(__builtin_bit_cast(elemx8, r_o.r[j]), __builtin_bit_cast(elemx8, r_do.r[j]));
 #pragma unroll
       for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
       const int row = tid / LPR + j * RSTEP;
@@ -970,7 +998,8 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
   // the exact-size dQ kernel (the dispatch's condition for it) forms delta itself and runs first
-  const bool dq_forms_delta = !both && (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
+  const bool exact = (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
+  const bool dq_forms_delta = !both && exact;
   hipError_t e;
   dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
@@ -981,8 +1010,15 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
     return hipGetLastError();
   }
   const int64_t n_pairs = (int64_t)b * s * a;
-  hipLaunchKernelGGL(attn_delta_general_kernel, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a, d,
-                     (const elem_t*)o, (const elem_t*)dout, delta);
+  if (exact && d == 64)
+    hipLaunchKernelGGL(attn_delta_kernel<64>, dim3((unsigned)((n_pairs + 31) / 32)), dim3(256), 0, st, n_pairs, s, a,
+                       (const elem_t*)o, (const elem_t*)dout, delta);
+  else if (exact)
+    hipLaunchKernelGGL(attn_delta_kernel<128>, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a,
+                       (const elem_t*)o, (const elem_t*)dout, delta);
+  else
+    hipLaunchKernelGGL(attn_delta_general_kernel, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a, d,
+                       (const elem_t*)o, (const elem_t*)dout, delta);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (both) {

@@ -167,15 +167,18 @@ __device__ __forceinline__ elem_t f2bf(float v) { return (elem_t)v; }
 // Stegun 7.1.26, absolute error <= 1.5e-7, i.e. one fp32 ulp of values near 1); Phi takes erfc(|x|/sqrt2)
 // on the side of the tail, so there is no cancellation for negative x.  `e` returns exp(-x^2/2), which
 // the derivative needs as well.
+// The fused multiply-adds are written out and no others formed: a result must not depend on the kernel (the tile) that the
+// compiler made the choice in.
 __device__ __forceinline__ float normal_cdf_f(float x, float& e) {
+#pragma clang fp contract(off)
   const float z = fabsf(x) * 0.70710678118654752440f;
-  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * z);   // v_rcp_f32 (1 ulp), not the 10-instruction IEEE division
+  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, z, 1.0f));   // v_rcp_f32 (1 ulp), not the 10-instruction IEEE division
   e = __expf(-z * z);
   float p = 1.061405429f;
-  p = p * t - 1.453152027f;
-  p = p * t + 1.421413741f;
-  p = p * t - 0.284496736f;
-  p = p * t + 0.254829592f;
+  p = __builtin_fmaf(p, t, -1.453152027f);
+  p = __builtin_fmaf(p, t, 1.421413741f);
+  p = __builtin_fmaf(p, t, -0.284496736f);
+  p = __builtin_fmaf(p, t, 0.254829592f);
   const float half_erfc = 0.5f * p * t * e;
   return x >= 0.f ? 1.0f - half_erfc : half_erfc;
 }
@@ -186,14 +189,15 @@ __device__ __forceinline__ float gelu_f(float x) {
 __device__ __forceinline__ float gelu_grad_f(float x) {
   float e;
   const float cdf = normal_cdf_f(x, e);
-  return cdf + x * e * 0.39894228040143267794f;
+  return __builtin_fmaf(x * e, 0.39894228040143267794f, cdf);
 }
 // GeLU(x) and GeLU'(x) together (they share Phi and the exponential).
 __device__ __forceinline__ void gelu_with_grad_f(float x, float& y, float& dy) {
+#pragma clang fp contract(off)
   float e;
   const float cdf = normal_cdf_f(x, e);
   y = x * cdf;
-  dy = cdf + x * e * 0.39894228040143267794f;
+  dy = __builtin_fmaf(x * e, 0.39894228040143267794f, cdf);
 }
 #endif  // __HIPCC__
 
@@ -216,6 +220,8 @@ struct GemmArgs {
   int M, N, K;       // K = length of ONE segment
   int n_seg;
   int accumulate;
+  int rule_m;        // rows by which the kernel is chosen (0: M): one microbatch's where M is several of them, so that a
+                     // microbatch's sums are added in the same order whether it runs alone or with others
   int concurrent;    // other kernels share the chip with this launch: prefer the most efficient tile shape
                      // over one whose tile count fills the CUs a whole number of times
   int tiles_m, tiles_n;
@@ -248,20 +254,25 @@ hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const vo
                                 const float* stats, const void* gamma, const void* res_grad,
                                 void* dx, void* dgamma, void* dbeta, int acc_mode, bool dst_fp32,
                                 float* ws, hipStream_t s);
-// dx and the parameter-gradient sums of one call, added to (`first`: stored in) `partial`: layernorm_bwd_slices(T, h)
-// slices of 2 * h floats.  launch_layernorm_param_grads stores what the slices have collected in the gradient vectors.
+// dx and the parameter-gradient sums of one call, added to (`first`: stored in) the `slices` slices of 2 * h floats of
+// `partial`; layernorm_bwd_slices(T, h): as many as a call with T rows has use for, the same number in all calls that
+// collect in one `partial`.  launch_layernorm_param_grads stores what the slices have collected in the gradient vectors.
 int layernorm_bwd_slices(int64_t T, int64_t h);
 hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, const void* x, const float* stats,
-                                        const void* gamma, const void* res_grad, void* dx, float* partial, bool first,
-                                        hipStream_t s);
-hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
+                                        const void* gamma, const void* res_grad, void* dx, float* partial, int slices,
+                                        bool first, hipStream_t s);
+hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta,
                                         bool dst_fp32, hipStream_t s);
 // The same for both LayerNorms of n_layers layers (their slices lie behind one another) in one launch, into a 16-bit
 // gradient buffer: dgamma is the first layer's first one, each shift gradient follows its gain gradient.
-hipError_t launch_layernorm_param_grads_all(int64_t T, int64_t h, int n_layers, const float* partial, void* dgamma,
+hipError_t launch_layernorm_param_grads_all(int slices, int64_t h, int n_layers, const float* partial, void* dgamma,
                                             int64_t layer_stride, int64_t second_offset, hipStream_t s);
 hipError_t launch_colsum(int64_t T, int64_t N, const void* y, int64_t ldy, void* out, int acc_mode,
                          bool dst_fp32, float* ws, hipStream_t s);
+// n copies of `bytes` bytes each (a multiple of 16, like every address) in one launch.
+constexpr int kMaxCopies = 8;
+struct Copies { const void* src[kMaxCopies]; void* dst[kMaxCopies]; };
+hipError_t launch_copies(int n, uint64_t bytes, const Copies& c, hipStream_t s);
 hipError_t launch_f32_to_elem(uint64_t n, const float* src, void* dst, hipStream_t s);
 hipError_t launch_fill_elem(uint64_t n, void* dst, float value, hipStream_t s);
 // Counts the non-finite elements of x[0..n) into ws[kNonfiniteWsCounters - 1]; ws: kNonfiniteWsCounters

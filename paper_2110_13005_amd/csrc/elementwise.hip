@@ -405,6 +405,13 @@ __global__ __launch_bounds__(256) void colsum_final_kernel(int nrb, int N,
   }
 }
 
+// Several copies of the same length, one per grid row: the inputs and results of microbatches that run together.
+__global__ __launch_bounds__(256) void copies_kernel(uint64_t n16, const Copies c) {
+  const floatx4* __restrict__ src = reinterpret_cast<const floatx4*>(c.src[blockIdx.y]);
+  floatx4* __restrict__ dst = reinterpret_cast<floatx4*>(c.dst[blockIdx.y]);
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (uint64_t)gridDim.x * 256) dst[i] = src[i];
+}
+
 __global__ __launch_bounds__(256) void f32_to_elem_kernel(uint64_t n8, uint64_t n,
                                                           const float* __restrict__ src,
                                                           elem_t* __restrict__ dst) {
@@ -514,9 +521,9 @@ int layernorm_bwd_slices(int64_t T, int64_t h) {
   return (int)std::min<int64_t>(256, (T + rows - 1) / rows);
 }
 hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, const void* x, const float* stats,
-                                        const void* gamma, const void* res_grad, void* dx, float* partial, bool first,
-                                        hipStream_t s) {
-  const dim3 grid(layernorm_bwd_slices(T, h));
+                                        const void* gamma, const void* res_grad, void* dx, float* partial, int slices,
+                                        bool first, hipStream_t s) {
+  const dim3 grid((unsigned)slices);
 #define AXONN_LN(WPR, MAXC)                                                                               \
   hipLaunchKernelGGL((layernorm_bwd_kernel<WPR, MAXC>), grid, dim3(WPR > 4 ? 64 * WPR : 256), 0, s, (int)T, (int)h, \
                      (const elem_t*)dout, (const elem_t*)x, stats, (const elem_t*)gamma, (const elem_t*)res_grad, (elem_t*)dx, \
@@ -533,16 +540,16 @@ hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, 
 #undef AXONN_LN
   return hipGetLastError();
 }
-hipError_t launch_layernorm_param_grads(int64_t T, int64_t h, const float* partial, void* dgamma, void* dbeta,
+hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta,
                                         bool dst_fp32, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, layernorm_bwd_slices(T, h),
+  hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, slices,
                      (int)h, partial, dbeta, dgamma, 1, dst_fp32 ? 1 : 0, 0, 0);
   return hipGetLastError();
 }
-hipError_t launch_layernorm_param_grads_all(int64_t T, int64_t h, int n_layers, const float* partial, void* dgamma,
+hipError_t launch_layernorm_param_grads_all(int slices, int64_t h, int n_layers, const float* partial, void* dgamma,
                                             int64_t layer_stride, int64_t second_offset, hipStream_t s) {
   hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64), (unsigned)(2 * n_layers)), dim3(256), 0, s,
-                     layernorm_bwd_slices(T, h), (int)h, partial, (elem_t*)dgamma + h, dgamma, 1, 0, layer_stride, second_offset);
+                     slices, (int)h, partial, (elem_t*)dgamma + h, dgamma, 1, 0, layer_stride, second_offset);
   return hipGetLastError();
 }
 hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const void* x,
@@ -671,6 +678,12 @@ hipError_t launch_count_nonfinite(uint64_t n, const void* x, uint64_t* ws, hipSt
   return hipGetLastError();
 }
 
+hipError_t launch_copies(int n, uint64_t bytes, const Copies& c, hipStream_t s) {
+  if (n < 1 || n > kMaxCopies || bytes % 16) return hipErrorInvalidValue;
+  const unsigned blocks = (unsigned)std::min<uint64_t>(512, (bytes / 16 + 255) / 256);
+  hipLaunchKernelGGL(copies_kernel, dim3(blocks, (unsigned)n), dim3(256), 0, s, bytes / 16, c);
+  return hipGetLastError();
+}
 hipError_t launch_f32_to_elem(uint64_t n, const float* src, void* dst, hipStream_t s) {
   hipLaunchKernelGGL(f32_to_elem_kernel, dim3(grid_for(n / 8)), dim3(256), 0, s, n / 8, n, src,
                      (elem_t*)dst);

@@ -158,6 +158,11 @@ __device__ __forceinline__ void epi_finish(float (&v)[4], const float (&bv)[4], 
     for (int e = 0; e < 4; ++e) {
       float y, dy;
       gelu_with_grad_f(v[e], y, dy);
+#ifdef AXONN_ELEM_FP16
+      // keeps the rounding to half precision a step of its own: fused with the last multiply-add, in some kernels and for
+      // some elements only, it would make the result depend on the tile
+      asm("" : "+v"(dy));
+#endif
       v[e] = y;
       dv[e] = (elem_t)dy;
     }
@@ -1087,9 +1092,9 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
 
 // ---------------------------------------------------------------------------------------------
 // Ring kernel: problems that do not fill the chip with 256 x 256 tiles.  32*TM x 32*TN block tile, KG groups of 2 x 2
-// waves that share the k range of every stage (group j takes its share of the stage's 32-wide k slices), so that a
-// small tile still puts two waves on every SIMD without more LDS reads per MFMA; the groups' results are added
-// through LDS at the end.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
+// waves that share the k range of every stage (group j takes every KG-th of the stage's 32-wide k slices, the same ones
+// whatever the tile and the stage: a result does not depend on the tile), so that a small tile still puts two waves on
+// every SIMD without more LDS reads per MFMA; the groups' results are added through LDS at the end.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
 // the traffic into and out of LDS (32 KB copied in, 64 KB of fragments read per 512 MFMA clocks).
 //   * Tiles are copied into LDS by the memory pipeline, into a ring of NS stages of 64*NSUB k each: NS - 1 stages are
 //     in flight or being read, so a short k range is fetched in one memory latency, and a long one has two or three
@@ -1270,10 +1275,10 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
     for (int s = 0; s < SLICES; ++s) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, grp * SLICES + s, lane);
+        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, s * KG + grp, lane);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, grp * SLICES + s, lane);
+        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, s * KG + grp, lane);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -1602,8 +1607,9 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
   // not start at a multiple of 16 bytes: the ring kernel's copies into LDS are not used on them.  Tiles of 128 x 128 below
   // half a chip of 256 x 256 ones: weight gradient 1024 x 4096 over 270336 tokens 4.02 ms, with 256 x 256 tiles 7.19.
   const bool fits = fits_32bit_offsets(A_KC ? g.M : g.K, g.lda) && fits_32bit_offsets(B_KC ? g.N : g.K, g.ldb);
+  const int rule_m = g.rule_m > 0 ? g.rule_m : g.M;
   if (!fits || !aligned16(g)) {
-    const int64_t big_tiles = (int64_t)((g.M + 255) / 256) * ((g.N + 255) / 256), forced = big_tile_threshold();
+    const int64_t big_tiles = (int64_t)((rule_m + 255) / 256) * ((g.N + 255) / 256), forced = big_tile_threshold();
     if (big_tiles < (forced >= 0 ? forced : 128)) return launch_cfg<128, 128, 64, 2, 2, A_KC, B_KC>(epi, g, s);
     if (!fits) return launch_cfg<256, 256, 64, 2, 4, A_KC, B_KC>(epi, g, s);
   }
@@ -1620,7 +1626,8 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
       }
     }
   }
-  const int tile = aligned16(g) ? host::choose_ring_tile(g.M, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) : -1;
+  int tile = aligned16(g) ? host::choose_ring_tile(rule_m, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) : -1;
+  if (tile >= 0 && rule_m != g.M) tile = host::fastest_ring_tile(g.M, g.N, nk);
   if (tile >= 0) return launch_ring_tile<A_KC, B_KC>(tile, epi, g, s, 1);
   switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
     case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);

@@ -95,10 +95,10 @@ inline int wgrad_action(bool last_of_batch, int group, int n_awaiting) {
   if (last_of_batch) return WGRAD_FLUSH_FINAL;
   return (group > 0 && n_awaiting >= group) ? WGRAD_FLUSH : WGRAD_NONE;
 }
-// Are the gradients of every backward so far complete once the next one's work is queued (`n_awaiting` slots wait
-// before it)?  With checkpointing its weight gradients go with the chain; otherwise if a group closes.
-inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting) {
-  return ckpt || wgrad_action(last_of_batch, group, n_awaiting + 1) != WGRAD_NONE;
+// Are the gradients of every backward so far complete once the work of the next `n` is queued (`n_awaiting` slots wait
+// before them)?  With checkpointing their weight gradients go with the chain; otherwise if a group closes.
+inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting, int n = 1) {
+  return ckpt || wgrad_action(last_of_batch, group, n_awaiting + n) != WGRAD_NONE;
 }
 
 // ------------------------------------------------------------------------------ messages
@@ -128,6 +128,75 @@ int choose_message(size_t n_posted, Msg&& msg, Arrived&& arrived, const Slots& s
     return (int)i;
   }
   return -1;
+}
+
+// How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself).  A small
+// microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to 2^24 elements of an
+// activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of 256 x 256.  Whole batches
+// of 8 microbatches (4 at h = 4096, 6 with 3 in flight at 4096 tokens), each by itself / up to 2^22 / 2^23 / 2^24 / 2^25 elements,
+// ms: h 1024, 1024 tokens 6.01 / 4.35 / 4.03 / 4.02 / 4.03; h 2048, 2048 tokens 11.7 / 11.7 / 10.75 / 10.73 / 10.58; h 4096, 2048
+// tokens 18.2 / 18.2 / 18.2 / 16.3 / 16.0; h 6144, 512 tokens - / 22.1 / 19.8 / 19.6 / 19.1; h 1024, 4096 tokens - / 7.64 / 7.32 /
+// 7.62 / 7.60.  Beyond 2^24 little is gained, and results come later than they have to.
+constexpr int kMaxMerge = 8;
+constexpr int64_t kMergeElements = int64_t(1) << 24;
+// A backward pass of several microbatches keeps a gradient of h columns and one float per head in the place of the f columns
+// of GeLU': narrower MLPs run one by one.
+inline int merge_limit(int64_t T, int64_t h, int64_t f, int64_t heads, int pipeline_limit) {
+  if (f < h + 2 * heads) return 1;
+  const int64_t widest = std::max<int64_t>(h, (f + 3) / 4);
+  return (int)std::max<int64_t>(1, std::min<int64_t>({kMaxMerge, pipeline_limit, kMergeElements / (T * widest)}));
+}
+
+// What the loop needs to know of a posted message to run it together with others.  `alone`: its own completion is waited
+// for (a done_event: the neighbour's message hangs on it), so it is not made to wait for others.
+struct MessageSpan {
+  int kind, mb_id;
+  bool alone;
+  uint64_t in, in_end, out, out_end;          // payload and result in device memory
+};
+// May `later` start together with `earlier`, posted before it?  Not if one of the two reads or writes what the other writes.
+inline bool independent(const MessageSpan& earlier, const MessageSpan& later) {
+  const auto overlap = [](uint64_t a, uint64_t a_end, uint64_t b, uint64_t b_end) { return a < b_end && b < a_end; };
+  return !overlap(earlier.out, earlier.out_end, later.in, later.in_end) &&
+         !overlap(earlier.out, earlier.out_end, later.out, later.out_end) &&
+         !overlap(earlier.in, earlier.in_end, later.out, later.out_end);
+}
+// The posted messages that run together with `chosen` (the choice of choose_message, for which a forward has a free slot):
+// messages of its kind that have arrived, are admissible then and there, and are independent of every message posted before
+// them.  Their slots are consecutive, so that each tensor of the stash is one matrix over all their tokens.
+// span(i) -> MessageSpan of posted message i.  picked: positions, in slot order, the chosen message first; returns their number.
+template <class Slots, class Span, class Arrived>
+int merge_messages(size_t n_posted, Span&& span, Arrived&& arrived, int chosen, const Slots& slots, int in_flight,
+                   int pipeline_limit, int max_merge, int* picked) {
+  picked[0] = chosen;
+  const MessageSpan first = span((size_t)chosen);
+  if (first.alone || max_merge < 2) return 1;
+  int n = 1;
+  const auto joins = [&](size_t i) {
+    const MessageSpan m = span(i);
+    if (m.kind != first.kind || m.alone || arrived(i) != 1) return false;
+    for (size_t j = 0; j < i; ++j)
+      if (!independent(span(j), m)) return false;
+    for (int k = 0; k < n; ++k) {
+      if ((size_t)picked[k] == i || span((size_t)picked[k]).mb_id == m.mb_id) return false;
+      if ((size_t)picked[k] > i && !independent(m, span((size_t)picked[k]))) return false;
+    }
+    return true;
+  };
+  const int slot0 = first.kind == 0 ? find_free(slots) : find_live(slots, first.mb_id);
+  for (; slot0 >= 0 && n < max_merge && slot0 + n < (int)slots.size(); ++n) {
+    const auto& next = slots[slot0 + n];
+    int found = -1;
+    for (size_t i = 0; i < n_posted && found < 0; ++i) {
+      const MessageSpan m = span(i);
+      const bool fits = m.kind == 0 ? next.state == SLOT_FREE && in_flight + n < pipeline_limit && find_live(slots, m.mb_id) < 0
+                                    : next.state == SLOT_LIVE && next.mb_id == m.mb_id;
+      if (fits && joins(i)) found = (int)i;
+    }
+    if (found < 0) break;
+    picked[n] = found;
+  }
+  return n;
 }
 
 // post(): a message is refused if one of the same kind for the same microbatch is already posted, or if the
@@ -237,6 +306,14 @@ inline double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
          (last > 0 ? c.fixed + steps * (c.step_few + (c.step_full - c.step_few) * last) : 0.0);
 }
 
+// The fastest ring tile for an M x N x (nk k-steps) problem.
+inline int fastest_ring_tile(int64_t M, int64_t N, int64_t nk) {
+  int best = 0;
+  for (int t = 1; t < RING_TILES; ++t)
+    if (tile_cost(kRingCost[t], M, N, nk) < tile_cost(kRingCost[best], M, N, nk)) best = t;
+  return best;
+}
+
 // Which ring tile an M x N x (nk k-steps) problem takes; -1: a large-problem kernel.  Those stay where their 256 x 256
 // tiles fill the chip, and where the model prefers one of their widths.  Measured (bf16, single launches, the kernels
 // before / now): 256 x 256 x 1024 17.0 / 5.7 us, 1024 x 1024 x 4096 52.6 / 16.1, 2048 x 1024 x 4096 52.6 / 23.8, 2048 x 2048 x
@@ -253,13 +330,8 @@ inline double tile_cost(const TileCost& c, int64_t M, int64_t N, int64_t nk) {
 inline int choose_ring_tile(int64_t M, int64_t N, int64_t nk, int64_t forced, bool fp32_result) {
   const int64_t big_tiles = ((M + 255) / 256) * ((N + 255) / 256);
   if (big_tiles >= (forced >= 0 ? forced : 256)) return -1;
-  int best = RING_64x64;
-  double best_cost = tile_cost(kRingCost[0], M, N, nk);
-  for (int t = 1; t < RING_TILES; ++t) {
-    const double cost = tile_cost(kRingCost[t], M, N, nk);
-    if (cost < best_cost) { best = t; best_cost = cost; }
-  }
-  const double limit = best_cost * (big_tiles >= 128 ? 1.08 : 1.0) / (fp32_result ? kBigFp32 : 1.0);
+  const int best = fastest_ring_tile(M, N, nk);
+  const double limit = tile_cost(kRingCost[best], M, N, nk) * (big_tiles >= 128 ? 1.08 : 1.0) / (fp32_result ? kBigFp32 : 1.0);
   if (forced < 0)
     for (const TileCost& c : kBigCost)
       if (tile_cost(c, M, N, nk) < limit) return -1;

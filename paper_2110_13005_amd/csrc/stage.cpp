@@ -113,7 +113,6 @@ using host::SLOT_LIVE;
 struct Slot {
   int state = SLOT_FREE;
   int mb_id = -1;          // valid while SLOT_LIVE (forward issued, backward not yet)
-  char* base = nullptr;
   std::vector<LayerStash> layers;
   // fwd_done: forward finished; dgrad_done: backward's activation-gradient chain finished;
   // released: the weight-gradient contraction that read the slot finished (slot reusable)
@@ -190,8 +189,13 @@ struct axonn_stage {
   elem_t* grads = nullptr;
   float* grads32 = nullptr;
   uint64_t* nonfinite_ws = nullptr;   // counters of launch_count_nonfinite, allocated on first use
+  // stash slots: each tensor of all slots lies in one piece, slot behind slot, so that the microbatches of consecutive
+  // slots are one matrix
   std::vector<Slot> slots;
-  uint64_t slot_bytes = 0;
+  char* stash_base = nullptr;
+  uint64_t stash_bytes = 0;
+  int max_merge = 1;                  // microbatches that may run as one (host::merge_limit)
+  int ln_slices = 0;                  // of ln_part, per LayerNorm
   // backward workspace
   char* ws_base = nullptr;
   uint64_t ws_bytes = 0;
@@ -250,13 +254,14 @@ static thread_local int t_concurrent = 0;
 
 int gemm(bool a_kc, bool b_kc, int epi, int M, int N, int K, const void* A, int64_t lda,
          const void* B, int64_t ldb, void* C, int64_t ldc, const void* bias, const void* res,
-         int64_t ld_res, void* aux, int64_t ld_aux, int accumulate, hipStream_t s, float* split_ws = nullptr, int64_t split_floats = 0) {
+         int64_t ld_res, void* aux, int64_t ld_aux, int accumulate, hipStream_t s, int rule_m = 0, float* split_ws = nullptr,
+         int64_t split_floats = 0) {
   GemmArgs g;
   memset(&g, 0, sizeof g);
   g.A_seg[0] = (const elem_t*)A; g.B_seg[0] = (const elem_t*)B; g.C = C; g.n_seg = 1;
   g.bias = (const elem_t*)bias; g.res = (const elem_t*)res; g.aux = (elem_t*)aux;
   g.lda = lda; g.ldb = ldb; g.ldc = ldc; g.ld_res = ld_res; g.ld_aux = ld_aux;
-  g.M = M; g.N = N; g.K = K; g.accumulate = accumulate; g.tiles_m = g.tiles_n = 0;
+  g.M = M; g.N = N; g.K = K; g.accumulate = accumulate; g.rule_m = rule_m;
   g.concurrent = t_concurrent;
   g.split_ws = split_ws; g.split_floats = split_floats;
   ProfScope ps(a_kc ? (b_kc ? PC_GEMM_DGRAD : PC_GEMM_FWD) : PC_GEMM_WGRAD, s);
@@ -269,18 +274,19 @@ int ln_fwd(int64_t T, int64_t h, const void* x, const void* g, const void* b, fl
   ProfScope ps(PC_LN_FWD, s);
   return check_launch(launch_layernorm_fwd(T, h, x, g, b, eps, out, out_lo, stats, s), "layernorm_fwd");
 }
-// LayerNorm backward of layer `layer` (which: 0 the first, 1 the second).  The parameter gradients of a batch collect in
+// LayerNorm backward of layer `layer` (which: 0 the first, 1 the second) for n microbatches.  The parameter gradients of a batch collect in
 // the LayerNorm's slices of st->ln_part (acc == 0: the batch's first microbatch) and are stored in the gradient
 // accumulators behind the batch's last one (and by store_ln_grads).
-int ln_bwd(axonn_stage* st, int layer, int which, int64_t T, int64_t h, const void* dout, const void* x,
-           const float* stats, const void* res, void* dx, int acc, hipStream_t s) {
+int ln_bwd(axonn_stage* st, int layer, int which, int n, const void* dout, const void* x, const float* stats,
+           const void* res, void* dx, int acc, hipStream_t s) {
+  const int64_t T = (int64_t)n * st->T, h = st->h;
   ProfScope ps(PC_LN_BWD, s);
   const int which_g = which ? P_LN2G : P_LN1G, which_b = which ? P_LN2B : P_LN1B;
-  float* const part = st->ln_part + (uint64_t)(2 * layer + which) * 2 * h * layernorm_bwd_slices(T, h);
+  float* const part = st->ln_part + (uint64_t)(2 * layer + which) * 2 * h * st->ln_slices;
   AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, dout, x, stats, param_ptr(st, layer, which_g), res, dx, part,
-                                                   acc == 0, s), "layernorm_bwd"));
-  if (st->bwd_count + 1 < st->cfg.n_microbatches) return AXONN_OK;
-  return check_launch(launch_layernorm_param_grads(T, h, part, grad_ptr(st, layer, which_g), grad_ptr(st, layer, which_b),
+                                                   st->ln_slices, acc == 0, s), "layernorm_bwd"));
+  if (st->bwd_count + n < st->cfg.n_microbatches) return AXONN_OK;
+  return check_launch(launch_layernorm_param_grads(st->ln_slices, h, part, grad_ptr(st, layer, which_g), grad_ptr(st, layer, which_b),
                                                    st->cfg.grad_accum_fp32 != 0, s), "layernorm parameter gradients");
 }
 // Stores what all LayerNorms have collected so far in the 16-bit gradient buffer.
@@ -288,7 +294,7 @@ int store_ln_grads(axonn_stage* st, hipStream_t s) {
   ProfScope ps(PC_LN_BWD, s);
   const uint64_t ln1 = st->tensors[P_LN1G].offset, ln2 = st->tensors[P_LN2G].offset;
   const uint64_t layer = st->cfg.n_layers > 1 ? st->tensors[kTensorsPerLayer + P_LN1G].offset - ln1 : 0;
-  return check_launch(launch_layernorm_param_grads_all(st->T, st->h, st->cfg.n_layers, st->ln_part, st->grads + ln1,
+  return check_launch(launch_layernorm_param_grads_all(st->ln_slices, st->h, st->cfg.n_layers, st->ln_part, st->grads + ln1,
                                                        (int64_t)layer, (int64_t)(ln2 - ln1), s),
                       "layernorm parameter gradients");
 }
@@ -309,9 +315,10 @@ int adam(uint64_t n, float* th, float* m, float* v, const void* g16, void* p16, 
 
 // ------------------------------------------------------------------- forward of a layer
 // Runs layer l on a.x, filling the activations of `a`; z receives the layer's output (null: the last
-// contraction is left out, for a regenerated layer whose output nobody reads).
-int forward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* z, hipStream_t s) {
-  const int T = st->T, h = st->h, f = st->f;
+// contraction is left out, for a regenerated layer whose output nobody reads).  n: microbatches, whose activations follow
+// `a`'s in memory (consecutive stash slots).
+int forward_layer(axonn_stage* st, int l, const LayerStash& a, int n, elem_t* z, hipStream_t s) {
+  const int T = n * st->T, h = st->h, f = st->f, rule_m = st->T;
   AX_TRY(ln_fwd(T, h, a.x, param_ptr(st, l, P_LN1G), param_ptr(st, l, P_LN1B), st->cfg.ln_eps, a.u, a.u_lo,
                 a.stats1, s));
   if (a.u_lo) {
@@ -324,7 +331,7 @@ int forward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* z, hipStr
     g.A_seg[0] = a.u; g.A_seg[1] = a.u_lo;
     g.B_seg[0] = g.B_seg[1] = param_ptr(st, l, P_WQKV);
     g.n_seg = 2; g.C = a.qkv; g.bias = param_ptr(st, l, P_BQKV);
-    g.lda = h; g.ldb = 3 * h; g.ldc = 3 * h; g.M = T; g.N = n_split; g.K = h;
+    g.lda = h; g.ldb = 3 * h; g.ldc = 3 * h; g.M = T; g.N = n_split; g.K = h; g.rule_m = rule_m;
     g.concurrent = t_concurrent;
     {
       ProfScope ps(PC_GEMM_FWD, s);
@@ -332,28 +339,28 @@ int forward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* z, hipStr
     }
     if (n_split < 3 * h)
       AX_TRY(gemm(true, false, EPI_BIAS, T, h, h, a.u, h, param_ptr(st, l, P_WQKV) + 2 * h, 3 * h, a.qkv + 2 * h, 3 * h,
-                  param_ptr(st, l, P_BQKV) + 2 * h, nullptr, 0, nullptr, 0, 0, s));
+                  param_ptr(st, l, P_BQKV) + 2 * h, nullptr, 0, nullptr, 0, 0, s, rule_m));
   } else {
     AX_TRY(gemm(true, false, EPI_BIAS, T, 3 * h, h, a.u, h, param_ptr(st, l, P_WQKV), 3 * h, a.qkv, 3 * h,
-                param_ptr(st, l, P_BQKV), nullptr, 0, nullptr, 0, 0, s));
+                param_ptr(st, l, P_BQKV), nullptr, 0, nullptr, 0, 0, s, rule_m));
   }
-  AX_TRY(attn_fwd(st->cfg.microbatch_size, st->cfg.seq_len, st->cfg.n_heads, st->d, a.qkv, a.o, a.lse, s));
+  AX_TRY(attn_fwd(n * st->cfg.microbatch_size, st->cfg.seq_len, st->cfg.n_heads, st->d, a.qkv, a.o, a.lse, s));
   AX_TRY(gemm(true, false, EPI_BIAS_RES, T, h, h, a.o, h, param_ptr(st, l, P_WO), h, a.y, h,
-              param_ptr(st, l, P_BO), a.x, h, nullptr, 0, 0, s));
+              param_ptr(st, l, P_BO), a.x, h, nullptr, 0, 0, s, rule_m));
   AX_TRY(ln_fwd(T, h, a.y, param_ptr(st, l, P_LN2G), param_ptr(st, l, P_LN2B), st->cfg.ln_eps, a.w, nullptr,
                 a.stats2, s));
   AX_TRY(gemm(true, false, EPI_BIAS_GELU, T, f, h, a.w, h, param_ptr(st, l, P_WFC1), f, a.g, f,
-              param_ptr(st, l, P_BFC1), nullptr, 0, a.pre, f, 0, s));
+              param_ptr(st, l, P_BFC1), nullptr, 0, a.pre, f, 0, s, rule_m));
   if (z)
     AX_TRY(gemm(true, false, EPI_BIAS_RES, T, h, f, a.g, f, param_ptr(st, l, P_WFC2), h, z, h,
-                param_ptr(st, l, P_BFC2), a.y, h, nullptr, 0, 0, s));
+                param_ptr(st, l, P_BFC2), a.y, h, nullptr, 0, 0, s, rule_m));
   return AXONN_OK;
 }
 
-int forward_layers(axonn_stage* st, Slot& slot, void* y_out, hipStream_t s) {
+int forward_layers(axonn_stage* st, Slot& slot, int n, void* y_out, hipStream_t s) {
   const int L = st->cfg.n_layers;
   for (int l = 0; l < L; ++l)
-    AX_TRY(forward_layer(st, l, slot.layers[l], (l + 1 < L) ? slot.layers[l + 1].x : (elem_t*)y_out, s));
+    AX_TRY(forward_layer(st, l, slot.layers[l], n, (l + 1 < L) ? slot.layers[l + 1].x : (elem_t*)y_out, s));
   return AXONN_OK;
 }
 
@@ -368,7 +375,7 @@ int forward_layers_ckpt(axonn_stage* st, Slot& slot, void* y_out, hipStream_t s)
     LayerStash a = F.layers[0];
     a.x = (l % ac == 0) ? slot.layers[l].x : xb[l & 1];
     elem_t* z = (l + 1 == L) ? (elem_t*)y_out : ((l + 1) % ac == 0) ? slot.layers[l + 1].x : xb[(l + 1) & 1];
-    AX_TRY(forward_layer(st, l, a, z, s));
+    AX_TRY(forward_layer(st, l, a, 1, z, s));
   }
   HIP_TRY(hipEventRecord(F.released, s));
   F.released_recorded = true;
@@ -379,42 +386,72 @@ int forward_layers_ckpt(axonn_stage* st, Slot& slot, void* y_out, hipStream_t s)
 // Given dL/d(output) in a.dz, writes dL/d(input) to d_out, the output gradients of the four linear maps
 // to a.dpre, a.dy_mid, a.dqkv (a.dz is the fourth) and adds the LayerNorm gradients.  The bias gradients, column
 // sums of those four, are left to the weight-gradient pass, which reads the same four matrices.
-int backward_layer(axonn_stage* st, int l, const LayerStash& a, elem_t* d_out, int acc, hipStream_t s) {
-  const int T = st->T, h = st->h, f = st->f;
+int backward_layer(axonn_stage* st, int l, const LayerStash& a, int n, elem_t* d_out, int acc, hipStream_t s) {
+  const int T = n * st->T, h = st->h, f = st->f, rule_m = st->T;
   const elem_t* d_in = a.dz;
+  // one microbatch's gradients between the kernels have a workspace; several microbatches' take the place of GeLU', which
+  // nobody reads after the first contraction (each is read by the next kernel only, so one place will do)
+  elem_t *dw = st->dw, *dattn = st->dattn, *du = st->du;
+  float* delta = st->delta;
+  if (n > 1) {
+    dw = dattn = du = a.pre;
+    delta = (float*)(a.pre + (uint64_t)T * h);
+  }
   // z = y + g W2 + b2
   AX_TRY(gemm(true, true, EPI_DGELU, T, f, h, d_in, h, param_ptr(st, l, P_WFC2), h, a.dpre, f,
-              nullptr, nullptr, 0, a.pre, f, 0, s));
+              nullptr, nullptr, 0, a.pre, f, 0, s, rule_m));
   // pre = w W1 + b1
-  AX_TRY(gemm(true, true, EPI_BIAS, T, h, f, a.dpre, f, param_ptr(st, l, P_WFC1), f, st->dw, h,
-              nullptr, nullptr, 0, nullptr, 0, 0, s));
+  AX_TRY(gemm(true, true, EPI_BIAS, T, h, f, a.dpre, f, param_ptr(st, l, P_WFC1), f, dw, h,
+              nullptr, nullptr, 0, nullptr, 0, 0, s, rule_m));
   // w = LN2(y); residual: dy = d_in + dLN2
-  AX_TRY(ln_bwd(st, l, 1, T, h, st->dw, a.y, a.stats2, d_in, a.dy_mid, acc, s));
+  AX_TRY(ln_bwd(st, l, 1, n, dw, a.y, a.stats2, d_in, a.dy_mid, acc, s));
   // y = x + o Wo + bo
-  AX_TRY(gemm(true, true, EPI_BIAS, T, h, h, a.dy_mid, h, param_ptr(st, l, P_WO), h, st->dattn, h,
-              nullptr, nullptr, 0, nullptr, 0, 0, s));
+  AX_TRY(gemm(true, true, EPI_BIAS, T, h, h, a.dy_mid, h, param_ptr(st, l, P_WO), h, dattn, h,
+              nullptr, nullptr, 0, nullptr, 0, 0, s, rule_m));
   // attention
-  AX_TRY(attn_bwd(st->cfg.microbatch_size, st->cfg.seq_len, st->cfg.n_heads, st->d, a.qkv, a.o, a.lse, st->dattn,
-                  a.dqkv, st->delta, s));
+  AX_TRY(attn_bwd(n * st->cfg.microbatch_size, st->cfg.seq_len, st->cfg.n_heads, st->d, a.qkv, a.o, a.lse, dattn,
+                  a.dqkv, delta, s));
   // qkv = u Wqkv + b
-  AX_TRY(gemm(true, true, EPI_BIAS, T, h, 3 * h, a.dqkv, 3 * h, param_ptr(st, l, P_WQKV), 3 * h, st->du, h,
-              nullptr, nullptr, 0, nullptr, 0, 0, s));
+  AX_TRY(gemm(true, true, EPI_BIAS, T, h, 3 * h, a.dqkv, 3 * h, param_ptr(st, l, P_WQKV), 3 * h, du, h,
+              nullptr, nullptr, 0, nullptr, 0, 0, s, rule_m));
   // u = LN1(x); residual: dx = dy + dLN1
-  AX_TRY(ln_bwd(st, l, 0, T, h, st->du, a.x, a.stats1, a.dy_mid, d_out, acc, s));
+  AX_TRY(ln_bwd(st, l, 0, n, du, a.x, a.stats1, a.dy_mid, d_out, acc, s));
   return AXONN_OK;
 }
 
-int backward_layers(axonn_stage* st, Slot& slot, const void* dy_in, void* dx_out, int acc, bool last,
-                    hipStream_t s) {
-  const int T = st->T, h = st->h, L = st->cfg.n_layers;
+// A microbatch as a message or a direct call names it: its id, payload and result.
+struct Work { int mb_id; const void* in; void* out; };
+
+// Copies of n microbatches' payloads into the stash (`to_stash`) or of their results out of it; `stash` holds the first
+// one's rows, the others' follow.
+int copy_microbatches(axonn_stage* st, const Work* w, int n, elem_t* stash, bool to_stash, hipStream_t s) {
+  const uint64_t elems = (uint64_t)st->T * st->h, bytes = elems * sizeof(elem_t);
+  ProfScope ps(PC_COPY_IN, s);
+  Copies c;
+  bool aligned = n > 1 && n <= kMaxCopies;
+  for (int i = 0; i < n; ++i) {
+    const void* src = to_stash ? w[i].in : (const void*)(stash + i * elems);
+    void* dst = to_stash ? (void*)(stash + i * elems) : w[i].out;
+    if (i < kMaxCopies) { c.src[i] = src; c.dst[i] = dst; }
+    aligned = aligned && ((uintptr_t)src | (uintptr_t)dst) % 16 == 0;
+  }
+  if (aligned) return check_launch(launch_copies(n, bytes, c, s), "copies");
+  for (int i = 0; i < n; ++i)
+    HIP_TRY(hipMemcpyAsync(to_stash ? (void*)(stash + i * elems) : w[i].out, to_stash ? w[i].in : (const void*)(stash + i * elems),
+                           bytes, hipMemcpyDeviceToDevice, s));
+  return AXONN_OK;
+}
+
+// `slot`: the first of n microbatches'.  The result of one goes straight to its caller's buffer; several leave theirs in
+// place of the first layer's q, k and v, which nobody reads after its attention.
+elem_t* merged_dx(Slot& slot) { return slot.layers[0].qkv; }
+int backward_layers(axonn_stage* st, Slot& slot, const Work* w, int n, void* dx_out, int acc, bool last, hipStream_t s) {
+  const int L = st->cfg.n_layers;
   // the upstream gradient is copied into the stash: it is an operand of the deferred weight
   // gradient and the caller may recycle its receive buffer
-  {
-    ProfScope ps(PC_COPY_IN, s);
-    HIP_TRY(hipMemcpyAsync(slot.layers[L - 1].dz, dy_in, (uint64_t)T * h * sizeof(elem_t), hipMemcpyDeviceToDevice, s));
-  }
+  AX_TRY(copy_microbatches(st, w, n, slot.layers[L - 1].dz, true, s));
   for (int l = L - 1; l >= 0; --l) {
-    AX_TRY(backward_layer(st, l, slot.layers[l], (l == 0) ? (elem_t*)dx_out : slot.layers[l - 1].dz, acc, s));
+    AX_TRY(backward_layer(st, l, slot.layers[l], n, (l == 0) ? (elem_t*)dx_out : slot.layers[l - 1].dz, acc, s));
     if (last) HIP_TRY(hipEventRecord(st->chain_layer[l], s));
   }
   return AXONN_OK;
@@ -470,18 +507,18 @@ int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
   return AXONN_OK;
 }
 
-// Weight gradients of every slot that has finished its backward chain (see above).  `last_slot` is the
-// slot of the batch's last microbatch when this is the batch's final pass (else null): the pass then
-// follows that microbatch's chain layer by layer from the last layer down, and finishes each layer's
+// Weight gradients of every slot that has finished its backward chain (see above).  `last_slot` is the first of the
+// n_last slots of the batch's last chain when this is the batch's final pass (else null): the pass then
+// follows that chain layer by layer from the last layer down, and finishes each layer's
 // gradients as soon as its contractions are queued.
-int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr) {
+int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr, int n_last = 0) {
   std::vector<Slot*> ready;
   for (Slot& sl : st->slots)
     if (sl.state == SLOT_AWAIT_WGRAD) ready.push_back(&sl);
   if (ready.empty()) return AXONN_OK;
   const int L = st->cfg.n_layers;
   for (Slot* sl : ready)
-    if (sl != last_slot) HIP_TRY(hipStreamWaitEvent(s, sl->dgrad_done, 0));
+    if (!last_slot || sl < last_slot || sl >= last_slot + n_last) HIP_TRY(hipStreamWaitEvent(s, sl->dgrad_done, 0));
   if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   for (int i = 0; i < L; ++i) {
     const int l = last_slot ? L - 1 - i : i;
@@ -531,10 +568,10 @@ int backward_layers_ckpt(axonn_stage* st, Slot& slot, const void* dy_in, void* d
     std::vector<LayerStash> rec(R.layers.begin(), R.layers.begin() + ac);
     rec[0].x = slot.layers[seg * ac].x;
     for (int i = 0; i < ac; ++i)
-      AX_TRY(forward_layer(st, seg * ac + i, rec[i], (i + 1 < ac) ? rec[i + 1].x : nullptr, s));
+      AX_TRY(forward_layer(st, seg * ac + i, rec[i], 1, (i + 1 < ac) ? rec[i + 1].x : nullptr, s));
     for (int i = ac - 1; i >= 0; --i) {
       elem_t* d_out = (i > 0) ? rec[i - 1].dz : (seg == 0) ? (elem_t*)dx_out : Rnext.layers[ac - 1].dz;
-      AX_TRY(backward_layer(st, seg * ac + i, rec[i], d_out, acc, s));
+      AX_TRY(backward_layer(st, seg * ac + i, rec[i], 1, d_out, acc, s));
     }
     HIP_TRY(hipEventRecord(R.chain_done, s));
     if (ws != s) HIP_TRY(hipStreamWaitEvent(ws, R.chain_done, 0));
@@ -564,8 +601,10 @@ Slot* find_live(axonn_stage* st, int mb_id) {
 // `ws` is the stream weight-gradient passes go to (the caller's stream in direct mode).
 int embed_forward(axonn_embed* e, const int32_t* tokens, void* x, hipStream_t s);
 
-// `x` holds [b,s,h] bf16 activations, or, on a stage with an embedding attached, [b,s] int32 token ids.
-int do_forward(axonn_stage* st, int mb_id, const void* x, void* y, hipStream_t s, hipStream_t ws) {
+// Forward of n microbatches that have a free slot each behind the first one's (n == 1: any).
+// A payload holds [b,s,h] bf16 activations, or, on a stage with an embedding attached, [b,s] int32 token ids.
+int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t ws) {
+  const int mb_id = w[0].mb_id;
   int si = -1;
   int adm = host::admit_forward(st->slots, mb_id, st->in_flight, st->cfg.pipeline_limit, &si);
   if (adm == host::FWD_NEEDS_FLUSH) {
@@ -582,46 +621,56 @@ int do_forward(axonn_stage* st, int mb_id, const void* x, void* y, hipStream_t s
     default: return fail(AXONN_ESTATE, "forward: no free stash slot");
   }
   Slot* slot = &st->slots[si];
-  // the weight-gradient pass that read the slot's previous contents must have finished
-  if (slot->released_recorded) HIP_TRY(hipStreamWaitEvent(s, slot->released, 0));
-  const uint64_t bytes = (uint64_t)st->T * st->h * sizeof(elem_t);
-  if (st->head) y = slot->head_y;   // the last stage's output goes to its own head, not onwards
+  const uint64_t elems = (uint64_t)st->T * st->h;
+  // the weight-gradient pass that read a slot's previous contents must have finished
+  for (int i = 0; i < n; ++i)
+    if (slot[i].released_recorded) HIP_TRY(hipStreamWaitEvent(s, slot[i].released, 0));
+  elem_t* const x = slot->layers[0].x;
   if (st->embed) {
-    slot->tokens = (const int32_t*)x;
-    AX_TRY(embed_forward(st->embed, slot->tokens, slot->layers[0].x, s));
+    for (int i = 0; i < n; ++i) {
+      slot[i].tokens = (const int32_t*)w[i].in;
+      AX_TRY(embed_forward(st->embed, slot[i].tokens, x + i * elems, s));
+    }
   } else {
-    ProfScope ps(PC_COPY_IN, s);
-    HIP_TRY(hipMemcpyAsync(slot->layers[0].x, x, bytes, hipMemcpyDeviceToDevice, s));
+    AX_TRY(copy_microbatches(st, w, n, x, true, s));
   }
+  // the results of several microbatches leave by way of the last layer's dz, which their backward pass fills later
+  void* y = st->head ? slot->head_y   // the last stage's output goes to its own head, not onwards
+                     : n == 1 ? w[0].out : slot->layers[st->cfg.n_layers - 1].dz;
   if (st->cfg.ckpt_stride > 0) AX_TRY(forward_layers_ckpt(st, *slot, y, s));
-  else AX_TRY(forward_layers(st, *slot, y, s));
-  HIP_TRY(hipEventRecord(slot->fwd_done, s));
-  host::commit_forward(st->slots, si, mb_id, &st->in_flight);
+  else AX_TRY(forward_layers(st, *slot, n, y, s));
+  if (n > 1) AX_TRY(copy_microbatches(st, w, n, (elem_t*)y, false, s));
+  for (int i = 0; i < n; ++i) {
+    HIP_TRY(hipEventRecord(slot[i].fwd_done, s));
+    host::commit_forward(st->slots, si + i, w[i].mb_id, &st->in_flight);
+  }
   return AXONN_OK;
 }
 
-int do_backward(axonn_stage* st, int mb_id, const void* dy, void* dx, hipStream_t s, hipStream_t ws) {
-  const int si = host::admit_backward(st->slots, mb_id);
-  if (si < 0) return fail(AXONN_ESTATE, "backward: microbatch %d has no forward in flight", mb_id);
+// Backward of n microbatches whose slots follow the first one's.
+int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t ws) {
+  const int si = host::admit_backward(st->slots, w[0].mb_id);
+  if (si < 0) return fail(AXONN_ESTATE, "backward: microbatch %d has no forward in flight", w[0].mb_id);
   Slot* slot = &st->slots[si];
-  HIP_TRY(hipStreamWaitEvent(s, slot->fwd_done, 0));
+  for (int i = 0; i < n; ++i) HIP_TRY(hipStreamWaitEvent(s, slot[i].fwd_done, 0));
   // backward chains share the workspace and the bias / LayerNorm accumulators: keep them in order
   if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
   const int acc = st->bwd_count > 0 ? 1 : 0;
   const bool ckpt = st->cfg.ckpt_stride > 0;
-  const bool last = st->bwd_count + 1 == st->cfg.n_microbatches;
-  if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, dy, dx, acc, last, s, ws));
-  else AX_TRY(backward_layers(st, *slot, dy, dx, acc, last, s));
+  const bool last = st->bwd_count + n == st->cfg.n_microbatches;
+  const int awaiting = slots_in_state(st, SLOT_AWAIT_WGRAD);
+  if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, w[0].in, w[0].out, acc, last, s, ws));
+  else AX_TRY(backward_layers(st, *slot, w, n, n == 1 ? w[0].out : merged_dx(*slot), acc, last, s));
+  if (n > 1 && !st->embed) AX_TRY(copy_microbatches(st, w, n, merged_dx(*slot), false, s));
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
-  if (st->bwd_count + 1 < st->cfg.n_microbatches && !st->cfg.grad_accum_fp32 &&
-      host::gradients_complete(ckpt, last, st->cfg.wgrad_group, slots_in_state(st, SLOT_AWAIT_WGRAD)))
+  if (!last && !st->cfg.grad_accum_fp32 && host::gradients_complete(ckpt, last, st->cfg.wgrad_group, awaiting, n))
     AX_TRY(store_ln_grads(st, s));
-  st->bwd_count++;
-  HIP_TRY(hipEventRecord(slot->dgrad_done, s));
+  st->bwd_count += n;
+  for (int i = 0; i < n; ++i) HIP_TRY(hipEventRecord(slot[i].dgrad_done, s));
   HIP_TRY(hipEventRecord(st->last_bwd, s));
   st->last_bwd_recorded = true;
-  host::commit_backward(st->slots, si, ckpt, &st->in_flight);
+  for (int i = 0; i < n; ++i) host::commit_backward(st->slots, si + i, ckpt, &st->in_flight);
   if (ckpt) {
     // the weight gradients are already queued and read the shared sets: the slot (kept inputs only) is
     // free as soon as the chain on `s` is through
@@ -629,8 +678,8 @@ int do_backward(axonn_stage* st, int mb_id, const void* dy, void* dx, hipStream_
     slot->released_recorded = true;
     if (last) st->grads_final_recorded = true;
   } else {
-    switch (host::wgrad_action(last, st->cfg.wgrad_group, slots_in_state(st, SLOT_AWAIT_WGRAD))) {
-      case host::WGRAD_FLUSH_FINAL: AX_TRY(flush_wgrad(st, ws, slot)); break;
+    switch (host::wgrad_action(last, st->cfg.wgrad_group, awaiting + n)) {
+      case host::WGRAD_FLUSH_FINAL: AX_TRY(flush_wgrad(st, ws, slot, n)); break;
       case host::WGRAD_FLUSH: AX_TRY(flush_wgrad(st, ws)); break;
       default: break;
     }
@@ -640,14 +689,17 @@ int do_backward(axonn_stage* st, int mb_id, const void* dy, void* dx, hipStream_
 
 int embed_backward(axonn_embed* e, const int32_t* tokens, const void* dx, hipStream_t s);
 
-// Backward(msg), followed on the first stage by the embedding's backward pass.
-int backward_msg(axonn_stage* st, int mb_id, const void* dy, void* dx, hipStream_t s, hipStream_t ws) {
-  if (!st->embed) return do_backward(st, mb_id, dy, dx, s, ws);
-  Slot* slot = (mb_id >= 0) ? find_live(st, mb_id) : nullptr;
-  const int32_t* tokens = slot ? slot->tokens : nullptr;
-  AX_TRY(do_backward(st, mb_id, dy, st->embed_dx, s, ws));
-  AX_TRY(embed_backward(st->embed, tokens, st->embed_dx, s));
-  // the next backward chain overwrites embed_dx: it must follow the embedding's pass as well
+// Backward(msg) of n microbatches, followed on the first stage by the embedding's backward passes.
+int backward_msg(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t ws) {
+  if (!st->embed) return do_backward(st, w, n, s, ws);
+  const int si = host::admit_backward(st->slots, w[0].mb_id);
+  const int32_t* tokens[host::kMaxMerge] = {};
+  for (int i = 0; i < n && si >= 0; ++i) tokens[i] = st->slots[si + i].tokens;
+  const Work one = {w[0].mb_id, w[0].in, st->embed_dx};
+  AX_TRY(do_backward(st, n == 1 ? &one : w, n, s, ws));
+  const elem_t* dx = n == 1 ? st->embed_dx : merged_dx(st->slots[si]);
+  for (int i = 0; i < n; ++i) AX_TRY(embed_backward(st->embed, tokens[i], dx + i * (uint64_t)st->T * st->h, s));
+  // the next backward chain overwrites that gradient: it must follow the embedding's pass as well
   HIP_TRY(hipEventRecord(st->last_bwd, s));
   return AXONN_OK;
 }
@@ -692,8 +744,8 @@ void destroy_stage(axonn_stage* st) {
   (void)hipSetDevice(st->cfg.device);
   (void)hipDeviceSynchronize();
   destroy_adam(st->opt);
+  if (st->stash_base) (void)hipFree(st->stash_base);
   for (Slot& s : st->slots) {
-    if (s.base) (void)hipFree(s.base);
     if (s.fwd_done) (void)hipEventDestroy(s.fwd_done);
     if (s.dgrad_done) (void)hipEventDestroy(s.dgrad_done);
     if (s.released) (void)hipEventDestroy(s.released);
@@ -791,13 +843,14 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
     const elem_t* B[1] = {hd->logits};
     AX_TRY(gemm_seg(EPI_ACC_BF16, h, V, T, A, h, B, V, 1, hd->grads + 2 * (uint64_t)h, V, nullptr, nullptr, acc, s));
   }
-  AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s,
+  AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s, 0,
               hd->split_ws, hd->split_floats));
   {
     ProfScope ps(PC_LN_BWD, s);
-    AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part, !acc, s),
+    AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part,
+                                                     layernorm_bwd_slices(T, h), !acc, s),
                         "layernorm_bwd (head)"));
-    AX_TRY(check_launch(launch_layernorm_param_grads(T, h, hd->ln_part, hd->grads, hd->grads + h, false, s),
+    AX_TRY(check_launch(launch_layernorm_param_grads(layernorm_bwd_slices(T, h), h, hd->ln_part, hd->grads, hd->grads + h, false, s),
                         "layernorm parameter gradients (head)"));
   }
   hd->count++;
@@ -879,56 +932,68 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   // activation stash: per layer x,u,o,y,w [T,h], qkv [T,3h], pre (GeLU' of the pre-activation),g [T,f],
   // stats [T,2]x2, lse [b,a,s]
   // plus the output gradients kept for the deferred weight gradients: dz,dy_mid [T,h], dpre [T,f], dqkv [T,3h]
-  const uint64_t e_th = align_up((uint64_t)T * h * 2, 256), e_t3h = align_up((uint64_t)T * 3 * h * 2, 256),
-                 e_tf = align_up((uint64_t)T * f * 2, 256), e_st = align_up((uint64_t)T * 2 * 4, 256),
-                 e_lse = align_up((uint64_t)cfg->microbatch_size * cfg->n_heads * cfg->seq_len * 4, 256);
-  const uint64_t per_layer = (cfg->qkv_input_split ? 8 : 7) * e_th + 2 * e_t3h + 3 * e_tf + 2 * e_st + e_lse;
-  // carves one layer's record out of p
-  auto carve = [&](char*& p, LayerStash& a) {
-    a.x = (elem_t*)p; p += e_th;  a.u = (elem_t*)p; p += e_th;  a.o = (elem_t*)p; p += e_th;
-    a.y = (elem_t*)p; p += e_th;  a.w = (elem_t*)p; p += e_th;  a.qkv = (elem_t*)p; p += e_t3h;
-    a.pre = (elem_t*)p; p += e_tf; a.g = (elem_t*)p; p += e_tf;
-    a.stats1 = (float*)p; p += e_st; a.stats2 = (float*)p; p += e_st; a.lse = (float*)p; p += e_lse;
-    a.dz = (elem_t*)p; p += e_th; a.dy_mid = (elem_t*)p; p += e_th;
-    a.dpre = (elem_t*)p; p += e_tf; a.dqkv = (elem_t*)p; p += e_t3h;
-    a.u_lo = nullptr;
-    if (cfg->qkv_input_split) { a.u_lo = (elem_t*)p; p += e_th; }
+  // Lays out n records of one layer from `base + at` on, each tensor of all of them in one piece.  T * h, T * 3h and T * f
+  // are multiples of 64 elements, so every record's tensors start at a multiple of 128 bytes (stats and lse: 32).
+  const uint64_t b_th = (uint64_t)T * h * 2, b_tf = (uint64_t)T * f * 2, b_st = (uint64_t)T * 2 * 4,
+                 b_lse = (uint64_t)cfg->microbatch_size * cfg->n_heads * cfg->seq_len * 4;
+  const auto place = [](char* base, uint64_t& at, uint64_t bytes, const std::vector<LayerStash*>& recs, auto field) {
+    for (size_t i = 0; i < recs.size(); ++i)
+      recs[i]->*field = reinterpret_cast<std::remove_reference_t<decltype(recs[i]->*field)>>(base + at + i * bytes);
+    at += align_up(bytes * recs.size(), 256);
+  };
+  const auto carve = [&](char* base, uint64_t& at, const std::vector<LayerStash*>& recs) {
+    using R = LayerStash;
+    for (auto t : {&R::x, &R::u, &R::o, &R::y, &R::w}) place(base, at, b_th, recs, t);
+    place(base, at, 3 * b_th, recs, &R::qkv);
+    for (auto t : {&R::pre, &R::g}) place(base, at, b_tf, recs, t);
+    for (auto t : {&R::stats1, &R::stats2}) place(base, at, b_st, recs, t);
+    place(base, at, b_lse, recs, &R::lse);
+    for (auto t : {&R::dz, &R::dy_mid}) place(base, at, b_th, recs, t);
+    place(base, at, b_tf, recs, &R::dpre);
+    place(base, at, 3 * b_th, recs, &R::dqkv);
+    if (cfg->qkv_input_split) place(base, at, b_th, recs, &R::u_lo);
   };
   const int ac = cfg->ckpt_stride;
-  st->slot_bytes = ac > 0 ? (uint64_t)(cfg->n_layers / ac) * e_th : per_layer * cfg->n_layers;
+  st->max_merge = ac > 0 ? 1 : host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit);
   st->slots.resize(cfg->pipeline_limit);
   for (Slot& s : st->slots) {
-    CREATE_TRY(hipMalloc((void**)&s.base, st->slot_bytes));
     CREATE_TRY(hipEventCreateWithFlags(&s.fwd_done, hipEventDisableTiming));
     CREATE_TRY(hipEventCreateWithFlags(&s.dgrad_done, hipEventDisableTiming));
     CREATE_TRY(hipEventCreateWithFlags(&s.released, hipEventDisableTiming));
-    s.layers.resize(cfg->n_layers);
-    char* p = s.base;
-    for (int l = 0; l < cfg->n_layers; ++l) {
-      LayerStash& a = s.layers[l];
-      if (ac > 0) {
-        // only the inputs of layers 0, ac, 2ac, ... are kept (Sec. 5.1)
-        memset(&a, 0, sizeof a);
-        if (l % ac == 0) { a.x = (elem_t*)p; p += e_th; }
-      } else {
-        carve(p, a);
-      }
-    }
+    s.layers.assign(cfg->n_layers, LayerStash{});
   }
+  // with checkpointing only the inputs of layers 0, ac, 2ac, ... are kept (Sec. 5.1)
+  const auto carve_slots = [&](char* base) {
+    uint64_t at = 0;
+    for (int l = 0; l < cfg->n_layers; ++l) {
+      std::vector<LayerStash*> recs;
+      for (Slot& s : st->slots) recs.push_back(&s.layers[l]);
+      if (ac == 0) carve(base, at, recs);
+      else if (l % ac == 0) place(base, at, b_th, recs, &LayerStash::x);
+    }
+    return at;
+  };
+  st->stash_bytes = carve_slots(nullptr);
+  CREATE_TRY(hipMalloc((void**)&st->stash_base, st->stash_bytes));
+  (void)carve_slots(st->stash_base);
   if (ac > 0) {
     // shared activation sets: two one-layer sets for forward passes (one more buffer each for the layer
     // inputs that are not kept), three ac-layer sets for regeneration in backward passes
     auto make_set = [&](ActSet& a, int n_layers, bool second_x) -> hipError_t {
-      const uint64_t bytes = (uint64_t)n_layers * per_layer + (second_x ? e_th : 0);
+      a.layers.resize(n_layers);
+      const auto carve_set = [&](char* base) {
+        uint64_t at = 0;
+        for (LayerStash& l : a.layers) carve(base, at, {&l});
+        return at;
+      };
+      const uint64_t layer_bytes = carve_set(nullptr), bytes = layer_bytes + (second_x ? b_th : 0);
       hipError_t e = hipMalloc((void**)&a.base, bytes);
       if (e != hipSuccess) return e;
       st->act_set_bytes += bytes;
       if ((e = hipEventCreateWithFlags(&a.chain_done, hipEventDisableTiming)) != hipSuccess) return e;
       if ((e = hipEventCreateWithFlags(&a.released, hipEventDisableTiming)) != hipSuccess) return e;
-      a.layers.resize(n_layers);
-      char* p = a.base;
-      for (LayerStash& l : a.layers) carve(p, l);
-      if (second_x) { a.x2 = (elem_t*)p; p += e_th; }
+      (void)carve_set(a.base);
+      if (second_x) a.x2 = (elem_t*)(a.base + layer_bytes);
       return hipSuccess;
     };
     st->fwd_sets.resize(2);
@@ -940,7 +1005,9 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   const int64_t wide = std::max<int64_t>(f, 3 * h);
   // partial sums of the LayerNorm parameter gradients, which collect over a batch (two LayerNorms per layer; gradient
   // chain), and of the bias gradients where a weight-gradient kernel does not form them itself (weight-gradient stream)
-  const uint64_t e_red = align_up((uint64_t)2 * cfg->n_layers * 2 * layernorm_bwd_slices(T, h) * h * 4, 256);
+  st->ln_slices = layernorm_bwd_slices(T, h);
+  const uint64_t e_th = align_up(b_th, 256), e_lse = align_up(b_lse, 256);
+  const uint64_t e_red = align_up((uint64_t)2 * cfg->n_layers * 2 * st->ln_slices * h * 4, 256);
   const uint64_t e_wred = align_up((uint64_t)((T + 63) / 64) * wide * 4, 256);
   st->ws_bytes = 3 * e_th + e_lse + e_red + e_wred;
   CREATE_TRY(hipMalloc((void**)&st->ws_base, st->ws_bytes));
@@ -1027,7 +1094,7 @@ int axonn_stage_device_bytes(const axonn_stage_t* st, uint64_t bytes[6]) {
   bytes[0] = st->n_params * 2;
   bytes[1] = st->n_params * 2;
   bytes[2] = st->grads32 ? st->n_params * 4 : 0;
-  bytes[3] = st->slot_bytes * st->slots.size();
+  bytes[3] = st->stash_bytes;
   bytes[4] = st->ws_bytes + st->act_set_bytes;
   bytes[5] = st->opt ? st->opt->device_bytes : 0;
   return AXONN_OK;
@@ -1038,14 +1105,16 @@ int axonn_stage_forward(axonn_stage_t* st, int32_t mb_id, const void* x, void* y
   if (st->embed || st->head)
     return fail(AXONN_ESTATE, "forward: a stage with the pipeline's ends attached runs in message-driven mode");
   HIP_TRY(hipSetDevice(st->cfg.device));
-  return do_forward(st, mb_id, x, y, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
+  const Work w = {mb_id, x, y};
+  return do_forward(st, &w, 1, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
 }
 int axonn_stage_backward(axonn_stage_t* st, int32_t mb_id, const void* dy, void* dx, void* hip_stream) {
   if (!st || !dy || !dx) return fail(AXONN_EINVAL, "backward: null argument");
   if (st->embed || st->head)
     return fail(AXONN_ESTATE, "backward: a stage with the pipeline's ends attached runs in message-driven mode");
   HIP_TRY(hipSetDevice(st->cfg.device));
-  return do_backward(st, mb_id, dy, dx, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
+  const Work w = {mb_id, dy, dx};
+  return do_backward(st, &w, 1, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
 }
 
 int axonn_stage_post(axonn_stage_t* st, const axonn_msg* msg) {
@@ -1114,6 +1183,16 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     query_error = q;
     return -1;
   };
+  // what a message reads and writes: activations, or, from the first stage's embedding on, token ids
+  const uint64_t act_bytes = (uint64_t)st->T * st->h * sizeof(elem_t);
+  const auto span = [st, act_bytes](size_t i) {
+    const axonn_msg& m = st->inbox[i].m;
+    const uint64_t in = (uint64_t)(uintptr_t)m.payload_dev, out = (uint64_t)(uintptr_t)m.result_dev;
+    const bool result = out != 0 && !(st->embed && m.kind == 1);
+    return host::MessageSpan{m.kind, m.mb_id, m.done_event != nullptr, in,
+                             in + (st->embed && m.kind == 0 ? (uint64_t)st->T * sizeof(int32_t) : act_bytes),
+                             result ? out : 0, result ? out + act_bytes : 0};
+  };
   while (st->fwd_issued < M || st->bwd_issued < M) {
     // first posted message that has arrived and is admissible
     bool any_admissible = false;
@@ -1138,14 +1217,25 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     }
     wait.dispatched();
     const axonn_msg m = st->inbox[chosen].m;
-    st->inbox.erase(st->inbox.begin() + chosen);
+    // a forward needs its slot before it is known which messages run with it
+    if (m.kind == 0 && host::find_free(st->slots) < 0) AX_TRY(flush_wgrad(st, ws));
+    int picked[host::kMaxMerge];
+    const int n = host::merge_messages(st->inbox.size(), span, arrived, chosen, st->slots, st->in_flight,
+                                       st->cfg.pipeline_limit, st->head ? 1 : st->max_merge, picked);
     const int si = host::stream_index(m.kind, n_streams, &st->fwd_rr);
     hipStream_t s = st->streams[si];
-    if (m.ready_event) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)m.ready_event, 0));
+    Work w[host::kMaxMerge];
+    for (int i = 0; i < n; ++i) {
+      const axonn_msg& mi = st->inbox[picked[i]].m;
+      w[i] = Work{mi.mb_id, mi.payload_dev, mi.result_dev};
+      if (mi.ready_event) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)mi.ready_event, 0));
+    }
+    std::sort(picked, picked + n);
+    for (int i = n - 1; i >= 0; --i) st->inbox.erase(st->inbox.begin() + picked[i]);
     if (m.kind == 0) {
-      AX_TRY(do_forward(st, m.mb_id, m.payload_dev, m.result_dev, s, ws));
-      st->fwd_issued++;
-      st->dispatch_log.push_back(m.mb_id * 2);
+      AX_TRY(do_forward(st, w, n, s, ws));
+      st->fwd_issued += n;
+      for (int i = 0; i < n; ++i) st->dispatch_log.push_back(w[i].mb_id * 2);
       if (st->head) {
         // last stage (Alg. 2): the loss follows the forward pass and Backward(1) starts at once, on the
         // stream of the backward chains
@@ -1155,19 +1245,20 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
         if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(bs, st->last_bwd, 0));   // head_dx is shared
         AX_TRY(head_forward_backward(st->head, slot->head_y, (const int32_t*)m.targets_dev, (float*)m.loss_dev,
                                      st->head_dx, bs));
-        AX_TRY(backward_msg(st, m.mb_id, st->head_dx, m.result_dev, bs, ws));
+        const Work back = {m.mb_id, st->head_dx, m.result_dev};
+        AX_TRY(backward_msg(st, &back, 1, bs, ws));
         st->bwd_issued++;
         st->dispatch_log.push_back(m.mb_id * 2 + 1);
         s = bs;
       }
     } else {
-      AX_TRY(backward_msg(st, m.mb_id, m.payload_dev, m.result_dev, s, ws));
-      st->bwd_issued++;
-      st->dispatch_log.push_back(m.mb_id * 2 + 1);
+      AX_TRY(backward_msg(st, w, n, s, ws));
+      st->bwd_issued += n;
+      for (int i = 0; i < n; ++i) st->dispatch_log.push_back(w[i].mb_id * 2 + 1);
     }
     // the result buffer is complete once this fires: what a neighbouring stage's message waits for
     if (m.done_event) HIP_TRY(hipEventRecord((hipEvent_t)m.done_event, s));
-    if (n_dispatched) ++*n_dispatched;
+    if (n_dispatched) *n_dispatched += n;
   }
   return AXONN_OK;
 }

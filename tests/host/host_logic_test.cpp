@@ -351,6 +351,103 @@ void test_gemm_tiles() {
   }
 }
 
+void test_merged_messages() {
+  // sizes: one microbatch each where an activation has 2^24 elements, never more than 8 or pipeline_limit, wide MLPs count
+  CHECK(merge_limit(4096, 4096, 16384, 32, 8) == 1 && merge_limit(8192, 8192, 32768, 64, 8) == 1);
+  CHECK(merge_limit(2048, 2048, 8192, 16, 8) == 4 && merge_limit(2048, 4096, 16384, 32, 8) == 2);
+  CHECK(merge_limit(256, 256, 1024, 4, 3) == 3 && merge_limit(256, 256, 1024, 4, 64) == kMaxMerge);
+  CHECK(merge_limit(2048, 2048, 32768, 16, 8) == 1 && merge_limit(256, 256, 256, 4, 8) == 1 && merge_limit(256, 256, 264, 4, 8) == 8);
+
+  std::vector<MessageSpan> box;
+  std::vector<int> here;                       // arrived(i)
+  std::vector<SlotRec> slots(6);
+  int picked[kMaxMerge];
+  const auto span = [&](size_t i) { return box[i]; };
+  const auto arrived = [&](size_t i) { return here[i]; };
+  const auto add = [&](int kind, int mb, uint64_t in, uint64_t out, bool alone = false, int arr = 1) {
+    box.push_back(MessageSpan{kind, mb, alone, in, in + 100, out, out ? out + 100 : 0});
+    here.push_back(arr);
+  };
+  const auto merge = [&](int chosen, int in_flight, int limit, int max) {
+    return merge_messages(box.size(), span, arrived, chosen, slots, in_flight, limit, max, picked);
+  };
+  for (int i = 0; i < 6; ++i) add(0, i, 1000 + 100 * i, 5000 + 100 * i);
+  CHECK(merge(0, 0, 6, 4) == 4 && picked[0] == 0 && picked[3] == 3);
+  CHECK(merge(0, 0, 3, 8) == 3);               // pipeline_limit
+  CHECK(merge(0, 0, 6, 1) == 1);
+  slots[2].state = SLOT_AWAIT_WGRAD;           // consecutive free slots only
+  CHECK(merge(0, 0, 6, 8) == 2);
+  slots[2].state = SLOT_FREE;
+  here[1] = 0;                                 // not arrived: passed over, and so is one whose completion is waited for
+  box[2].alone = true;
+  CHECK(merge(0, 0, 6, 8) == 4 && picked[1] == 3 && picked[2] == 4 && picked[3] == 5);
+  CHECK(merge(2, 0, 6, 8) == 1);
+  here[1] = 1;
+  box[2].alone = false;
+  box[3].in = box[1].out + 50; box[3].in_end = box[3].in + 100;        // message 3 reads what message 1 (and 2) writes
+  CHECK(merge(0, 0, 6, 8) == 5 && picked[3] == 4);
+  box[4].out = box[2].in; box[4].out_end = box[2].in_end;              // message 4 overwrites what message 2 reads
+  box[5].out = box[0].out; box[5].out_end = box[0].out_end;            // two results in one buffer
+  CHECK(merge(0, 0, 6, 8) == 3);
+
+  // backwards: the microbatches of the slots behind the chosen one's, in slot order, also past a forward between them
+  box.clear(); here.clear();
+  for (int i = 0; i < 6; ++i) { slots[i].state = SLOT_LIVE; slots[i].mb_id = 10 + i; }
+  add(1, 11, 1000, 5000); add(1, 13, 1100, 5100); add(0, 20, 1200, 5200); add(1, 12, 1300, 5300); add(1, 10, 1400, 0);
+  CHECK(merge(0, 6, 6, 8) == 3 && picked[1] == 3 && picked[2] == 1);   // 11, 12, 13; 14 is not posted, 10 lies before
+  CHECK(merge(4, 6, 6, 2) == 2 && picked[1] == 0);
+  box[3].in = 5200; box[3].in_end = 5300;      // 12 reads what the forward posted before it writes
+  CHECK(merge(0, 6, 6, 8) == 1);
+  slots[2].state = SLOT_AWAIT_WGRAD;
+  CHECK(merge(0, 6, 6, 8) == 1);
+  CHECK(!gradients_complete(false, false, 4, 1, 2) && gradients_complete(false, false, 4, 1, 3));
+
+  // whatever is merged is a subset of what the loop could have taken one by one, in every state
+  std::mt19937 rng(9);
+  for (int rep = 0; rep < 3000; ++rep) {
+    box.clear(); here.clear();
+    int in_flight = 0;
+    std::set<int> live;
+    for (int i = 0; i < 6; ++i) {
+      slots[i].state = (int)(rng() % 3);
+      slots[i].mb_id = slots[i].state == SLOT_LIVE ? i : -1;
+      if (slots[i].state == SLOT_LIVE) { ++in_flight; live.insert(i); }
+    }
+    const int limit = std::max(in_flight, 1 + (int)(rng() % 6));
+    std::set<std::pair<int, int>> posted;
+    for (int i = 0; i < 10; ++i) {
+      const int kind = (int)(rng() % 2), mb = (int)(rng() % 12);
+      if (!posted.insert({kind, mb}).second) continue;
+      add(kind, mb, 1000 + 100 * (rng() % 30), 1000 + 100 * (rng() % 30), rng() % 5 == 0, rng() % 4 != 0);
+    }
+    bool any = false;
+    int err = 0;
+    const auto msg = [&](size_t i) { return std::make_pair(box[i].kind, box[i].mb_id); };
+    const int c = choose_message(box.size(), msg, arrived, slots, in_flight, limit, &any, &err);
+    if (c < 0) continue;
+    if (box[c].kind == 0 && find_free(slots) < 0) release_awaiting(slots);
+    if (box[c].kind == 0 && find_free(slots) < 0) continue;
+    const int n = merge(c, in_flight, limit, kMaxMerge);
+    CHECK(n >= 1 && picked[0] == c);
+    std::set<int> mbs;
+    int flying = in_flight;
+    const int s0 = box[c].kind == 0 ? find_free(slots) : find_live(slots, box[c].mb_id);
+    for (int k = 0; k < n; ++k) {
+      const MessageSpan& m = box[picked[k]];
+      CHECK(m.kind == box[c].kind && here[picked[k]] == 1 && mbs.insert(m.mb_id).second && (n == 1 || !m.alone));
+      CHECK(admissible(m.kind, m.mb_id, slots, flying, limit));
+      CHECK(m.kind == 0 ? slots[s0 + k].state == SLOT_FREE : slots[s0 + k].mb_id == m.mb_id);
+      if (m.kind == 0) ++flying;
+      for (int q = 0; q < k; ++q) {
+        const MessageSpan& o = box[picked[q]];
+        CHECK(m.out + 100 <= o.out || o.out + 100 <= m.out);
+        CHECK(m.out + 100 <= o.in || o.in + 100 <= m.out);
+        CHECK(m.in + 100 <= o.out || o.out + 100 <= m.in);
+      }
+    }
+  }
+}
+
 void test_two_stages_two_threads() {
   // handles are independent: two host threads each drive a stage of their own (no shared state in the logic)
   auto work = [](unsigned seed) { test_pipeline_limit_and_order(seed); test_bucket_plan(seed); };
@@ -379,6 +476,7 @@ int main(int argc, char** argv) {
   test_addressable_in_place();
   test_workgroup_order();
   test_gemm_tiles();
+  test_merged_messages();
   test_two_stages_two_threads();
   std::puts("host logic: all checks passed");
   return 0;

@@ -202,6 +202,51 @@ def test_message_driven_run_matches_oracle_and_respects_pipeline_limit(n_streams
         check_batch([host(y) for y in Y], [host(d) for d in DX], st.grads_numpy(), ref)
 
 
+@pytest.mark.parametrize("sh,limit,opts", [
+    (StageShape(2, 256, 4, 128, 2, 5), 5, dict(wgrad_group=3)),            # up to 5 microbatches in one pass
+    (StageShape(2, 384, 3, 200, 2, 4, 1000), 3, dict(grad_accum_fp32=0)),  # ragged tiles, passes of 3 and 1
+    (StageShape(1, 376, 2, 72, 1, 9), 9, dict(grad_accum_fp32=0, wgrad_group=1)),   # masked head dimension, 8 and 1
+    (StageShape(1, 1024, 8, 1024, 1, 3), 3, dict()),                       # separate attention backward kernels from 2 on
+    (StageShape(1, 1024, 16, 512, 2, 4), 2, dict(qkv_input_split=2)),      # backwards past the forwards between them
+    (StageShape(2, 256, 4, 64, 1, 4, 264), 4, dict()),                     # the narrowest MLP: its activations just hold the gradients
+], ids=["tiny5", "ragged3", "headdim188", "attn_tiles", "limit2", "narrow_mlp"])
+@pytest.mark.parametrize("n_streams", [1, 2])
+def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, opts, n_streams):
+    """Messages that run as one pass over all their tokens: every y and dx bit for bit that of direct calls; with a
+    done_event per message (nothing merged) and with overlapping result buffers (not merged either) too."""
+    import torch
+    layers, xs, dys = make_stage_inputs(sh, seed=4, perturb=True)
+    M = sh.n_microbatches
+    X = [dev_bf16(x) for x in xs]; DY = [dev_bf16(d) for d in dys]
+    with Stage(sh, pipeline_limit=limit, **opts) as st, Stage(sh, **opts) as whole:
+        st.load_params(layers); whole.load_params(layers)
+        outs, dxs, grads = run_direct(whole, xs, dys)
+        for events, shared in ((False, False), (True, False), (False, True)):
+            Y = [torch.zeros_like(X[0]) for _ in range(M)]; DX = [torch.zeros_like(X[0]) for _ in range(M)]
+            if shared:
+                Y = [Y[0]] * M
+            evs = [torch.cuda.Event() for _ in range(2 * M)]
+            for e in evs:
+                e.record()                                    # torch creates the event behind it at the first record
+            torch.cuda.synchronize()
+            st.zero_grad()
+            order = [(0, i) for i in range(limit)]
+            for i in range(M):
+                order += [(1, i)] + ([(0, limit + i)] if limit + i < M else [])
+            for kind, i in order:
+                st.post(kind, i, (X, DY)[kind][i], (Y, DX)[kind][i], **({"done_event": evs[2 * i + kind]} if events else {}))
+            st.run(n_streams); st.join()
+            torch.cuda.synchronize()
+            for i in range(M):
+                if not shared or i == M - 1:
+                    assert np.array_equal(host(Y[i]), outs[i]), (events, shared, i)
+                assert np.array_equal(host(DX[i]), dxs[i]), (events, shared, i)
+            for ga, gb in zip(st.grads_numpy(), grads):
+                for k in ga:
+                    # sums over the microbatches in another order, and rounded to 16 bits after other groups of them
+                    assert rel_fro(ga[k], gb[k]) <= (1e-3 if opts.get("grad_accum_fp32", 1) else 8e-3), (events, shared, k)
+
+
 def test_message_arrival_order_follows_ready_events():
     """A message whose payload has not arrived (event not yet signalled) is passed over for one
     that has: forward vs backward is decided by what is ready, not by posting order."""
