@@ -470,7 +470,8 @@ int axonn_adam_bucket(uint64_t n, float* theta, float* m, float* v, const void* 
  * library makes is bracketed by a pair of HIP events on the stream it is launched on;
  * collect() waits for them, adds up elapsed milliseconds and launch counts per category
  * and clears the records.  Categories (num_categories of them, names by index): the three
- * GEMM layouts (the bias gradients come with the weight-gradient launches), attention
+ * GEMM layouts (the bias gradients come with the weight-gradient launches; a launch that
+ * forms several weight gradients counts as that many), attention
  * forward / backward, LayerNorm forward / backward (the backward with the reduction of its
  * gain and shift gradients), gradient conversion, Adam, input copy, embedding,
  * cross-entropy.  Process-wide, not thread-safe.  Intervals of kernels that overlap on different streams are each counted

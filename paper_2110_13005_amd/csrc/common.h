@@ -236,11 +236,18 @@ struct GemmArgs {
   float* split_ws;
   int64_t split_floats;
 };
+// Weight gradients of the same K and segments that may share a launch: a layer's four.
+constexpr int kMaxGroup = 4;
+struct GemmGroup {
+  GemmArgs g[kMaxGroup];
+  int n;
+};
 // Workspace of that kind that the launcher can use for an M x N x K problem (0: it would not split it).
 int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K);
 
 // All return hipError_t of the launch (hipGetLastError) and validate nothing: callers check.
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epilogue, const GemmArgs& g, hipStream_t s);
+hipError_t launch_wgrad_group(int epilogue, GemmGroup& grp, hipStream_t s);
 // Launcher settings behind axonn_tuning(): knob 0 copy-kernel mask, 1 large-kernel threshold in tiles, 2 forced
 // block width (0 or -1: the launcher's rule).  false: unknown knob or value out of range.
 bool set_gemm_tuning(int knob, int64_t value);

@@ -46,12 +46,7 @@ __device__ __forceinline__ void lds_barrier() {
 // A number of tiles that is no multiple of 8 is remapped only if ANY_COUNT.  The ring kernel, whose smaller tiles fetch
 // more per MFMA, needs it (230 tiles of 128 x 256, 640 x 11776 x 9632 input gradient: 174 -> 141 us); with tiles of 256 x 256
 // it is as often 4 % slower (4624 x 10448 x 1440 with GeLU, 779 tiles: 194 -> 201 us) as faster.
-template <bool ANY_COUNT = false>
-__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
-  int pid = blockIdx.x;
-  const int nblk = gridDim.x;
-  if (ANY_COUNT) pid = (int)host::xcd_contiguous(blockIdx.x, gridDim.x);
-  else if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
+__device__ __forceinline__ void tile_at(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int BAND = 8;
   const bool wide = tiles_m <= tiles_n;                    // bands of tile rows, walked column by column
   const int t_band = wide ? tiles_m : tiles_n, t_walk = wide ? tiles_n : tiles_m;
@@ -61,6 +56,14 @@ __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm,
   const int a = band * BAND + in_band % band_w, b = in_band / band_w;
   tm = wide ? a : b;
   tn = wide ? b : a;
+}
+template <bool ANY_COUNT = false>
+__device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
+  int pid = blockIdx.x;
+  const int nblk = gridDim.x;
+  if (ANY_COUNT) pid = (int)host::xcd_contiguous(blockIdx.x, gridDim.x);
+  else if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
+  tile_at(pid, tiles_m, tiles_n, tm, tn);
 }
 
 template <int ROWS, int BK, bool KC>
@@ -1153,8 +1156,9 @@ __device__ __forceinline__ elemx8 ring_fragment(const char* base, int r0, int sl
   return u.v;
 }
 
+// (tm, tn): the workgroup's tile of problem `g`.
 template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS>
-__global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
+__device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const int tn) {
   constexpr int BM = 32 * TM, BN = 32 * TN, BK = 64 * NSUB, W = 4 * KG, NT = 64 * W;
   constexpr int SA = BM * BK * 2, SB = BN * BK * 2, STAGE = SA + SB;
   constexpr int NDA = SA / 1024 / W, NDB = SB / 1024 / W, ND = NDA + NDB;    // copy instructions per wave and stage
@@ -1173,8 +1177,6 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = wave >> 2, wm = (wave >> 1) & 1, wn = wave & 1;
-  int tm, tn;
-  tile_of_block<true>(g.tiles_m, g.tiles_n, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
 
   const uint32_t lda = (uint32_t)g.lda, ldb = (uint32_t)g.ldb;
@@ -1399,6 +1401,25 @@ __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
   }
 }
 
+template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS>
+__global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
+  int tm, tn;
+  tile_of_block<true>(g.tiles_m, g.tiles_n, tm, tn);
+  gemm_ring<A_KC, B_KC, EPI, TM, TN, KG, NSUB, NS>(g, tm, tn);
+}
+// Weight gradients: the tiles of up to kMaxGroup problems, problem after problem, in one grid.
+template <int EPI, int TM, int TN, int KG, int NSUB, int NS>
+__global__ __launch_bounds__(256 * KG) void gemm_ring_group_kernel(const GemmGroup grp) {
+  int pos = (int)host::xcd_contiguous(blockIdx.x, gridDim.x), i = 0;
+  while (i + 1 < grp.n && pos >= grp.g[i].tiles_m * grp.g[i].tiles_n) {
+    pos -= grp.g[i].tiles_m * grp.g[i].tiles_n;
+    ++i;
+  }
+  int tm, tn;
+  tile_at(pos, grp.g[i].tiles_m, grp.g[i].tiles_n, tm, tn);
+  gemm_ring<false, false, EPI, TM, TN, KG, NSUB, NS>(grp.g[i], tm, tn);
+}
+
 // The sums of a split launch's parts, added in their order, through the epilogue: 4 columns per thread.
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_split_sum_kernel(const GemmArgs g, int parts) {
@@ -1519,30 +1540,51 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   return hipGetLastError();          // both kernels form the column sums of a weight gradient themselves
 }
 
+template <int TM, int TN, int KG, int NSUB, int NS>
+static hipError_t launch_ring_group(int epi, GemmGroup& grp, hipStream_t s) {
+  int tiles = 0;
+  for (int i = 0; i < grp.n; ++i) {
+    GemmArgs& g = grp.g[i];
+    g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
+    g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
+    tiles += g.tiles_m * g.tiles_n;
+  }
+  const dim3 grid(tiles), block(256 * KG);
+  if (epi == EPI_ACC_F32) hipLaunchKernelGGL((gemm_ring_group_kernel<EPI_ACC_F32, TM, TN, KG, NSUB, NS>), grid, block, 0, s, grp);
+  else if (epi == EPI_ACC_BF16) hipLaunchKernelGGL((gemm_ring_group_kernel<EPI_ACC_BF16, TM, TN, KG, NSUB, NS>), grid, block, 0, s, grp);
+  else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
 template <bool A_KC, bool B_KC, int TM, int TN, int KG, int NSUB, int NS>
 static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s, int parts = 1) {
-  g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
-  g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
-  const dim3 grid(g.tiles_m * g.tiles_n, parts), block(256 * KG);
+  if constexpr (!A_KC && !B_KC) {                       // weight gradients: a group of one
+    GemmGroup grp;
+    grp.n = 1;
+    grp.g[0] = g;
+    return launch_ring_group<TM, TN, KG, NSUB, NS>(epi, grp, s);
+  } else {
+    g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
+    g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
+    const dim3 grid(g.tiles_m * g.tiles_n, parts), block(256 * KG);
 #define AXONN_GEMM_CASE(E)                                                                      \
-  case E:                                                                                       \
-    if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
-      hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, E, TM, TN, KG, NSUB, NS>), grid, block, 0, s, g); \
-      break;                                                                                    \
-    } else {                                                                                    \
-      return hipErrorInvalidValue;                                                              \
+    case E:                                                                                       \
+      if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
+        hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, E, TM, TN, KG, NSUB, NS>), grid, block, 0, s, g); \
+        break;                                                                                    \
+      } else {                                                                                    \
+        return hipErrorInvalidValue;                                                              \
+      }
+    switch (epi) {
+      AXONN_GEMM_CASE(EPI_BIAS)
+      AXONN_GEMM_CASE(EPI_BIAS_RES)
+      AXONN_GEMM_CASE(EPI_BIAS_GELU)
+      AXONN_GEMM_CASE(EPI_DGELU)
+          default: return hipErrorInvalidValue;
     }
-  switch (epi) {
-    AXONN_GEMM_CASE(EPI_BIAS)
-    AXONN_GEMM_CASE(EPI_BIAS_RES)
-    AXONN_GEMM_CASE(EPI_BIAS_GELU)
-    AXONN_GEMM_CASE(EPI_DGELU)
-    AXONN_GEMM_CASE(EPI_ACC_F32)
-    AXONN_GEMM_CASE(EPI_ACC_BF16)
-    default: return hipErrorInvalidValue;
-  }
 #undef AXONN_GEMM_CASE
-  return hipGetLastError();
+    return hipGetLastError();
+  }
 }
 
 // The kernels that copy tiles with buffer instructions address an operand with 32-bit byte offsets from the segment base.
@@ -1595,6 +1637,16 @@ int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K) {
   return r.parts > 1 ? r.parts * M * N : 0;
 }
 
+static hipError_t launch_ring_group_tile(int tile, int epi, GemmGroup& grp, hipStream_t s) {
+  switch (tile) {
+    case host::RING_64x64: return launch_ring_group<2, 2, 2, 2, 4>(epi, grp, s);
+    case host::RING_128x64: return launch_ring_group<4, 2, 2, 2, 3>(epi, grp, s);
+    case host::RING_128x128: return launch_ring_group<4, 4, 2, 1, 4>(epi, grp, s);
+    case host::RING_128x192: return launch_ring_group<4, 6, 2, 1, 3>(epi, grp, s);
+    default: return launch_ring_group<4, 8, 2, 1, 3>(epi, grp, s);
+  }
+}
+
 static bool aligned16(const GemmArgs& g) {
   uintptr_t bits = 0;
   for (int i = 0; i < g.n_seg; ++i) bits |= (uintptr_t)g.A_seg[i] | (uintptr_t)g.B_seg[i];
@@ -1634,6 +1686,34 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
     case 6: return launch_big<A_KC, B_KC, 6>(epi, g, s);
     default: return launch_big<A_KC, B_KC, 8>(epi, g, s);
   }
+}
+
+// One launch where every problem takes a ring tile: what small weight gradients (5 to 7 us each at 1000 x 384 over 1200
+// tokens) spend on launching, filling and draining is paid once.  Beside other streams only up to one workgroup per CU: a
+// longer queue of tiles keeps the backward chain's kernels waiting, which get their CUs between separate launches.  Whole
+// batches, separate / one launch: 3 layers of h 384 742 / 692 us; 4 of h 1024, 8192 tokens, 768 tiles, one stream 4.15 / 3.97 ms,
+// two streams 4.00 / 4.15.
+hipError_t launch_wgrad_group(int epi, GemmGroup& grp, hipStream_t s) {
+  int64_t M[kMaxGroup], N[kMaxGroup];
+  bool ring = grp.n >= 1 && grp.n <= kMaxGroup;
+  for (int i = 0; ring && i < grp.n; ++i) {
+    const GemmArgs& g = grp.g[i];
+    const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
+    M[i] = g.M;
+    N[i] = g.N;
+    ring = g.K == grp.g[0].K && g.n_seg == grp.g[0].n_seg && fits_32bit_offsets(g.K, g.lda) && fits_32bit_offsets(g.K, g.ldb) &&
+           aligned16(g) && host::choose_ring_tile(g.M, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) >= 0;
+  }
+  if (ring) {
+    const int64_t nk = (int64_t)((grp.g[0].K + 63) / 64) * grp.g[0].n_seg;
+    const host::GroupTile r = host::choose_group_tile(grp.n, M, N, nk);
+    if (r.tiles <= 256 || !grp.g[0].concurrent) return launch_ring_group_tile(r.tile, epi, grp, s);
+  }
+  for (int i = 0; i < grp.n; ++i) {
+    const hipError_t e = launch_layout<false, false>(epi, grp.g[i], s);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_gemm(bool a_kc, bool b_kc, int epi, const GemmArgs& g, hipStream_t s) {

@@ -338,6 +338,22 @@ inline int choose_ring_tile(int64_t M, int64_t N, int64_t nk, int64_t forced, bo
   return best;
 }
 
+// The tile for n weight gradients whose tiles share one grid (modelled like one problem of all their tiles), and how many
+// of them there are.
+struct GroupTile { int tile; int64_t tiles; };
+inline GroupTile choose_group_tile(int n, const int64_t* M, const int64_t* N, int64_t nk) {
+  GroupTile best = {-1, 0};
+  double best_cost = 0;
+  for (int t = 0; t < RING_TILES; ++t) {
+    const TileCost& c = kRingCost[t];
+    int64_t tiles = 0;
+    for (int i = 0; i < n; ++i) tiles += ((M[i] + c.bm - 1) / c.bm) * ((N[i] + c.bn - 1) / c.bn);
+    const double cost = tile_cost({1, 1, c.fixed, c.step_few, c.step_full}, tiles, 1, nk);
+    if (best.tile < 0 || cost < best_cost) { best = {t, tiles}; best_cost = cost; }
+  }
+  return best;
+}
+
 // Split of a long contraction with a small output over workgroups, for callers that can hand over a workspace: tile and
 // number of parts (1: not split) with the lowest modelled time.  The parts cost a write and a read of their fp32 sums
 // (4 TB/s) and a launch (5 us).  The LM head's input gradient, 2048 x 1024 x 51200 in four parts of 128 x 256 tiles: 345 -> 205 us.

@@ -57,7 +57,7 @@ enum ProfCat { PC_GEMM_FWD, PC_GEMM_DGRAD, PC_GEMM_WGRAD, PC_ATTN_FWD, PC_ATTN_B
 const char* const kProfNames[PC_COUNT] = {
     "gemm_fwd", "gemm_dgrad", "gemm_wgrad", "attention_fwd", "attention_bwd", "layernorm_fwd",
     "layernorm_bwd", "grad_convert", "adam", "copy_in", "embedding", "cross_entropy"};
-struct ProfRec { int cat; hipEvent_t a, b; };
+struct ProfRec { int cat, n; hipEvent_t a, b; };   // n: contractions of a launch that forms several
 bool g_prof_on = false;
 std::vector<ProfRec> g_prof_recs;
 std::vector<hipEvent_t> g_prof_pool;
@@ -69,8 +69,8 @@ hipEvent_t prof_event() {
   return e;
 }
 struct ProfScope {
-  hipStream_t s; hipEvent_t a = nullptr, b = nullptr; int cat;
-  ProfScope(int cat_, hipStream_t s_) : s(s_), cat(cat_) {
+  hipStream_t s; hipEvent_t a = nullptr, b = nullptr; int cat, n;
+  ProfScope(int cat_, hipStream_t s_, int n_ = 1) : s(s_), cat(cat_), n(n_) {
     if (!g_prof_on) return;
     a = prof_event(); b = prof_event();
     if (a && b) (void)hipEventRecord(a, s);
@@ -78,7 +78,7 @@ struct ProfScope {
   ~ProfScope() {
     if (!a || !b) return;
     (void)hipEventRecord(b, s);
-    g_prof_recs.push_back(ProfRec{cat, a, b});
+    g_prof_recs.push_back(ProfRec{cat, n, a, b});
   }
 };
 
@@ -461,9 +461,8 @@ int backward_layers(axonn_stage* st, Slot& slot, const Work* w, int n, void* dx_
 // microbatches inside one contraction per weight (the token index of all of them is the
 // contraction index): dW = sum_mb x_mb^T dy_mb.  Runs on `s` after the chains it reads and after
 // the previous such pass (they update the same accumulators), then releases the slots.
-int gemm_seg(int epi, int M, int N, int K, const elem_t* const* A, int64_t lda, const elem_t* const* B,
-             int64_t ldb, int n_seg, void* C, int64_t ldc, void* colsum, float* colsum_ws, int accumulate,
-             hipStream_t s) {
+GemmArgs wgrad_args(int M, int N, int K, const elem_t* const* A, int64_t lda, const elem_t* const* B, int64_t ldb,
+                    int n_seg, void* C, int64_t ldc, void* colsum, float* colsum_ws, int accumulate) {
   GemmArgs g;
   memset(&g, 0, sizeof g);
   for (int i = 0; i < n_seg; ++i) { g.A_seg[i] = A[i]; g.B_seg[i] = B[i]; }
@@ -471,8 +470,7 @@ int gemm_seg(int epi, int M, int N, int K, const elem_t* const* A, int64_t lda, 
   g.M = M; g.N = N; g.K = K; g.accumulate = accumulate;
   g.colsum = colsum; g.colsum_ws = colsum_ws;
   g.concurrent = t_concurrent;
-  ProfScope ps(PC_GEMM_WGRAD, s);
-  return check_launch(launch_gemm(false, false, epi, g, s), "gemm (weight gradient)");
+  return g;
 }
 
 // dW += sum_i in_i^T dout_i for the four weights of layer l over n activation records, and with each the bias
@@ -482,16 +480,18 @@ int wgrad_layer(axonn_stage* st, int l, const LayerStash* const* rec, int n, int
   const int epi = st->cfg.grad_accum_fp32 ? EPI_ACC_F32 : EPI_ACC_BF16;
   float* const cws = st->wgrad_red_ws;
   const elem_t *A[kMaxKSegments], *B[kMaxKSegments];
+  GemmGroup grp;
+  grp.n = 4;
   for (int i = 0; i < n; ++i) { A[i] = rec[i]->g; B[i] = rec[i]->dz; }
-  AX_TRY(gemm_seg(epi, f, h, T, A, f, B, h, n, grad_ptr(st, l, P_WFC2), h, grad_ptr(st, l, P_BFC2), cws, acc, s));
+  grp.g[0] = wgrad_args(f, h, T, A, f, B, h, n, grad_ptr(st, l, P_WFC2), h, grad_ptr(st, l, P_BFC2), cws, acc);
   for (int i = 0; i < n; ++i) { A[i] = rec[i]->w; B[i] = rec[i]->dpre; }
-  AX_TRY(gemm_seg(epi, h, f, T, A, h, B, f, n, grad_ptr(st, l, P_WFC1), f, grad_ptr(st, l, P_BFC1), cws, acc, s));
+  grp.g[1] = wgrad_args(h, f, T, A, h, B, f, n, grad_ptr(st, l, P_WFC1), f, grad_ptr(st, l, P_BFC1), cws, acc);
   for (int i = 0; i < n; ++i) { A[i] = rec[i]->o; B[i] = rec[i]->dy_mid; }
-  AX_TRY(gemm_seg(epi, h, h, T, A, h, B, h, n, grad_ptr(st, l, P_WO), h, grad_ptr(st, l, P_BO), cws, acc, s));
+  grp.g[2] = wgrad_args(h, h, T, A, h, B, h, n, grad_ptr(st, l, P_WO), h, grad_ptr(st, l, P_BO), cws, acc);
   for (int i = 0; i < n; ++i) { A[i] = rec[i]->u; B[i] = rec[i]->dqkv; }
-  AX_TRY(gemm_seg(epi, h, 3 * h, T, A, h, B, 3 * h, n, grad_ptr(st, l, P_WQKV), 3 * h, grad_ptr(st, l, P_BQKV), cws,
-                  acc, s));
-  return AXONN_OK;
+  grp.g[3] = wgrad_args(h, 3 * h, T, A, h, B, 3 * h, n, grad_ptr(st, l, P_WQKV), 3 * h, grad_ptr(st, l, P_BQKV), cws, acc);
+  ProfScope ps(PC_GEMM_WGRAD, s, grp.n);
+  return check_launch(launch_wgrad_group(epi, grp, s), "gemm (weight gradients)");
 }
 
 // Rounds layer l's fp32 gradient accumulators into the bf16 gradient buffer (fp32 accumulation only) and
@@ -841,7 +841,9 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
   {
     const elem_t* A[1] = {hd->a};
     const elem_t* B[1] = {hd->logits};
-    AX_TRY(gemm_seg(EPI_ACC_BF16, h, V, T, A, h, B, V, 1, hd->grads + 2 * (uint64_t)h, V, nullptr, nullptr, acc, s));
+    const GemmArgs wg = wgrad_args(h, V, T, A, h, B, V, 1, hd->grads + 2 * (uint64_t)h, V, nullptr, nullptr, acc);
+    ProfScope ps(PC_GEMM_WGRAD, s);
+    AX_TRY(check_launch(launch_gemm(false, false, EPI_ACC_BF16, wg, s), "gemm (head weight gradient)"));
   }
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, V, hd->logits, V, W, V, hd->da, h, nullptr, nullptr, 0, nullptr, 0, 0, s, 0,
               hd->split_ws, hd->split_floats));
@@ -1820,7 +1822,7 @@ int axonn_profile_collect(double* total_ms, int64_t* launches, int32_t n_categor
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, r.a, r.b);
     if (e != hipSuccess && rc == AXONN_OK)
       rc = fail(AXONN_EHIP, "profile_collect: %s", hipGetErrorString(e));
-    if (e == hipSuccess) { total_ms[r.cat] += ms; launches[r.cat]++; }
+    if (e == hipSuccess) { total_ms[r.cat] += ms; launches[r.cat] += r.n; }
     g_prof_pool.push_back(r.a);
     g_prof_pool.push_back(r.b);
   }
@@ -1917,8 +1919,9 @@ int axonn_gemm_wgrad_colsum(int32_t epilogue, int64_t M, int64_t N, int64_t K, c
   if (lda < M || ldb < N || ldc < N) return fail(AXONN_EINVAL, "gemm_wgrad_colsum: leading dimension too small");
   const elem_t* a1[1] = {(const elem_t*)A};
   const elem_t* b1[1] = {(const elem_t*)B};
-  return gemm_seg(epilogue, (int)M, (int)N, (int)K, a1, lda, b1, ldb, 1, C, ldc, colsum, workspace, accumulate,
-                  (hipStream_t)hip_stream);
+  const GemmArgs g = wgrad_args((int)M, (int)N, (int)K, a1, lda, b1, ldb, 1, C, ldc, colsum, workspace, accumulate);
+  ProfScope ps(PC_GEMM_WGRAD, (hipStream_t)hip_stream);
+  return check_launch(launch_gemm(false, false, epilogue, g, (hipStream_t)hip_stream), "gemm (weight gradient)");
 }
 
 int axonn_layernorm_fwd(int64_t T, int64_t h, const void* x, const void* gamma, const void* beta, float eps,

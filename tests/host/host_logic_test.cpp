@@ -341,6 +341,10 @@ void test_gemm_tiles() {
   // the ring kernel where a round of its tiles covers the problem: 28.5 us against 35.6, 137 against 226
   CHECK(choose_ring_tile(2048, 4096, 16, -1, false) == RING_128x256 && choose_ring_tile(2048, 3072, 192, -1, false) >= 0);
   CHECK(choose_ring_tile(256, 256, 16, -1, false) == RING_64x64);
+  // a group's tile covers all its problems; a group of one takes the tile of the problem alone
+  const int64_t gm[4] = {1000, 384, 384, 384}, gn[4] = {384, 1000, 384, 1152};
+  const GroupTile grp = choose_group_tile(4, gm, gn, 21);
+  CHECK(grp.tiles > 0 && grp.tiles <= 256 && choose_group_tile(1, gm, gn, 21).tile == fastest_ring_tile(1000, 384, 21));
   // a split is bounded (16 parts of 16 k-steps at least) and none where the problem fills the chip
   std::mt19937 rng(3);
   for (int rep = 0; rep < 2000; ++rep) {

@@ -247,6 +247,33 @@ def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, opts, n_str
                     assert rel_fro(ga[k], gb[k]) <= (1e-3 if opts.get("grad_accum_fp32", 1) else 8e-3), (events, shared, k)
 
 
+@pytest.mark.parametrize("sh,fp32_acc", [
+    (StageShape(1, 1024, 16, 256, 1, 1), 1),       # 768 tiles: one launch by direct calls, four beside another stream
+    (StageShape(1, 1024, 8, 200, 1, 1, 1000), 0),  # the same, ragged in every dimension
+    (StageShape(2, 72, 2, 8, 1, 1, 264), 1),       # one or two ragged tiles per problem, one launch either way
+], ids=["tiles768", "ragged", "smallest"])
+def test_weight_gradients_of_a_layer_in_one_launch(sh, fp32_acc):
+    """A layer's four weight gradients (and bias gradients) as one grid: the oracle's, and bit for bit the same from
+    separate launches (other tiles add k in the same order)."""
+    import torch
+    layers, xs, dys = make_stage_inputs(sh, seed=6, perturb=True)
+    ref = oracle.stage_batch(xs, dys, layers, sh.n_heads, EPS)
+    with Stage(sh, grad_accum_fp32=fp32_acc) as st:
+        st.load_params(layers)
+        outs, dxs, grads = run_direct(st, xs, dys)
+        check_batch(outs, dxs, grads, ref)
+        X, DY = dev_bf16(xs[0]), dev_bf16(dys[0])
+        Y, DX = torch.zeros_like(X), torch.zeros_like(X)
+        torch.cuda.synchronize()
+        st.zero_grad()
+        st.post(0, 0, X, Y); st.post(1, 0, DY, DX)
+        st.run(2); st.join()
+        torch.cuda.synchronize()
+        for ga, gb in zip(st.grads_numpy(), grads):
+            for k in ga:
+                assert np.array_equal(ga[k], gb[k]), k
+
+
 def test_message_arrival_order_follows_ready_events():
     """A message whose payload has not arrived (event not yet signalled) is passed over for one
     that has: forward vs backward is decided by what is ready, not by posting order."""
