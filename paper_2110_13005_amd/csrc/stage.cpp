@@ -447,9 +447,9 @@ int copy_microbatches(axonn_stage* st, const Work* w, int n, elem_t* stash, bool
 elem_t* merged_dx(Slot& slot) { return slot.layers[0].qkv; }
 int backward_layers(axonn_stage* st, Slot& slot, const Work* w, int n, void* dx_out, int acc, bool last, hipStream_t s) {
   const int L = st->cfg.n_layers;
-  // the upstream gradient is copied into the stash: it is an operand of the deferred weight
-  // gradient and the caller may recycle its receive buffer
-  AX_TRY(copy_microbatches(st, w, n, slot.layers[L - 1].dz, true, s));
+  // the upstream gradient is copied into the stash (the last stage's head leaves it there): it is an operand of the
+  // deferred weight gradient and the caller may recycle its receive buffer
+  if (w[0].in != slot.layers[L - 1].dz) AX_TRY(copy_microbatches(st, w, n, slot.layers[L - 1].dz, true, s));
   for (int l = L - 1; l >= 0; --l) {
     AX_TRY(backward_layer(st, l, slot.layers[l], n, (l == 0) ? (elem_t*)dx_out : slot.layers[l - 1].dz, acc, s));
     if (last) HIP_TRY(hipEventRecord(st->chain_layer[l], s));
@@ -639,7 +639,7 @@ int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t
                      : n == 1 ? w[0].out : slot->layers[st->cfg.n_layers - 1].dz;
   if (st->cfg.ckpt_stride > 0) AX_TRY(forward_layers_ckpt(st, *slot, y, s));
   else AX_TRY(forward_layers(st, *slot, n, y, s));
-  if (n > 1) AX_TRY(copy_microbatches(st, w, n, (elem_t*)y, false, s));
+  if (n > 1 && !st->head) AX_TRY(copy_microbatches(st, w, n, (elem_t*)y, false, s));
   for (int i = 0; i < n; ++i) {
     HIP_TRY(hipEventRecord(slot[i].fwd_done, s));
     host::commit_forward(st->slots, si + i, w[i].mb_id, &st->in_flight);
@@ -1190,7 +1190,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
   const auto span = [st, act_bytes](size_t i) {
     const axonn_msg& m = st->inbox[i].m;
     const uint64_t in = (uint64_t)(uintptr_t)m.payload_dev, out = (uint64_t)(uintptr_t)m.result_dev;
-    const bool result = out != 0 && !(st->embed && m.kind == 1);
+    const bool result = out != 0 && !(st->embed && (m.kind == 1 || st->head));
     return host::MessageSpan{m.kind, m.mb_id, m.done_event != nullptr, in,
                              in + (st->embed && m.kind == 0 ? (uint64_t)st->T * sizeof(int32_t) : act_bytes),
                              result ? out : 0, result ? out + act_bytes : 0};
@@ -1223,13 +1223,17 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     if (m.kind == 0 && host::find_free(st->slots) < 0) AX_TRY(flush_wgrad(st, ws));
     int picked[host::kMaxMerge];
     const int n = host::merge_messages(st->inbox.size(), span, arrived, chosen, st->slots, st->in_flight,
-                                       st->cfg.pipeline_limit, st->head ? 1 : st->max_merge, picked);
+                                       st->cfg.pipeline_limit, st->max_merge, picked);
     const int si = host::stream_index(m.kind, n_streams, &st->fwd_rr);
     hipStream_t s = st->streams[si];
     Work w[host::kMaxMerge];
+    const int32_t* targets[host::kMaxMerge];
+    float* loss[host::kMaxMerge];
     for (int i = 0; i < n; ++i) {
       const axonn_msg& mi = st->inbox[picked[i]].m;
       w[i] = Work{mi.mb_id, mi.payload_dev, mi.result_dev};
+      targets[i] = (const int32_t*)mi.targets_dev;
+      loss[i] = (float*)mi.loss_dev;
       if (mi.ready_event) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)mi.ready_event, 0));
     }
     std::sort(picked, picked + n);
@@ -1237,20 +1241,26 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     if (m.kind == 0) {
       AX_TRY(do_forward(st, w, n, s, ws));
       st->fwd_issued += n;
-      for (int i = 0; i < n; ++i) st->dispatch_log.push_back(w[i].mb_id * 2);
+      for (int i = 0; i < n; ++i) {
+        st->dispatch_log.push_back(w[i].mb_id * 2);
+        if (st->head) st->dispatch_log.push_back(w[i].mb_id * 2 + 1);   // each Forward is followed by its Backward
+      }
       if (st->head) {
         // last stage (Alg. 2): the loss follows the forward pass and Backward(1) starts at once, on the
         // stream of the backward chains
-        Slot* slot = find_live(st, m.mb_id);
+        const int si = host::find_live(st->slots, w[0].mb_id);
         hipStream_t bs = st->streams[0];
-        HIP_TRY(hipStreamWaitEvent(bs, slot->fwd_done, 0));
-        if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(bs, st->last_bwd, 0));   // head_dx is shared
-        AX_TRY(head_forward_backward(st->head, slot->head_y, (const int32_t*)m.targets_dev, (float*)m.loss_dev,
-                                     st->head_dx, bs));
-        const Work back = {m.mb_id, st->head_dx, m.result_dev};
-        AX_TRY(backward_msg(st, &back, 1, bs, ws));
-        st->bwd_issued++;
-        st->dispatch_log.push_back(m.mb_id * 2 + 1);
+        HIP_TRY(hipStreamWaitEvent(bs, st->slots[si + n - 1].fwd_done, 0));
+        if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(bs, st->last_bwd, 0));   // the head's buffers are shared
+        Work back[host::kMaxMerge];
+        for (int i = 0; i < n; ++i) {
+          Slot& slot = st->slots[si + i];
+          elem_t* const dx = st->cfg.ckpt_stride > 0 ? st->head_dx : slot.layers[st->cfg.n_layers - 1].dz;
+          AX_TRY(head_forward_backward(st->head, slot.head_y, targets[i], loss[i], dx, bs));
+          back[i] = Work{w[i].mb_id, dx, w[i].out};
+        }
+        AX_TRY(backward_msg(st, back, n, bs, ws));
+        st->bwd_issued += n;
         s = bs;
       }
     } else {
@@ -1779,10 +1789,11 @@ int axonn_stage_attach_ends(axonn_stage_t* st, axonn_embed_t* embed, axonn_head_
   HIP_TRY(hipDeviceSynchronize());
   const uint64_t e_th = align_up((uint64_t)st->T * st->h * 2, 256);
   if (embed && !st->embed_dx) HIP_TRY(hipMalloc((void**)&st->embed_dx, e_th));
-  if (head && !st->head_dx) {
-    HIP_TRY(hipMalloc((void**)&st->head_dx, e_th));
-    HIP_TRY(hipMalloc((void**)&st->head_y_base, e_th * st->slots.size()));
-    for (size_t i = 0; i < st->slots.size(); ++i) st->slots[i].head_y = (elem_t*)((char*)st->head_y_base + i * e_th);
+  if (head && !st->head_y_base) {
+    // one behind the other, like the tensors of the stash
+    HIP_TRY(hipMalloc((void**)&st->head_y_base, (uint64_t)st->T * st->h * 2 * st->slots.size()));
+    for (size_t i = 0; i < st->slots.size(); ++i) st->slots[i].head_y = st->head_y_base + i * (uint64_t)st->T * st->h;
+    if (st->cfg.ckpt_stride > 0) HIP_TRY(hipMalloc((void**)&st->head_dx, e_th));
   }
   st->embed = embed;
   st->head = head;

@@ -280,3 +280,47 @@ def test_head_input_gradient_split_over_the_vocabulary(T, h, V):
         assert np.array_equal(got[0], got[1])
     finally:
         hd.close()
+
+
+@pytest.mark.parametrize("sh,limit", [(StageShape(2, 128, 2, 64, 1, 5), 5), (StageShape(1, 264, 2, 72, 1, 4, 1000), 3)],
+                         ids=["one_pass", "three_and_one"])
+@pytest.mark.parametrize("with_embed", [True, False])
+def test_merged_microbatches_through_the_head(sh, limit, with_embed):
+    """Forwards and backwards of several microbatches as one pass with the head between them: losses and input gradients bit
+    for bit those of a run that takes them one by one (a done_event each)."""
+    import torch
+    V, M = 520, sh.n_microbatches
+    layers, xs, _ = make_stage_inputs(sh, seed=31, perturb=True)
+    tokens, targets, wte, wpe, g, bt, W = make_lm_inputs(sh, V, seed=32)
+    e = EmbedHandle(V, sh.hidden, sh.seq_len, sh.microbatch_size, wte, wpe) if with_embed else None
+    hd = HeadHandle(V, sh.hidden, sh.tokens, M, g, bt, W)
+    got = []
+    try:
+        with Stage(sh, pipeline_limit=limit) as st:
+            st.load_params(layers)
+            B.axonn_stage_attach_ends(st.handle, e.h if e else None, hd.h)
+            X = [dev_i32(t) for t in tokens] if e else [dev_bf16(x) for x in xs]
+            TG = [dev_i32(t) for t in targets]
+            for events in (False, True):
+                evs = [torch.cuda.Event() for _ in range(M)]
+                for ev in evs:
+                    ev.record()
+                DX = [None if e else torch.zeros_like(X[0]) for _ in range(M)]
+                losses = torch.zeros(M, device="cuda")
+                torch.cuda.synchronize()
+                st.zero_grad()
+                for i in range(M):
+                    st.post(0, i, X[i], DX[i], targets=TG[i], loss=losses[i:i + 1], done_event=evs[i] if events else None)
+                st.run(2); st.join(); torch.cuda.synchronize()
+                assert B.axonn_stage_dispatch_log(st.handle) == [(i, k) for i in range(M) for k in (0, 1)]
+                got.append((losses.cpu().numpy(), [None if d is None else host(d) for d in DX], st.grads_numpy()))
+    finally:
+        hd.close()
+        if e:
+            e.close()
+    (la, xa, ga), (lb, xb, gb) = got
+    assert np.array_equal(la, lb)
+    assert e or all(np.array_equal(a, b) for a, b in zip(xa, xb))
+    for p, q in zip(ga, gb):
+        for k in p:
+            assert rel_fro(p[k], q[k]) <= 1e-3, k          # sums over the microbatches, in another order
