@@ -956,7 +956,7 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
     if (cfg->qkv_input_split) place(base, at, b_th, recs, &R::u_lo);
   };
   const int ac = cfg->ckpt_stride;
-  st->max_merge = ac > 0 ? 1 : host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit);
+  st->max_merge = ac > 0 ? 1 : host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches);
   st->slots.resize(cfg->pipeline_limit);
   for (Slot& s : st->slots) {
     CREATE_TRY(hipEventCreateWithFlags(&s.fwd_done, hipEventDisableTiming));

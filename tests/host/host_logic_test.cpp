@@ -357,10 +357,13 @@ void test_gemm_tiles() {
 
 void test_merged_messages() {
   // sizes: one microbatch each where an activation has 2^24 elements, never more than 8 or pipeline_limit, wide MLPs count
-  CHECK(merge_limit(4096, 4096, 16384, 32, 8) == 1 && merge_limit(8192, 8192, 32768, 64, 8) == 1);
-  CHECK(merge_limit(2048, 2048, 8192, 16, 8) == 4 && merge_limit(2048, 4096, 16384, 32, 8) == 2);
-  CHECK(merge_limit(256, 256, 1024, 4, 3) == 3 && merge_limit(256, 256, 1024, 4, 64) == kMaxMerge);
-  CHECK(merge_limit(2048, 2048, 32768, 16, 8) == 1 && merge_limit(256, 256, 256, 4, 8) == 1 && merge_limit(256, 256, 264, 4, 8) == 8);
+  const auto limit_of = [](int64_t T, int64_t h, int64_t f, int slots, int M) { return merge_limit(T, h, f, h / 64, slots, M); };
+  CHECK(limit_of(4096, 4096, 16384, 8, 8) == 1 && limit_of(8192, 8192, 32768, 8, 8) == 1);
+  CHECK(limit_of(2048, 2048, 8192, 8, 8) == 4 && limit_of(2048, 4096, 16384, 8, 8) == 2);
+  CHECK(limit_of(256, 256, 1024, 3, 3) == 3 && limit_of(256, 256, 1024, 64, 64) == kMaxMerge && limit_of(256, 256, 1024, 9, 9) == 5);
+  CHECK(limit_of(2048, 2048, 32768, 8, 8) == 1 && limit_of(256, 256, 256, 8, 8) == 1 && limit_of(256, 256, 264, 8, 8) == 8);
+  const int refilled[9] = {0, 1, 2, 2, 4, 3, 3, 4, 4};       // fewer slots than microbatches
+  for (int p = 1; p <= 8; ++p) CHECK(limit_of(256, 256, 1024, p, 16) == refilled[p]);
 
   std::vector<MessageSpan> box;
   std::vector<int> here;                       // arrived(i)

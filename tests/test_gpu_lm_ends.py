@@ -282,8 +282,8 @@ def test_head_input_gradient_split_over_the_vocabulary(T, h, V):
         hd.close()
 
 
-@pytest.mark.parametrize("sh,limit", [(StageShape(2, 128, 2, 64, 1, 5), 5), (StageShape(1, 264, 2, 72, 1, 4, 1000), 3)],
-                         ids=["one_pass", "three_and_one"])
+@pytest.mark.parametrize("sh,limit", [(StageShape(2, 128, 2, 64, 1, 5), 5), (StageShape(1, 264, 2, 72, 1, 5, 1000), 4)],
+                         ids=["one_pass", "four_and_one"])
 @pytest.mark.parametrize("with_embed", [True, False])
 def test_merged_microbatches_through_the_head(sh, limit, with_embed):
     """Forwards and backwards of several microbatches as one pass with the head between them: losses and input gradients bit
