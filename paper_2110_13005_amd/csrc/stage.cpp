@@ -115,9 +115,11 @@ struct Slot {
   int mb_id = -1;          // valid while SLOT_LIVE (forward issued, backward not yet)
   std::vector<LayerStash> layers;
   // fwd_done: forward finished; dgrad_done: backward's activation-gradient chain finished;
-  // released: the weight-gradient contraction that read the slot finished (slot reusable)
+  // released: the weight-gradient contraction that read the slot finished (slot reusable; null: never used).  Work that
+  // several slots share is marked by one event, an `own` one of the first of them: a record costs the host about as much
+  // as a launch.  When that slot has gone on and its event stands for later work, waiting for it implies the earlier.
   hipEvent_t fwd_done = nullptr, dgrad_done = nullptr, released = nullptr;
-  bool released_recorded = false;
+  struct { hipEvent_t fwd_done = nullptr, dgrad_done = nullptr, released = nullptr; } own;
   const int32_t* tokens = nullptr;   // first stage: the microbatch's token ids, needed again by Backward
   elem_t* head_y = nullptr;          // last stage: the stage output the head consumes
 };
@@ -208,8 +210,10 @@ struct axonn_stage {
   // state
   int in_flight = 0;
   int bwd_count = 0;  // backwards since the last zero_grad
-  hipEvent_t last_bwd = nullptr, last_wgrad = nullptr, fork_ev = nullptr;
-  bool last_bwd_recorded = false, last_wgrad_recorded = false;
+  // the events behind the last backward chain and the last weight-gradient pass (null: none yet)
+  hipEvent_t last_bwd = nullptr, last_wgrad = nullptr;
+  hipEvent_t fork_ev = nullptr, embed_bwd = nullptr;
+  bool join_all = false;              // a dispatch failed half-way: join waits for every library stream
   int wgrad_flushes = 0;              // weight-gradient contractions since the last zero_grad
   // per layer, for the last microbatch of a batch: chain_layer[l] = its backward chain has passed layer l;
   // grads_final[l] = every gradient of layer l is final in the bf16 buffer (the overlapped optimizer step
@@ -445,14 +449,14 @@ int copy_microbatches(axonn_stage* st, const Work* w, int n, elem_t* stash, bool
 // `slot`: the first of n microbatches'.  The result of one goes straight to its caller's buffer; several leave theirs in
 // place of the first layer's q, k and v, which nobody reads after its attention.
 elem_t* merged_dx(Slot& slot) { return slot.layers[0].qkv; }
-int backward_layers(axonn_stage* st, Slot& slot, const Work* w, int n, void* dx_out, int acc, bool last, hipStream_t s) {
+int backward_layers(axonn_stage* st, Slot& slot, const Work* w, int n, void* dx_out, int acc, bool mark_layers, hipStream_t s) {
   const int L = st->cfg.n_layers;
   // the upstream gradient is copied into the stash (the last stage's head leaves it there): it is an operand of the
   // deferred weight gradient and the caller may recycle its receive buffer
   if (w[0].in != slot.layers[L - 1].dz) AX_TRY(copy_microbatches(st, w, n, slot.layers[L - 1].dz, true, s));
   for (int l = L - 1; l >= 0; --l) {
     AX_TRY(backward_layer(st, l, slot.layers[l], n, (l == 0) ? (elem_t*)dx_out : slot.layers[l - 1].dz, acc, s));
-    if (last) HIP_TRY(hipEventRecord(st->chain_layer[l], s));
+    if (mark_layers) HIP_TRY(hipEventRecord(st->chain_layer[l], s));
   }
   return AXONN_OK;
 }
@@ -509,20 +513,24 @@ int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
 
 // Weight gradients of every slot that has finished its backward chain (see above).  `last_slot` is the first of the
 // n_last slots of the batch's last chain when this is the batch's final pass (else null): the pass then
-// follows that chain layer by layer from the last layer down, and finishes each layer's
-// gradients as soon as its contractions are queued.
-int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr, int n_last = 0) {
+// follows that chain (by its events, if it runs on another stream: follow_chain) layer by layer from the last layer down,
+// and finishes each layer's gradients as soon as its contractions are queued.
+int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr, int n_last = 0, bool follow_chain = false) {
   std::vector<Slot*> ready;
   for (Slot& sl : st->slots)
     if (sl.state == SLOT_AWAIT_WGRAD) ready.push_back(&sl);
   if (ready.empty()) return AXONN_OK;
   const int L = st->cfg.n_layers;
+  hipEvent_t waited = nullptr;
   for (Slot* sl : ready)
-    if (!last_slot || sl < last_slot || sl >= last_slot + n_last) HIP_TRY(hipStreamWaitEvent(s, sl->dgrad_done, 0));
-  if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
+    if ((!last_slot || sl < last_slot || sl >= last_slot + n_last) && sl->dgrad_done != waited) {
+      waited = sl->dgrad_done;
+      HIP_TRY(hipStreamWaitEvent(s, waited, 0));
+    }
+  if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   for (int i = 0; i < L; ++i) {
     const int l = last_slot ? L - 1 - i : i;
-    if (last_slot) HIP_TRY(hipStreamWaitEvent(s, st->chain_layer[l], 0));
+    if (last_slot && follow_chain) HIP_TRY(hipStreamWaitEvent(s, st->chain_layer[l], 0));
     for (size_t first = 0; first < ready.size(); first += kMaxKSegments) {
       const int n = (int)std::min<size_t>(kMaxKSegments, ready.size() - first);
       const int acc = (st->wgrad_flushes > 0 || first > 0) ? 1 : 0;
@@ -534,12 +542,9 @@ int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr, int n
   }
   st->wgrad_flushes++;
   if (last_slot) st->grads_final_recorded = true;
-  HIP_TRY(hipEventRecord(st->last_wgrad, s));
-  st->last_wgrad_recorded = true;
-  for (Slot* sl : ready) {
-    HIP_TRY(hipEventRecord(sl->released, s));
-    sl->released_recorded = true;
-  }
+  HIP_TRY(hipEventRecord(ready[0]->own.released, s));
+  for (Slot* sl : ready) sl->released = ready[0]->own.released;
+  st->last_wgrad = ready[0]->own.released;
   host::release_awaiting(st->slots);
   return AXONN_OK;
 }
@@ -575,7 +580,7 @@ int backward_layers_ckpt(axonn_stage* st, Slot& slot, const void* dy_in, void* d
     }
     HIP_TRY(hipEventRecord(R.chain_done, s));
     if (ws != s) HIP_TRY(hipStreamWaitEvent(ws, R.chain_done, 0));
-    if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(ws, st->last_wgrad, 0));
+    if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(ws, st->last_wgrad, 0));
     for (int i = 0; i < ac; ++i) {
       const LayerStash* one[1] = {&rec[i]};
       AX_TRY(wgrad_layer(st, seg * ac + i, one, 1, acc, ws));
@@ -583,10 +588,9 @@ int backward_layers_ckpt(axonn_stage* st, Slot& slot, const void* dy_in, void* d
     // last microbatch of the batch: the segment's gradients are final (the chain has passed its layers)
     if (last)
       for (int i = ac - 1; i >= 0; --i) AX_TRY(finish_layer_grads(st, seg * ac + i, ws));
-    HIP_TRY(hipEventRecord(st->last_wgrad, ws));
-    st->last_wgrad_recorded = true;
     HIP_TRY(hipEventRecord(R.released, ws));
     R.released_recorded = true;
+    st->last_wgrad = R.released;
   }
   return AXONN_OK;
 }
@@ -624,7 +628,8 @@ int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t
   const uint64_t elems = (uint64_t)st->T * st->h;
   // the weight-gradient pass that read a slot's previous contents must have finished
   for (int i = 0; i < n; ++i)
-    if (slot[i].released_recorded) HIP_TRY(hipStreamWaitEvent(s, slot[i].released, 0));
+    if (slot[i].released && (i == 0 || slot[i].released != slot[i - 1].released))
+      HIP_TRY(hipStreamWaitEvent(s, slot[i].released, 0));
   elem_t* const x = slot->layers[0].x;
   if (st->embed) {
     for (int i = 0; i < n; ++i) {
@@ -640,8 +645,9 @@ int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t
   if (st->cfg.ckpt_stride > 0) AX_TRY(forward_layers_ckpt(st, *slot, y, s));
   else AX_TRY(forward_layers(st, *slot, n, y, s));
   if (n > 1 && !st->head) AX_TRY(copy_microbatches(st, w, n, (elem_t*)y, false, s));
+  HIP_TRY(hipEventRecord(slot->own.fwd_done, s));
   for (int i = 0; i < n; ++i) {
-    HIP_TRY(hipEventRecord(slot[i].fwd_done, s));
+    slot[i].fwd_done = slot->own.fwd_done;
     host::commit_forward(st->slots, si + i, w[i].mb_id, &st->in_flight);
   }
   return AXONN_OK;
@@ -652,34 +658,34 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   const int si = host::admit_backward(st->slots, w[0].mb_id);
   if (si < 0) return fail(AXONN_ESTATE, "backward: microbatch %d has no forward in flight", w[0].mb_id);
   Slot* slot = &st->slots[si];
-  for (int i = 0; i < n; ++i) HIP_TRY(hipStreamWaitEvent(s, slot[i].fwd_done, 0));
+  for (int i = 0; i < n; ++i)
+    if (i == 0 || slot[i].fwd_done != slot[i - 1].fwd_done) HIP_TRY(hipStreamWaitEvent(s, slot[i].fwd_done, 0));
   // backward chains share the workspace and the bias / LayerNorm accumulators: keep them in order
-  if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
+  if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
   const int acc = st->bwd_count > 0 ? 1 : 0;
   const bool ckpt = st->cfg.ckpt_stride > 0;
   const bool last = st->bwd_count + n == st->cfg.n_microbatches;
   const int awaiting = slots_in_state(st, SLOT_AWAIT_WGRAD);
   if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, w[0].in, w[0].out, acc, last, s, ws));
-  else AX_TRY(backward_layers(st, *slot, w, n, n == 1 ? w[0].out : merged_dx(*slot), acc, last, s));
+  else AX_TRY(backward_layers(st, *slot, w, n, n == 1 ? w[0].out : merged_dx(*slot), acc, last && ws != s, s));
   if (n > 1 && !st->embed) AX_TRY(copy_microbatches(st, w, n, merged_dx(*slot), false, s));
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
   if (!last && !st->cfg.grad_accum_fp32 && host::gradients_complete(ckpt, last, st->cfg.wgrad_group, awaiting, n))
     AX_TRY(store_ln_grads(st, s));
   st->bwd_count += n;
-  for (int i = 0; i < n; ++i) HIP_TRY(hipEventRecord(slot[i].dgrad_done, s));
-  HIP_TRY(hipEventRecord(st->last_bwd, s));
-  st->last_bwd_recorded = true;
+  HIP_TRY(hipEventRecord(slot->own.dgrad_done, s));
+  for (int i = 0; i < n; ++i) slot[i].dgrad_done = slot->own.dgrad_done;
+  st->last_bwd = slot->own.dgrad_done;
   for (int i = 0; i < n; ++i) host::commit_backward(st->slots, si + i, ckpt, &st->in_flight);
   if (ckpt) {
     // the weight gradients are already queued and read the shared sets: the slot (kept inputs only) is
     // free as soon as the chain on `s` is through
-    HIP_TRY(hipEventRecord(slot->released, s));
-    slot->released_recorded = true;
+    slot->released = slot->dgrad_done;
     if (last) st->grads_final_recorded = true;
   } else {
     switch (host::wgrad_action(last, st->cfg.wgrad_group, awaiting + n)) {
-      case host::WGRAD_FLUSH_FINAL: AX_TRY(flush_wgrad(st, ws, slot, n)); break;
+      case host::WGRAD_FLUSH_FINAL: AX_TRY(flush_wgrad(st, ws, slot, n, ws != s)); break;
       case host::WGRAD_FLUSH: AX_TRY(flush_wgrad(st, ws)); break;
       default: break;
     }
@@ -700,7 +706,8 @@ int backward_msg(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream
   const elem_t* dx = n == 1 ? st->embed_dx : merged_dx(st->slots[si]);
   for (int i = 0; i < n; ++i) AX_TRY(embed_backward(st->embed, tokens[i], dx + i * (uint64_t)st->T * st->h, s));
   // the next backward chain overwrites that gradient: it must follow the embedding's pass as well
-  HIP_TRY(hipEventRecord(st->last_bwd, s));
+  HIP_TRY(hipEventRecord(st->embed_bwd, s));
+  st->last_bwd = st->embed_bwd;
   return AXONN_OK;
 }
 
@@ -746,17 +753,16 @@ void destroy_stage(axonn_stage* st) {
   destroy_adam(st->opt);
   if (st->stash_base) (void)hipFree(st->stash_base);
   for (Slot& s : st->slots) {
-    if (s.fwd_done) (void)hipEventDestroy(s.fwd_done);
-    if (s.dgrad_done) (void)hipEventDestroy(s.dgrad_done);
-    if (s.released) (void)hipEventDestroy(s.released);
+    if (s.own.fwd_done) (void)hipEventDestroy(s.own.fwd_done);
+    if (s.own.dgrad_done) (void)hipEventDestroy(s.own.dgrad_done);
+    if (s.own.released) (void)hipEventDestroy(s.own.released);
   }
   for (hipStream_t s : st->streams) (void)hipStreamDestroy(s);
   for (hipEvent_t e : st->stream_tail) (void)hipEventDestroy(e);
   for (hipEvent_t e : st->chain_layer) if (e) (void)hipEventDestroy(e);
   for (hipEvent_t e : st->grads_final) if (e) (void)hipEventDestroy(e);
-  if (st->last_bwd) (void)hipEventDestroy(st->last_bwd);
+  if (st->embed_bwd) (void)hipEventDestroy(st->embed_bwd);
   if (st->fork_ev) (void)hipEventDestroy(st->fork_ev);
-  if (st->last_wgrad) (void)hipEventDestroy(st->last_wgrad);
   if (st->wgrad_tail) (void)hipEventDestroy(st->wgrad_tail);
   if (st->wgrad_stream) (void)hipStreamDestroy(st->wgrad_stream);
   for (std::vector<ActSet>* sets : {&st->fwd_sets, &st->regen_sets})
@@ -959,9 +965,9 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   st->max_merge = ac > 0 ? 1 : host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches);
   st->slots.resize(cfg->pipeline_limit);
   for (Slot& s : st->slots) {
-    CREATE_TRY(hipEventCreateWithFlags(&s.fwd_done, hipEventDisableTiming));
-    CREATE_TRY(hipEventCreateWithFlags(&s.dgrad_done, hipEventDisableTiming));
-    CREATE_TRY(hipEventCreateWithFlags(&s.released, hipEventDisableTiming));
+    CREATE_TRY(hipEventCreateWithFlags(&s.own.fwd_done, hipEventDisableTiming));
+    CREATE_TRY(hipEventCreateWithFlags(&s.own.dgrad_done, hipEventDisableTiming));
+    CREATE_TRY(hipEventCreateWithFlags(&s.own.released, hipEventDisableTiming));
     s.layers.assign(cfg->n_layers, LayerStash{});
   }
   // with checkpointing only the inputs of layers 0, ac, 2ac, ... are kept (Sec. 5.1)
@@ -1019,8 +1025,7 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
     st->delta = (float*)p; p += e_lse; st->ln_part = (float*)p; p += e_red;
     st->wgrad_red_ws = (float*)p; p += e_wred;
   }
-  CREATE_TRY(hipEventCreateWithFlags(&st->last_bwd, hipEventDisableTiming));
-  CREATE_TRY(hipEventCreateWithFlags(&st->last_wgrad, hipEventDisableTiming));
+  CREATE_TRY(hipEventCreateWithFlags(&st->embed_bwd, hipEventDisableTiming));
   CREATE_TRY(hipEventCreateWithFlags(&st->wgrad_tail, hipEventDisableTiming));
   CREATE_TRY(hipEventCreateWithFlags(&st->fork_ev, hipEventDisableTiming));
   st->chain_layer.assign(cfg->n_layers, nullptr);
@@ -1077,8 +1082,8 @@ int axonn_stage_zero_grad(axonn_stage_t* st, void* hip_stream) {
   if (st->in_flight) return fail(AXONN_ESTATE, "zero_grad: %d microbatches in flight", st->in_flight);
   HIP_TRY(hipSetDevice(st->cfg.device));
   hipStream_t s = (hipStream_t)hip_stream;
-  if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
-  if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
+  if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
+  if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   // no memory is touched: the first backward / weight-gradient pass of a batch overwrites the
   // accumulators.  Microbatches whose weight gradients were still pending are dropped.
   host::release_awaiting(st->slots);
@@ -1219,6 +1224,8 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     }
     wait.dispatched();
     const axonn_msg m = st->inbox[chosen].m;
+    const bool join_all = st->join_all;
+    st->join_all = true;                        // until the dispatch is through
     // a forward needs its slot before it is known which messages run with it
     if (m.kind == 0 && host::find_free(st->slots) < 0) AX_TRY(flush_wgrad(st, ws));
     int picked[host::kMaxMerge];
@@ -1251,7 +1258,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
         const int si = host::find_live(st->slots, w[0].mb_id);
         hipStream_t bs = st->streams[0];
         HIP_TRY(hipStreamWaitEvent(bs, st->slots[si + n - 1].fwd_done, 0));
-        if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(bs, st->last_bwd, 0));   // the head's buffers are shared
+        if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(bs, st->last_bwd, 0));   // the head's buffers are shared
         Work back[host::kMaxMerge];
         for (int i = 0; i < n; ++i) {
           Slot& slot = st->slots[si + i];
@@ -1271,6 +1278,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     // the result buffer is complete once this fires: what a neighbouring stage's message waits for
     if (m.done_event) HIP_TRY(hipEventRecord((hipEvent_t)m.done_event, s));
     if (n_dispatched) *n_dispatched += n;
+    st->join_all = join_all;
   }
   return AXONN_OK;
 }
@@ -1302,13 +1310,20 @@ int axonn_stage_set_message_wait(axonn_stage_t* st, double seconds) {
 int axonn_stage_join(axonn_stage_t* st, void* user_stream) {
   if (!st) return fail(AXONN_EINVAL, "join: null handle");
   HIP_TRY(hipSetDevice(st->cfg.device));
+  const hipStream_t user = (hipStream_t)user_stream;
+  if (st->in_flight == 0 && !st->join_all) {
+    // every forward has its backward, which waits for it: the last chain and the last weight-gradient pass are the ends
+    if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(user, st->last_bwd, 0));
+    if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(user, st->last_wgrad, 0));
+    return AXONN_OK;
+  }
   for (size_t i = 0; i < st->streams.size(); ++i) {
     HIP_TRY(hipEventRecord(st->stream_tail[i], st->streams[i]));
-    HIP_TRY(hipStreamWaitEvent((hipStream_t)user_stream, st->stream_tail[i], 0));
+    HIP_TRY(hipStreamWaitEvent(user, st->stream_tail[i], 0));
   }
   if (st->wgrad_stream) {
     HIP_TRY(hipEventRecord(st->wgrad_tail, st->wgrad_stream));
-    HIP_TRY(hipStreamWaitEvent((hipStream_t)user_stream, st->wgrad_tail, 0));
+    HIP_TRY(hipStreamWaitEvent(user, st->wgrad_tail, 0));
   }
   return AXONN_OK;
 }
@@ -1544,8 +1559,8 @@ int axonn_stage_optimizer_step(axonn_stage_t* st, double lr, double beta1, doubl
   if (st->in_flight) return fail(AXONN_ESTATE, "optimizer_step: %d microbatches in flight", st->in_flight);
   HIP_TRY(hipSetDevice(st->cfg.device));
   hipStream_t user = (hipStream_t)hip_stream;
-  if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(user, st->last_bwd, 0));
-  if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(user, st->last_wgrad, 0));
+  if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(user, st->last_bwd, 0));
+  if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(user, st->last_wgrad, 0));
   if (slots_in_state(st, SLOT_AWAIT_WGRAD))
     return fail(AXONN_ESTATE, "optimizer_step: %d microbatches still await their weight gradients (fewer than "
                 "n_microbatches backwards since zero_grad)", slots_in_state(st, SLOT_AWAIT_WGRAD));
@@ -1588,8 +1603,8 @@ int axonn_count_nonfinite(const void* x_dev, uint64_t n, uint64_t* workspace_dev
 // Orders `user` behind the batch's gradients, as the optimizer entry points do.
 static int wait_for_gradients(axonn_stage_t* st, hipStream_t user, const char* who) {
   if (st->in_flight) return fail(AXONN_ESTATE, "%s: %d microbatches in flight", who, st->in_flight);
-  if (st->last_bwd_recorded) HIP_TRY(hipStreamWaitEvent(user, st->last_bwd, 0));
-  if (st->last_wgrad_recorded) HIP_TRY(hipStreamWaitEvent(user, st->last_wgrad, 0));
+  if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(user, st->last_bwd, 0));
+  if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(user, st->last_wgrad, 0));
   if (slots_in_state(st, SLOT_AWAIT_WGRAD))
     return fail(AXONN_ESTATE, "%s: %d microbatches still await their weight gradients (fewer than "
                 "n_microbatches backwards since zero_grad)", who, slots_in_state(st, SLOT_AWAIT_WGRAD));
