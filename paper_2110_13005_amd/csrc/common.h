@@ -212,19 +212,24 @@ enum GemmEpilogue {
 // A_seg[s].  This is how a weight gradient is summed over several microbatches in one launch.
 constexpr int kMaxKSegments = 16;
 struct GemmArgs {
-  const elem_t* A_seg[kMaxKSegments];
-  const elem_t* B_seg[kMaxKSegments];
-  void* C;
-  const elem_t* bias; const elem_t* res; elem_t* aux;
-  int64_t lda, ldb, ldc, ld_res, ld_aux;
+  // what a kernel reads first lies in the first cache lines of its arguments, the segment pointers (one, but for weight
+  // gradients) behind
   int M, N, K;       // K = length of ONE segment
   int n_seg;
+  int tiles_m, tiles_n;
+  uint32_t walk_band, walk_last;   // reciprocals for the ring kernel's tile walk (ring_walk)
+  int64_t lda, ldb;
+  void* C;
+  const elem_t* bias; const elem_t* res; elem_t* aux;
+  int64_t ldc, ld_res, ld_aux;
   int accumulate;
   int rule_m;        // rows by which the kernel is chosen (0: M): one microbatch's where M is several of them, so that a
                      // microbatch's sums are added in the same order whether it runs alone or with others
   int concurrent;    // other kernels share the chip with this launch: prefer the most efficient tile shape
                      // over one whose tile count fills the CUs a whole number of times
-  int tiles_m, tiles_n;
+  uint32_t tiles_n_recip;          // reciprocal of tiles_n (ring kernel's column sums)
+  const elem_t* A_seg[kMaxKSegments];
+  const elem_t* B_seg[kMaxKSegments];
   // Weight gradients (both operands k-strided, accumulating epilogues) only: if colsum is not null, the sums
   // over k (all segments) of B's N columns are stored in colsum[0..N), or added to it if `accumulate`; colsum
   // has C's element type.  The large-problem kernels form them on the way; for the others colsum_ws must hold
@@ -239,8 +244,8 @@ struct GemmArgs {
 // Weight gradients of the same K and segments that may share a launch: a layer's four.
 constexpr int kMaxGroup = 4;
 struct GemmGroup {
+  int n, tiles;      // problems, and the tiles of all of them
   GemmArgs g[kMaxGroup];
-  int n;
 };
 // Workspace of that kind that the launcher can use for an M x N x K problem (0: it would not split it).
 int64_t gemm_split_ws_floats(int64_t M, int64_t N, int64_t K);

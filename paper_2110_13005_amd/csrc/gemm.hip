@@ -43,8 +43,8 @@ __device__ __forceinline__ void lds_barrier() {
 // the eight XCDs together work on few bands at a time (bands across the longer side -- 80 x 20 tiles, the
 // weight gradient of the second MLP matrix -- put a different band, with 8 panels of the wide operand, on
 // every XCD: 192 MB of panels in flight, beyond what the 256 MB last-level cache holds beside the rest).
-// A number of tiles that is no multiple of 8 is remapped only if ANY_COUNT.  The ring kernel, whose smaller tiles fetch
-// more per MFMA, needs it (230 tiles of 128 x 256, 640 x 11776 x 9632 input gradient: 174 -> 141 us); with tiles of 256 x 256
+// A number of tiles that is no multiple of 8 is remapped in the ring kernel only (ring_walk).  Its smaller tiles fetch
+// more per MFMA and need it (230 tiles of 128 x 256, 640 x 11776 x 9632 input gradient: 174 -> 141 us); with tiles of 256 x 256
 // it is as often 4 % slower (4624 x 10448 x 1440 with GeLU, 779 tiles: 194 -> 201 us) as faster.
 __device__ __forceinline__ void tile_at(int pid, int tiles_m, int tiles_n, int& tm, int& tn) {
   constexpr int BAND = 8;
@@ -57,13 +57,36 @@ __device__ __forceinline__ void tile_at(int pid, int tiles_m, int tiles_n, int& 
   tm = wide ? a : b;
   tn = wide ? b : a;
 }
-template <bool ANY_COUNT = false>
 __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm, int& tn) {
   int pid = blockIdx.x;
   const int nblk = gridDim.x;
-  if (ANY_COUNT) pid = (int)host::xcd_contiguous(blockIdx.x, gridDim.x);
-  else if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
+  if ((nblk & 7) == 0) pid = (pid & 7) * (nblk >> 3) + (pid >> 3);
   tile_at(pid, tiles_m, tiles_n, tm, tn);
+}
+// The same walk for the ring kernel, whose small problems feel the instructions in front of the first load: no division,
+// and the reciprocals come with the arguments (set_ring_walk).
+__device__ __forceinline__ void ring_walk(const GemmArgs& g, uint32_t pid, int& tm, int& tn) {
+  constexpr uint32_t BAND = 8;
+  const bool wide = g.tiles_m <= g.tiles_n;
+  const uint32_t t_band = wide ? g.tiles_m : g.tiles_n, t_walk = wide ? g.tiles_n : g.tiles_m;
+  const uint32_t band = host::recip_div(pid, BAND * t_walk, g.walk_band), in_band = pid - band * BAND * t_walk;
+  uint32_t b = in_band / BAND, a = in_band % BAND;
+  if (band * BAND + BAND > t_band) {                      // the last, narrower band
+    const uint32_t w = t_band - band * BAND;
+    b = host::recip_div(in_band, w, g.walk_last);
+    a = in_band - b * w;
+  }
+  a += band * BAND;
+  tm = (int)(wide ? a : b);
+  tn = (int)(wide ? b : a);
+}
+static void set_ring_walk(GemmArgs& g, int bm, int bn) {
+  g.tiles_m = (g.M + bm - 1) / bm;
+  g.tiles_n = (g.N + bn - 1) / bn;
+  const uint32_t t_band = std::min(g.tiles_m, g.tiles_n), t_walk = std::max(g.tiles_m, g.tiles_n);
+  g.walk_band = host::recip_of(8 * t_walk);
+  g.walk_last = host::recip_of(t_band % 8 ? t_band % 8 : 8);
+  g.tiles_n_recip = host::recip_of(g.tiles_n);
 }
 
 template <int ROWS, int BK, bool KC>
@@ -1109,6 +1132,9 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
 // Stage layout: a k-contiguous operand in blocks of 64 k, 128 bytes per row, chunk q of row r in slot q ^ ((r >> 1) & 7);
 // a k-strided one as k rows of ROWS elements, the 32-byte pieces of row k permuted by ring_swizzle(k), so that the
 // eight k rows that one transposing read touches (k0 .. k0+3 and k0+8 .. k0+11) fall into different banks.
+// A small problem feels everything in front of its first copy and behind its last MFMA: the tile comes without divisions, the
+// arguments in one round trip and the result's address before it is needed.  Single launches back to back, before / after, us:
+// 64 x 64 x 64 3.8 / 3.1, 400 x 1152 x 384 4.8 / 4.2, 256 x 256 x 1024 6.1 / 5.6, 1024 x 1024 x 1024 6.6 / 6.3 (an empty kernel 1.9).
 // 256 tiles of 128 x 128 take 0.47 us per 64-wide k-step (2048 x 2048 x 8192: 67 us, 1030 TFLOP/s); with the copies issued
 // behind the barrier instead of between the MFMAs it is the same, with one set of fragment registers 0.52.
 template <int ROWS>
@@ -1157,7 +1183,7 @@ __device__ __forceinline__ elemx8 ring_fragment(const char* base, int r0, int sl
 }
 
 // (tm, tn): the workgroup's tile of problem `g`.
-template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS>
+template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS, bool SPLIT>
 __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const int tn) {
   constexpr int BM = 32 * TM, BN = 32 * TN, BK = 64 * NSUB, W = 4 * KG, NT = 64 * W;
   constexpr int SA = BM * BK * 2, SB = BN * BK * 2, STAGE = SA + SB;
@@ -1192,10 +1218,11 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   const uint32_t sa = A_KC ? BK * 2u : BK * lda * 2u, sb = B_KC ? BK * 2u : BK * ldb * 2u;
   const uint32_t nra = (uint32_t)(A_KC ? g.M : g.K) * lda * 2u, nrb = (uint32_t)(B_KC ? g.N : g.K) * ldb * 2u;
   // a split launch (gridDim.y parts): part y multiplies its share of the k-tiles and leaves fp32 sums in g.split_ws
-  const int K = g.K, tps = (K + BK - 1) / BK, parts = gridDim.y, part = blockIdx.y;
-  const int k_first = (int)((int64_t)tps * g.n_seg * part / parts);
-  const int nk = (int)((int64_t)tps * g.n_seg * (part + 1) / parts) - k_first;
-  int ld_seg = k_first / tps, ld_kin = k_first % tps;  // segment and k-tile within it of the NEXT tile to fetch
+  const int K = g.K, n_seg = g.n_seg, tps = (K + BK - 1) / BK, parts = SPLIT ? gridDim.y : 1, part = SPLIT ? blockIdx.y : 0;
+  const int k_first = SPLIT ? (int)((int64_t)tps * n_seg * part / parts) : 0;
+  const int nk = SPLIT ? (int)((int64_t)tps * n_seg * (part + 1) / parts) - k_first : tps * n_seg;
+  // segment and k-tile within it of the NEXT tile to fetch
+  int ld_seg = SPLIT ? k_first / tps : 0, ld_kin = SPLIT ? k_first % tps : 0;
   u32x4 rsa = rsrc_words(g.A_seg[ld_seg], nra), rsb = rsrc_words(g.B_seg[ld_seg], nrb);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(AXONN_LDS char*)smem + (uint32_t)wave * 1024u;
 
@@ -1215,11 +1242,12 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   auto copy_done = [&]() {                             // on to the next k-tile
     if (++ld_kin == tps) {
       ld_kin = 0;
-      ++ld_seg;
-      const bool live = ld_seg < g.n_seg;
-      const int sidx = live ? ld_seg : 0;
-      rsa = rsrc_words(g.A_seg[sidx], live ? nra : 0u);
-      rsb = rsrc_words(g.B_seg[sidx], live ? nrb : 0u);
+      if (++ld_seg < n_seg) {
+        rsa = rsrc_words(g.A_seg[ld_seg], nra);
+        rsb = rsrc_words(g.B_seg[ld_seg], nrb);
+      } else {
+        rsa[2] = rsb[2] = 0u;                          // number of bytes: none
+      }
     }
   };
 
@@ -1229,6 +1257,10 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
     for (int c = 0; c < ND; ++c) copy(c, t * STAGE);
     copy_done();
   }
+  // the result's address and the like are fetched beside the first copies: behind the k loop they would be a cache miss in
+  // front of the first store
+  asm volatile("" : : "s"(g.C), "s"(g.ldc), "s"(g.accumulate));
+  if (EPI == EPI_BIAS_GELU) asm volatile("" : : "s"(g.aux));
 
   // bias and what the epilogue reads at this thread's output positions are fetched beside the k loop
   constexpr int NP = BM * BN / 4 / NT, CW = BN / 4;    // positions per thread (4 columns each), positions per row
@@ -1259,8 +1291,9 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   constexpr bool CS = epilogue_sums_columns(A_KC, B_KC, EPI);
-  const bool cs_on = CS && g.colsum != nullptr && wm == 0 &&              // the same for all lanes of a wave
-                     tm == (int)((int64_t)tn * g.tiles_m / g.tiles_n);
+  const bool cs_tile = CS && g.colsum != nullptr &&
+                       (uint32_t)tm == host::recip_div((uint32_t)tn * (uint32_t)g.tiles_m, g.tiles_n, g.tiles_n_recip);
+  const bool cs_on = cs_tile && wm == 0;               // the same for all lanes of a wave
   float cs[TN];
 #pragma unroll
   for (int j = 0; j < TN; ++j) cs[j] = 0.f;
@@ -1387,7 +1420,7 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
       epi_finish<EPI>(v, bv[NBV == 1 ? 0 : p], opnd[p], g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
     }
   }
-  if (CS && g.colsum != nullptr && tm == (int)((int64_t)tn * g.tiles_m / g.tiles_n) && tid < BN && n0 + tid < g.N) {
+  if (cs_tile && tid < BN && n0 + tid < g.N) {
     float v = sums[tid];
 #pragma unroll
     for (int q = 1; q < KG; ++q) v += sums[q * BN + tid];
@@ -1401,23 +1434,34 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   }
 }
 
-template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS>
+// Has what a ring kernel needs in front of its first copy fetched at once: left to their uses, the argument loads are
+// three cache misses one behind the other.
+__device__ __forceinline__ void fetch_args(const GemmArgs& g) {
+  asm volatile("" : : "s"(g.M), "s"(g.N), "s"(g.K), "s"(g.n_seg), "s"(g.tiles_m), "s"(g.tiles_n), "s"(g.walk_band), "s"(g.walk_last),
+               "s"(g.lda), "s"(g.ldb), "s"(g.A_seg[0]), "s"(g.B_seg[0]));
+}
+// SPLIT: gridDim.y workgroups share the k range of a tile.
+template <bool A_KC, bool B_KC, int EPI, int TM, int TN, int KG, int NSUB, int NS, bool SPLIT>
 __global__ __launch_bounds__(256 * KG) void gemm_ring_kernel(const GemmArgs g) {
+  fetch_args(g);
   int tm, tn;
-  tile_of_block<true>(g.tiles_m, g.tiles_n, tm, tn);
-  gemm_ring<A_KC, B_KC, EPI, TM, TN, KG, NSUB, NS>(g, tm, tn);
+  ring_walk(g, host::xcd_contiguous(blockIdx.x, (uint32_t)(g.tiles_m * g.tiles_n)), tm, tn);
+  gemm_ring<A_KC, B_KC, EPI, TM, TN, KG, NSUB, NS, SPLIT>(g, tm, tn);
 }
 // Weight gradients: the tiles of up to kMaxGroup problems, problem after problem, in one grid.
 template <int EPI, int TM, int TN, int KG, int NSUB, int NS>
 __global__ __launch_bounds__(256 * KG) void gemm_ring_group_kernel(const GemmGroup grp) {
-  int pos = (int)host::xcd_contiguous(blockIdx.x, gridDim.x), i = 0;
-  while (i + 1 < grp.n && pos >= grp.g[i].tiles_m * grp.g[i].tiles_n) {
-    pos -= grp.g[i].tiles_m * grp.g[i].tiles_n;
+  int i = 0;
+  uint32_t pos = host::xcd_contiguous(blockIdx.x, (uint32_t)grp.tiles), tiles = grp.g[0].tiles_m * grp.g[0].tiles_n;
+  while (i + 1 < grp.n && pos >= tiles) {
+    pos -= tiles;
     ++i;
+    tiles = grp.g[i].tiles_m * grp.g[i].tiles_n;
   }
+  fetch_args(grp.g[i]);
   int tm, tn;
-  tile_at(pos, grp.g[i].tiles_m, grp.g[i].tiles_n, tm, tn);
-  gemm_ring<false, false, EPI, TM, TN, KG, NSUB, NS>(grp.g[i], tm, tn);
+  ring_walk(grp.g[i], pos, tm, tn);
+  gemm_ring<false, false, EPI, TM, TN, KG, NSUB, NS, false>(grp.g[i], tm, tn);
 }
 
 // The sums of a split launch's parts, added in their order, through the epilogue: 4 columns per thread.
@@ -1542,14 +1586,12 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
 
 template <int TM, int TN, int KG, int NSUB, int NS>
 static hipError_t launch_ring_group(int epi, GemmGroup& grp, hipStream_t s) {
-  int tiles = 0;
+  grp.tiles = 0;
   for (int i = 0; i < grp.n; ++i) {
-    GemmArgs& g = grp.g[i];
-    g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
-    g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
-    tiles += g.tiles_m * g.tiles_n;
+    set_ring_walk(grp.g[i], 32 * TM, 32 * TN);
+    grp.tiles += grp.g[i].tiles_m * grp.g[i].tiles_n;
   }
-  const dim3 grid(tiles), block(256 * KG);
+  const dim3 grid(grp.tiles), block(256 * KG);
   if (epi == EPI_ACC_F32) hipLaunchKernelGGL((gemm_ring_group_kernel<EPI_ACC_F32, TM, TN, KG, NSUB, NS>), grid, block, 0, s, grp);
   else if (epi == EPI_ACC_BF16) hipLaunchKernelGGL((gemm_ring_group_kernel<EPI_ACC_BF16, TM, TN, KG, NSUB, NS>), grid, block, 0, s, grp);
   else return hipErrorInvalidValue;
@@ -1564,13 +1606,19 @@ static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s, int parts = 1)
     grp.g[0] = g;
     return launch_ring_group<TM, TN, KG, NSUB, NS>(epi, grp, s);
   } else {
-    g.tiles_m = (g.M + 32 * TM - 1) / (32 * TM);
-    g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
+    set_ring_walk(g, 32 * TM, 32 * TN);
     const dim3 grid(g.tiles_m * g.tiles_n, parts), block(256 * KG);
+    if constexpr (A_KC && B_KC) {
+      if (parts > 1) {
+        if (epi != EPI_BIAS) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, EPI_BIAS, TM, TN, KG, NSUB, NS, true>), grid, block, 0, s, g);
+        return hipGetLastError();
+      }
+    }
 #define AXONN_GEMM_CASE(E)                                                                      \
     case E:                                                                                       \
       if constexpr (epilogue_allowed(A_KC, B_KC, E)) {                                            \
-        hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, E, TM, TN, KG, NSUB, NS>), grid, block, 0, s, g); \
+        hipLaunchKernelGGL((gemm_ring_kernel<A_KC, B_KC, E, TM, TN, KG, NSUB, NS, false>), grid, block, 0, s, g); \
         break;                                                                                    \
       } else {                                                                                    \
         return hipErrorInvalidValue;                                                              \

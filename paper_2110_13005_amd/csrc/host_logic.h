@@ -290,6 +290,16 @@ constexpr uint32_t xcd_contiguous(uint32_t id, uint32_t n_workgroups) {
   return xcd * (n_workgroups / 8) + (xcd < left ? xcd : left) + id / 8;
 }
 
+// Division by a number the host knows: recip_of(d) for recip_div on the GPU, exact for 0 <= n < 2^31, 1 <= d < 2^31 (an estimate
+// that is at most one too large).  0 stands for d == 1, whose reciprocal does not fit.
+constexpr uint32_t recip_of(uint32_t d) { return d <= 1 ? 0u : (uint32_t)((uint64_t(1) << 32) / d + 1); }
+constexpr uint32_t recip_div(uint32_t n, uint32_t d, uint32_t recip) {
+  if (recip == 0) return n;
+  uint32_t q = (uint32_t)(((uint64_t)n * recip) >> 32);
+  if (q * d > n) --q;
+  return q;
+}
+
 // ------------------------------------------------------------------------------ tiles of the GEMM launcher
 // Tile of the ring kernel for a problem that 256 x 256 tiles would not fill the chip with.
 enum RingTile { RING_64x64, RING_128x64, RING_128x128, RING_128x192, RING_128x256, RING_TILES };
