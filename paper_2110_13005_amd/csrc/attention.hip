@@ -366,40 +366,22 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 
 // ============================================================================ backward
 // delta[b][a][i] = sum_d dO[i][d] * O[i][d]
-// Launched in front of the general kernels and of the one-launch backward; the exact-size dQ kernel in a launch of its own
-// forms delta itself.  For the exact head dimensions: D / 8 lanes per (row, head), 8 elements each, added in the order of
-// that dQ kernel, so that a gradient does not depend on which of the two forms it.
-__device__ __forceinline__ float delta_of_8(elemx8 ov, elemx8 dv) {
-  float p = 0.f;
+// p + the products of 4 elements, one after the other.
+template <class V>
+__device__ __forceinline__ float delta_add4(float p, V ov, V dv, int first) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    float x = (float)ov[e];
+  for (int e = 0; e < 4; ++e) {
+    float x = (float)ov[first + e];
 #ifdef AXONN_ELEM_FP16
-    asm("" : "+v"(x));   // else one of the two kernels gets two-element dot products, whose sums are rounded differently
+    asm("" : "+v"(x));   // else one of the kernels gets two-element dot products, whose sums are rounded differently
 #endif
-    p = fmaf(x, (float)dv[e], p);
+    p = fmaf(x, (float)dv[first + e], p);
   }
   return p;
 }
-template <int D>
-__global__ __launch_bounds__(256) void attn_delta_kernel(int64_t n_pairs, int s, int a, const elem_t* __restrict__ o,
-                                                         const elem_t* __restrict__ dout, float* __restrict__ delta) {
-  constexpr int LPR = D / 8;
-  const int64_t pair = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;   // (row, head)
-  const int j = threadIdx.x % LPR;
-  float p = 0.f;
-  if (pair < n_pairs)                                                             // rows are a * D long
-    p = delta_of_8(*reinterpret_cast<const elemx8*>(o + pair * D + 8 * j), *reinterpret_cast<const elemx8*>(dout + pair * D + 8 * j));
-#pragma unroll
-  for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
-  if (pair < n_pairs && j == 0) {
-    const int64_t row = pair / a;
-    const int hd = (int)(pair % a);
-    const int64_t bi = row / s, i = row % s;
-    delta[(bi * a + hd) * s + i] = p;
-  }
-}
 // For any head dimension d that is a multiple of 4: 16 lanes per (row, head), 4 elements per lane and step.
+// (Launched in front of the general kernels and of the one-launch backward of either kind; the exact-size dQ kernel in a
+// launch of its own forms delta itself.)
 __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs, int s, int a, int d,
                                                                  const elem_t* __restrict__ o,
                                                                  const elem_t* __restrict__ dout,
@@ -411,10 +393,7 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
     const elem_t* op = o + pair * d;          // rows are a * d long: pair * d = row * a * d + head * d
     const elem_t* dp = dout + pair * d;
     for (int c = 4 * j; c < d; c += 64) {
-      const elemx4 ov = *reinterpret_cast<const elemx4*>(op + c);
-      const elemx4 dv = *reinterpret_cast<const elemx4*>(dp + c);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) p += (float)ov[e] * (float)dv[e];
+      p = delta_add4(p, *reinterpret_cast<const elemx4*>(op + c), *reinterpret_cast<const elemx4*>(dp + c), 0);
     }
   }
 #pragma unroll
@@ -775,12 +754,13 @@ struct DqLds {
   __align__(16) elem_t tiles[2 * BKV * LDK];          // K and V tile; at the ends the staged Q, dO and dQ rows
   float delta[128];
 };
-// FORM_DELTA: delta is formed here, kept, and written out for a dK / dV launch behind this one; else it is read.
+// FORM_DELTA: delta is formed here, kept, and written out for a dK / dV launch behind this one; else it is read.  by_4: its
+// sums in the order of the launch of its own, for sequences that take that launch when they do not run with others.
 template <int D, bool EXACT, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dq(
     DqLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ o, const elem_t* __restrict__ dout, const float* __restrict__ lse, float* delta,
-    elem_t* __restrict__ dqkv) {
+    elem_t* __restrict__ dqkv, int by_4) {
   static_assert(EXACT || !FORM_DELTA, "the general kernels read delta");
   constexpr int BKV = DqLds<D>::BKV, LDK = DqLds<D>::LDK, DT = D / 32, KK = D / 16;
   elem_t* const smem = lds.tiles;
@@ -825,9 +805,28 @@ __device__ __forceinline__ void attn_bwd_dq(
     r_do.template store<D + 8>(smem, tid);
 #pragma unroll
     for (int j = 0; FORM_DELTA && j < Rows::NCH; ++j) {
-      float p = delta_of_8(__builtin_bit_cast(elemx8, r_o.r[j]), __builtin_bit_cast(elemx8, r_do.r[j]));
+      const elemx8 ov = __builtin_bit_cast(elemx8, r_o.r[j]), dv = __builtin_bit_cast(elemx8, r_do.r[j]);
+      float p;
+      if (by_4) {
+        // the launch of its own's order: 4 elements of every 64 per lane, here in pairs of such lanes; at D = 128 the lanes
+        // of the upper half go on from the sums of the lower half's
+        float lo = delta_add4(0.f, ov, dv, 0), hi = delta_add4(0.f, ov, dv, 4);
+        if (LPR == 16) {
+          const float lo0 = __shfl_xor(lo, 8, 64), hi0 = __shfl_xor(hi, 8, 64);
+          lo = delta_add4(lo0, ov, dv, 0);               // of the upper half's lanes; the lower half's are not used
+          hi = delta_add4(hi0, ov, dv, 4);
+        }
 #pragma unroll
-      for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
+        for (int off = 4; off > 0; off >>= 1) { lo += __shfl_xor(lo, off, 64); hi += __shfl_xor(hi, off, 64); }
+        p = lo + hi;
+        if (LPR == 16) p = __shfl_xor(p, 8, 64);         // to the lane that keeps it
+      } else {
+        p = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) p += (float)ov[e] * (float)dv[e];
+#pragma unroll
+        for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
+      }
       const int row = tid / LPR + j * RSTEP;
       if (tid % LPR == 0) {
         s_delta[row] = p;
@@ -943,9 +942,9 @@ template <int D, bool EXACT>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
-    elem_t* __restrict__ dqkv) {
+    elem_t* __restrict__ dqkv, int by_4) {
   __shared__ DqLds<D> lds;
-  attn_bwd_dq<D, EXACT, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv);
+  attn_bwd_dq<D, EXACT, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv, by_4);
 }
 // Both at once, for problems whose tiles do not fill the chip: the first half of the workgroups forms dK and dV, the second
 // dQ; delta is there already.  Each half alone is a chain of up to s / 128 (s / 64) tiles per workgroup on a part of the
@@ -957,7 +956,7 @@ __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
   __shared__ union { DkdvLds<D> dkdv; DqLds<D> dq; } lds;
   const int n = gridDim.x >> 1, id = blockIdx.x;
   if (id < n) attn_bwd_dkdv<D, EXACT>(lds.dkdv, id, n, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
-  else attn_bwd_dq<D, EXACT, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv);
+  else attn_bwd_dq<D, EXACT, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
 }
 
 // ------------------------------------------------------------------------- launchers
@@ -993,32 +992,26 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
 
 hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, const void* o,
                                 const float* lse, const void* dout, void* dqkv, float* delta,
-                                hipStream_t st) {
+                                hipStream_t st, int rule_b) {
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
-  // the exact-size dQ kernel (the dispatch's condition for it) forms delta itself and runs first
-  const bool exact = (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
-  const bool dq_forms_delta = !both && exact;
+  // the exact-size dQ kernel (the dispatch's condition for it) forms delta itself and runs first; sequences that run together
+  // get the sums in the order that rule_b of them have
+  const bool dq_forms_delta = !both && (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
+  const int by_4 = ((s + 127) / 128) * (rule_b > 0 ? rule_b : b) * a <= kBothMaxTiles;
   hipError_t e;
   dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
-    AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
+    AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, by_4);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
     return hipGetLastError();
   }
   const int64_t n_pairs = (int64_t)b * s * a;
-  if (exact && d == 64)
-    hipLaunchKernelGGL(attn_delta_kernel<64>, dim3((unsigned)((n_pairs + 31) / 32)), dim3(256), 0, st, n_pairs, s, a,
-                       (const elem_t*)o, (const elem_t*)dout, delta);
-  else if (exact)
-    hipLaunchKernelGGL(attn_delta_kernel<128>, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a,
-                       (const elem_t*)o, (const elem_t*)dout, delta);
-  else
-    hipLaunchKernelGGL(attn_delta_general_kernel, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a, d,
-                       (const elem_t*)o, (const elem_t*)dout, delta);
+  hipLaunchKernelGGL(attn_delta_general_kernel, dim3((unsigned)((n_pairs + 15) / 16)), dim3(256), 0, st, n_pairs, s, a, d,
+                     (const elem_t*)o, (const elem_t*)dout, delta);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (both) {
@@ -1029,7 +1022,7 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
+  AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, 0);
   return hipGetLastError();
 }
 #undef AXONN_ATTN_DISPATCH

@@ -167,18 +167,15 @@ __device__ __forceinline__ elem_t f2bf(float v) { return (elem_t)v; }
 // Stegun 7.1.26, absolute error <= 1.5e-7, i.e. one fp32 ulp of values near 1); Phi takes erfc(|x|/sqrt2)
 // on the side of the tail, so there is no cancellation for negative x.  `e` returns exp(-x^2/2), which
 // the derivative needs as well.
-// The fused multiply-adds are written out and no others formed: a result must not depend on the kernel (the tile) that the
-// compiler made the choice in.
 __device__ __forceinline__ float normal_cdf_f(float x, float& e) {
-#pragma clang fp contract(off)
   const float z = fabsf(x) * 0.70710678118654752440f;
-  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f, z, 1.0f));   // v_rcp_f32 (1 ulp), not the 10-instruction IEEE division
+  const float t = __builtin_amdgcn_rcpf(1.0f + 0.3275911f * z);   // v_rcp_f32 (1 ulp), not the 10-instruction IEEE division
   e = __expf(-z * z);
   float p = 1.061405429f;
-  p = __builtin_fmaf(p, t, -1.453152027f);
-  p = __builtin_fmaf(p, t, 1.421413741f);
-  p = __builtin_fmaf(p, t, -0.284496736f);
-  p = __builtin_fmaf(p, t, 0.254829592f);
+  p = p * t - 1.453152027f;
+  p = p * t + 1.421413741f;
+  p = p * t - 0.284496736f;
+  p = p * t + 0.254829592f;
   const float half_erfc = 0.5f * p * t * e;
   return x >= 0.f ? 1.0f - half_erfc : half_erfc;
 }
@@ -189,15 +186,14 @@ __device__ __forceinline__ float gelu_f(float x) {
 __device__ __forceinline__ float gelu_grad_f(float x) {
   float e;
   const float cdf = normal_cdf_f(x, e);
-  return __builtin_fmaf(x * e, 0.39894228040143267794f, cdf);
+  return cdf + x * e * 0.39894228040143267794f;
 }
 // GeLU(x) and GeLU'(x) together (they share Phi and the exponential).
 __device__ __forceinline__ void gelu_with_grad_f(float x, float& y, float& dy) {
-#pragma clang fp contract(off)
   float e;
   const float cdf = normal_cdf_f(x, e);
   y = x * cdf;
-  dy = __builtin_fmaf(x * e, 0.39894228040143267794f, cdf);
+  dy = cdf + x * e * 0.39894228040143267794f;
 }
 #endif  // __HIPCC__
 
@@ -227,6 +223,7 @@ struct GemmArgs {
                      // microbatch's sums are added in the same order whether it runs alone or with others
   int concurrent;    // other kernels share the chip with this launch: prefer the most efficient tile shape
                      // over one whose tile count fills the CUs a whole number of times
+  int halves_128;    // ring kernel with 64-wide stages: k in the order of the kernels with 128-wide ones (0: in its own)
   uint32_t tiles_n_recip;          // reciprocal of tiles_n (ring kernel's column sums)
   const elem_t* A_seg[kMaxKSegments];
   const elem_t* B_seg[kMaxKSegments];
@@ -295,7 +292,7 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
                                 float* lse, hipStream_t st);
 hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, const void* o,
                                 const float* lse, const void* dout, void* dqkv, float* delta,
-                                hipStream_t st);
+                                hipStream_t st, int rule_b = 0);
 hipError_t launch_embed_fwd(int T, int h, int s, int vocab, const int* tokens, const void* wte, const void* wpe,
                             void* x, hipStream_t st);
 hipError_t launch_embed_bwd(int b, int s, int h, int vocab, const int* tokens, const void* dx, void* dwte,

@@ -1118,9 +1118,12 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
 
 // ---------------------------------------------------------------------------------------------
 // Ring kernel: problems that do not fill the chip with 256 x 256 tiles.  32*TM x 32*TN block tile, KG groups of 2 x 2
-// waves that share the k range of every stage (group j takes every KG-th of the stage's 32-wide k slices, the same ones
-// whatever the tile and the stage: a result does not depend on the tile), so that a small tile still puts two waves on
-// every SIMD without more LDS reads per MFMA; the groups' results are added through LDS at the end.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
+// waves that share the k range of every stage (group j takes its share of the stage's 32-wide k slices), so that a
+// small tile still puts two waves on every SIMD without more LDS reads per MFMA; the groups' results are added
+// through LDS at the end.  A stage of 128 k gives each group 64 of them in a row, one of 64 k gives it 32.  With g.halves_128
+// the 64-wide stages come in pairs that hold a block of 128 k, k 0..31 and 64..95 first, so that each group adds the same k in
+// the same order as with 128-wide stages: a large tile then gives the bits of a small one.  A k-contiguous operand is then
+// copied in half cache lines: 8192 x 1024 input gradients over 1024, 3072 and 4096 k 68 us on average, in the own order 61.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
 // the traffic into and out of LDS (32 KB copied in, 64 KB of fragments read per 512 MFMA clocks).
 //   * Tiles are copied into LDS by the memory pipeline, into a ring of NS stages of 64*NSUB k each: NS - 1 stages are
 //     in flight or being read, so a short k range is fetched in one memory latency, and a long one has two or three
@@ -1143,17 +1146,20 @@ __device__ __forceinline__ int ring_swizzle(int k) {
 }
 // Copy instruction i of a stage of one operand: what lane `lane` fetches.  k: its k within the stage; returns the
 // lane's byte offset from the segment base in k-tile 0, or kOutOfRange outside the matrix.
+// `apart`: by how much the second half of the stage's 64 k lies further on than the first's end (g.halves_128).
 template <bool KC, int ROWS>
-__device__ __forceinline__ uint32_t ring_source(int i, int lane, int row0, int rows, uint32_t ld, int& k) {
+__device__ __forceinline__ uint32_t ring_source(int i, int lane, int row0, int rows, uint32_t ld, int apart, int& k) {
   if (KC) {
     const int sub = i / (ROWS / 8), r = (i % (ROWS / 8)) * 8 + (lane >> 3);
     k = sub * 64 + (((lane & 7) ^ ((r >> 1) & 7)) << 3);
+    k += k & 32 ? apart : 0;
     return row0 + r < rows ? ((uint32_t)(row0 + r) * ld + k) * 2u : kOutOfRange;
   }
   constexpr int CPR = ROWS / 8;                        // chunks per k row
   const int chunk = i * 64 + lane;
   k = chunk / CPR;
   const int s = chunk % CPR, ch = (((s >> 1) ^ ring_swizzle<ROWS>(k)) << 1) | (s & 1);
+  k += k & 32 ? apart : 0;
   return row0 + ch * 8 < rows ? ((uint32_t)k * ld + row0 + ch * 8) * 2u : kOutOfRange;
 }
 // k-strided operands: consecutive copy instructions of one of `waves` waves fetch the same columns this many k further
@@ -1209,20 +1215,25 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   // one source offset and k per copy instruction, or one for all of them
   constexpr int STEP_A = ring_k_step<A_KC, BM>(W), STEP_B = ring_k_step<B_KC, BN>(W);
   constexpr int NVA = STEP_A ? 1 : NDA, NVB = STEP_B ? 1 : NDB;
+  // a stage's first k: BK * its number, or 128 * (number / 2) + 32 * (number % 2) where the halves of 128 k are dealt
+  const int apart = NSUB == 1 && g.halves_128 ? 32 : 0;
+  const auto stage_k = [=](int n) { return BK * n - (NSUB == 1 ? (n & 1) * apart : 0); };
+  [[maybe_unused]] const auto step_k = [=](int c, int step) { return c * step + ((c * step) & 32 ? apart : 0); };
   uint32_t va[NVA], vb[NVB];
   int ka[NVA], kb[NVB];
 #pragma unroll
-  for (int c = 0; c < NVA; ++c) va[c] = ring_source<A_KC, BM>(c * W + wave, lane, m0, g.M, lda, ka[c]);
+  for (int c = 0; c < NVA; ++c) va[c] = ring_source<A_KC, BM>(c * W + wave, lane, m0, g.M, lda, apart, ka[c]);
 #pragma unroll
-  for (int c = 0; c < NVB; ++c) vb[c] = ring_source<B_KC, BN>(c * W + wave, lane, n0, g.N, ldb, kb[c]);
-  const uint32_t sa = A_KC ? BK * 2u : BK * lda * 2u, sb = B_KC ? BK * 2u : BK * ldb * 2u;
+  for (int c = 0; c < NVB; ++c) vb[c] = ring_source<B_KC, BN>(c * W + wave, lane, n0, g.N, ldb, apart, kb[c]);
+  const uint32_t sa = A_KC ? 2u : lda * 2u, sb = B_KC ? 2u : ldb * 2u;   // bytes from one k to the next
   const uint32_t nra = (uint32_t)(A_KC ? g.M : g.K) * lda * 2u, nrb = (uint32_t)(B_KC ? g.N : g.K) * ldb * 2u;
   // a split launch (gridDim.y parts): part y multiplies its share of the k-tiles and leaves fp32 sums in g.split_ws
-  const int K = g.K, n_seg = g.n_seg, tps = (K + BK - 1) / BK, parts = SPLIT ? gridDim.y : 1, part = SPLIT ? blockIdx.y : 0;
+  const int K = g.K, n_seg = g.n_seg, tps = apart ? (K + 127) / 128 * 2 : (K + BK - 1) / BK, parts = SPLIT ? gridDim.y : 1, part = SPLIT ? blockIdx.y : 0;
   const int k_first = SPLIT ? (int)((int64_t)tps * n_seg * part / parts) : 0;
   const int nk = SPLIT ? (int)((int64_t)tps * n_seg * (part + 1) / parts) - k_first : tps * n_seg;
   // segment and k-tile within it of the NEXT tile to fetch
   int ld_seg = SPLIT ? k_first / tps : 0, ld_kin = SPLIT ? k_first % tps : 0;
+  int ld_k = stage_k(ld_kin);                          // and that tile's first k
   u32x4 rsa = rsrc_words(g.A_seg[ld_seg], nra), rsb = rsrc_words(g.B_seg[ld_seg], nrb);
   const uint32_t lds0 = (uint32_t)(uintptr_t)(AXONN_LDS char*)smem + (uint32_t)wave * 1024u;
 
@@ -1230,13 +1241,11 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   // tiles beyond the last one read zeros.
   auto copy = [&](int c, uint32_t at) {
     if (c < NDA) {
-      const int v = c < NVA ? c : 0;
-      dma_chunk16(rsa, ld_kin * BK + c * STEP_A + ka[v] < K ? va[v] : kOutOfRange,
-                  (uint32_t)ld_kin * sa + c * STEP_A * lda * 2u, lds0 + at + c * (W * 1024));
+      const int v = c < NVA ? c : 0, k = ld_k + step_k(c, STEP_A);
+      dma_chunk16(rsa, k + ka[v] < K ? va[v] : kOutOfRange, (uint32_t)k * sa, lds0 + at + c * (W * 1024));
     } else {
-      const int d = c - NDA, v = d < NVB ? d : 0;
-      dma_chunk16(rsb, ld_kin * BK + d * STEP_B + kb[v] < K ? vb[v] : kOutOfRange,
-                  (uint32_t)ld_kin * sb + d * STEP_B * ldb * 2u, lds0 + at + SA + d * (W * 1024));
+      const int d = c - NDA, v = d < NVB ? d : 0, k = ld_k + step_k(d, STEP_B);
+      dma_chunk16(rsb, k + kb[v] < K ? vb[v] : kOutOfRange, (uint32_t)k * sb, lds0 + at + SA + d * (W * 1024));
     }
   };
   auto copy_done = [&]() {                             // on to the next k-tile
@@ -1249,6 +1258,7 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
         rsa[2] = rsb[2] = 0u;                          // number of bytes: none
       }
     }
+    ld_k = stage_k(ld_kin);
   };
 
 #pragma unroll
@@ -1310,10 +1320,10 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
     for (int s = 0; s < SLICES; ++s) {
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, s * KG + grp, lane);
+        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, grp * SLICES + s, lane);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
-        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, s * KG + grp, lane);
+        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, grp * SLICES + s, lane);
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -1726,8 +1736,14 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
       }
     }
   }
-  int tile = aligned16(g) ? host::choose_ring_tile(rule_m, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) : -1;
-  if (tile >= 0 && rule_m != g.M) tile = host::fastest_ring_tile(g.M, g.N, nk);
+  const int tile = aligned16(g) ? host::choose_ring_tile(rule_m, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) : -1;
+  if (tile >= 0 && rule_m != g.M) {
+    GemmArgs several = g;
+    const int64_t M[1] = {g.M}, N[1] = {g.N};
+    const host::RingChoice r = host::same_order_tile(1, M, N, nk, &tile);
+    several.halves_128 = r.halves_128[0];
+    return launch_ring_tile<A_KC, B_KC>(r.tile, epi, several, s, 1);
+  }
   if (tile >= 0) return launch_ring_tile<A_KC, B_KC>(tile, epi, g, s, 1);
   switch (choose_tn(g.M, g.N, nk, g.concurrent != 0)) {
     case 5: return launch_big<A_KC, B_KC, 5>(epi, g, s);
@@ -1743,19 +1759,23 @@ static hipError_t launch_layout(int epi, const GemmArgs& g, hipStream_t s) {
 // two streams 4.00 / 4.15.
 hipError_t launch_wgrad_group(int epi, GemmGroup& grp, hipStream_t s) {
   int64_t M[kMaxGroup], N[kMaxGroup];
+  int own[kMaxGroup];
   bool ring = grp.n >= 1 && grp.n <= kMaxGroup;
+  const int64_t nk = (int64_t)((grp.g[0].K + 63) / 64) * grp.g[0].n_seg;
   for (int i = 0; ring && i < grp.n; ++i) {
     const GemmArgs& g = grp.g[i];
-    const int64_t nk = (int64_t)((g.K + 63) / 64) * g.n_seg;
     M[i] = g.M;
     N[i] = g.N;
+    own[i] = host::choose_ring_tile(g.M, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32);
     ring = g.K == grp.g[0].K && g.n_seg == grp.g[0].n_seg && fits_32bit_offsets(g.K, g.lda) && fits_32bit_offsets(g.K, g.ldb) &&
-           aligned16(g) && host::choose_ring_tile(g.M, g.N, nk, big_tile_threshold(), epi == EPI_ACC_F32) >= 0;
+           aligned16(g) && own[i] >= 0;
   }
   if (ring) {
-    const int64_t nk = (int64_t)((grp.g[0].K + 63) / 64) * grp.g[0].n_seg;
-    const host::GroupTile r = host::choose_group_tile(grp.n, M, N, nk);
-    if (r.tiles <= 256 || !grp.g[0].concurrent) return launch_ring_group_tile(r.tile, epi, grp, s);
+    const host::RingChoice r = host::same_order_tile(grp.n, M, N, nk, own);
+    if (r.tiles <= 256 || !grp.g[0].concurrent) {
+      for (int i = 0; i < grp.n; ++i) grp.g[i].halves_128 = r.halves_128[i];
+      return launch_ring_group_tile(r.tile, epi, grp, s);
+    }
   }
   for (int i = 0; i < grp.n; ++i) {
     const hipError_t e = launch_layout<false, false>(epi, grp.g[i], s);

@@ -356,19 +356,27 @@ inline int choose_ring_tile(int64_t M, int64_t N, int64_t nk, int64_t forced, bo
   return best;
 }
 
-// The tile for n weight gradients whose tiles share one grid (modelled like one problem of all their tiles), and how many
-// of them there are.
-struct GroupTile { int tile; int64_t tiles; };
-inline GroupTile choose_group_tile(int n, const int64_t* M, const int64_t* N, int64_t nk) {
-  GroupTile best = {-1, 0};
+// The 64 x 64 and 128 x 64 tiles have stages of 128 k and add it in another order than the others do by themselves.
+constexpr bool adds_halves_of_128(int tile) { return tile == RING_64x64 || tile == RING_128x64; }
+
+// The fastest tile for n problems whose tiles share one grid (modelled like one problem of all their tiles), such that each
+// problem's sums are added in the order of own[i], the tile it takes by itself: halves_128[i] asks a kernel with 64-wide stages
+// for the other order; one with 128-wide stages has only its own.
+struct RingChoice { int tile; int64_t tiles; bool halves_128[4]; };
+inline RingChoice same_order_tile(int n, const int64_t* M, const int64_t* N, int64_t nk, const int* own) {
+  RingChoice best = {-1, 0, {}};
   double best_cost = 0;
+  bool all_halves = true;
+  for (int i = 0; i < n; ++i) all_halves = all_halves && adds_halves_of_128(own[i]);
   for (int t = 0; t < RING_TILES; ++t) {
+    if (adds_halves_of_128(t) && !all_halves) continue;
     const TileCost& c = kRingCost[t];
     int64_t tiles = 0;
     for (int i = 0; i < n; ++i) tiles += ((M[i] + c.bm - 1) / c.bm) * ((N[i] + c.bn - 1) / c.bn);
     const double cost = tile_cost({1, 1, c.fixed, c.step_few, c.step_full}, tiles, 1, nk);
-    if (best.tile < 0 || cost < best_cost) { best = {t, tiles}; best_cost = cost; }
+    if (best.tile < 0 || cost < best_cost) { best.tile = t; best.tiles = tiles; best_cost = cost; }
   }
+  for (int i = 0; i < n; ++i) best.halves_128[i] = adds_halves_of_128(own[i]) && !adds_halves_of_128(best.tile);
   return best;
 }
 

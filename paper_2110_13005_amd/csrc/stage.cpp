@@ -307,9 +307,9 @@ int attn_fwd(int b, int sq, int a, int d, const void* qkv, void* o, float* lse, 
   return check_launch(launch_attention_fwd(b, sq, a, d, qkv, o, lse, s), "attention_fwd");
 }
 int attn_bwd(int b, int sq, int a, int d, const void* qkv, const void* o, const float* lse, const void* dout,
-             void* dqkv, float* delta, hipStream_t s) {
+             void* dqkv, float* delta, hipStream_t s, int rule_b = 0) {
   ProfScope ps(PC_ATTN_BWD, s);
-  return check_launch(launch_attention_bwd(b, sq, a, d, qkv, o, lse, dout, dqkv, delta, s), "attention_bwd");
+  return check_launch(launch_attention_bwd(b, sq, a, d, qkv, o, lse, dout, dqkv, delta, s, rule_b), "attention_bwd");
 }
 int adam(uint64_t n, float* th, float* m, float* v, const void* g16, void* p16, double lr, double b1, double b2,
          double eps, double wd, int64_t step, double gs, hipStream_t s) {
@@ -414,7 +414,7 @@ int backward_layer(axonn_stage* st, int l, const LayerStash& a, int n, elem_t* d
               nullptr, nullptr, 0, nullptr, 0, 0, s, rule_m));
   // attention
   AX_TRY(attn_bwd(n * st->cfg.microbatch_size, st->cfg.seq_len, st->cfg.n_heads, st->d, a.qkv, a.o, a.lse, dattn,
-                  a.dqkv, delta, s));
+                  a.dqkv, delta, s, st->cfg.microbatch_size));
   // qkv = u Wqkv + b
   AX_TRY(gemm(true, true, EPI_BIAS, T, h, 3 * h, a.dqkv, 3 * h, param_ptr(st, l, P_WQKV), 3 * h, du, h,
               nullptr, nullptr, 0, nullptr, 0, 0, s, rule_m));

@@ -341,10 +341,22 @@ void test_gemm_tiles() {
   // the ring kernel where a round of its tiles covers the problem: 28.5 us against 35.6, 137 against 226
   CHECK(choose_ring_tile(2048, 4096, 16, -1, false) == RING_128x256 && choose_ring_tile(2048, 3072, 192, -1, false) >= 0);
   CHECK(choose_ring_tile(256, 256, 16, -1, false) == RING_64x64);
-  // a group's tile covers all its problems; a group of one takes the tile of the problem alone
+  // division by reciprocal
+  for (uint32_t d : {1u, 2u, 3u, 7u, 8u, 24u, 1000u, 65535u, 65536u, 1u << 30, (1u << 31) - 1})
+    for (uint32_t n : {0u, 1u, d - 1, d, d + 1, 3 * d - 1, 12345u, (1u << 31) - 1})
+      if (n < 1u << 31) CHECK(recip_div(n, d, recip_of(d)) == n / d);
+  // a shared grid keeps the order of sums that each problem has by itself
   const int64_t gm[4] = {1000, 384, 384, 384}, gn[4] = {384, 1000, 384, 1152};
-  const GroupTile grp = choose_group_tile(4, gm, gn, 21);
-  CHECK(grp.tiles > 0 && grp.tiles <= 256 && choose_group_tile(1, gm, gn, 21).tile == fastest_ring_tile(1000, 384, 21));
+  for (int mask = 0; mask < 16; ++mask) {
+    int own[4];
+    for (int i = 0; i < 4; ++i) own[i] = mask >> i & 1 ? RING_128x128 : RING_64x64;
+    const RingChoice r = same_order_tile(4, gm, gn, 21, own);
+    CHECK(r.tile >= 0 && r.tiles > 0 && (mask == 0 || !adds_halves_of_128(r.tile)));
+    for (int i = 0; i < 4; ++i)
+      CHECK(adds_halves_of_128(own[i]) == (adds_halves_of_128(r.tile) || r.halves_128[i]));
+  }
+  const int alone = RING_64x64;
+  CHECK(same_order_tile(1, gm, gn, 21, &alone).tile == fastest_ring_tile(1000, 384, 21));
   // a split is bounded (16 parts of 16 k-steps at least) and none where the problem fills the chip
   std::mt19937 rng(3);
   for (int rep = 0; rep < 2000; ++rep) {

@@ -206,10 +206,11 @@ def test_message_driven_run_matches_oracle_and_respects_pipeline_limit(n_streams
     (StageShape(2, 256, 4, 128, 2, 5), 5, dict(wgrad_group=3)),            # up to 5 microbatches in one pass
     (StageShape(2, 384, 3, 200, 2, 4, 1000), 3, dict(grad_accum_fp32=0)),  # ragged tiles, passes of 2 and 1
     (StageShape(1, 376, 2, 72, 1, 9), 9, dict(grad_accum_fp32=0, wgrad_group=1)),   # masked head dimension, 5 and 4
-    (StageShape(1, 1024, 8, 1024, 1, 3), 3, dict()),                       # separate attention backward kernels from 2 on
+    (StageShape(1, 1024, 8, 1024, 1, 3), 3, dict()),                       # separate attention backward kernels from 3 on, d 128
+    (StageShape(1, 1024, 16, 1000, 1, 2), 2, dict()),                      # from 2 on, d 64, ragged
     (StageShape(1, 1024, 16, 512, 2, 4), 2, dict(qkv_input_split=2)),      # backwards past the forwards between them
     (StageShape(2, 256, 4, 64, 1, 4, 264), 4, dict()),                     # the narrowest MLP: its activations just hold the gradients
-], ids=["tiny5", "ragged", "headdim188", "attn_tiles", "limit2", "narrow_mlp"])
+], ids=["tiny5", "ragged", "headdim188", "attn_tiles128", "attn_tiles64", "limit2", "narrow_mlp"])
 @pytest.mark.parametrize("n_streams", [1, 2])
 def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, opts, n_streams):
     """Messages that run as one pass over all their tokens: every y and dx bit for bit that of direct calls; with a
