@@ -1123,8 +1123,9 @@ __global__ __launch_bounds__(256) void gemm_dma_kernel(const GemmArgs g) {
 // through LDS at the end.  A stage of 128 k gives each group 64 of them in a row, one of 64 k gives it 32.  With g.halves_128
 // the 64-wide stages come in pairs that hold a block of 128 k, k 0..31 and 64..95 first, so that each group adds the same k in
 // the same order as with 128-wide stages: a large tile then gives the bits of a small one.  A k-contiguous operand is then
-// copied in half cache lines: 8192 x 1024 input gradients over 1024, 3072 and 4096 k 68 us on average, in the own order 61.  What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128
-// the traffic into and out of LDS (32 KB copied in, 64 KB of fragments read per 512 MFMA clocks).
+// copied in half cache lines: 8192 x 1024 input gradients over 1024, 3072 and 4096 k 68 us on average, in the own order 61.
+// What bounds it: with few tiles the latency of a k-step chain, with 256 tiles of 128 x 128 the traffic into and out of LDS
+// (32 KB copied in, 64 KB of fragments read per 512 MFMA clocks).
 //   * Tiles are copied into LDS by the memory pipeline, into a ring of NS stages of 64*NSUB k each: NS - 1 stages are
 //     in flight or being read, so a short k range is fetched in one memory latency, and a long one has two or three
 //     steps for every copy to arrive.  One barrier per step.

@@ -133,7 +133,7 @@ int choose_message(size_t n_posted, Msg&& msg, Arrived&& arrived, const Slots& s
 // How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself).  A small
 // microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to 2^24 elements of an
 // activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of 256 x 256.  Whole batches
-// of 8 microbatches (4 at h = 4096, 6 with 3 in flight at 4096 tokens), each by itself / up to 2^22 / 2^23 / 2^24 / 2^25 elements,
+// of 8 microbatches (4 at h = 4096, 6 with 3 in flight at 4096 tokens; the kernels as they were then), each by itself / up to 2^22 / 2^23 / 2^24 / 2^25 elements,
 // ms: h 1024, 1024 tokens 6.01 / 4.35 / 4.03 / 4.02 / 4.03; h 2048, 2048 tokens 11.7 / 11.7 / 10.75 / 10.73 / 10.58; h 4096, 2048
 // tokens 18.2 / 18.2 / 18.2 / 16.3 / 16.0; h 6144, 512 tokens - / 22.1 / 19.8 / 19.6 / 19.1; h 1024, 4096 tokens - / 7.64 / 7.32 /
 // 7.62 / 7.60.  Beyond 2^24 little is gained, and results come later than they have to.
