@@ -1639,7 +1639,7 @@ static hipError_t launch_ring(int epi, GemmArgs g, hipStream_t s, int parts = 1)
       AXONN_GEMM_CASE(EPI_BIAS_RES)
       AXONN_GEMM_CASE(EPI_BIAS_GELU)
       AXONN_GEMM_CASE(EPI_DGELU)
-          default: return hipErrorInvalidValue;
+      default: return hipErrorInvalidValue;
     }
 #undef AXONN_GEMM_CASE
     return hipGetLastError();
