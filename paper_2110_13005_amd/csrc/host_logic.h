@@ -78,7 +78,7 @@ void commit_backward(Slots& slots, int slot, bool wgrad_issued_with_chain, int* 
   slots[slot].state = wgrad_issued_with_chain ? SLOT_FREE : SLOT_AWAIT_WGRAD;
   --*in_flight;
 }
-// A weight-gradient pass over all waiting slots is issued (or a new batch drops them).
+// Weight-gradient passes over all waiting slots are issued (or a new batch drops them).
 template <class Slots>
 int release_awaiting(Slots& slots) {
   int n = 0;
@@ -95,10 +95,25 @@ inline int wgrad_action(bool last_of_batch, int group, int n_awaiting) {
   if (last_of_batch) return WGRAD_FLUSH_FINAL;
   return (group > 0 && n_awaiting >= group) ? WGRAD_FLUSH : WGRAD_NONE;
 }
+// The weight-gradient passes behind n backwards that run together, `n_awaiting` slots waiting before them: the same passes as
+// behind n that come one by one.  through[i]: how many of the n pass i takes them up to (the rest wait); returns the number of
+// passes, the batch's final one among them if the n end it.
+inline int wgrad_actions(bool last_of_batch, int group, int n_awaiting, int n, int* through) {
+  int passes = 0;
+  for (int i = 1, waiting = n_awaiting; i <= n; ++i) {
+    if (wgrad_action(last_of_batch && i == n, group, ++waiting) == WGRAD_NONE) continue;
+    through[passes++] = i;
+    waiting = 0;
+  }
+  return passes;
+}
 // Are the gradients of every backward so far complete once the work of the next `n` is queued (`n_awaiting` slots wait
-// before them)?  With checkpointing their weight gradients go with the chain; otherwise if a group closes.
+// before them)?  With checkpointing their weight gradients go with the chain; otherwise if a group closes behind the last.
 inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting, int n = 1) {
-  return ckpt || wgrad_action(last_of_batch, group, n_awaiting + n) != WGRAD_NONE;
+  if (ckpt) return true;
+  int waiting = n_awaiting;
+  for (int i = 1; i < n; ++i) waiting = wgrad_action(false, group, waiting + 1) == WGRAD_NONE ? waiting + 1 : 0;
+  return wgrad_action(last_of_batch, group, waiting + 1) != WGRAD_NONE;
 }
 
 // ------------------------------------------------------------------------------ messages

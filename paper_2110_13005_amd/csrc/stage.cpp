@@ -511,41 +511,54 @@ int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
   return AXONN_OK;
 }
 
-// Weight gradients of every slot that has finished its backward chain (see above).  `last_slot` is the first of the
-// n_last slots of the batch's last chain when this is the batch's final pass (else null): the pass then
-// follows that chain (by its events, if it runs on another stream: follow_chain) layer by layer from the last layer down,
-// and finishes each layer's gradients as soon as its contractions are queued.
-int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* last_slot = nullptr, int n_last = 0, bool follow_chain = false) {
+// Weight gradients of slots that have finished their backward chain (see above): of all that wait, in one pass, or, behind a
+// chain of n_chain microbatches from slot `chain` on, in `passes` passes: pass i takes the chain's up to through[i], the first
+// one also those that have waited before.  In the batch's final call (`final`) the passes follow that chain (by its events, if it
+// runs on another stream: follow_chain) layer by layer from the last layer down, and finish each layer's gradients as soon as
+// its contractions are queued.
+int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* chain = nullptr, int n_chain = 0, const int* through = nullptr,
+                int passes = 1, bool final = false, bool follow_chain = false) {
   std::vector<Slot*> ready;
+  std::vector<size_t> ends;           // of the passes, in `ready`
   for (Slot& sl : st->slots)
-    if (sl.state == SLOT_AWAIT_WGRAD) ready.push_back(&sl);
+    if (sl.state == SLOT_AWAIT_WGRAD && (!chain || &sl < chain + through[0] || &sl >= chain + n_chain)) ready.push_back(&sl);
+  for (int i = 1; i < passes; ++i) {
+    ends.push_back(ready.size());
+    for (int k = through[i - 1]; k < through[i]; ++k) ready.push_back(chain + k);
+  }
   if (ready.empty()) return AXONN_OK;
+  ends.push_back(ready.size());
   const int L = st->cfg.n_layers;
   hipEvent_t waited = nullptr;
   for (Slot* sl : ready)
-    if ((!last_slot || sl < last_slot || sl >= last_slot + n_last) && sl->dgrad_done != waited) {
+    if ((!final || sl < chain || sl >= chain + n_chain) && sl->dgrad_done != waited) {
       waited = sl->dgrad_done;
       HIP_TRY(hipStreamWaitEvent(s, waited, 0));
     }
   if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   for (int i = 0; i < L; ++i) {
-    const int l = last_slot ? L - 1 - i : i;
-    if (last_slot && follow_chain) HIP_TRY(hipStreamWaitEvent(s, st->chain_layer[l], 0));
-    for (size_t first = 0; first < ready.size(); first += kMaxKSegments) {
-      const int n = (int)std::min<size_t>(kMaxKSegments, ready.size() - first);
-      const int acc = (st->wgrad_flushes > 0 || first > 0) ? 1 : 0;
-      const LayerStash* rec[kMaxKSegments];
-      for (int k = 0; k < n; ++k) rec[k] = &ready[first + k]->layers[l];
-      AX_TRY(wgrad_layer(st, l, rec, n, acc, s));
-    }
-    if (last_slot) AX_TRY(finish_layer_grads(st, l, s));
+    const int l = final ? L - 1 - i : i;
+    if (final && follow_chain) HIP_TRY(hipStreamWaitEvent(s, st->chain_layer[l], 0));
+    size_t first = 0;
+    for (const size_t end : ends)
+      while (first < end) {
+        const int n = (int)std::min<size_t>(kMaxKSegments, end - first);
+        const int acc = (st->wgrad_flushes > 0 || first > 0) ? 1 : 0;
+        const LayerStash* rec[kMaxKSegments];
+        for (int k = 0; k < n; ++k) rec[k] = &ready[first + k]->layers[l];
+        AX_TRY(wgrad_layer(st, l, rec, n, acc, s));
+        first += n;
+      }
+    if (final) AX_TRY(finish_layer_grads(st, l, s));
   }
   st->wgrad_flushes++;
-  if (last_slot) st->grads_final_recorded = true;
+  if (final) st->grads_final_recorded = true;
   HIP_TRY(hipEventRecord(ready[0]->own.released, s));
-  for (Slot* sl : ready) sl->released = ready[0]->own.released;
+  for (Slot* sl : ready) {
+    sl->released = ready[0]->own.released;
+    sl->state = SLOT_FREE;
+  }
   st->last_wgrad = ready[0]->own.released;
-  host::release_awaiting(st->slots);
   return AXONN_OK;
 }
 
@@ -684,11 +697,9 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
     slot->released = slot->dgrad_done;
     if (last) st->grads_final_recorded = true;
   } else {
-    switch (host::wgrad_action(last, st->cfg.wgrad_group, awaiting + n)) {
-      case host::WGRAD_FLUSH_FINAL: AX_TRY(flush_wgrad(st, ws, slot, n, ws != s)); break;
-      case host::WGRAD_FLUSH: AX_TRY(flush_wgrad(st, ws)); break;
-      default: break;
-    }
+    int through[host::kMaxMerge];
+    const int passes = host::wgrad_actions(last, st->cfg.wgrad_group, awaiting, n, through);
+    if (passes) AX_TRY(flush_wgrad(st, ws, slot, n, through, passes, last, ws != s));
   }
   return AXONN_OK;
 }
