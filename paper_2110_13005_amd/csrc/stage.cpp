@@ -679,8 +679,10 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   const bool ckpt = st->cfg.ckpt_stride > 0;
   const bool last = st->bwd_count + n == st->cfg.n_microbatches;
   const int awaiting = slots_in_state(st, SLOT_AWAIT_WGRAD);
-  if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, w[0].in, w[0].out, acc, last, s, ws));
-  else AX_TRY(backward_layers(st, *slot, w, n, n == 1 ? w[0].out : merged_dx(*slot), acc, last && ws != s, s));
+  // the embedding's pass reads the input gradient behind this chain, when the slots may be in use again: a buffer of its own
+  void* const dx = st->embed ? st->embed_dx : n == 1 ? w[0].out : merged_dx(*slot);
+  if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, w[0].in, dx, acc, last, s, ws));
+  else AX_TRY(backward_layers(st, *slot, w, n, dx, acc, last && ws != s, s));
   if (n > 1 && !st->embed) AX_TRY(copy_microbatches(st, w, n, merged_dx(*slot), false, s));
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
@@ -712,10 +714,8 @@ int backward_msg(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream
   const int si = host::admit_backward(st->slots, w[0].mb_id);
   const int32_t* tokens[host::kMaxMerge] = {};
   for (int i = 0; i < n && si >= 0; ++i) tokens[i] = st->slots[si + i].tokens;
-  const Work one = {w[0].mb_id, w[0].in, st->embed_dx};
-  AX_TRY(do_backward(st, n == 1 ? &one : w, n, s, ws));
-  const elem_t* dx = n == 1 ? st->embed_dx : merged_dx(st->slots[si]);
-  for (int i = 0; i < n; ++i) AX_TRY(embed_backward(st->embed, tokens[i], dx + i * (uint64_t)st->T * st->h, s));
+  AX_TRY(do_backward(st, w, n, s, ws));
+  for (int i = 0; i < n; ++i) AX_TRY(embed_backward(st->embed, tokens[i], st->embed_dx + i * (uint64_t)st->T * st->h, s));
   // the next backward chain overwrites that gradient: it must follow the embedding's pass as well
   HIP_TRY(hipEventRecord(st->embed_bwd, s));
   st->last_bwd = st->embed_bwd;
@@ -1814,7 +1814,7 @@ int axonn_stage_attach_ends(axonn_stage_t* st, axonn_embed_t* embed, axonn_head_
   HIP_TRY(hipSetDevice(st->cfg.device));
   HIP_TRY(hipDeviceSynchronize());
   const uint64_t e_th = align_up((uint64_t)st->T * st->h * 2, 256);
-  if (embed && !st->embed_dx) HIP_TRY(hipMalloc((void**)&st->embed_dx, e_th));
+  if (embed && !st->embed_dx) HIP_TRY(hipMalloc((void**)&st->embed_dx, st->max_merge * e_th));
   if (head && !st->head_y_base) {
     // one behind the other, like the tensors of the stash
     HIP_TRY(hipMalloc((void**)&st->head_y_base, (uint64_t)st->T * st->h * 2 * st->slots.size()));

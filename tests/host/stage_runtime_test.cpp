@@ -11,7 +11,7 @@
 
 #include <cstdlib>
 #include <map>
-#include <set>
+#include <unordered_map>
 
 #define CHECK(cond)                                                            \
   do {                                                                         \
@@ -32,7 +32,8 @@ std::map<hipStream_t, int> stream_ids;
 std::map<int, Clock> clocks;
 std::map<hipEvent_t, Clock> events;                          // recorded ones
 Clock host;
-std::vector<Access> accesses;
+constexpr uint64_t kPage = 4096;
+std::unordered_map<uint64_t, std::vector<Access>> accesses;   // by page
 std::vector<std::string> races;
 std::map<std::string, int> launches;
 std::vector<int> wgrad_segments;                             // microbatches of each weight-gradient launch, in order
@@ -45,12 +46,25 @@ Clock& clock(hipStream_t s) {
 }
 void access(hipStream_t s, const char* what, Range r, bool write) {
   if (!r.p || !r.bytes) return;
-  Clock& c = clock(s);
-  const Access a = {(uint64_t)(uintptr_t)r.p, (uint64_t)(uintptr_t)r.p + r.bytes, id(s), c[id(s)], write, what};
-  for (const Access& b : accesses)
-    if ((a.write || b.write) && a.lo < b.hi && b.lo < a.hi && b.time > c[b.stream] && races.size() < 8)
-      races.push_back(std::string(b.what) + (b.write ? " (write)" : " (read)") + " and " + what + (write ? " (write)" : " (read)"));
-  accesses.push_back(a);
+  const Clock& c = clock(s);
+  const int stream = id(s);
+  const auto past = [&c](const Access& b) { const auto t = c.find(b.stream); return t != c.end() && b.time <= t->second; };
+  const uint64_t lo = (uint64_t)(uintptr_t)r.p, hi = lo + r.bytes;
+  for (uint64_t page = lo / kPage; page * kPage < hi; ++page) {
+    const Access a = {std::max(lo, page * kPage), std::min(hi, (page + 1) * kPage), stream, c.at(stream), write, what};
+    std::vector<Access>& here = accesses[page];
+    size_t kept = 0;
+    for (const Access& b : here) {
+      const bool apart = a.hi <= b.lo || b.hi <= a.lo, before = apart || past(b);
+      if (!apart && (write || b.write) && !before && races.size() < 8)
+        races.push_back(std::string(b.what) + (b.write ? " (write)" : " (read)") + " and " + what + (write ? " (write)" : " (read)"));
+      // who comes after a write, or a read on the same stream, comes after what that covers
+      const bool covered = a.lo <= b.lo && b.hi <= a.hi && before && !apart && (write || (!b.write && b.stream == stream));
+      if (!covered) here[kept++] = b;
+    }
+    here.resize(kept);
+    here.push_back(a);
+  }
 }
 hipError_t launch(hipStream_t s, const char* what, std::initializer_list<Range> reads, std::initializer_list<Range> writes) {
   ++clock(s)[id(s)];
@@ -60,7 +74,7 @@ hipError_t launch(hipStream_t s, const char* what, std::initializer_list<Range> 
   return hipSuccess;
 }
 void forget() {                                              // a fresh start, everything before is in the past
-  for (const auto& c : clocks) merge(host, c.second);
+  stream_ids.clear(); clocks.clear(); events.clear(); host.clear();
   accesses.clear(); races.clear(); launches.clear(); wgrad_segments.clear();
 }
 Range elems(const void* p, int64_t n) { return {p, (uint64_t)n * sizeof(axonn::elem_t)}; }
@@ -334,9 +348,32 @@ void test_weight_gradient_groups() {
     expect_ordered(p.c, n_streams, "cut short");
   }
 }
+
+// Nothing a batch reads or writes is left to chance, nor what its user reads behind the join; two batches, so that every
+// slot is used again.
+void test_order_of_accesses() {
+  for (int ends = 0; ends < 4; ++ends)
+    for (int M : {1, 2, 3, 5})
+      for (int limit : {1, 2, 3, 4, 5})
+        for (int group : {0, 1, 3})
+          for (int mode = 0; mode < 3 && limit <= M; ++mode)           // 16-bit, fp32 sums, checkpointing
+            for (int n_streams = 1; n_streams <= 3; ++n_streams)
+              for (bool events : {false, true}) {
+                Program p({2, 64, 2, 256, 16, 1, M, limit, group, mode == 2 ? 1 : 0, mode == 1, 512, ends % 2 == 1, ends >= 2});
+                const hipStream_t u = stream();
+                for (int batch = 0; batch < 2; ++batch) {
+                  CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+                  p.post_batch(events);
+                  CHECK(axonn_stage_run(p.st, n_streams, u) == AXONN_OK && axonn_stage_join(p.st, u) == AXONN_OK);
+                  p.read_results(u);
+                }
+                expect_ordered(p.c, n_streams, events ? "done events" : "merged");
+              }
+}
 }  // namespace
 
 int main() {
+  test_order_of_accesses();
   test_weight_gradient_groups();
   std::puts("stage runtime: all checks passed");
   return 0;

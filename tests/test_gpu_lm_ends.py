@@ -282,14 +282,16 @@ def test_head_input_gradient_split_over_the_vocabulary(T, h, V):
         hd.close()
 
 
-@pytest.mark.parametrize("sh,limit", [(StageShape(2, 128, 2, 64, 1, 5), 5), (StageShape(1, 264, 2, 72, 1, 5, 1000), 4)],
-                         ids=["one_pass", "four_and_one"])
+# the last: slots taken again while a large table's gradient is formed, which one layer's weight gradients do not hide
+@pytest.mark.parametrize("sh,limit,V", [(StageShape(2, 128, 2, 64, 1, 5), 5, 520), (StageShape(1, 264, 2, 72, 1, 5, 1000), 4, 520),
+                                        (StageShape(1, 256, 4, 64, 1, 8), 4, 51200)],
+                         ids=["one_pass", "four_and_one", "large_table"])
 @pytest.mark.parametrize("with_embed", [True, False])
-def test_merged_microbatches_through_the_head(sh, limit, with_embed):
-    """Forwards and backwards of several microbatches as one pass with the head between them: losses and input gradients bit
-    for bit those of a run that takes them one by one (a done_event each)."""
+def test_merged_microbatches_through_the_head(sh, limit, V, with_embed):
+    """Forwards and backwards of several microbatches as one pass with the head between them: losses, input gradients and the
+    gradients of both ends bit for bit those of a run that takes them one by one (a done_event each)."""
     import torch
-    V, M = 520, sh.n_microbatches
+    M = sh.n_microbatches
     layers, xs, _ = make_stage_inputs(sh, seed=31, perturb=True)
     tokens, targets, wte, wpe, g, bt, W = make_lm_inputs(sh, V, seed=32)
     e = EmbedHandle(V, sh.hidden, sh.seq_len, sh.microbatch_size, wte, wpe) if with_embed else None
@@ -313,14 +315,16 @@ def test_merged_microbatches_through_the_head(sh, limit, with_embed):
                     st.post(0, i, X[i], DX[i], targets=TG[i], loss=losses[i:i + 1], done_event=evs[i] if events else None)
                 st.run(2); st.join(); torch.cuda.synchronize()
                 assert B.axonn_stage_dispatch_log(st.handle) == [(i, k) for i in range(M) for k in (0, 1)]
-                got.append((losses.cpu().numpy(), [None if d is None else host(d) for d in DX], st.grads_numpy()))
+                got.append((losses.cpu().numpy(), [None if d is None else host(d) for d in DX], st.grads_numpy(),
+                            [*hd.grads_numpy().values(), *(e.grads_numpy() if e else ())]))
     finally:
         hd.close()
         if e:
             e.close()
-    (la, xa, ga), (lb, xb, gb) = got
+    (la, xa, ga, ea), (lb, xb, gb, eb) = got
     assert np.array_equal(la, lb)
     assert e or all(np.array_equal(a, b) for a, b in zip(xa, xb))
+    assert len(ea) == len(eb) == (5 if e else 3) and all(np.array_equal(a, b) and a.any() for a, b in zip(ea, eb))
     for p, q in zip(ga, gb):
         for k in p:
             assert rel_fro(p[k], q[k]) <= 1e-3, k          # sums over the microbatches, in another order
