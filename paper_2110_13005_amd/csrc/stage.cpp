@@ -553,6 +553,8 @@ int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* chain = nullptr, int n_cha
   }
   st->wgrad_flushes++;
   if (final) st->grads_final_recorded = true;
+  // several microbatches' input gradients are copied out of their slots behind the last layer of the chain
+  if (final && follow_chain && n_chain > 1 && !st->embed) HIP_TRY(hipStreamWaitEvent(s, chain->dgrad_done, 0));
   HIP_TRY(hipEventRecord(ready[0]->own.released, s));
   for (Slot* sl : ready) {
     sl->released = ready[0]->own.released;

@@ -350,7 +350,8 @@ void test_weight_gradient_groups() {
 }
 
 // Nothing a batch reads or writes is left to chance, nor what its user reads behind the join; two batches, so that every
-// slot is used again.
+// slot is used again.  `apart`: the second batch gets buffers and streams of its own, in no order with the first one's; what
+// the stage itself holds is in order all the same.
 void test_order_of_accesses() {
   for (int ends = 0; ends < 4; ++ends)
     for (int M : {1, 2, 3, 5})
@@ -358,16 +359,18 @@ void test_order_of_accesses() {
         for (int group : {0, 1, 3})
           for (int mode = 0; mode < 3 && limit <= M; ++mode)           // 16-bit, fp32 sums, checkpointing
             for (int n_streams = 1; n_streams <= 3; ++n_streams)
-              for (bool events : {false, true}) {
+              for (int how = 0; how < 4; ++how) {
+                const bool events = how & 1, apart = how & 2;
                 Program p({2, 64, 2, 256, 16, 1, M, limit, group, mode == 2 ? 1 : 0, mode == 1, 512, ends % 2 == 1, ends >= 2});
-                const hipStream_t u = stream();
+                hipStream_t u = stream();
                 for (int batch = 0; batch < 2; ++batch) {
                   CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+                  if (apart) { p.new_buffers(); u = stream(); }
                   p.post_batch(events);
                   CHECK(axonn_stage_run(p.st, n_streams, u) == AXONN_OK && axonn_stage_join(p.st, u) == AXONN_OK);
-                  p.read_results(u);
+                  if (!apart) p.read_results(u);
                 }
-                expect_ordered(p.c, n_streams, events ? "done events" : "merged");
+                expect_ordered(p.c, n_streams, events ? "done events" : apart ? "merged, two users" : "merged");
               }
 }
 }  // namespace
