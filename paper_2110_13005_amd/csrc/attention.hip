@@ -366,16 +366,23 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 
 // ============================================================================ backward
 // delta[b][a][i] = sum_d dO[i][d] * O[i][d]
-// p + the products of 4 elements, one after the other.
-template <class V>
-__device__ __forceinline__ float delta_add4(float p, V ov, V dv, int first) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    float x = (float)ov[first + e];
+// p + the products of elements first .. first + N - 1, one after the other (PAIRS: half precision in two-element dot
+// products).  Both forms are fixed here: left to contraction, which of them a sum gets depends on the kernel around it.
+template <int N, bool PAIRS, class V>
+__device__ __forceinline__ float delta_add(float p, V ov, V dv, int first) {
 #ifdef AXONN_ELEM_FP16
-    asm("" : "+v"(x));   // else one of the kernels gets two-element dot products, whose sums are rounded differently
+  if (PAIRS) {
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int e = first; e < first + N; e += 2)
+      p = __builtin_amdgcn_fdot2(halfx2{ov[e], ov[e + 1]}, halfx2{dv[e], dv[e + 1]}, p, false);
+    return p;
+  }
 #endif
-    p = fmaf(x, (float)dv[first + e], p);
+  {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int e = first; e < first + N; ++e) p = __builtin_fmaf((float)ov[e], (float)dv[e], p);
   }
   return p;
 }
@@ -393,7 +400,7 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
     const elem_t* op = o + pair * d;          // rows are a * d long: pair * d = row * a * d + head * d
     const elem_t* dp = dout + pair * d;
     for (int c = 4 * j; c < d; c += 64) {
-      p = delta_add4(p, *reinterpret_cast<const elemx4*>(op + c), *reinterpret_cast<const elemx4*>(dp + c), 0);
+      p = delta_add<4, true>(p, *reinterpret_cast<const elemx4*>(op + c), *reinterpret_cast<const elemx4*>(dp + c), 0);
     }
   }
 #pragma unroll
@@ -810,20 +817,18 @@ __device__ __forceinline__ void attn_bwd_dq(
       if (by_4) {
         // the launch of its own's order: 4 elements of every 64 per lane, here in pairs of such lanes; at D = 128 the lanes
         // of the upper half go on from the sums of the lower half's
-        float lo = delta_add4(0.f, ov, dv, 0), hi = delta_add4(0.f, ov, dv, 4);
+        float lo = delta_add<4, true>(0.f, ov, dv, 0), hi = delta_add<4, true>(0.f, ov, dv, 4);
         if (LPR == 16) {
           const float lo0 = __shfl_xor(lo, 8, 64), hi0 = __shfl_xor(hi, 8, 64);
-          lo = delta_add4(lo0, ov, dv, 0);               // of the upper half's lanes; the lower half's are not used
-          hi = delta_add4(hi0, ov, dv, 4);
+          lo = delta_add<4, true>(lo0, ov, dv, 0);       // of the upper half's lanes; the lower half's are not used
+          hi = delta_add<4, true>(hi0, ov, dv, 4);
         }
 #pragma unroll
         for (int off = 4; off > 0; off >>= 1) { lo += __shfl_xor(lo, off, 64); hi += __shfl_xor(hi, off, 64); }
         p = lo + hi;
         if (LPR == 16) p = __shfl_xor(p, 8, 64);         // to the lane that keeps it
       } else {
-        p = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p += (float)ov[e] * (float)dv[e];
+        p = delta_add<8, false>(0.f, ov, dv, 0);
 #pragma unroll
         for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
       }

@@ -420,6 +420,29 @@ def test_attention_around_the_one_launch_backward(b, s, a, d):
     test_attention_fwd_bwd(b, s, a, d)
 
 
+@pytest.mark.parametrize("b,s,a,d", [(2, 72, 66, 64), (4, 72, 33, 128)])
+def test_attention_delta_is_the_sum_of_products_in_element_order(b, s, a, d):
+    """Where the dQ kernel forms delta = sum_d dO O itself (more than 128 tiles): 8 products per lane one after the other, then
+    the lanes' sums in a tree, in 32 bits and in both element types.  A product of two 16-bit numbers is exact in 32 bits, so
+    a fused multiply-add is an addition of it: the same bits."""
+    import torch
+    rng = np.random.default_rng(d)
+    h = a * d
+    qkv, dout = _rng_bf16(rng, (b * s, 3 * h)), _rng_bf16(rng, (b * s, h))
+    o = torch.zeros(b * s, h, dtype=B.torch_elem_dtype(), device="cuda"); dqkv = torch.zeros(b * s, 3 * h, dtype=o.dtype, device="cuda")
+    lse, delta = (torch.zeros(b * a * s, dtype=torch.float32, device="cuda") for _ in range(2))
+    QKV, DO = dev_bf16(qkv), dev_bf16(dout)
+    B.axonn_attention_fwd(b, s, a, d, QKV, o, lse)
+    B.axonn_attention_bwd(b, s, a, d, QKV, o, lse, DO, dqkv, delta)
+    prod = (host(o).astype(np.float32) * host(DO).astype(np.float32)).reshape(b, s, a, d // 8, 8)
+    p = np.zeros(prod.shape[:-1], np.float32)
+    for e in range(8):
+        p = p + prod[..., e]
+    while p.shape[-1] > 1:
+        p = p[..., :p.shape[-1] // 2] + p[..., p.shape[-1] // 2:]
+    assert np.array_equal(delta.cpu().numpy().reshape(b, a, s), p[..., 0].transpose(0, 2, 1))
+
+
 def test_attention_large_scores_stay_finite():
     """Scores of order +-100: the running-max subtraction must keep exp in range."""
     import torch
