@@ -184,13 +184,14 @@ __device__ __forceinline__ void epi_finish(float (&v)[4], const float (&bv)[4], 
     for (int e = 0; e < 4; ++e) {
       float y, dy;
       gelu_with_grad_f(v[e], y, dy);
-#ifdef AXONN_ELEM_FP16
-      // keeps the rounding to half precision a step of its own: fused with the last multiply-add, in some kernels and for
-      // some elements only, it would make the result depend on the tile
-      asm("" : "+v"(dy));
-#endif
       v[e] = y;
-      dv[e] = (elem_t)dy;
+      elem_t r = (elem_t)dy;
+#ifdef AXONN_ELEM_FP16
+      // each rounding to half precision by itself is one with the last multiply-add (v_fma_mixlo_f16); in pairs some are a
+      // conversion of their own, a second rounding, and which ones depends on the tile
+      asm("" : "+v"(r));
+#endif
+      dv[e] = r;
     }
     *reinterpret_cast<elemx4*>(g.aux + off_side) = dv;
   }

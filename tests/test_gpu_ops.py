@@ -224,6 +224,39 @@ def test_gemm_both_large_kernels_all_layouts_and_results(mask, min_tiles):
         B.axonn_tuning(7, 0)
 
 
+def test_gelu_of_every_value_does_not_depend_on_the_kernel():
+    """GeLU and GeLU' of every finite 16-bit number (as bias under a product of zeros), from each tile of the ring kernel, in
+    this order, and both large-problem kernels: the same bits in every row of every launch."""
+    import torch
+    bits = torch.arange(1 << 16, dtype=torch.int32).to(torch.int16).cuda()
+    values = bits.view(B.torch_elem_dtype())
+    values = values[torch.isfinite(values)]
+    seen = []
+    try:
+        for M, N, min_tiles, mask in ((64, 2048, 1 << 20, -1), (1024, 2048, 1 << 20, -1), (1536, 2048, 1 << 20, -1),
+                                      (2048, 3072, 1 << 20, -1), (2048, 4096, 1 << 20, -1), (64, 2048, 1, 15), (64, 2048, 1, 0)):
+            B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, min_tiles)
+            B.axonn_tuning(B.TUNE_GEMM_COPY_MASK, mask)
+            K = 64
+            a, w = (torch.zeros(n, dtype=values.dtype, device="cuda") for n in (M * K, K * N))
+            got = []
+            for first in range(0, len(values), N):
+                bias = torch.zeros(N, dtype=values.dtype, device="cuda")
+                piece = values[first:first + N]
+                bias[:len(piece)] = piece
+                y, aux = (torch.zeros(M, N, dtype=values.dtype, device="cuda") for _ in range(2))
+                B.axonn_gemm_bf16(1, 0, B.EPI_BIAS_GELU, M, N, K, a, K, w, N, y, N, bias=bias, aux=aux, ld_aux=N)
+                both = torch.stack([y, aux]).view(torch.int16)[:, :, :len(piece)]
+                assert bool((both == both[:, :1]).all()), (M, N, first)
+                got.append(both[:, 0])
+            seen.append(torch.cat(got, dim=1))
+    finally:
+        for knob in (B.TUNE_GEMM_COPY_MASK, B.TUNE_GEMM_BIG_MIN_TILES):
+            B.axonn_tuning(knob, -1)
+    for other in seen[1:]:
+        assert torch.equal(seen[0], other)
+
+
 def _wide(rows, width, ld, offset=0):
     """rows x width random elements with leading dimension ld, `offset` elements into a buffer that is NaN elsewhere near
     them -> (values, tensor that starts at the first element)."""
