@@ -1821,8 +1821,8 @@ int axonn_stage_attach_ends(axonn_stage_t* st, axonn_embed_t* embed, axonn_head_
     // one behind the other, like the tensors of the stash
     HIP_TRY(hipMalloc((void**)&st->head_y_base, (uint64_t)st->T * st->h * 2 * st->slots.size()));
     for (size_t i = 0; i < st->slots.size(); ++i) st->slots[i].head_y = st->head_y_base + i * (uint64_t)st->T * st->h;
-    if (st->cfg.ckpt_stride > 0) HIP_TRY(hipMalloc((void**)&st->head_dx, e_th));
   }
+  if (head && st->cfg.ckpt_stride > 0 && !st->head_dx) HIP_TRY(hipMalloc((void**)&st->head_dx, e_th));
   st->embed = embed;
   st->head = head;
   return AXONN_OK;

@@ -373,11 +373,28 @@ void test_order_of_accesses() {
                 expect_ordered(p.c, n_streams, events ? "done events" : apart ? "merged, two users" : "merged");
               }
 }
+
+// attach_ends after an allocation of it has failed: the next call makes what is missing.
+void test_attach_after_failed_allocation() {
+  for (int stride : {0, 1})
+    for (int fails = 0; fails < 4; ++fails) {
+      Program p({2, 64, 2, 256, 16, 1, 2, 2, 0, stride, 0, 512, false, false});
+      CHECK(axonn_embed_create(0, 512, 64, 16, 1, &p.embed) == AXONN_OK && axonn_head_create(0, 512, 64, 16, 2, 1e-5f, &p.head) == AXONN_OK);
+      mallocs_until_failure = fails;
+      const int needed = stride ? 3 : 2;                     // one for the embedding, one or two for the head
+      CHECK((axonn_stage_attach_ends(p.st, p.embed, p.head) == AXONN_OK) == (fails >= needed));
+      mallocs_until_failure = -1;
+      CHECK(axonn_stage_attach_ends(p.st, p.embed, p.head) == AXONN_OK);
+      CHECK(p.st->embed_dx && p.st->head_y_base && (p.st->head_dx != nullptr) == (stride > 0));
+      for (const Slot& slot : p.st->slots) CHECK(slot.head_y);
+    }
+}
 }  // namespace
 
 int main() {
   test_order_of_accesses();
   test_weight_gradient_groups();
+  test_attach_after_failed_allocation();
   std::puts("stage runtime: all checks passed");
   return 0;
 }
