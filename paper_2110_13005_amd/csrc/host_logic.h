@@ -147,24 +147,45 @@ int choose_message(size_t n_posted, Msg&& msg, Arrived&& arrived, const Slots& s
 
 // How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself).  A small
 // microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to 2^24 elements of an
-// activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of 256 x 256.  Whole batches
-// of 8 microbatches (4 at h = 4096, 6 with 3 in flight at 4096 tokens; the kernels as they were then), each by itself / up to 2^22 / 2^23 / 2^24 / 2^25 elements,
-// ms: h 1024, 1024 tokens 6.01 / 4.35 / 4.03 / 4.02 / 4.03; h 2048, 2048 tokens 11.7 / 11.7 / 10.75 / 10.73 / 10.58; h 4096, 2048
-// tokens 18.2 / 18.2 / 18.2 / 16.3 / 16.0; h 6144, 512 tokens - / 22.1 / 19.8 / 19.6 / 19.1; h 1024, 4096 tokens - / 7.64 / 7.32 /
-// 7.62 / 7.60.  Beyond 2^24 little is gained, and results come later than they have to.
+// activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of 256 x 256.
+// Whole batches of two layers, 2 streams, ms, by the largest activation of a pass (a slot per microbatch but for the last):
+//   hidden, tokens, microbatches    each alone   2^22    2^23    2^24    2^25
+//   1024, 1024, 8                      2.84      2.28    2.08    2.07    2.09
+//   2048, 2048, 8                     11.01     10.96   10.25   10.21    9.92
+//   2048, 2048, 2                      2.88      2.87    2.67    2.67    2.67
+//   2048, 2048, 3                      4.19      4.19    4.01    4.07    4.06
+//   4096, 2048, 4                     17.2      17.2    17.2    16.0    16.0
+//   4096, 1024, 6                     14.18     14.16   13.14   14.31   13.15      (passes of 1, 1, 2, 3 and 6)
+//   6144, 512, 8                      22.0      22.0    19.8    19.3    19.1
+//   1024, 4096, 6 (3 slots)            5.89      5.89    5.60    5.58    5.62
+// Beyond 2^24 little is gained, and results come later than they have to.
 constexpr int kMaxMerge = 8;
 constexpr int64_t kMergeElements = int64_t(1) << 24;
 // A backward pass of several microbatches keeps a gradient of h columns and one float per head in the place of the f columns
 // of GeLU': narrower MLPs run one by one.
 // The slots are dealt to passes of equal size.  With fewer slots than microbatches a pass takes at most 4 of them, and never
-// all of an odd number: a pass that holds every slot has nothing to overlap with.  Whole batches of 8 with 3 / 4 / 5 / 6 slots at h
-// 1536, 1280 tokens, by the size of a pass, ms: 2: 5.16 / 4.83 / 5.04 / 4.84; 3: 5.27 / 4.99 / 4.65 / 4.66; 4: - / 4.69 / 4.70 / 4.61;
-// 5: - / - / 4.92 / 4.90; with 8 slots 4: 4.35, 5: 4.64, 6: 4.62.
-inline int merge_limit(int64_t T, int64_t h, int64_t f, int64_t heads, int slots, int n_microbatches) {
+// all of an odd number: a pass that holds every slot has nothing to overlap with.  8 microbatches of 1280 tokens at h 1536, by
+// the size of a pass, ms:
+//   slots      1       2       3       4       5       6       8
+//   2        6.26    6.34
+//   3        6.64    6.10    5.86
+//   4        6.00    5.29    5.31    5.03
+//   5        5.90    5.44    5.05    5.04    5.27
+//   6        5.86    5.23    5.08    4.99    5.24    5.31
+//   8        5.72    5.22    5.03    4.72    4.98    4.89    4.62
+// Two slots and an odd number of microbatches: the last one's two passes stand behind all others with nothing beside them,
+// where on several streams (`overlap`) every forward runs beside a backward if they come one by one.  Random stages with 3 to 7
+// microbatches, 2 or 3 streams, one by one / together: up to 2^20 elements 0.99 to 1.4 (67 stages), above it 0.89 to 1.12, 0.98 on
+// average (44); with weight-gradient passes of one microbatch each up to 2^18 elements 1.02 to 1.27 (13; one 0.94), above it
+// 0.85 to 1.11, 0.97 on average (39).  On one stream 34 stages of all sizes gained.
+inline int merge_limit(int64_t T, int64_t h, int64_t f, int64_t heads, int slots, int n_microbatches, bool overlap = false,
+                       int wgrad_group = 0) {
   if (f < h + 2 * heads) return 1;
-  const int64_t fits = std::min<int64_t>(kMaxMerge, kMergeElements / (T * std::max<int64_t>(h, (f + 3) / 4)));
+  const int64_t elements = T * std::max<int64_t>(h, (f + 3) / 4);
+  const int64_t fits = std::min<int64_t>(kMaxMerge, kMergeElements / elements);
   if (fits < 1) return 1;
   const bool refill = slots < n_microbatches;
+  if (overlap && refill && slots == 2 && n_microbatches % 2 && elements > int64_t(1) << (wgrad_group == 1 ? 18 : 20)) return 1;
   const int64_t most = refill ? std::min<int64_t>(fits, 4) : fits;
   const int64_t passes = std::max<int64_t>((slots + most - 1) / most, refill && slots > 1 && slots % 2 ? 2 : 1);
   return (int)((slots + passes - 1) / passes);

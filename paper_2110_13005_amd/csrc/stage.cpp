@@ -197,6 +197,7 @@ struct axonn_stage {
   char* stash_base = nullptr;
   uint64_t stash_bytes = 0;
   int max_merge = 1;                  // microbatches that may run as one (host::merge_limit)
+  int max_merge_overlap = 1;          // on several streams; never more
   int ln_slices = 0;                  // of ln_part, per LayerNorm
   // backward workspace
   char* ws_base = nullptr;
@@ -975,7 +976,13 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
     if (cfg->qkv_input_split) place(base, at, b_th, recs, &R::u_lo);
   };
   const int ac = cfg->ckpt_stride;
-  st->max_merge = ac > 0 ? 1 : host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches);
+  if (ac == 0) {
+    const auto merge_limit = [&](bool overlap) {
+      return host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches, overlap, cfg->wgrad_group);
+    };
+    st->max_merge = merge_limit(false);
+    st->max_merge_overlap = merge_limit(true);
+  }
   st->slots.resize(cfg->pipeline_limit);
   for (Slot& s : st->slots) {
     CREATE_TRY(hipEventCreateWithFlags(&s.own.fwd_done, hipEventDisableTiming));
@@ -1243,7 +1250,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
     if (m.kind == 0 && host::find_free(st->slots) < 0) AX_TRY(flush_wgrad(st, ws));
     int picked[host::kMaxMerge];
     const int n = host::merge_messages(st->inbox.size(), span, arrived, chosen, st->slots, st->in_flight,
-                                       st->cfg.pipeline_limit, st->max_merge, picked);
+                                       st->cfg.pipeline_limit, n_streams > 1 ? st->max_merge_overlap : st->max_merge, picked);
     const int si = host::stream_index(m.kind, n_streams, &st->fwd_rr);
     hipStream_t s = st->streams[si];
     Work w[host::kMaxMerge];

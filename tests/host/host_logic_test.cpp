@@ -376,6 +376,13 @@ void test_merged_messages() {
   CHECK(limit_of(2048, 2048, 32768, 8, 8) == 1 && limit_of(256, 256, 256, 8, 8) == 1 && limit_of(256, 256, 264, 8, 8) == 8);
   const int refilled[9] = {0, 1, 2, 2, 4, 3, 3, 4, 4};       // fewer slots than microbatches
   for (int p = 1; p <= 8; ++p) CHECK(limit_of(256, 256, 1024, p, 16) == refilled[p]);
+  // two slots and an odd number of microbatches on several streams: up to 2^20 elements, 2^18 with weight gradients one by one
+  const auto two_slots = [](int64_t T, int64_t f, int slots, int M, bool overlap, int group) { return merge_limit(T, 256, f, 4, slots, M, overlap, group); };
+  CHECK(two_slots(4096, 1024, 2, 3, true, 0) == 2 && two_slots(4104, 1024, 2, 3, true, 0) == 1 && two_slots(4096, 1032, 2, 7, true, 3) == 1);
+  CHECK(two_slots(1024, 1024, 2, 3, true, 1) == 2 && two_slots(1032, 1024, 2, 3, true, 1) == 1 && two_slots(1032, 1024, 2, 3, true, 3) == 2);
+  for (int group : {0, 1, 3})
+    CHECK(two_slots(8192, 1024, 2, 3, false, group) == 2 && two_slots(8192, 1024, 2, 4, true, group) == 2 &&
+          two_slots(8192, 1024, 2, 2, true, group) == 2 && two_slots(8192, 1024, 4, 5, true, group) == 4);
 
   std::vector<MessageSpan> box;
   std::vector<int> here;                       // arrived(i)

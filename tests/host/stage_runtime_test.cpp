@@ -374,6 +374,28 @@ void test_order_of_accesses() {
               }
 }
 
+// How many passes the microbatches of a batch make, forward and backward.
+void test_passes() {
+  const auto passes = [](int s, int M, int limit, int group, int n_streams, bool events) {
+    Program p({1, 256, 4, 1024, s, 1, M, limit, group, 0, 0, 0, false, false});
+    hipStream_t u = stream();
+    CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+    p.post_batch(events);
+    CHECK(axonn_stage_run(p.st, n_streams, u) == AXONN_OK && axonn_stage_join(p.st, u) == AXONN_OK);
+    CHECK((int)p.log().size() == 2 * M);
+    return std::make_pair(launches["attention"], launches["attention backward"]);
+  };
+  typedef std::pair<int, int> Passes;
+  for (int n_streams = 1; n_streams <= 3; ++n_streams) {
+    CHECK(passes(64, 8, 8, 0, n_streams, false) == Passes(1, 1) && passes(64, 8, 8, 0, n_streams, true) == Passes(8, 8));
+    CHECK(passes(64, 8, 4, 0, n_streams, false) == Passes(2, 2) && passes(64, 4, 2, 0, n_streams, false) == Passes(2, 2));
+    // two slots, an odd number of microbatches: together on one stream, on several only small ones
+    CHECK(passes(4096, 3, 2, 0, n_streams, false) == Passes(2, 2) && passes(1024, 3, 2, 1, n_streams, false) == Passes(2, 2));
+    const Passes large = n_streams == 1 ? Passes(2, 2) : Passes(3, 3);
+    CHECK(passes(4160, 3, 2, 0, n_streams, false) == large && passes(1088, 3, 2, 1, n_streams, false) == large);
+  }
+}
+
 // attach_ends after an allocation of it has failed: the next call makes what is missing.
 void test_attach_after_failed_allocation() {
   for (int stride : {0, 1})
@@ -394,6 +416,7 @@ void test_attach_after_failed_allocation() {
 int main() {
   test_order_of_accesses();
   test_weight_gradient_groups();
+  test_passes();
   test_attach_after_failed_allocation();
   std::puts("stage runtime: all checks passed");
   return 0;
