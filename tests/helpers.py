@@ -216,3 +216,15 @@ def oracle_model(tokens, targets, wte, wpe, layers, g, bt, W, n_heads, M):
     return losses, tot
 
 
+def passes_of(run, n_layers):
+    """Calls run() and returns how many passes over the layers it made: (forwards, backwards)."""
+    import torch
+    torch.cuda.synchronize()
+    B.axonn_profile_enable(True)
+    try:
+        run()
+        torch.cuda.synchronize()
+        got = B.axonn_profile_collect()
+    finally:
+        B.axonn_profile_enable(False)
+    return tuple(got[k][1] // n_layers for k in ("attention_fwd", "attention_bwd"))

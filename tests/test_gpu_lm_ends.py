@@ -9,7 +9,8 @@ from oracle import transformer as OT
 from paper_2110_13005_amd import binding as B
 from paper_2110_13005_amd.inputs import StageShape, make_stage_inputs, make_lm_inputs, snap_elem
 from paper_2110_13005_amd.stage import Stage, view_bf16
-from helpers import rel_fro, dev_bf16, host, dev_i32, EmbedHandle, HeadHandle, oracle_model, FWD_TOL, GRAD_TOL, EPS
+from helpers import (rel_fro, dev_bf16, host, dev_i32, EmbedHandle, HeadHandle, oracle_model, passes_of, FWD_TOL, GRAD_TOL,
+                     EPS)
 
 pytestmark = pytest.mark.gpu
 
@@ -283,11 +284,12 @@ def test_head_input_gradient_split_over_the_vocabulary(T, h, V):
 
 
 # the last: slots taken again while a large table's gradient is formed, which one layer's weight gradients do not hide
-@pytest.mark.parametrize("sh,limit,V", [(StageShape(2, 128, 2, 64, 1, 5), 5, 520), (StageShape(1, 264, 2, 72, 1, 5, 1000), 4, 520),
-                                        (StageShape(1, 256, 4, 64, 1, 8), 4, 51200)],
+@pytest.mark.parametrize("sh,limit,passes,V", [(StageShape(2, 128, 2, 64, 1, 5), 5, 1, 520),
+                                               (StageShape(1, 264, 2, 72, 1, 5, 1000), 4, 2, 520),
+                                               (StageShape(1, 256, 4, 64, 1, 8), 4, 2, 51200)],
                          ids=["one_pass", "four_and_one", "large_table"])
 @pytest.mark.parametrize("with_embed", [True, False])
-def test_merged_microbatches_through_the_head(sh, limit, V, with_embed):
+def test_merged_microbatches_through_the_head(sh, limit, passes, V, with_embed):
     """Forwards and backwards of several microbatches as one pass with the head between them: losses, input gradients and the
     gradients of both ends bit for bit those of a run that takes them one by one (a done_event each)."""
     import torch
@@ -313,7 +315,9 @@ def test_merged_microbatches_through_the_head(sh, limit, V, with_embed):
                 st.zero_grad()
                 for i in range(M):
                     st.post(0, i, X[i], DX[i], targets=TG[i], loss=losses[i:i + 1], done_event=evs[i] if events else None)
-                st.run(2); st.join(); torch.cuda.synchronize()
+                made = passes_of(lambda: (st.run(2), st.join()), sh.n_layers)
+                assert made == ((M, M) if events else (passes, passes)), (events, made)
+                # message by message, in whatever order their kernels run
                 assert B.axonn_stage_dispatch_log(st.handle) == [(i, k) for i in range(M) for k in (0, 1)]
                 got.append((losses.cpu().numpy(), [None if d is None else host(d) for d in DX], st.grads_numpy(),
                             [*hd.grads_numpy().values(), *(e.grads_numpy() if e else ())]))

@@ -11,8 +11,8 @@ from oracle import transformer as OT
 from paper_2110_13005_amd import binding as B
 from paper_2110_13005_amd.inputs import CONFIGS, StageShape, make_stage_inputs, make_adam_inputs
 from paper_2110_13005_amd.stage import Stage
-from helpers import (rel_fro, dev_bf16, dev_f32, host, parity, round_elem, run_direct, check_batch, schedules, FWD_TOL,
-                     GRAD_TOL, ADAM_TOL, EPS)
+from helpers import (rel_fro, dev_bf16, dev_f32, host, parity, round_elem, run_direct, check_batch, passes_of, schedules,
+                     FWD_TOL, GRAD_TOL, ADAM_TOL, EPS)
 
 pytestmark = pytest.mark.gpu
 
@@ -202,19 +202,20 @@ def test_message_driven_run_matches_oracle_and_respects_pipeline_limit(n_streams
         check_batch([host(y) for y in Y], [host(d) for d in DX], st.grads_numpy(), ref)
 
 
-@pytest.mark.parametrize("sh,limit,opts", [
-    (StageShape(2, 256, 4, 128, 2, 5), 5, dict(wgrad_group=3)),            # up to 5 microbatches in one pass
-    (StageShape(2, 384, 3, 200, 2, 4, 1000), 3, dict(grad_accum_fp32=0)),  # ragged tiles, passes of 2 and 1
-    (StageShape(1, 376, 2, 72, 1, 9), 9, dict(grad_accum_fp32=0, wgrad_group=1)),   # masked head dimension, 5 and 4
-    (StageShape(1, 1024, 8, 1024, 1, 3), 3, dict()),                       # separate attention backward kernels from 3 on, d 128
-    (StageShape(1, 1024, 16, 1000, 1, 2), 2, dict()),                      # from 2 on, d 64, ragged
-    (StageShape(1, 1024, 16, 512, 2, 4), 2, dict(qkv_input_split=2)),      # backwards past the forwards between them
-    (StageShape(2, 256, 4, 64, 1, 4, 264), 4, dict()),                     # the narrowest MLP: its activations just hold the gradients
+@pytest.mark.parametrize("sh,limit,passes,opts", [
+    (StageShape(2, 256, 4, 128, 2, 5), 5, 1, dict(wgrad_group=3)),            # up to 5 microbatches in one pass
+    (StageShape(2, 384, 3, 200, 2, 4, 1000), 3, 3, dict(grad_accum_fp32=0)),  # ragged tiles, two of one and one of two
+    (StageShape(1, 376, 2, 72, 1, 9), 9, 2, dict(grad_accum_fp32=0, wgrad_group=1)),   # masked head dimension, 5 and 4
+    (StageShape(1, 1024, 8, 1024, 1, 3), 3, 1, dict()),                       # separate attention backward kernels from 3 on, d 128
+    (StageShape(1, 1024, 16, 1000, 1, 2), 2, 1, dict()),                      # from 2 on, d 64, ragged
+    (StageShape(1, 1024, 16, 512, 2, 4), 2, 2, dict(qkv_input_split=2)),      # backwards past the forwards between them
+    (StageShape(2, 256, 4, 64, 1, 4, 264), 4, 1, dict()),                     # the narrowest MLP: its activations just hold the gradients
 ], ids=["tiny5", "ragged", "headdim188", "attn_tiles128", "attn_tiles64", "limit2", "narrow_mlp"])
 @pytest.mark.parametrize("n_streams", [1, 2])
-def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, opts, n_streams):
+def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, passes, opts, n_streams):
     """Messages that run as one pass over all their tokens: every y and dx bit for bit that of direct calls; with a
-    done_event per message (nothing merged) and with overlapping result buffers (not merged either) too."""
+    done_event per message (nothing merged) and with overlapping result buffers (forwards not merged) too.  `passes`: how
+    many forward and backward passes there are, by the library's own count of launches."""
     import torch
     layers, xs, dys = make_stage_inputs(sh, seed=4, perturb=True)
     M = sh.n_microbatches
@@ -236,8 +237,8 @@ def test_merged_microbatches_give_the_bits_of_single_ones(sh, limit, opts, n_str
                 order += [(1, i)] + ([(0, limit + i)] if limit + i < M else [])
             for kind, i in order:
                 st.post(kind, i, (X, DY)[kind][i], (Y, DX)[kind][i], **({"done_event": evs[2 * i + kind]} if events else {}))
-            st.run(n_streams); st.join()
-            torch.cuda.synchronize()
+            made = passes_of(lambda: (st.run(n_streams), st.join()), sh.n_layers)
+            assert made == ((M, M) if events else (M, made[1]) if shared else (passes, passes)), (events, shared, made)
             for i in range(M):
                 if not shared or i == M - 1:
                     assert np.array_equal(host(Y[i]), outs[i]), (events, shared, i)
