@@ -191,7 +191,9 @@ int axonn_stage_set_message_wait(axonn_stage_t* st, double seconds);
 int axonn_stage_join(axonn_stage_t* st, void* user_stream);
 /* Blocks the host until all enqueued work of the stage is complete. */
 int axonn_stage_synchronize(axonn_stage_t* st);
-/* Order in which run() dispatched messages: entries are mb_id*2 + kind. */
+/* Order in which run() dispatched messages: entries are mb_id*2 + kind; a message to the last stage has two, its Forward's and
+ * its Backward's.  Messages that ran together are listed one behind the other, as they would be one by one: on the last stage
+ * the kernels of all their Forwards run before those of their Backwards. */
 int axonn_stage_dispatch_log(const axonn_stage_t* st, int32_t* out, int32_t capacity,
                              int32_t* n_written);
 

@@ -1270,7 +1270,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
       st->fwd_issued += n;
       for (int i = 0; i < n; ++i) {
         st->dispatch_log.push_back(w[i].mb_id * 2);
-        if (st->head) st->dispatch_log.push_back(w[i].mb_id * 2 + 1);   // each Forward is followed by its Backward
+        if (st->head) st->dispatch_log.push_back(w[i].mb_id * 2 + 1);   // the log goes message by message
       }
       if (st->head) {
         // last stage (Alg. 2): the loss follows the forward pass and Backward(1) starts at once, on the
