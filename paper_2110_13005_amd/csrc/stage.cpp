@@ -1105,7 +1105,9 @@ int axonn_stage_zero_grad(axonn_stage_t* st, void* hip_stream) {
   if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
   if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   // no memory is touched: the first backward / weight-gradient pass of a batch overwrites the
-  // accumulators.  Microbatches whose weight gradients were still pending are dropped.
+  // accumulators.  Microbatches whose weight gradients were still pending are dropped; their chains alone use the slots.
+  for (Slot& sl : st->slots)
+    if (sl.state == SLOT_AWAIT_WGRAD) sl.released = sl.dgrad_done;
   host::release_awaiting(st->slots);
   st->bwd_count = 0;
   st->wgrad_flushes = 0;

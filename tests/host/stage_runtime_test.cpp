@@ -374,6 +374,26 @@ void test_order_of_accesses() {
               }
 }
 
+// A batch given up with weight gradients pending: the next one's forwards take the slots behind its chains, whatever streams
+// its caller uses.
+void test_dropped_microbatches() {
+  for (int n_streams = 1; n_streams <= 3; ++n_streams)
+    for (bool events : {false, true}) {
+      Program p({2, 64, 2, 256, 16, 1, 5, 3, 0, 0, 0, 0, false, false});
+      hipStream_t u = stream();
+      CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+      for (int i = 0; i < 2; ++i) { p.post(0, i, events); p.post(1, i, events); }
+      int32_t n = 0, left = 0;
+      CHECK(axonn_stage_poll(p.st, n_streams, u, &n, &left) == AXONN_OK && n == 4);
+      CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+      p.new_buffers();
+      u = stream();
+      p.post_batch(events);
+      CHECK(axonn_stage_run(p.st, n_streams, u) == AXONN_OK && axonn_stage_join(p.st, u) == AXONN_OK);
+      expect_ordered(p.c, n_streams, "given up");
+    }
+}
+
 // How many passes the microbatches of a batch make, forward and backward.
 void test_passes() {
   const auto passes = [](int s, int M, int limit, int group, int n_streams, bool events) {
@@ -416,6 +436,7 @@ void test_attach_after_failed_allocation() {
 int main() {
   test_order_of_accesses();
   test_weight_gradient_groups();
+  test_dropped_microbatches();
   test_passes();
   test_attach_after_failed_allocation();
   std::puts("stage runtime: all checks passed");
