@@ -172,9 +172,8 @@ int axonn_stage_post(axonn_stage_t* st, const axonn_msg* msg);
  * axonn_stage_join to make hip_stream wait for them in turn).  Messages without a done_event whose payloads
  * have arrived and whose buffers do not overlap may run together with the message that was taken
  * (at most 8 of one kind, on small stages only): one pass over all their tokens.  Each
- * microbatch's results are bit for bit those of a run by itself; the parameter gradients are the
- * same sums over the microbatches, whose rounding may differ in their order (and, with
- * grad_accum_fp32 = 0, in what has been run when a slot is needed).  Returns AXONN_ESTATE if messages remain but none can ever
+ * microbatch's results are bit for bit those of a run by itself; so are the weight and bias
+ * gradients; the LayerNorm gradients are the same sums over all tokens, in another order.  Returns AXONN_ESTATE if messages remain but none can ever
  * become admissible.  Work is only enqueued; see axonn_stage_synchronize. */
 int axonn_stage_run(axonn_stage_t* st, int32_t n_streams, void* hip_stream);
 /* The same loop without blocking: dispatches the posted messages that are admissible and have

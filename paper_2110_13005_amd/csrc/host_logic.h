@@ -10,6 +10,8 @@
 
 #include <algorithm>
 #include <cstddef>
+#include <deque>
+#include <vector>
 
 namespace axonn {
 namespace host {
@@ -78,7 +80,7 @@ void commit_backward(Slots& slots, int slot, bool wgrad_issued_with_chain, int* 
   slots[slot].state = wgrad_issued_with_chain ? SLOT_FREE : SLOT_AWAIT_WGRAD;
   --*in_flight;
 }
-// Weight-gradient passes over all waiting slots are issued (or a new batch drops them).
+// A weight-gradient pass over all waiting slots is issued (or a new batch drops them).
 template <class Slots>
 int release_awaiting(Slots& slots) {
   int n = 0;
@@ -95,25 +97,10 @@ inline int wgrad_action(bool last_of_batch, int group, int n_awaiting) {
   if (last_of_batch) return WGRAD_FLUSH_FINAL;
   return (group > 0 && n_awaiting >= group) ? WGRAD_FLUSH : WGRAD_NONE;
 }
-// The weight-gradient passes behind n backwards that run together, `n_awaiting` slots waiting before them: the same passes as
-// behind n that come one by one.  through[i]: how many of the n pass i takes them up to (the rest wait); returns the number of
-// passes, the batch's final one among them if the n end it.
-inline int wgrad_actions(bool last_of_batch, int group, int n_awaiting, int n, int* through) {
-  int passes = 0;
-  for (int i = 1, waiting = n_awaiting; i <= n; ++i) {
-    if (wgrad_action(last_of_batch && i == n, group, ++waiting) == WGRAD_NONE) continue;
-    through[passes++] = i;
-    waiting = 0;
-  }
-  return passes;
-}
-// Are the gradients of every backward so far complete once the work of the next `n` is queued (`n_awaiting` slots wait
-// before them)?  With checkpointing their weight gradients go with the chain; otherwise if a group closes behind the last.
-inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting, int n = 1) {
-  if (ckpt) return true;
-  int waiting = n_awaiting;
-  for (int i = 1; i < n; ++i) waiting = wgrad_action(false, group, waiting + 1) == WGRAD_NONE ? waiting + 1 : 0;
-  return wgrad_action(last_of_batch, group, waiting + 1) != WGRAD_NONE;
+// Are the gradients of every backward so far complete once the next one's work is queued (`n_awaiting` slots wait
+// before it)?  With checkpointing its weight gradients go with the chain; otherwise if a group closes.
+inline bool gradients_complete(bool ckpt, bool last_of_batch, int group, int n_awaiting) {
+  return ckpt || wgrad_action(last_of_batch, group, n_awaiting + 1) != WGRAD_NONE;
 }
 
 // ------------------------------------------------------------------------------ messages
@@ -144,6 +131,54 @@ int choose_message(size_t n_posted, Msg&& msg, Arrived&& arrived, const Slots& s
   }
   return -1;
 }
+
+// The stage as it would be if every message ran by itself.  What that decides does not change when messages run together: the
+// order in which messages are taken, and which microbatches' weight gradients are formed in one pass (so how their sums are
+// rounded, and what is pending when a batch is cut short).  Microbatches go by a number of their own here, as an id may come
+// again within a batch.
+class OneByOne {
+ public:
+  struct Place { int state = SLOT_FREE, mb_id = -1, number = -1; };
+  typedef std::vector<int> Pass;                  // numbers of one pass's microbatches, in the order of their sum
+
+  void new_batch(int n_slots) {
+    places.assign((size_t)n_slots, Place{});
+    in_flight = backwards = 0;
+    passes.clear();
+  }
+  // Of an admissible message; returns the microbatch's number (-1: it is not admissible).
+  int forward(int mb_id) {
+    if (find_free(places) < 0) close();
+    const int i = find_free(places);
+    if (i < 0) return -1;
+    commit_forward(places, i, mb_id, &in_flight);
+    return places[(size_t)i].number = next_number++;
+  }
+  int backward(int mb_id, bool ckpt) {
+    const int i = find_live(places, mb_id);
+    if (i < 0) return -1;
+    commit_backward(places, i, ckpt, &in_flight);
+    ++backwards;
+    return places[(size_t)i].number;
+  }
+  int awaiting() const { return count_state(places, SLOT_AWAIT_WGRAD); }
+  // The weight gradients of all waiting microbatches are formed here.
+  void close() {
+    Pass p;
+    for (const Place& q : places)
+      if (q.state == SLOT_AWAIT_WGRAD) p.push_back(q.number);
+    if (p.empty()) return;
+    passes.push_back(p);
+    release_awaiting(places);
+  }
+
+  std::vector<Place> places;
+  int in_flight = 0, backwards = 0;
+  std::deque<Pass> passes;     // closed, not yet taken by the stage
+
+ private:
+  int next_number = 0;
+};
 
 // How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself).  A small
 // microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to 2^24 elements of an
@@ -205,10 +240,11 @@ inline bool independent(const MessageSpan& earlier, const MessageSpan& later) {
          !overlap(earlier.out, earlier.out_end, later.out, later.out_end) &&
          !overlap(earlier.in, earlier.in_end, later.out, later.out_end);
 }
-// The posted messages that run together with `chosen` (the choice of choose_message, for which a forward has a free slot):
-// messages of its kind that have arrived, are admissible then and there, and are independent of every message posted before
-// them.  Their slots are consecutive, so that each tensor of the stash is one matrix over all their tokens.
-// span(i) -> MessageSpan of posted message i.  picked: positions, in slot order, the chosen message first; returns their number.
+// The messages that run together with `chosen` (which a forward has a free slot for), out of those in the order that OneByOne
+// takes them: messages of its kind that have arrived, are admissible then and there, and are independent of every message before
+// them.  A forward does not pass another one by: each then finds the slot that it has one by one.  Their slots are consecutive,
+// so that each tensor of the stash is one matrix over all their tokens.
+// span(i) -> MessageSpan of message i.  picked: positions, in slot order, the chosen message first; returns their number.
 template <class Slots, class Span, class Arrived>
 int merge_messages(size_t n_posted, Span&& span, Arrived&& arrived, int chosen, const Slots& slots, int in_flight,
                    int pipeline_limit, int max_merge, int* picked) {
@@ -220,7 +256,8 @@ int merge_messages(size_t n_posted, Span&& span, Arrived&& arrived, int chosen, 
     const MessageSpan m = span(i);
     if (m.kind != first.kind || m.alone || arrived(i) != 1) return false;
     for (size_t j = 0; j < i; ++j)
-      if (!independent(span(j), m)) return false;
+      if (!independent(span(j), m) || (m.kind == 0 && span(j).kind == 0 && arrived(j) == 1 && std::find(picked, picked + n, (int)j) == picked + n))
+        return false;
     for (int k = 0; k < n; ++k) {
       if ((size_t)picked[k] == i || span((size_t)picked[k]).mb_id == m.mb_id) return false;
       if ((size_t)picked[k] > i && !independent(m, span((size_t)picked[k]))) return false;

@@ -113,6 +113,7 @@ using host::SLOT_LIVE;
 struct Slot {
   int state = SLOT_FREE;
   int mb_id = -1;          // valid while SLOT_LIVE (forward issued, backward not yet)
+  int number = -1;         // the microbatch's number (host::OneByOne), valid until its weight gradients are formed
   std::vector<LayerStash> layers;
   // fwd_done: forward finished; dgrad_done: backward's activation-gradient chain finished;
   // released: the weight-gradient contraction that read the slot finished (slot reusable; null: never used).  Work that
@@ -126,6 +127,8 @@ struct Slot {
 
 struct PendingMsg {
   axonn_msg m;
+  int number = -1;         // the microbatch's (host::OneByOne), once the message is taken
+  bool complete = false;   // take_backward
 };
 
 // With activation checkpointing (Sec. 5.1) a slot keeps only the inputs of layers 0, ac, 2ac, ...; every
@@ -225,6 +228,8 @@ struct axonn_stage {
   hipEvent_t wgrad_tail = nullptr;
   // message-driven mode
   std::deque<PendingMsg> inbox;
+  std::deque<PendingMsg> taken;       // out of the inbox, in the order of `order`; run() dispatches all of them
+  host::OneByOne order;
   std::vector<hipStream_t> streams;
   std::vector<hipEvent_t> stream_tail;
   int fwd_rr = 0;
@@ -424,8 +429,8 @@ int backward_layer(axonn_stage* st, int l, const LayerStash& a, int n, elem_t* d
   return AXONN_OK;
 }
 
-// A microbatch as a message or a direct call names it: its id, payload and result.
-struct Work { int mb_id; const void* in; void* out; };
+// A microbatch as a message or a direct call names it: its id, payload and result; number and `complete`: see PendingMsg.
+struct Work { int mb_id; const void* in; void* out; int number; bool complete; };
 
 // Copies of n microbatches' payloads into the stash (`to_stash`) or of their results out of it; `stash` holds the first
 // one's rows, the others' follow.
@@ -512,43 +517,62 @@ int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
   return AXONN_OK;
 }
 
-// Weight gradients of slots that have finished their backward chain (see above): of all that wait, in one pass, or, behind a
-// chain of n_chain microbatches from slot `chain` on, in `passes` passes: pass i takes the chain's up to through[i], the first
-// one also those that have waited before.  In the batch's final call (`final`) the passes follow that chain (by its events, if it
+// A backward's turn has come: its microbatch's number, and whether the gradients of all backwards so far are complete behind it.
+int take_backward(axonn_stage* st, int mb_id, bool* complete) {
+  const bool ckpt = st->cfg.ckpt_stride > 0, last = st->order.backwards + 1 == st->cfg.n_microbatches;
+  const int awaiting = st->order.awaiting();
+  const int number = st->order.backward(mb_id, ckpt);
+  *complete = host::gradients_complete(ckpt, last, st->cfg.wgrad_group, awaiting);
+  if (*complete) st->order.close();
+  return number;
+}
+// The weight-gradient passes that are closed and whose microbatches have all run, in order.
+std::vector<std::vector<Slot*>> take_passes(axonn_stage* st) {
+  std::vector<std::vector<Slot*>> out;
+  while (!st->order.passes.empty()) {
+    const host::OneByOne::Pass& pass = st->order.passes.front();
+    std::vector<Slot*> members;
+    for (const int number : pass)
+      for (Slot& sl : st->slots)
+        if (sl.state == SLOT_AWAIT_WGRAD && sl.number == number) members.push_back(&sl);
+    if (members.size() < pass.size()) break;
+    out.push_back(members);
+    st->order.passes.pop_front();
+  }
+  return out;
+}
+
+// Weight gradients of slots that have finished their backward chain (see above), pass by pass.  In the batch's final call
+// (`final`, behind the chain of n_chain microbatches from slot `chain` on) the passes follow that chain (by its events, if it
 // runs on another stream: follow_chain) layer by layer from the last layer down, and finish each layer's gradients as soon as
 // its contractions are queued.
-int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* chain = nullptr, int n_chain = 0, const int* through = nullptr,
-                int passes = 1, bool final = false, bool follow_chain = false) {
-  std::vector<Slot*> ready;
-  std::vector<size_t> ends;           // of the passes, in `ready`
-  for (Slot& sl : st->slots)
-    if (sl.state == SLOT_AWAIT_WGRAD && (!chain || &sl < chain + through[0] || &sl >= chain + n_chain)) ready.push_back(&sl);
-  for (int i = 1; i < passes; ++i) {
-    ends.push_back(ready.size());
-    for (int k = through[i - 1]; k < through[i]; ++k) ready.push_back(chain + k);
+int flush_wgrad(axonn_stage* st, hipStream_t s, const std::vector<std::vector<Slot*>>& passes, Slot* chain = nullptr,
+                int n_chain = 0, bool final = false, bool follow_chain = false) {
+  if (passes.empty()) return AXONN_OK;
+  if (!final && passes.size() > 1) {
+    for (const auto& p : passes) AX_TRY(flush_wgrad(st, s, {p}));
+    return AXONN_OK;
   }
-  if (ready.empty()) return AXONN_OK;
-  ends.push_back(ready.size());
   const int L = st->cfg.n_layers;
   hipEvent_t waited = nullptr;
-  for (Slot* sl : ready)
-    if ((!final || sl < chain || sl >= chain + n_chain) && sl->dgrad_done != waited) {
-      waited = sl->dgrad_done;
-      HIP_TRY(hipStreamWaitEvent(s, waited, 0));
-    }
+  for (const auto& pass : passes)
+    for (Slot* sl : pass)
+      if ((!final || sl < chain || sl >= chain + n_chain) && sl->dgrad_done != waited) {
+        waited = sl->dgrad_done;
+        HIP_TRY(hipStreamWaitEvent(s, waited, 0));
+      }
   if (st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   for (int i = 0; i < L; ++i) {
     const int l = final ? L - 1 - i : i;
     if (final && follow_chain) HIP_TRY(hipStreamWaitEvent(s, st->chain_layer[l], 0));
-    size_t first = 0;
-    for (const size_t end : ends)
-      while (first < end) {
-        const int n = (int)std::min<size_t>(kMaxKSegments, end - first);
-        const int acc = (st->wgrad_flushes > 0 || first > 0) ? 1 : 0;
+    int acc = st->wgrad_flushes > 0 ? 1 : 0;
+    for (const auto& pass : passes)
+      for (size_t first = 0; first < pass.size(); first += kMaxKSegments) {
+        const int n = (int)std::min<size_t>(kMaxKSegments, pass.size() - first);
         const LayerStash* rec[kMaxKSegments];
-        for (int k = 0; k < n; ++k) rec[k] = &ready[first + k]->layers[l];
+        for (int k = 0; k < n; ++k) rec[k] = &pass[first + k]->layers[l];
         AX_TRY(wgrad_layer(st, l, rec, n, acc, s));
-        first += n;
+        acc = 1;
       }
     if (final) AX_TRY(finish_layer_grads(st, l, s));
   }
@@ -556,12 +580,14 @@ int flush_wgrad(axonn_stage* st, hipStream_t s, Slot* chain = nullptr, int n_cha
   if (final) st->grads_final_recorded = true;
   // several microbatches' input gradients are copied out of their slots behind the last layer of the chain
   if (final && follow_chain && n_chain > 1 && !st->embed) HIP_TRY(hipStreamWaitEvent(s, chain->dgrad_done, 0));
-  HIP_TRY(hipEventRecord(ready[0]->own.released, s));
-  for (Slot* sl : ready) {
-    sl->released = ready[0]->own.released;
-    sl->state = SLOT_FREE;
-  }
-  st->last_wgrad = ready[0]->own.released;
+  const hipEvent_t released = passes[0][0]->own.released;
+  HIP_TRY(hipEventRecord(released, s));
+  for (const auto& pass : passes)
+    for (Slot* sl : pass) {
+      sl->released = released;
+      sl->state = SLOT_FREE;
+    }
+  st->last_wgrad = released;
   return AXONN_OK;
 }
 
@@ -626,13 +652,9 @@ int embed_forward(axonn_embed* e, const int32_t* tokens, void* x, hipStream_t s)
 int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t ws) {
   const int mb_id = w[0].mb_id;
   int si = -1;
-  int adm = host::admit_forward(st->slots, mb_id, st->in_flight, st->cfg.pipeline_limit, &si);
-  if (adm == host::FWD_NEEDS_FLUSH) {
-    // every slot not in flight is waiting for its weight gradients: form them now
-    AX_TRY(flush_wgrad(st, ws));
-    adm = host::admit_forward(st->slots, mb_id, st->in_flight, st->cfg.pipeline_limit, &si);
-  }
-  switch (adm) {
+  // a pass that this forward has closed, or one before it, frees the slot it needs
+  AX_TRY(flush_wgrad(st, ws, take_passes(st)));
+  switch (host::admit_forward(st->slots, mb_id, st->in_flight, st->cfg.pipeline_limit, &si)) {
     case host::FWD_OK: break;
     case host::FWD_NEGATIVE_ID: return fail(AXONN_EINVAL, "forward: negative microbatch id %d", mb_id);
     case host::FWD_ALREADY_LIVE: return fail(AXONN_ESTATE, "forward: microbatch %d is already in flight", mb_id);
@@ -664,6 +686,7 @@ int do_forward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_t
   HIP_TRY(hipEventRecord(slot->own.fwd_done, s));
   for (int i = 0; i < n; ++i) {
     slot[i].fwd_done = slot->own.fwd_done;
+    slot[i].number = w[i].number;
     host::commit_forward(st->slots, si + i, w[i].mb_id, &st->in_flight);
   }
   return AXONN_OK;
@@ -681,30 +704,32 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   const int acc = st->bwd_count > 0 ? 1 : 0;
   const bool ckpt = st->cfg.ckpt_stride > 0;
   const bool last = st->bwd_count + n == st->cfg.n_microbatches;
-  const int awaiting = slots_in_state(st, SLOT_AWAIT_WGRAD);
   // the embedding's pass reads the input gradient behind this chain, when the slots may be in use again: a buffer of its own
   void* const dx = st->embed ? st->embed_dx : n == 1 ? w[0].out : merged_dx(*slot);
   if (ckpt) AX_TRY(backward_layers_ckpt(st, *slot, w[0].in, dx, acc, last, s, ws));
   else AX_TRY(backward_layers(st, *slot, w, n, dx, acc, last && ws != s, s));
   if (n > 1 && !st->embed) AX_TRY(copy_microbatches(st, w, n, merged_dx(*slot), false, s));
+  for (int i = 0; i < n; ++i) host::commit_backward(st->slots, si + i, ckpt, &st->in_flight);
+  const std::vector<std::vector<Slot*>> passes = take_passes(st);
+  int pending = slots_in_state(st, SLOT_AWAIT_WGRAD);
+  for (const auto& pass : passes) pending -= (int)pass.size();
+  bool complete = false;
+  for (int i = 0; i < n; ++i) complete = complete || w[i].complete;
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
-  if (!last && !st->cfg.grad_accum_fp32 && host::gradients_complete(ckpt, last, st->cfg.wgrad_group, awaiting, n))
-    AX_TRY(store_ln_grads(st, s));
+  if (!last && !st->cfg.grad_accum_fp32 && complete && pending == 0) AX_TRY(store_ln_grads(st, s));
   st->bwd_count += n;
   HIP_TRY(hipEventRecord(slot->own.dgrad_done, s));
   for (int i = 0; i < n; ++i) slot[i].dgrad_done = slot->own.dgrad_done;
   st->last_bwd = slot->own.dgrad_done;
-  for (int i = 0; i < n; ++i) host::commit_backward(st->slots, si + i, ckpt, &st->in_flight);
   if (ckpt) {
     // the weight gradients are already queued and read the shared sets: the slot (kept inputs only) is
     // free as soon as the chain on `s` is through
     slot->released = slot->dgrad_done;
     if (last) st->grads_final_recorded = true;
   } else {
-    int through[host::kMaxMerge];
-    const int passes = host::wgrad_actions(last, st->cfg.wgrad_group, awaiting, n, through);
-    if (passes) AX_TRY(flush_wgrad(st, ws, slot, n, through, passes, last, ws != s));
+    const bool final = host::wgrad_action(last, st->cfg.wgrad_group, pending) == host::WGRAD_FLUSH_FINAL;
+    AX_TRY(flush_wgrad(st, ws, passes, slot, n, final, ws != s));
   }
   return AXONN_OK;
 }
@@ -984,6 +1009,7 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
     st->max_merge_overlap = merge_limit(true);
   }
   st->slots.resize(cfg->pipeline_limit);
+  st->order.new_batch(cfg->pipeline_limit);
   for (Slot& s : st->slots) {
     CREATE_TRY(hipEventCreateWithFlags(&s.own.fwd_done, hipEventDisableTiming));
     CREATE_TRY(hipEventCreateWithFlags(&s.own.dgrad_done, hipEventDisableTiming));
@@ -1109,6 +1135,8 @@ int axonn_stage_zero_grad(axonn_stage_t* st, void* hip_stream) {
   for (Slot& sl : st->slots)
     if (sl.state == SLOT_AWAIT_WGRAD) sl.released = sl.dgrad_done;
   host::release_awaiting(st->slots);
+  st->order.new_batch(st->cfg.pipeline_limit);
+  for (; !st->taken.empty(); st->taken.pop_back()) st->inbox.push_front(st->taken.back());   // of a dispatch that failed
   st->bwd_count = 0;
   st->wgrad_flushes = 0;
   st->grads_final_recorded = false;
@@ -1134,7 +1162,10 @@ int axonn_stage_forward(axonn_stage_t* st, int32_t mb_id, const void* x, void* y
   if (st->embed || st->head)
     return fail(AXONN_ESTATE, "forward: a stage with the pipeline's ends attached runs in message-driven mode");
   HIP_TRY(hipSetDevice(st->cfg.device));
-  const Work w = {mb_id, x, y};
+  int si, number = -1;
+  const int adm = host::admit_forward(st->slots, mb_id, st->in_flight, st->cfg.pipeline_limit, &si);
+  if (adm == host::FWD_OK || adm == host::FWD_NEEDS_FLUSH) number = st->order.forward(mb_id);
+  const Work w = {mb_id, x, y, number, false};
   return do_forward(st, &w, 1, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
 }
 int axonn_stage_backward(axonn_stage_t* st, int32_t mb_id, const void* dy, void* dx, void* hip_stream) {
@@ -1142,7 +1173,8 @@ int axonn_stage_backward(axonn_stage_t* st, int32_t mb_id, const void* dy, void*
   if (st->embed || st->head)
     return fail(AXONN_ESTATE, "backward: a stage with the pipeline's ends attached runs in message-driven mode");
   HIP_TRY(hipSetDevice(st->cfg.device));
-  const Work w = {mb_id, dy, dx};
+  Work w = {mb_id, dy, dx, -1, false};
+  if (host::admit_backward(st->slots, mb_id) >= 0) w.number = take_backward(st, mb_id, &w.complete);
   return do_backward(st, &w, 1, (hipStream_t)hip_stream, (hipStream_t)hip_stream);
 }
 
@@ -1159,8 +1191,13 @@ int axonn_stage_post(axonn_stage_t* st, const axonn_msg* msg) {
   if (st->head && msg->kind == 0 && (!msg->targets_dev || !msg->loss_dev))
     return fail(AXONN_EINVAL, "post: a forward message to the last stage needs targets_dev and loss_dev");
   if (msg->mb_id < 0) return fail(AXONN_EINVAL, "post: negative microbatch id");
-  const auto posted = [st](size_t i) { return std::make_pair((int)st->inbox[i].m.kind, (int)st->inbox[i].m.mb_id); };
-  switch (host::check_post(msg->kind, msg->mb_id, st->inbox.size(), posted,
+  // messages that are taken but not dispatched are there only after a dispatch that has failed
+  const size_t n_taken = st->taken.size();
+  const auto posted = [st, n_taken](size_t i) {
+    const axonn_msg& m = i < n_taken ? st->taken[i].m : st->inbox[i - n_taken].m;
+    return std::make_pair((int)m.kind, (int)m.mb_id);
+  };
+  switch (host::check_post(msg->kind, msg->mb_id, n_taken + st->inbox.size(), posted,
                            msg->kind == 0 ? st->fwd_issued : st->bwd_issued, st->cfg.n_microbatches)) {
     case host::POST_DUPLICATE: return fail(AXONN_ESTATE, "post: duplicate message for microbatch %d", msg->mb_id);
     case host::POST_SURPLUS:
@@ -1215,7 +1252,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
   // what a message reads and writes: activations, or, from the first stage's embedding on, token ids
   const uint64_t act_bytes = (uint64_t)st->T * st->h * sizeof(elem_t);
   const auto span = [st, act_bytes](size_t i) {
-    const axonn_msg& m = st->inbox[i].m;
+    const axonn_msg& m = st->taken[i].m;
     const uint64_t in = (uint64_t)(uintptr_t)m.payload_dev, out = (uint64_t)(uintptr_t)m.result_dev;
     const bool result = out != 0 && !(st->embed && (m.kind == 1 || st->head));
     return host::MessageSpan{m.kind, m.mb_id, m.done_event != nullptr, in,
@@ -1223,13 +1260,24 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
                              result ? out : 0, result ? out + act_bytes : 0};
   };
   while (st->fwd_issued < M || st->bwd_issued < M) {
-    // first posted message that has arrived and is admissible
+    // The first posted message that has arrived and is admissible, and, where messages may run together, those that would
+    // follow it at once.
+    const int max_merge = n_streams > 1 ? st->max_merge_overlap : st->max_merge;
     bool any_admissible = false;
-    int err = 0;
-    const int chosen = host::choose_message(st->inbox.size(), posted, arrived, st->slots, st->in_flight,
-                                            st->cfg.pipeline_limit, &any_admissible, &err);
-    if (err) return fail(AXONN_EHIP, "run: hipEventQuery failed: %s", hipGetErrorString(query_error));
-    if (chosen < 0) {
+    while (st->taken.empty() || max_merge > 1) {
+      int err = 0;
+      const int chosen = host::choose_message(st->inbox.size(), posted, arrived, st->order.places, st->order.in_flight,
+                                              st->cfg.pipeline_limit, &any_admissible, &err);
+      if (err && st->taken.empty()) return fail(AXONN_EHIP, "run: hipEventQuery failed: %s", hipGetErrorString(query_error));
+      if (chosen < 0) break;
+      PendingMsg msg = st->inbox[chosen];
+      st->inbox.erase(st->inbox.begin() + chosen);
+      if (msg.m.kind == 0) msg.number = st->order.forward(msg.m.mb_id);
+      if (msg.m.kind == 1 || st->head)               // the last stage's Backward follows at once
+        msg.number = take_backward(st, msg.m.mb_id, &msg.complete);
+      st->taken.push_back(msg);
+    }
+    if (st->taken.empty()) {
       if (!blocking) break;
       if (!any_admissible)
         return fail(AXONN_ESTATE,
@@ -1245,28 +1293,28 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
       continue;
     }
     wait.dispatched();
-    const axonn_msg m = st->inbox[chosen].m;
+    const axonn_msg m = st->taken[0].m;
     const bool join_all = st->join_all;
     st->join_all = true;                        // until the dispatch is through
     // a forward needs its slot before it is known which messages run with it
-    if (m.kind == 0 && host::find_free(st->slots) < 0) AX_TRY(flush_wgrad(st, ws));
+    if (m.kind == 0) AX_TRY(flush_wgrad(st, ws, take_passes(st)));
     int picked[host::kMaxMerge];
-    const int n = host::merge_messages(st->inbox.size(), span, arrived, chosen, st->slots, st->in_flight,
-                                       st->cfg.pipeline_limit, n_streams > 1 ? st->max_merge_overlap : st->max_merge, picked);
+    const int n = host::merge_messages(st->taken.size(), span, [](size_t) { return 1; }, 0, st->slots, st->in_flight,
+                                       st->cfg.pipeline_limit, max_merge, picked);
     const int si = host::stream_index(m.kind, n_streams, &st->fwd_rr);
     hipStream_t s = st->streams[si];
     Work w[host::kMaxMerge];
     const int32_t* targets[host::kMaxMerge];
     float* loss[host::kMaxMerge];
     for (int i = 0; i < n; ++i) {
-      const axonn_msg& mi = st->inbox[picked[i]].m;
-      w[i] = Work{mi.mb_id, mi.payload_dev, mi.result_dev};
+      const axonn_msg& mi = st->taken[picked[i]].m;
+      w[i] = Work{mi.mb_id, mi.payload_dev, mi.result_dev, st->taken[picked[i]].number, st->taken[picked[i]].complete};
       targets[i] = (const int32_t*)mi.targets_dev;
       loss[i] = (float*)mi.loss_dev;
       if (mi.ready_event) HIP_TRY(hipStreamWaitEvent(s, (hipEvent_t)mi.ready_event, 0));
     }
     std::sort(picked, picked + n);
-    for (int i = n - 1; i >= 0; --i) st->inbox.erase(st->inbox.begin() + picked[i]);
+    for (int i = n - 1; i >= 0; --i) st->taken.erase(st->taken.begin() + picked[i]);
     if (m.kind == 0) {
       AX_TRY(do_forward(st, w, n, s, ws));
       st->fwd_issued += n;
@@ -1286,7 +1334,7 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
           Slot& slot = st->slots[si + i];
           elem_t* const dx = st->cfg.ckpt_stride > 0 ? st->head_dx : slot.layers[st->cfg.n_layers - 1].dz;
           AX_TRY(head_forward_backward(st->head, slot.head_y, targets[i], loss[i], dx, bs));
-          back[i] = Work{w[i].mb_id, dx, w[i].out};
+          back[i] = Work{w[i].mb_id, dx, w[i].out, w[i].number, w[i].complete};
         }
         AX_TRY(backward_msg(st, back, n, bs, ws));
         st->bwd_issued += n;
@@ -1813,7 +1861,7 @@ int axonn_head_forward_backward(axonn_head_t* hd, const void* x_dev_bf16, const 
 
 int axonn_stage_attach_ends(axonn_stage_t* st, axonn_embed_t* embed, axonn_head_t* head) {
   if (!st) return fail(AXONN_EINVAL, "attach_ends: null handle");
-  if (st->in_flight || !st->inbox.empty()) return fail(AXONN_ESTATE, "attach_ends: work in flight");
+  if (st->in_flight || !st->inbox.empty() || !st->taken.empty()) return fail(AXONN_ESTATE, "attach_ends: work in flight");
   if (embed && (embed->h != st->h || embed->s != st->cfg.seq_len || embed->b != st->cfg.microbatch_size ||
                 embed->device != st->cfg.device))
     return fail(AXONN_EINVAL, "attach_ends: the embedding's hidden size, sequence length, microbatch size or device "

@@ -7,6 +7,7 @@
 
 #include <cstdio>
 #include <cstdlib>
+#include <map>
 #include <random>
 #include <set>
 #include <string>
@@ -40,12 +41,14 @@ struct ModelStage {
   std::vector<std::pair<int, int>> log;            // (kind, mb) in dispatch order
   std::vector<std::vector<int>> wgrad_passes;      // microbatches of each weight-gradient pass
   std::vector<int> awaiting_mb;                    // microbatch of each slot in AWAIT_WGRAD, by slot
+  OneByOne order;                                  // told of the same messages
+  std::map<int, int> mb_of;                        // its number -> microbatch
   std::vector<int> stream_of;                      // stream index per dispatched message
   bool final_pass_seen = false;
   int max_in_flight = 0;
 
   ModelStage(int M_, int P_, int group_, int n_streams_, bool ckpt_ = false)
-      : M(M_), P(P_), group(group_), n_streams(n_streams_), ckpt(ckpt_), slots(P_), awaiting_mb(P_, -1) {}
+      : M(M_), P(P_), group(group_), n_streams(n_streams_), ckpt(ckpt_), slots(P_), awaiting_mb(P_, -1) { order.new_batch(P); }
 
   int post(int kind, int mb, long ready_at) {
     const auto posted = [this](size_t i) { return std::make_pair(inbox[i].kind, inbox[i].mb_id); };
@@ -72,6 +75,7 @@ struct ModelStage {
     }
     if (adm != FWD_OK) return adm;
     commit_forward(slots, si, mb, &in_flight);
+    mb_of[order.forward(mb)] = mb;
     max_in_flight = std::max(max_in_flight, in_flight);
     return FWD_OK;
   }
@@ -81,6 +85,8 @@ struct ModelStage {
     const bool last = bwd_count + 1 == M;
     ++bwd_count;
     commit_backward(slots, si, ckpt, &in_flight);
+    CHECK(mb_of[order.backward(mb, ckpt)] == mb && order.in_flight == in_flight && order.backwards == bwd_count);
+    if (!ckpt && gradients_complete(false, last, group, order.awaiting() - 1)) order.close();
     if (ckpt) {
       wgrad_passes.push_back({mb});
     } else {
@@ -141,6 +147,13 @@ struct ModelStage {
     for (int i = 0; i < M; ++i) CHECK(seen.count(i) == 1);
     CHECK(count_state(slots, SLOT_AWAIT_WGRAD) == 0 && in_flight == 0);
     if (!ckpt) CHECK(final_pass_seen);
+    // the passes that OneByOne closes
+    std::vector<std::vector<int>> closed;
+    for (const OneByOne::Pass& p : order.passes) {
+      closed.emplace_back();
+      for (int number : p) closed.back().push_back(mb_of.at(number));
+    }
+    CHECK(closed == (ckpt ? std::vector<std::vector<int>>() : wgrad_passes));
   }
 };
 
@@ -404,17 +417,20 @@ void test_merged_messages() {
   slots[2].state = SLOT_AWAIT_WGRAD;           // consecutive free slots only
   CHECK(merge(0, 0, 6, 8) == 2);
   slots[2].state = SLOT_FREE;
-  here[1] = 0;                                 // not arrived: passed over, and so is one whose completion is waited for
-  box[2].alone = true;
-  CHECK(merge(0, 0, 6, 8) == 4 && picked[1] == 3 && picked[2] == 4 && picked[3] == 5);
-  CHECK(merge(2, 0, 6, 8) == 1);
+  here[1] = 0;                                 // not arrived: passed over
+  CHECK(merge(0, 0, 6, 8) == 5 && picked[1] == 2 && picked[4] == 5);
+  box[2].alone = true;                         // its completion is waited for: by itself, and no later forward passes it by
+  CHECK(merge(0, 0, 6, 8) == 1 && merge(2, 0, 6, 8) == 1);
   here[1] = 1;
+  CHECK(merge(0, 0, 6, 8) == 2);
   box[2].alone = false;
   box[3].in = box[1].out + 50; box[3].in_end = box[3].in + 100;        // message 3 reads what message 1 (and 2) writes
-  CHECK(merge(0, 0, 6, 8) == 5 && picked[3] == 4);
+  CHECK(merge(0, 0, 6, 8) == 3);
+  box[3].in = 1300; box[3].in_end = 1400;
+  CHECK(merge(0, 0, 6, 8) == 6);
   box[4].out = box[2].in; box[4].out_end = box[2].in_end;              // message 4 overwrites what message 2 reads
   box[5].out = box[0].out; box[5].out_end = box[0].out_end;            // two results in one buffer
-  CHECK(merge(0, 0, 6, 8) == 3);
+  CHECK(merge(0, 0, 6, 8) == 4);
 
   // backwards: the microbatches of the slots behind the chosen one's, in slot order, also past a forward between them
   box.clear(); here.clear();
@@ -426,7 +442,6 @@ void test_merged_messages() {
   CHECK(merge(0, 6, 6, 8) == 1);
   slots[2].state = SLOT_AWAIT_WGRAD;
   CHECK(merge(0, 6, 6, 8) == 1);
-  CHECK(!gradients_complete(false, false, 4, 1, 2) && gradients_complete(false, false, 4, 1, 3));
 
   // whatever is merged is a subset of what the loop could have taken one by one, in every state
   std::mt19937 rng(9);

@@ -331,10 +331,38 @@ void test_weight_gradient_groups() {
   };
   for (int n_streams = 1; n_streams <= 3; ++n_streams) {
     CHECK((segments(8, 8, 3, n_streams, false) == std::vector<int>{3, 3, 2}));
+    // where slots run out a forward closes a group: here after each of the first five
+    CHECK((segments(8, 3, 0, n_streams, false) == std::vector<int>{1, 1, 1, 1, 1, 3}));
     for (int M = 2; M <= 9; ++M)
-      for (int group = 0; group <= 4; ++group) CHECK(segments(M, M, group, n_streams, false) == segments(M, M, group, n_streams, true));
+      for (int limit = 2; limit <= M; ++limit)
+        for (int group = 0; group <= 4; ++group)
+          CHECK(segments(M, limit, group, n_streams, false) == segments(M, limit, group, n_streams, true));
   }
 
+  // a batch cut short is accepted or refused by what a run one by one leaves pending
+  for (int limit = 1; limit <= 4; ++limit)
+    for (int group = 0; group <= 3; ++group)
+      for (int cut = 1; cut < 8; ++cut)
+        for (int n_streams = 1; n_streams <= 2; ++n_streams) {
+          int status[2];
+          for (bool events : {false, true}) {
+            Program p({1, 256, 4, 1024, 64, 1, 8, limit, group, 0, 0, 0, false, false});
+            hipStream_t u = stream();
+            CHECK(axonn_stage_zero_grad(p.st, u) == AXONN_OK);
+            for (int i = 0; i < std::min(limit, cut); ++i) p.post(0, i, events);
+            for (int i = 0; i < cut; ++i) {
+              p.post(1, i, events);
+              if (limit + i < cut) p.post(0, limit + i, events);
+            }
+            int32_t n = 0, left = 0;
+            CHECK(axonn_stage_poll(p.st, n_streams, u, &n, &left) == AXONN_OK && n == 2 * cut);
+            uint64_t bad = 0;
+            status[events] = axonn_stage_count_nonfinite_grads(p.st, u, &bad);
+            expect_ordered(p.c, n_streams, "cut short");
+          }
+          if (status[0] != status[1]) std::printf("limit %d group %d cut %d: %d, one by one %d\n", limit, group, cut, status[0], status[1]);
+          CHECK(status[0] == status[1]);
+        }
   // a batch cut short at a multiple of the group: no weight gradients are pending, and the optimizer's calls accept it
   for (int n_streams = 1; n_streams <= 3; ++n_streams) {
     Program p({1, 256, 4, 1024, 64, 1, 8, 4, 3, 0, 0, 0, false, false});
