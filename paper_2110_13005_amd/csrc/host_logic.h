@@ -180,47 +180,49 @@ class OneByOne {
   int next_number = 0;
 };
 
-// How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself).  A small
-// microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to 2^24 elements of an
-// activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of 256 x 256.
-// Whole batches of two layers, 2 streams, ms, by the largest activation of a pass (a slot per microbatch but for the last):
+// How many microbatches of T tokens may run as one pass over their concatenated tokens (1: each by itself); `overlap`: on
+// several streams.  A small microbatch is bound by the latency of its launches and by tiles that do not fill the chip; up to
+// 2^24 elements of an activation the narrowest contraction of a layer (T x h outputs) has at most a round of 256 tiles of
+// 256 x 256.  Whole batches of two layers with a slot per microbatch, 2 streams, ms, by the largest activation of a pass:
 //   hidden, tokens, microbatches    each alone   2^22    2^23    2^24    2^25
-//   1024, 1024, 8                      2.84      2.28    2.08    2.07    2.09
-//   2048, 2048, 8                     11.01     10.96   10.25   10.21    9.92
-//   2048, 2048, 2                      2.88      2.87    2.67    2.67    2.67
-//   2048, 2048, 3                      4.19      4.19    4.01    4.07    4.06
-//   4096, 2048, 4                     17.2      17.2    17.2    16.0    16.0
-//   4096, 1024, 6                     14.18     14.16   13.14   14.31   13.15      (passes of 1, 1, 2, 3 and 6)
-//   6144, 512, 8                      22.0      22.0    19.8    19.3    19.1
-//   1024, 4096, 6 (3 slots)            5.89      5.89    5.60    5.58    5.62
+//   1024, 1024, 8                      2.92      2.40    2.17    2.17    2.17
+//   2048, 2048, 8                     11.04     11.09   10.19   10.08    9.89
+//   2048, 2048, 2                      2.95      2.95    2.75    2.76    2.75
+//   4096, 2048, 4                     17.0      17.0    17.0    15.9    15.7
+//   4096, 1024, 6                     14.01     14.01   13.03   14.21   12.99      (passes of 1, 1, 2, 3 and 6)
+//   6144, 512, 8                      21.9      21.9    19.7    19.2    18.9
 // Beyond 2^24 little is gained, and results come later than they have to.
 constexpr int kMaxMerge = 8;
 constexpr int64_t kMergeElements = int64_t(1) << 24;
 // A backward pass of several microbatches keeps a gradient of h columns and one float per head in the place of the f columns
 // of GeLU': narrower MLPs run one by one.
-// The slots are dealt to passes of equal size.  With fewer slots than microbatches a pass takes at most 4 of them, and never
-// all of an odd number: a pass that holds every slot has nothing to overlap with.  8 microbatches of 1280 tokens at h 1536, by
-// the size of a pass, ms:
+// The slots are dealt to passes of equal size (a smaller size where its T x h outputs fill the rounds of 256 tiles better was
+// slower on 60 of 110 random stages, by up to 15 %).  With fewer slots than microbatches a pass takes at most 4 of them, and
+// never all of an odd number: a pass that holds every slot has nothing to overlap with.  8 microbatches of 1280 tokens at h 1536,
+// by the size of a pass, ms:
 //   slots      1       2       3       4       5       6       8
-//   2        6.26    6.34
-//   3        6.64    6.10    5.86
-//   4        6.00    5.29    5.31    5.03
-//   5        5.90    5.44    5.05    5.04    5.27
-//   6        5.86    5.23    5.08    4.99    5.24    5.31
-//   8        5.72    5.22    5.03    4.72    4.98    4.89    4.62
-// Two slots and an odd number of microbatches: the last one's two passes stand behind all others with nothing beside them,
-// where on several streams (`overlap`) every forward runs beside a backward if they come one by one.  Random stages with 3 to 7
-// microbatches, 2 or 3 streams, one by one / together: up to 2^20 elements 0.99 to 1.4 (67 stages), above it 0.89 to 1.12, 0.98 on
-// average (44); with weight-gradient passes of one microbatch each up to 2^18 elements 1.02 to 1.27 (13; one 0.94), above it
-// 0.85 to 1.11, 0.97 on average (39).  On one stream 34 stages of all sizes gained.
-inline int merge_limit(int64_t T, int64_t h, int64_t f, int64_t heads, int slots, int n_microbatches, bool overlap = false,
-                       int wgrad_group = 0) {
+//   2        6.35    6.93
+//   3        6.76    6.43    6.54
+//   4        6.14    5.57    5.83    5.67
+//   5        6.07    5.85    5.59    5.80    5.98
+//   6        6.02    5.39    5.63    5.61    5.87    5.77
+//   8        5.80    5.33    5.28    4.83    5.16    5.10    4.81
+// On several streams the forwards of single microbatches run beside backwards, which is worth more the better one of them
+// fills the chip and the fewer slots there are.  Random stages with fewer slots than microbatches, one by one / together:
+//   2 slots, even number      up to 2^20 elements 0.98 to 1.31 (26 stages), above 0.89 to 1.17, mean 0.98 (28)
+//   2 slots, odd number       up to 2^17          0.95 to 1.15 (7),         above 0.88 to 1.14, mean 0.99 (16)
+//   3 slots                   up to 2^20          0.98 to 1.59 (58),        above 0.95 to 1.31, mean 1.04 (60)
+//   4 slots                   up to 2^21          0.99 to 1.76 (57),        above 0.96 to 1.10, mean 1.02 (12)
+//   more                      1.01 to 1.94 at all sizes (60)
+// (an odd number leaves the last microbatch's two passes behind all others; the upper ends are stages whose streams shared a
+// hardware queue).  On one stream all gain.
+inline int merge_limit(int64_t T, int64_t h, int64_t f, int64_t heads, int slots, int n_microbatches, bool overlap = false) {
   if (f < h + 2 * heads) return 1;
   const int64_t elements = T * std::max<int64_t>(h, (f + 3) / 4);
   const int64_t fits = std::min<int64_t>(kMaxMerge, kMergeElements / elements);
   if (fits < 1) return 1;
   const bool refill = slots < n_microbatches;
-  if (overlap && refill && slots == 2 && n_microbatches % 2 && elements > int64_t(1) << (wgrad_group == 1 ? 18 : 20)) return 1;
+  if (overlap && refill && slots <= 4 && elements > int64_t(1) << (slots == 4 ? 21 : slots == 2 && n_microbatches % 2 ? 17 : 20)) return 1;
   const int64_t most = refill ? std::min<int64_t>(fits, 4) : fits;
   const int64_t passes = std::max<int64_t>((slots + most - 1) / most, refill && slots > 1 && slots % 2 ? 2 : 1);
   return (int)((slots + passes - 1) / passes);

@@ -1003,7 +1003,7 @@ int axonn_stage_create(const axonn_stage_config* cfg, axonn_stage_t** out) {
   const int ac = cfg->ckpt_stride;
   if (ac == 0) {
     const auto merge_limit = [&](bool overlap) {
-      return host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches, overlap, cfg->wgrad_group);
+      return host::merge_limit(T, h, f, cfg->n_heads, cfg->pipeline_limit, cfg->n_microbatches, overlap);
     };
     st->max_merge = merge_limit(false);
     st->max_merge_overlap = merge_limit(true);

@@ -389,13 +389,14 @@ void test_merged_messages() {
   CHECK(limit_of(2048, 2048, 32768, 8, 8) == 1 && limit_of(256, 256, 256, 8, 8) == 1 && limit_of(256, 256, 264, 8, 8) == 8);
   const int refilled[9] = {0, 1, 2, 2, 4, 3, 3, 4, 4};       // fewer slots than microbatches
   for (int p = 1; p <= 8; ++p) CHECK(limit_of(256, 256, 1024, p, 16) == refilled[p]);
-  // two slots and an odd number of microbatches on several streams: up to 2^20 elements, 2^18 with weight gradients one by one
-  const auto two_slots = [](int64_t T, int64_t f, int slots, int M, bool overlap, int group) { return merge_limit(T, 256, f, 4, slots, M, overlap, group); };
-  CHECK(two_slots(4096, 1024, 2, 3, true, 0) == 2 && two_slots(4104, 1024, 2, 3, true, 0) == 1 && two_slots(4096, 1032, 2, 7, true, 3) == 1);
-  CHECK(two_slots(1024, 1024, 2, 3, true, 1) == 2 && two_slots(1032, 1024, 2, 3, true, 1) == 1 && two_slots(1032, 1024, 2, 3, true, 3) == 2);
-  for (int group : {0, 1, 3})
-    CHECK(two_slots(8192, 1024, 2, 3, false, group) == 2 && two_slots(8192, 1024, 2, 4, true, group) == 2 &&
-          two_slots(8192, 1024, 2, 2, true, group) == 2 && two_slots(8192, 1024, 4, 5, true, group) == 4);
+  // few slots and several streams: up to 2^20 elements with two or three (2^17 with two and an
+  // odd number of microbatches), 2^21 with four
+  const auto overlapped = [](int64_t T, int slots, int M, bool overlap = true) { return merge_limit(T, 256, 1024, 4, slots, M, overlap); };
+  CHECK(overlapped(4096, 2, 4) == 2 && overlapped(4104, 2, 4) == 1 && overlapped(512, 2, 3) == 2 && overlapped(520, 2, 3) == 1);
+  CHECK(overlapped(4096, 3, 4) == 2 && overlapped(4104, 3, 5) == 1 && overlapped(8192, 4, 5) == 4 && overlapped(8200, 4, 5) == 1);
+  CHECK(overlapped(8200, 5, 6) == 3 && overlapped(8200, 2, 2) == 2 && overlapped(8200, 4, 4) == 4 && limit_of(4097, 256, 1028, 2, 4) == 2);
+  for (int slots = 1; slots <= 8; ++slots)
+    for (int M = slots; M <= 9; ++M) CHECK(overlapped(8200, slots, M, false) >= overlapped(8200, slots, M));
 
   std::vector<MessageSpan> box;
   std::vector<int> here;                       // arrived(i)

@@ -437,10 +437,10 @@ void test_passes() {
   for (int n_streams = 1; n_streams <= 3; ++n_streams) {
     CHECK(passes(64, 8, 8, 0, n_streams, false) == Passes(1, 1) && passes(64, 8, 8, 0, n_streams, true) == Passes(8, 8));
     CHECK(passes(64, 8, 4, 0, n_streams, false) == Passes(2, 2) && passes(64, 4, 2, 0, n_streams, false) == Passes(2, 2));
-    // two slots, an odd number of microbatches: together on one stream, on several only small ones
-    CHECK(passes(4096, 3, 2, 0, n_streams, false) == Passes(2, 2) && passes(1024, 3, 2, 1, n_streams, false) == Passes(2, 2));
-    const Passes large = n_streams == 1 ? Passes(2, 2) : Passes(3, 3);
-    CHECK(passes(4160, 3, 2, 0, n_streams, false) == large && passes(1088, 3, 2, 1, n_streams, false) == large);
+    // two slots: together on one stream, on several only small ones
+    CHECK(passes(512, 3, 2, 0, n_streams, false) == Passes(2, 2) && passes(4096, 4, 2, 1, n_streams, false) == Passes(2, 2));
+    CHECK(passes(576, 3, 2, 0, n_streams, false) == (n_streams == 1 ? Passes(2, 2) : Passes(3, 3)));
+    CHECK(passes(4160, 4, 2, 1, n_streams, false) == (n_streams == 1 ? Passes(2, 2) : Passes(4, 4)));
   }
 }
 
