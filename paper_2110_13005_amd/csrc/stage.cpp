@@ -1261,10 +1261,10 @@ int run_loop(axonn_stage* st, int n_streams, void* hip_stream, bool blocking, in
   };
   while (st->fwd_issued < M || st->bwd_issued < M) {
     // The first posted message that has arrived and is admissible, and, where messages may run together, those that would
-    // follow it at once.
+    // follow it at once.  Not behind one that is waited for: what arrives while that is dispatched may come before the others.
     const int max_merge = n_streams > 1 ? st->max_merge_overlap : st->max_merge;
     bool any_admissible = false;
-    while (st->taken.empty() || max_merge > 1) {
+    while (st->taken.empty() || (max_merge > 1 && !st->taken.back().m.done_event)) {
       int err = 0;
       const int chosen = host::choose_message(st->inbox.size(), posted, arrived, st->order.places, st->order.in_flight,
                                               st->cfg.pipeline_limit, &any_admissible, &err);
