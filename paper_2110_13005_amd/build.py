@@ -21,7 +21,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          "-Wall", "-Wno-unused-function",
          # the GEMM main loops are written as fully unrolled loops over compile-time schedules (`#pragma unroll`):
          # left partly rolled, their fragment arrays would live in scratch memory instead of registers
-         "-mllvm", "-pragma-unroll-threshold=100000"]
+         "-mllvm", "-pragma-unroll-threshold=1000000"]
 
 
 def _compile(job):

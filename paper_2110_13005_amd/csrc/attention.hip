@@ -31,73 +31,144 @@ __device__ __forceinline__ float max_with_other_half(float v) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// The kernels are compiled for head dimensions D = 64, 128 and 192.  EXACT: the head dimension is D.
-// Otherwise the real head dimension d (a multiple of 4, d <= D) is a run-time argument and the columns
-// d .. D-1 of every head read as zero and are never written: zero columns add nothing to q.k, and the
-// padded columns of V give output columns nobody stores.  Heads then start at multiples of 8 bytes only, so
-// the 8 elements at columns [col, col + 8) of a head row are fetched as two 8-byte halves.
-template <bool EXACT>
-__device__ __forceinline__ uint4 load_cols8(const elem_t* p, int col, int d) {
-  if (EXACT) return *reinterpret_cast<const uint4*>(p);
-  uint4 v = make_uint4(0, 0, 0, 0);
-  if (col + 4 <= d) {
-    const uint2 lo = *reinterpret_cast<const uint2*>(p);
-    v.x = lo.x; v.y = lo.y;
+// The kernels are compiled for tiles of D = 64, 128 and 192 columns; a head of any dimension d that is a multiple of 4 runs
+// in the next of them.  The tile starts at the 16-byte boundary at or in front of the head: a multiple of 8 columns always,
+// or, where d is an odd multiple of 4 and the head is an odd one, 4 columns into the head before (`shift`).  So every chunk
+// of 16 bytes is aligned.  Chunks behind the head's last column read as zeros; the one chunk that is half another head's
+// (d an odd multiple of 4) has that half cleared in LDS.  Zero columns add nothing to a product over columns, and result
+// columns outside the head are never stored.
+struct HeadColumns {
+  int d, shift;
+  __device__ __forceinline__ HeadColumns(int d, int hd) : d(d), shift(d & 4 ? 4 * (hd & 1) : 0) {}
+  __device__ __forceinline__ int chunks() const { return (d + shift + 7) >> 3; }
+  __device__ __forceinline__ bool split() const { return d & 4; }
+  // byte within a row of the half chunk that is another head's
+  __device__ __forceinline__ int foreign() const { return shift ? 0 : 2 * d; }
+  __device__ __forceinline__ bool has4(int col) const { return col >= shift && col + 4 <= d + shift; }
+};
+
+// LDS tile of R rows x D columns: D / 64 blocks of 64 columns, each R rows of 128 bytes, no padding.  Row r holds its 16-byte
+// chunk c in place c ^ swizzle(r).  Both ways of reading are free of bank conflicts: 128-bit reads of 16 rows at one chunk
+// find 16 different places of the 256 bytes that two rows span, and the transposing 64-bit reads, which take 64 bytes from
+// each of 4 consecutive rows per half wave, find 4 different 64-byte quarters of it.  Clocks per wave instruction: 4.0 and
+// 2.3; with padded rows (76 words, the best stride for both) 4.0 and 4.0.  A tile is filled by the memory pipeline,
+// 1 KB (8 rows of one block) per instruction.
+struct LdsBytes {                     // a place in LDS, without the checks of a generic pointer's conversions
+  AXONN_LDS char* p;
+  __device__ __forceinline__ explicit LdsBytes(char* shared) : p((AXONN_LDS char*)shared) {}
+  __device__ __forceinline__ LdsBytes operator+(uint32_t bytes) const { LdsBytes r = *this; r.p += bytes; return r; }
+};
+__device__ __forceinline__ int tile_swizzle(int row) { return ((row & 2) << 1) | ((row >> 2) & 3); }
+template <int R, int D>
+struct Tile {
+  static constexpr int BYTES = R * D * 2, BLOCK = R * 128;
+  static __device__ __forceinline__ int chunk_at(int row, int ch) { return (ch >> 3) * BLOCK + row * 128 + (((ch & 7) ^ tile_swizzle(row)) << 4); }
+};
+// What a lane adds to a tile's address for its fragments: k-contiguous ones (MFMA operand rows = tile rows, contracted
+// over columns) by the fragment's columns modulo 64, k-strided ones (operand rows = tile columns, contracted over tile
+// rows, in the order in which an MFMA result tile keeps its m index in registers) by the fragment's columns modulo 64
+// and the half of its 16 tile rows.
+struct FragLanes {
+  uint32_t kc[4], tr[2][2];
+  __device__ __forceinline__ FragLanes(int lane) {
+    const int g = lane >> 5, row = lane & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) kc[j] = row * 128 + (((2 * j + g) ^ tile_swizzle(row)) << 4);
+    const int t = lane & 15, half = (lane >> 4) & 1;
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int hi = 0; hi < 2; ++hi) {
+        const int r = 8 * hi + 4 * g + (t >> 2), ch = 4 * b + 2 * half + ((t & 3) >> 1);
+        tr[b][hi] = r * 128 + ((ch ^ tile_swizzle(r)) << 4) + ((t & 1) << 3);
+      }
   }
-  if (col + 8 <= d) {
-    const uint2 hi = *reinterpret_cast<const uint2*>(p + 4);
-    v.z = hi.x; v.w = hi.y;
-  }
-  return v;
+};
+// rows 32 r32 .., columns 16 kk ..
+template <int R, int D>
+__device__ __forceinline__ elemx8 frag_rows(LdsBytes tile, const FragLanes& f, int r32, int kk) {
+  return *(const AXONN_LDS elemx8*)(tile.p + ((kk >> 2) * Tile<R, D>::BLOCK + r32 * (32 * 128)) + f.kc[kk & 3]);
+}
+// columns 32 dt .., rows 16 r16 ..
+template <int R, int D>
+__device__ __forceinline__ elemx8 frag_cols(LdsBytes tile, const FragLanes& f, int r16, int dt) {
+  AXONN_LDS char* p = tile.p + ((dt >> 1) * Tile<R, D>::BLOCK + r16 * (16 * 128));
+  union { elemx8 v; short4v h[2]; } u;
+  u.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((AXONN_LDS short4v*)(p + f.tr[dt & 1][0]));
+  u.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((AXONN_LDS short4v*)(p + f.tr[dt & 1][1]));
+  return u.v;
 }
 
-// Cooperative copy of a ROWS x D bf16 tile (rows row0.., zero beyond n_rows) by 256 threads:
-// global -> registers, then registers -> LDS with leading dimension LD.
-template <int ROWS, int D>
-struct TileRegs {
-  static constexpr int NCH = ROWS * D / 8 / 256;
-  uint4 r[NCH];
-  template <bool EXACT>
-  __device__ __forceinline__ void load(const elem_t* base, int64_t ld, int row0, int n_rows, int d, int tid) {
+// Fills tiles with rows of one head of a [rows][ld] matrix; rows beyond the last one read as zeros.  The descriptor starts at
+// the tile's first row, so that offsets stay small for any sequence length.
+template <int D, bool ALIGNED>
+struct TileSource {
+  const elem_t* base;                  // row 0, the tile's first column
+  uint32_t row_bytes, row_end;         // row_end: bytes of a row up to the head's last chunk
+  int rows;
+  uint32_t v, v_last;                  // lane offset of its chunk of block 0, and of the last block (or out of range)
+  uint32_t clear;                      // LDS place in a tile's first rows that this lane clears of another head's columns
+  HeadColumns cols;
+  int lane, wave;
+  __device__ __forceinline__ TileSource(const elem_t* head, int64_t ld, int rows, HeadColumns cols, int tid)
+      : base(head - cols.shift), row_bytes((uint32_t)ld * 2u), row_end((uint32_t)cols.chunks() * 16u), rows(rows), cols(cols),
+        lane(tid & 63), wave(__builtin_amdgcn_readfirstlane(tid >> 6)) {
+    // wave w fills row blocks w, w + 4, ...: their swizzle is the same
+    const int r = 8 * wave + (lane >> 3), ch = (lane & 7) ^ tile_swizzle(r);
+    v = (uint32_t)r * row_bytes + (uint32_t)ch * 16u;
+    v_last = 8 * (D / 64 - 1) + ch < cols.chunks() ? v + (D / 64 - 1) * 128u : kOutOfRange;
+    const int cr = 8 * wave + (lane & 7), at = cols.foreign();
+    clear = (uint32_t)cr * 128u + ((((at >> 4) & 7) ^ tile_swizzle(cr)) << 4) + (at & 8);
+  }
+  // the R rows from row0 on
+  template <int R>
+  __device__ __forceinline__ void fill(LdsBytes tile, int row0) const {
+    if (!ALIGNED) { fill_unaligned<R>(tile, row0); return; }
+    const Copies<R> c = copies<R>(tile, row0);
 #pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      const int c = tid + j * 256;
-      const int row = c / (D / 8), ch = c % (D / 8);
-      r[j] = (row0 + row < n_rows)
-                 ? load_cols8<EXACT>(base + (int64_t)(row0 + row) * ld + ch * 8, ch * 8, d)
-                 : make_uint4(0, 0, 0, 0);
+    for (int i = 0; i < Copies<R>::N; ++i) c.one(i, *this);
+  }
+  // The same one instruction at a time.
+  template <int R>
+  struct Copies {
+    static constexpr int N = R / 32 * (D / 64);
+    u32x4 rsrc;
+    uint32_t lds;
+    __device__ __forceinline__ void one(int i, const TileSource& s) const {
+      const int block = i % (D / 64), r32 = i / (D / 64);
+      const uint32_t v = block == D / 64 - 1 ? s.v_last : s.v + block * 128u;
+      dma_chunk16(rsrc, v + (uint32_t)(32 * r32) * s.row_bytes, 0, lds + block * Tile<R, D>::BLOCK + r32 * (32 * 128));
+    }
+  };
+  template <int R>
+  __device__ __forceinline__ Copies<R> copies(LdsBytes tile, int row0) const {
+    Copies<R> c;
+    const int left = min(rows - row0, R);
+    c.rsrc = rsrc_words(base + (int64_t)row0 * (row_bytes >> 1), left > 0 ? (uint32_t)(left - 1) * row_bytes + row_end : 0u);
+    c.lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)tile.p) + (uint32_t)wave * 1024u;
+    return c;
+  }
+  // Matrices that do not start at a 16-byte boundary: through registers.
+  template <int R>
+  __device__ __forceinline__ void fill_unaligned(LdsBytes tile, int row0) const {
+#pragma unroll 1
+    for (int i = 64 * wave + lane; i < R * (D / 8); i += 256) {
+      const int r = i / (D / 8), ch = i % (D / 8), row = row0 + r;
+      const elem_t* p = base + (int64_t)row * (row_bytes >> 1) + ch * 8;
+      uint2 lo = make_uint2(0, 0), hi = make_uint2(0, 0);
+      if (row < rows && cols.has4(8 * ch)) lo = *reinterpret_cast<const uint2*>(p);
+      if (row < rows && cols.has4(8 * ch + 4)) hi = *reinterpret_cast<const uint2*>(p + 4);
+      *(AXONN_LDS u32x4*)(tile.p + Tile<R, D>::chunk_at(r, ch)) = u32x4{lo.x, lo.y, hi.x, hi.y};
     }
   }
-  // The same tile of an exact-size head through buffer loads, with next to no address arithmetic per tile:
-  // `off0` = byte offset, from the descriptor's base, of this thread's first chunk in the tile that starts at
-  // row 0 (see offset0); the tile starts at row0; rows outside the descriptor's range read as zeros.
-  static __device__ __forceinline__ uint32_t offset0(uint32_t row_bytes, int tid) {
-    return (uint32_t)(tid / (D / 8)) * row_bytes + (uint32_t)(tid % (D / 8)) * 16u;
-  }
-  __device__ __forceinline__ void load_buffer(__amdgpu_buffer_rsrc_t rsrc, uint32_t off0, uint32_t row_bytes, int row0) {
-    constexpr int RSTEP = 256 / (D / 8);        // rows between consecutive chunks of a thread
-    const uint32_t base = off0 + (uint32_t)row0 * row_bytes;
+  // Behind the wait for this wave's copies and in front of the barrier: clears what they brought of another head.
+  template <int R>
+  __device__ __forceinline__ void clear_foreign(LdsBytes tile) const {
+    if (!cols.split()) return;
+    AXONN_LDS char* p = tile.p + (cols.foreign() >> 7) * Tile<R, D>::BLOCK + clear;
 #pragma unroll
-    for (int j = 0; j < NCH; ++j)
-      r[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, base + (uint32_t)(j * RSTEP) * row_bytes, 0, 0));
-  }
-  // chunk j alone: for kernels that spread a tile's loads and stores over their instruction stream
-  __device__ __forceinline__ void load_buffer_one(int j, __amdgpu_buffer_rsrc_t rsrc, uint32_t off0, uint32_t row_bytes, int row0) {
-    constexpr int RSTEP = 256 / (D / 8);
-    r[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off0 + (uint32_t)(row0 + j * RSTEP) * row_bytes, 0, 0));
-  }
-  template <int LD>
-  __device__ __forceinline__ void store_one(int j, elem_t* lds, int tid) const {
-    const int c = tid + j * 256;
-    *reinterpret_cast<uint4*>(lds + (c / (D / 8)) * LD + (c % (D / 8)) * 8) = r[j];
-  }
-  template <int LD>
-  __device__ __forceinline__ void store(elem_t* lds, int tid) const {
-#pragma unroll
-    for (int j = 0; j < NCH; ++j) {
-      const int c = tid + j * 256;
-      *reinterpret_cast<uint4*>(lds + (c / (D / 8)) * LD + (c % (D / 8)) * 8) = r[j];
-    }
+    for (int r32 = 0; r32 < R / 32; ++r32)
+      if (lane < 8) *(AXONN_LDS u32x2*)(p + r32 * (32 * 128)) = u32x2{0, 0};
   }
 };
 
@@ -106,17 +177,6 @@ __device__ __forceinline__ elemx8 pack8(const floatx16& t, int first) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = (elem_t)t[first + e];
   return o;
-}
-
-// Row fragment straight from global memory: lane holds row (row0 + lane%32), elements
-// [k0 + 8*(lane/32), +8) -- the MFMA operand layout.  Rows >= n_rows read as zero.
-template <bool EXACT>
-__device__ __forceinline__ elemx8 global_frag(const elem_t* base, int64_t ld, int row, int n_rows,
-                                              int k0, int lane, int d) {
-  uint4 v = make_uint4(0, 0, 0, 0);
-  const int col = k0 + 8 * (lane >> 5);
-  if (row < n_rows) v = load_cols8<EXACT>(base + (int64_t)row * ld + col, col, d);
-  return __builtin_bit_cast(elemx8, v);
 }
 
 // Work assignment of the attention kernels: block id of a 1-D grid of n_tiles * n_bh blocks -> (rank of
@@ -135,39 +195,17 @@ __device__ __forceinline__ void attn_block(int id, int n_blocks, int n_bh, int& 
   }
 }
 
-// Row stride (elements) of an LDS tile of D-element rows that is read both ways: with 128-bit reads of 16 rows
-// at one column (conflict-free when the stride is an odd multiple of 4 words) and with the transposing 64-bit
-// reads that take 32 bytes from each of 4 consecutive rows (conflict-free when 4 consecutive rows start at
-// least 8 words apart modulo the 64 banks).  12 or 52 words modulo 64 satisfy both.
+// One wave's 32 x D result (the MFMA result layout: lane = row lane % 32, registers 4q .. 4q+3 of tile dt = columns
+// 32 dt + 8 q + 4 (lane / 32) ..) times `mul`, rounded, to rows of `ld` elements at `head`, through LDS: stored straight from
+// the MFMA layout every lane touches a row of its own, 8 bytes at a time, a memory instruction then covers 32 different
+// lines, and the last stores alone took a tenth of the dK / dV kernel's time.  `stage` is 32 x (D + 8) elements of LDS that
+// only this wave touches (no barrier: a wave's LDS operations keep their order).
 template <int D>
-struct BothWaysStride {
-  static constexpr int WORDS_MOD = (D / 2) % 64;
-  static constexpr int PAD_WORDS = (12 - WORDS_MOD + 64) % 64 <= (52 - WORDS_MOD + 64) % 64 ? (12 - WORDS_MOD + 64) % 64
-                                                                                            : (52 - WORDS_MOD + 64) % 64;
-  static constexpr int LD = D + 2 * PAD_WORDS;
-  static_assert((LD / 2) % 64 == 12 || (LD / 2) % 64 == 52, "stride class");
-};
-
-// The rows a wave owns (32 of the workgroup's 128) enter and leave the kernels of the exact head dimensions through
-// LDS.  Fetched or stored straight from the MFMA layout, every lane touches a row of its own, 16 or 8 bytes at a time:
-// a memory instruction then covers 32 different lines, and the workgroups' first loads and last stores alone took a
-// fifth of the dK / dV kernel's time.  Staged, a load or store instruction covers whole rows (16 bytes per lane).
-//
-// stage_rows_in: the 128 x D tile at rows row0.. of a descriptor into LDS with row stride LD (all 256 threads; rows
-// beyond the descriptor's range read as zeros); the caller puts barriers around its use.
-template <int D, int LD>
-__device__ __forceinline__ void stage_rows_in(elem_t* lds, __amdgpu_buffer_rsrc_t rsrc, uint32_t row_bytes, int row0, int tid) {
-  TileRegs<128, D> t;
-  t.load_buffer(rsrc, TileRegs<128, D>::offset0(row_bytes, tid), row_bytes, row0);
-  t.template store<LD>(lds, tid);
-}
-// store_rows_out: one wave's 32 x D result (the MFMA result layout: lane = row lane % 32, registers 4q .. 4q+3 of
-// tile dt = columns 32 dt + 8 q + 4 (lane / 32) ..) times `mul`, rounded, to rows of `ld` elements at `dst`; `stage`
-// is 32 x (D + 8) elements of LDS that only this wave touches (no barrier: a wave's LDS operations keep their order).
-template <int D>
-__device__ __forceinline__ void store_rows_out(elem_t* stage, const floatx16* acc, float mul, elem_t* dst, int64_t ld,
-                                               int n_rows, int lane) {
+__device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, float mul, elem_t* head, int64_t ld,
+                                               int n_rows, HeadColumns cols, int lane) {
   constexpr int LDO = D + 8, DT = D / 32, CPR = D / 8;      // 16-byte chunks per row
+  elem_t* const stage = reinterpret_cast<elem_t*>(lds);
+  elem_t* const dst = head - cols.shift;
   const int g = lane >> 5;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -182,46 +220,59 @@ __device__ __forceinline__ void store_rows_out(elem_t* stage, const floatx16* ac
   for (int j = 0; j < 32 * CPR / 64; ++j) {
     const int idx = lane + 64 * j, row = idx / CPR, ch = idx % CPR;
     const uint4 v = *reinterpret_cast<const uint4*>(stage + row * LDO + ch * 8);
-    if (row < n_rows) *reinterpret_cast<uint4*>(dst + (int64_t)row * ld + ch * 8) = v;
+    if (row >= n_rows) continue;
+    elem_t* const p = dst + (int64_t)row * ld + ch * 8;
+    const bool lo = cols.has4(8 * ch), hi = cols.has4(8 * ch + 4);
+    if (lo && hi) *reinterpret_cast<uint4*>(p) = v;
+    else if (lo) *reinterpret_cast<uint2*>(p) = make_uint2(v.x, v.y);
+    else if (hi) *reinterpret_cast<uint2*>(p + 4) = make_uint2(v.z, v.w);
   }
 }
 
 // =============================================================================== forward
-// grid: (ceil(s/128), b*a); 4 waves; wave w owns queries q0 + 32w .. +31.
-template <int D, bool EXACT>
-__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, int d_arg,
-                                                       const elem_t* __restrict__ qkv,
-                                                       elem_t* __restrict__ o,
-                                                       float* __restrict__ lse) {
-  constexpr int BKV = 64, LDK = D + 8, LDV = D + 32, DT = D / 32, KK = D / 16;
-  __shared__ __align__(16) elem_t smem[BKV * (LDK + LDV)];      // K and V tile; at the ends the staged Q and O rows
-  static_assert(BKV * (LDK + LDV) >= 128 * (D + 8), "the workgroup's 128 rows fit the tile buffers");
-  elem_t* sK = smem;
-  elem_t* sV = smem + BKV * LDK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
+// grid: ceil(s/128) * b * a workgroups; 4 waves; wave w owns queries q0 + 32w .. +31 and walks the key tiles up to the diagonal.
+//
+// Two workgroups share a CU, two waves a SIMD; what bounds a wave is the chain of a tile's steps.  So the LDS reads of one step
+// run beside the MFMAs of another: the V fragments of a tile beside its score MFMAs, the K fragments of the next tile
+// beside the P V MFMAs, and the memory pipeline fills a tile's buffer a whole tile ahead.  K and V fragments being in
+// registers when the barrier of a tile is reached, its buffer is free behind it: two buffers and one barrier per tile.
+// Against tiles fetched into registers, stored between two barriers, and each tile's fragments read in one go, us: 40 heads of
+// 128 x 2048 59.4 -> 53.3, 16 of 128 x 8192 296 -> 264 (1040 TFLOP/s), 8 x 24 of 188 x 512 (every lane on a row of its own,
+// 8 bytes at a time) 80 -> 59, 2 x 36 of 176 x 2048 255 -> 165.
+template <int D, bool ALIGNED>
+__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, int d,
+                                                                        const elem_t* __restrict__ qkv,
+                                                                        elem_t* __restrict__ o,
+                                                                        float* __restrict__ lse) {
+  constexpr int BKV = 64, DT = D / 32, KK = D / 16, BUF = 2 * Tile<BKV, D>::BYTES;
+  constexpr int STAGED = 128 * (D + 8) * 2;
+  __shared__ __align__(1024) char smem[2 * BUF];     // K and V tile, two of each; in front the Q rows, behind the O rows
+  static_assert(Tile<128, D>::BYTES == BUF && STAGED <= 2 * BUF, "rows staged in the tile buffers");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
   int rank, bh;
   attn_block(blockIdx.x, gridDim.x, n_bh, rank, bh);
   const int qt = (s + 127) / 128 - 1 - rank;  // longest rows first
   const int bi = bh / a, hd = bh % a;
-  const int d = EXACT ? D : d_arg;
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
-  const elem_t* kb = qb + h;
-  const elem_t* vb = qb + 2 * h;
   const int q0 = qt * 128, qw0 = q0 + 32 * wave, qi = qw0 + (lane & 31);
   const float scale_log2 = kLog2e * rsqrtf((float)d);
+  const HeadColumns cols(d, hd);
+  const FragLanes fl(lane);
+  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid);
 
+  const LdsBytes buf0(smem);
+  q_src.template fill<128>(buf0 + BUF, q0);
+  k_src.template fill<BKV>(buf0, 0);
+  v_src.template fill<BKV>(buf0 + Tile<BKV, D>::BYTES, 0);
+  dma_wait_all();
+  q_src.template clear_foreign<128>(buf0 + BUF);
+  k_src.template clear_foreign<BKV>(buf0);
+  __syncthreads();
   elemx8 qf[KK];
-  if (EXACT) {
-    stage_rows_in<D, D + 8>(smem, make_rsrc(qb, (uint32_t)(((int64_t)(s - 1) * ld + D) * 2)), (uint32_t)ld * 2u, q0, tid);
-    __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = frag_kcontig(smem + (32 * wave) * (D + 8) + kk * 16, D + 8, lane);
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = global_frag<EXACT>(qb, ld, qi, s, kk * 16, lane, d);
-  }
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = frag_rows<128, D>(buf0 + BUF, fl, wave, kk);
 
   floatx16 oacc[DT];
 #pragma unroll
@@ -232,71 +283,43 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 
   const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
-  TileRegs<BKV, D> rk, rv;
-  // exact-size heads: tiles through buffer loads over the rows of this (batch, head)
-  const uint32_t row_bytes = (uint32_t)ld * 2u, tile_bytes = EXACT ? (uint32_t)(((int64_t)(s - 1) * ld + D) * 2) : 0u;
-  const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kb, tile_bytes), v_rsrc = make_rsrc(vb, tile_bytes);
-  const uint32_t off0 = TileRegs<BKV, D>::offset0(row_bytes, tid);
-  auto fetch = [&](int row0) {
-    if (EXACT) {
-      rk.load_buffer(k_rsrc, off0, row_bytes, row0);
-      rv.load_buffer(v_rsrc, off0, row_bytes, row0);
-    } else {
-      rk.template load<EXACT>(kb, ld, row0, s, d, tid);
-      rv.template load<EXACT>(vb, ld, row0, s, d, tid);
-    }
-  };
-  fetch(0);
+  // Fragments of a tile in the order of the MFMAs that take them: K's alternate between the tile's two 32-key halves.
+  auto k_frag = [&](LdsBytes buf, int i) { return frag_rows<BKV, D>(buf, fl, i & 1, i >> 1); };
+  auto v_frag = [&](LdsBytes buf, int i) { return frag_cols<BKV, D>(buf + Tile<BKV, D>::BYTES, fl, i / DT, i % DT); };
+  constexpr int NF = 2 * KK;                     // fragments of a K tile, and of a V tile
+  static_assert(NF == 4 * DT, "one V fragment per score MFMA and one K fragment per P V MFMA");
+  constexpr int EARLY = D == 128 ? 12 : NF;      // the other V fragments find registers when the scores have left theirs
+  elemx8 kfr[NF], vfr[NF];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) kfr[i] = k_frag(buf0, i);
+  __syncthreads();                               // the Q rows have been read
+  k_src.template fill<BKV>(buf0 + BUF, BKV);
+  v_src.template fill<BKV>(buf0 + BUF + Tile<BKV, D>::BYTES, BKV);
   for (int kt = 0; kt < n_kt; ++kt) {
     const int k0 = kt * BKV;
-    __syncthreads();
-    rk.template store<LDK>(sK, tid);
-    rv.template store<LDV>(sV, tid);
-    __syncthreads();
-    if (kt + 1 < n_kt) fetch(k0 + BKV);
-    if (k0 > qw0 + 31) continue;  // every key of the tile is in this wave's future
-
-    // All the K fragments of the tile are requested before the first MFMA, and the V fragments behind the last one,
-    // ahead of the exponentials: left to the compiler, every MFMA follows the LDS round trip of a read of its own.
-    // (Not where the fragments of a whole tile do not fit the registers: D = 192, and D = 128 with masked columns.)
-    constexpr bool BATCH = D <= 64 || (D <= 128 && EXACT);
-    elemx8 kfr[2][KK];
-    if (BATCH) {
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) kfr[ks][kk] = frag_kcontig(sK + (32 * ks) * LDK + kk * 16, LDK, lane);
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    const LdsBytes buf = buf0 + (kt & 1) * BUF, next = buf0 + (~kt & 1) * BUF;
     floatx16 sacc[2];
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[ks][r] = 0.f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-        sacc[ks] = mfma32(BATCH ? kfr[ks][kk] : frag_kcontig(sK + (32 * ks) * LDK + kk * 16, LDK, lane), qf[kk], sacc[ks]);
-    elemx8 vfr[4][DT];
-    if (BATCH) {
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int kc = 0; kc < 4; ++kc)
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) vfr[kc][dt] = frag_kstrided<true>(sV + (16 * kc) * LDV + dt * 32, LDV, lane);
+    for (int i = 0; i < NF; ++i) {
+      sacc[i & 1] = mfma32(kfr[i], qf[i >> 1], sacc[i & 1]);
+      if (i < EARLY) vfr[i] = v_frag(buf, i);
       __builtin_amdgcn_sched_barrier(0);
     }
     // Keys beyond the query are masked in the tiles that straddle the diagonal only: a real (wave-uniform)
     // branch, so that the other tiles do not pay for the comparisons.
     if (k0 + BKV - 1 > qw0) {
       asm volatile("" ::: "memory");            // keeps the compiler from turning the branch into selects
+      const int last = qi - k0 - 4 * g;         // the lane's last key, counted from its first one
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int key = k0 + 32 * ks + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (key > qi) sacc[ks][r] = -INFINITY;
+          if (32 * ks + 8 * (r >> 2) + (r & 3) > last) sacc[ks][r] = -INFINITY;
         }
     }
     // Row maximum of the raw scores; in units of the exponent (log2) it is mx * scale_log2 (the scale is positive).
@@ -330,38 +353,30 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
         psum += p;
       }
     l_run += psum;
+    elemx8 pf[4];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+    for (int c = 0; c < 4; ++c) pf[c] = pack8(sacc[c >> 1], 8 * (c & 1));
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const elemx8 pf = pack8(sacc[ks], 8 * c);
+    for (int i = EARLY; i < NF; ++i) vfr[i] = v_frag(buf, i);
+    // The next tile is in LDS, and everybody has taken this one's fragments: its buffer is filled with the tile after next.
+    dma_wait_all();
+    k_src.template clear_foreign<BKV>(next);
+    __syncthreads();
+    k_src.template fill<BKV>(buf, k0 + 2 * BKV);
+    v_src.template fill<BKV>(buf + Tile<BKV, D>::BYTES, k0 + 2 * BKV);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          oacc[dt] = mfma32(BATCH ? vfr[2 * ks + c][dt] : frag_kstrided<true>(sV + (32 * ks + 16 * c) * LDV + dt * 32, LDV, lane),
-                            pf, oacc[dt]);
-      }
+    for (int i = 0; i < NF; ++i) {
+      oacc[i % DT] = mfma32(vfr[i], pf[i / DT], oacc[i % DT]);
+      kfr[i] = k_frag(next, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-  if (EXACT) {
-    __syncthreads();              // the tiles in LDS are done with
-    store_rows_out<D>(smem + wave * (32 * (D + 8)), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, lane);
-    if (g == 0 && qi < s) lse[((int64_t)bi * a + hd) * s + qi] = (m_run + __log2f(l_tot)) * kLn2;
-    return;
-  }
-  if (qi < s) {
-    const float inv = 1.f / l_tot;
-    elem_t* orow = o + ((int64_t)bi * s + qi) * h + hd * d;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        elemx4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (elem_t)(oacc[dt][4 * q + e] * inv);
-        if (dt * 32 + 8 * q + 4 * g < d) *reinterpret_cast<elemx4*>(orow + dt * 32 + 8 * q + 4 * g) = v;
-      }
-    if (g == 0) lse[((int64_t)bi * a + hd) * s + qi] = (m_run + __log2f(l_tot)) * kLn2;
-  }
+  dma_wait_all();                 // copies of tiles beyond the last still write (zeros) to LDS
+  __syncthreads();                // the tiles in LDS are done with
+  store_rows_out<D>(smem + wave * (STAGED / 4), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, cols, lane);
+  if (g == 0 && qi < s) lse[((int64_t)bi * a + hd) * s + qi] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
 // ============================================================================ backward
@@ -414,442 +429,342 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
 }
 
 // dK / dV: one workgroup per tile of 128 keys and (batch, head); wave w owns keys k0 + 32w .. +31 and walks the query tiles at or below the
-// diagonal.  The Q / dO tiles alternate between two LDS buffers: the next tile is fetched into registers at the top
-// of a step and stored to the other buffer at the end, so one barrier per tile is enough.
+// diagonal.  The Q / dO tiles alternate between two LDS buffers, which the memory pipeline fills.
 //
 // A wave is alone on its SIMD (accumulators and K / V fragments take most of the register file), so nothing hides the
 // MFMA phases of a 32-query block behind its exponentials, or an LDS round trip behind an MFMA, unless the instruction
-// stream does.  Up to D = 128 a tile has 128 queries, four blocks, processed as two pairs in four phases each: S and
-// dP of the first block; S and dP of the second next to the exponentials of the first; the dV / dK MFMAs of the first
-// next to the exponentials of the second; the dV / dK MFMAs of the second.  A phase is a run of slots: one MFMA, the
-// LDS read of the fragment that the MFMA W - 1 slots later needs (a ring of W fragments, so the reads run ahead
-// across the phase boundaries and only the first few of a tile are waited for), and a share of the other block's
-// exponentials.  The MFMAs are volatile assembly: they keep this order, and the reads stay between them where they
-// are written.  The tile on the diagonal takes the same path with the mask applied to every element (a block above
-// the diagonal comes out as zeros; the wave with the lowest keys needs all four blocks anyway).
-// At D = 192 the registers do not hold two blocks: tiles of 64 queries, block by block.
+// stream does.  The blocks of all tiles form one pipeline.  Step k of a tile issues the score MFMAs (S and dP) of block k + 1
+// and the gradient MFMAs (dV and dK) of block k; half of block k + 1's exponentials run beside the gradient MFMAs, the other
+// half beside the next step's score MFMAs.  A step is a run of slots: one MFMA, the LDS read of the fragment that the MFMA
+// W - 1 slots later needs (a ring of W fragments, also across tiles), and a share of the exponentials.  The MFMAs are
+// volatile assembly: they keep this order, and the reads stay between them where they are written.  The tile on the diagonal
+// takes the same path with the mask applied to every element (a block above the diagonal comes out as zeros; the wave with
+// the lowest keys needs all blocks anyway).
+// What bounds a slot is what one wave issues: a vector instruction takes 5 clocks of its 32, an exponential 9, a conversion of
+// two elements 8; and the LDS, which gives a transposed fragment in 4.6 clocks without bank conflicts and in 8 with the two-way
+// ones of padded rows.  40 heads of 128 x 2048 117 -> 97 us, 16 of 128 x 8192 570 -> 472, 8 x 16 of 64 x 1024 64 -> 44 (two waves
+// per SIMD here, at 256 registers), against wait states in front of every MFMA, padded rows, tiles fetched into registers and
+// all of a block's exponentials beside 16 of its slots; 8 x 24 of 188 x 512 (block by block, tiles of 64) 140 -> 82.
 template <int D>
 struct DkdvLds {
-  static constexpr int BQ = D <= 128 ? 128 : 64, LDQ = BothWaysStride<D>::LD, NBUF = 2;
-  __align__(16) elem_t q[NBUF][BQ * LDQ];
-  __align__(16) elem_t dout[NBUF][BQ * LDQ];
-  __align__(16) float lse[NBUF][BQ];
-  __align__(16) float delta[NBUF][BQ];
+  static constexpr int BQ = D <= 128 ? 128 : 64, TILE = Tile<BQ, D>::BYTES, BUF = 2 * TILE, KEYS = Tile<128, D>::BYTES;
+  // the second buffer holds the workgroup's K and V rows first
+  __align__(1024) char tiles[BUF + (2 * KEYS > BUF ? 2 * KEYS : BUF)];
+  __align__(16) float lse[2][BQ];
+  __align__(16) float delta[2][BQ];
 };
-template <int D, bool EXACT>
+template <int D, bool ALIGNED>
 __device__ __forceinline__ void attn_bwd_dkdv(
-    DkdvLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv,
+    DkdvLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
     elem_t* __restrict__ dqkv) {
-  constexpr bool PAIR = D <= 128;
-  constexpr int BQ = DkdvLds<D>::BQ, LDQ = DkdvLds<D>::LDQ, DT = D / 32, KK = D / 16;
-  constexpr int NBUF = DkdvLds<D>::NBUF;
-  auto& sQ_ = lds.q;
-  auto& sdO_ = lds.dout;
-  auto& s_lse_ = lds.lse;
-  auto& s_delta_ = lds.delta;
-  static_assert(NBUF * BQ * LDQ >= 128 * LDQ, "the workgroup's 128 keys fit the tile buffers");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
+  using L = DkdvLds<D>;
+  constexpr int BQ = L::BQ, DT = D / 32, KK = D / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
   int rank, bh;
   attn_block(id, n_blocks, n_bh, rank, bh);    // key tile `rank` walks n_tiles - rank query tiles: longest first
   const int bi = bh / a, hd = bh % a;
-  const int d = EXACT ? D : d_arg;
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
-  const elem_t* kb = qb + h;
-  const elem_t* vb = qb + 2 * h;
-  const elem_t* dob = dout + (int64_t)bi * s * h + hd * d;
   const float* lse_b = lse + ((int64_t)bi * a + hd) * s;
   const float* delta_b = delta + ((int64_t)bi * a + hd) * s;
   const int k0 = rank * 128, kw0 = k0 + 32 * wave, kj = kw0 + (lane & 31);
   const float scale = rsqrtf((float)d), scale_log2 = kLog2e * scale;
+  const HeadColumns cols(d, hd);
+  const FragLanes fl(lane);
+  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid),
+      do_src(dout + (int64_t)bi * s * h + hd * d, h, s, cols, tid);
+  const int qt_begin = k0 / BQ, n_qt = (s + BQ - 1) / BQ;
+  const LdsBytes keys(lds.tiles + L::BUF), tile0(lds.tiles);
 
+  float r_lse, r_delta;
+  // by all threads, so that no branch stands in the stream of MFMAs: those beyond the tile's rows repeat the others' work
+  auto fetch_stats = [&](int qt) {
+    const int at = min(qt * BQ + (tid & (BQ - 1)), s - 1);
+    r_lse = lse_b[at];
+    r_delta = delta_b[at];
+  };
+  auto store_stats = [&](int buf, int qt) {
+    const bool in = qt * BQ + (tid & (BQ - 1)) < s;
+    lds.lse[buf][tid & (BQ - 1)] = in ? r_lse * kLog2e : 0.f;
+    lds.delta[buf][tid & (BQ - 1)] = in ? r_delta : 0.f;
+  };
+  k_src.template fill<128>(keys, k0);
+  v_src.template fill<128>(keys + L::KEYS, k0);
+  fetch_stats(qt_begin);
+  q_src.template fill<BQ>(tile0, qt_begin * BQ);
+  do_src.template fill<BQ>(tile0 + L::TILE, qt_begin * BQ);
+  store_stats(0, qt_begin);
+  dma_wait_all();
+  k_src.template clear_foreign<128>(keys);
+  v_src.template clear_foreign<128>(keys + L::KEYS);
+  q_src.template clear_foreign<BQ>(tile0);
+  do_src.template clear_foreign<BQ>(tile0 + L::TILE);
+  fetch_stats(qt_begin + 1);
+  __syncthreads();
   elemx8 kf[KK], vf[KK];
-  if (EXACT) {
-    const uint32_t kv_bytes = (uint32_t)(((int64_t)(s - 1) * ld + D) * 2);
-    stage_rows_in<D, LDQ>(&sQ_[0][0], make_rsrc(kb, kv_bytes), (uint32_t)ld * 2u, k0, tid);
-    stage_rows_in<D, LDQ>(&sdO_[0][0], make_rsrc(vb, kv_bytes), (uint32_t)ld * 2u, k0, tid);
-    __syncthreads();
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kk] = frag_kcontig(&sQ_[0][0] + (32 * wave) * LDQ + kk * 16, LDQ, lane);
-      vf[kk] = frag_kcontig(&sdO_[0][0] + (32 * wave) * LDQ + kk * 16, LDQ, lane);
-    }
-    __syncthreads();
-  } else {
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      kf[kk] = global_frag<EXACT>(kb, ld, kj, s, kk * 16, lane, d);
-      vf[kk] = global_frag<EXACT>(vb, ld, kj, s, kk * 16, lane, d);
-    }
+  for (int kk = 0; kk < KK; ++kk) {
+    kf[kk] = frag_rows<128, D>(keys, fl, wave, kk);
+    vf[kk] = frag_rows<128, D>(keys + L::KEYS, fl, wave, kk);
   }
   floatx16 dvacc[DT], dkacc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) dvacc[dt][r] = dkacc[dt][r] = 0.f;
+  // K fragments move to the accumulation registers, which the MFMAs below read them from; V's too where these hold both
+  constexpr bool VF_ACC = D <= 128;
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) {
+    asm volatile("" : "+a"(kf[kk]));
+    if (VF_ACC) asm volatile("" : "+a"(vf[kk]));
+  }
+  // the zeros are in place here, not written in front of an accumulator's first MFMA
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+a"(dvacc[dt]), "+a"(dkacc[dt]));
 
-  const int qt_begin = k0 / BQ, n_qt = (s + BQ - 1) / BQ;
-  TileRegs<BQ, D> rq, rdo;
-  float r_lse = 0.f, r_delta = 0.f;
-  const uint32_t q_row_bytes = (uint32_t)ld * 2u, do_row_bytes = (uint32_t)h * 2u;
-  const __amdgpu_buffer_rsrc_t q_rsrc = make_rsrc(qb, EXACT ? (uint32_t)(((int64_t)(s - 1) * ld + D) * 2) : 0u);
-  const __amdgpu_buffer_rsrc_t do_rsrc = make_rsrc(dob, EXACT ? (uint32_t)(((int64_t)(s - 1) * h + D) * 2) : 0u);
-  const uint32_t q_off0 = TileRegs<BQ, D>::offset0(q_row_bytes, tid), do_off0 = TileRegs<BQ, D>::offset0(do_row_bytes, tid);
-  auto prefetch_stats = [&](int qt) {
-    if (tid < BQ) {
-      const int qrow = qt * BQ + tid;
-      r_lse = qrow < s ? lse_b[qrow] : 0.f;
-      r_delta = qrow < s ? delta_b[qrow] : 0.f;
-    }
+  constexpr int NB = BQ / 32, NS = 2 * KK, NG = 4 * DT, STEP = NS + NG, NSLOT = NB * STEP, W = 8;
+  static_assert(NB % 2 == 0 && NSLOT % W == 0 && NS % W == 0 && NG == NS, "block parity and ring position are the same in every tile");
+  floatx16 sacc[2], pacc[2];            // scores and dP of two blocks: one being formed, one in its exponentials
+  uint32_t pfw[2][8], dsw[2][8];        // P and dS of a block rounded to 16 bits, two per word: MFMA operands
+  floatx4 l4[2], d4[2];                 // log-sum-exp and delta of the four queries of a group; two groups in flight
+  elemx8 ring[W];
+  // A block number is counted from the current tile's first block; block NB is the next tile's first one.
+  auto load_stats = [&](int buf, int blk, int q4) {
+    const int b = blk < NB ? buf : buf ^ 1, at = 32 * (blk % NB) + 8 * q4 + 4 * g;
+    l4[q4 & 1] = *reinterpret_cast<const floatx4*>(&lds.lse[b][at]);
+    d4[q4 & 1] = *reinterpret_cast<const floatx4*>(&lds.delta[b][at]);
   };
-  auto store_stats = [&](int buf) {
-    if (tid < BQ) {
-      s_lse_[buf][tid] = r_lse * kLog2e;
-      s_delta_[buf][tid] = r_delta;
+  // element r of block blk: P = exp(S - lse), dS = P (dP - delta), rounded once a pair of elements is complete.  Masked:
+  // keys beyond the query get no weight; `first`: the lane's key counted from the query of the tile's first row and its half.
+  auto softmax_elem = [&](int buf, int blk, int r, bool masked, int first) {
+    const int hf = blk & 1, q4 = r >> 2;
+    float x = fmaf(sacc[hf][r], scale_log2, -l4[q4 & 1][r & 3]);
+    if (masked && first > 32 * blk + 8 * q4 + (r & 3)) x = -INFINITY;
+    const float p = fast_exp2(x);
+    sacc[hf][r] = p;
+    pacc[hf][r] = p * (pacc[hf][r] - d4[q4 & 1][r & 3]);
+    if (r & 1) {
+      elemx2 pp, dd;
+      pp[0] = (elem_t)sacc[hf][r - 1]; pp[1] = (elem_t)sacc[hf][r];
+      dd[0] = (elem_t)pacc[hf][r - 1]; dd[1] = (elem_t)pacc[hf][r];
+      pfw[hf][r >> 1] = __builtin_bit_cast(uint32_t, pp);
+      dsw[hf][r >> 1] = __builtin_bit_cast(uint32_t, dd);
     }
+    // the group after next into the pair just used up
+    if ((r & 3) == 3) load_stats(buf, q4 + 2 < 4 ? blk : blk + 1, (q4 + 2) & 3);
   };
-  auto prefetch = [&](int qt) {
-    if (EXACT) {
-      rq.load_buffer(q_rsrc, q_off0, q_row_bytes, qt * BQ);
-      rdo.load_buffer(do_rsrc, do_off0, do_row_bytes, qt * BQ);
+  auto operand = [&](const uint32_t* w, int c) {
+    return __builtin_bit_cast(elemx8, make_uint4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]));
+  };
+  // score MFMA i of block blk, and its fragment
+  auto score_frag = [&](int buf, int blk, int i) -> elemx8 {
+    const int b = blk < NB ? buf : buf ^ 1;
+    return frag_rows<BQ, D>(tile0 + b * L::BUF + (i & 1) * L::TILE, fl, blk % NB, i >> 1);
+  };
+  auto score_mfma = [&](int blk, int i, elemx8 f) {
+    const int hf = blk & 1, kk = i >> 1;
+    if (i & 1) {
+      if (kk == 0) mfma32_vgpr_zero<VF_ACC>(pacc[hf], f, vf[kk]); else mfma32_vgpr<VF_ACC>(pacc[hf], f, vf[kk]);
     } else {
-      rq.template load<EXACT>(qb, ld, qt * BQ, s, d, tid);
-      rdo.template load<EXACT>(dob, h, qt * BQ, s, d, tid);
+      if (kk == 0) mfma32_vgpr_zero<true>(sacc[hf], f, kf[kk]); else mfma32_vgpr<true>(sacc[hf], f, kf[kk]);
     }
-    prefetch_stats(qt);
   };
-  auto store_tile = [&](int buf) {
-    rq.template store<LDQ>(sQ_[buf], tid);
-    rdo.template store<LDQ>(sdO_[buf], tid);
-    store_stats(buf);
+  // slot j of a tile: within its step k the score slots of block k + 1, then the gradient slots of block k; slots beyond
+  // the last are the next tile's first ones
+  auto load_frag = [&](int buf, int j) -> elemx8 {
+    if (j >= NSLOT) { buf ^= 1; j -= NSLOT; }
+    const int k = j / STEP, i = j % STEP;
+    if (i < NS) return score_frag(buf, k + 1, i);
+    const int gi = i - NS, c = gi / (2 * DT), dt = (gi % (2 * DT)) >> 1;
+    return frag_cols<BQ, D>(tile0 + buf * L::BUF + (gi & 1 ? 0 : L::TILE), fl, 2 * k + c, dt);
   };
-  // P and dS of one 32-query block from its scores and dP, in place, then rounded into MFMA operands:
-  // lane = key kj; register r = query 8*(r/4) + 4g + r%4 of the block
-  auto softmax_block = [&](const float* lse32, const float* delta32, floatx16& sacc, floatx16& pacc, elemx8* pf, elemx8* dsf) {
+  // The next tile is copied into the other buffer during the first steps of a tile, one instruction per slot, and its first
+  // block is read from slot READY on.  Rows beyond the sequence read as zeros, so a tile beyond the last one needs no case of
+  // its own.
+  constexpr int READY = (NB - 1) * STEP - (W - 1), NCP = TileSource<D, ALIGNED>::template Copies<BQ>::N;
+  static_assert(2 * NCP < READY, "copies are issued in front of the wait for them");
+  // masked: 0 no, 1 this tile, 2 the next one too
+  auto tile_stream = [&](int qt, auto masked) {
+    constexpr bool MASKED = decltype(masked)::value > 0, NEXT_MASKED = decltype(masked)::value > 1;
+    const int buf = (qt - qt_begin) & 1, first = kj - qt * BQ - 4 * g;
+    const LdsBytes next = tile0 + (buf ^ 1) * L::BUF;
+    // every wave has left the tile before, whose buffer is filled again (what a wave has read of it it has used)
+    asm volatile("s_barrier" : : : "memory");
+    if (!ALIGNED) {
+      q_src.template fill<BQ>(next, (qt + 1) * BQ);
+      do_src.template fill<BQ>(next + L::TILE, (qt + 1) * BQ);
+    }
+    const auto cq = q_src.template copies<BQ>(next, (qt + 1) * BQ);
+    const auto cdo = do_src.template copies<BQ>(next + L::TILE, (qt + 1) * BQ);
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const floatx4 l4 = *reinterpret_cast<const floatx4*>(&lse32[8 * q4 + 4 * g]);
-      const floatx4 d4 = *reinterpret_cast<const floatx4*>(&delta32[8 * q4 + 4 * g]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int r = 4 * q4 + e;
-        const float p = fast_exp2(fmaf(sacc[r], scale_log2, -l4[e]));
-        sacc[r] = p;
-        pacc[r] = p * (pacc[r] - d4[e]);
+    for (int j = 0; j < NSLOT; ++j) {
+      const int k = j / STEP, i = j % STEP, gi = i - NS;
+      if (gi < 0) {
+        score_mfma(k + 1, i, ring[j % W]);
+      } else {
+        const int c = gi / (2 * DT), dt = (gi % (2 * DT)) >> 1;
+        if (gi & 1) mfma32_agpr(dkacc[dt], ring[j % W], operand(dsw[k & 1], c));
+        else mfma32_agpr(dvacc[dt], ring[j % W], operand(pfw[k & 1], c));
       }
-    }
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      pf[c] = pack8(sacc, 8 * c);
-      dsf[c] = pack8(pacc, 8 * c);
-    }
-  };
-
-  prefetch(qt_begin);
-  store_tile(0);
-  if constexpr (!PAIR) {
-    for (int qt = qt_begin; qt < n_qt; ++qt) {
-      const int q0 = qt * BQ, buf = (qt - qt_begin) & 1;
-      const elem_t* sQ = sQ_[buf];
-      const elem_t* sdO = sdO_[buf];
-      const float* s_lse = s_lse_[buf];
-      const float* s_delta = s_delta_[buf];
-      const bool more = qt + 1 < n_qt;
-      __syncthreads();            // tile qt is in LDS; every wave has left tile qt - 1, whose buffer the next store takes
-      if (more) prefetch(qt + 1);
-#pragma unroll
-      for (int qs = 0; qs < BQ / 32; ++qs) {
-        const int qq0 = q0 + 32 * qs;
-        if (qq0 + 31 < kw0) continue;  // all these queries precede every key of this wave
-        floatx16 sacc, pacc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          sacc = mfma32(frag_kcontig(sQ + (32 * qs) * LDQ + kk * 16, LDQ, lane), kf[kk], sacc);
-          pacc = mfma32(frag_kcontig(sdO + (32 * qs) * LDQ + kk * 16, LDQ, lane), vf[kk], pacc);
-        }
-        // masking in the blocks that straddle the diagonal only (a wave-uniform branch, kept as one)
-        if (kw0 + 31 > qq0) {
-          asm volatile("" ::: "memory");
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int qrow = qq0 + 8 * (r >> 2) + 4 * g + (r & 3);
-            if (kj > qrow) sacc[r] = -INFINITY;
-          }
-        }
-        elemx8 pf[2], dsf[2];
-        softmax_block(s_lse + 32 * qs, s_delta + 32 * qs, sacc, pacc, pf, dsf);
-#pragma unroll
-        for (int c = 0; c < 2; ++c)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            dvacc[dt] = mfma32(frag_kstrided<true>(sdO + (32 * qs + 16 * c) * LDQ + dt * 32, LDQ, lane),
-                               pf[c], dvacc[dt]);
-            dkacc[dt] = mfma32(frag_kstrided<true>(sQ + (32 * qs + 16 * c) * LDQ + dt * 32, LDQ, lane),
-                               dsf[c], dkacc[dt]);
-          }
+      // The scores of block k + 1 have settled when the third MFMA behind their last one has been issued (one occupies the
+      // pipe for nearly the distance asked for); nothing takes them from their registers before this statement.
+      if (gi == 2) asm volatile("" : "+v"(sacc[(k + 1) & 1]), "+v"(pacc[(k + 1) & 1]));
+      if (j == READY) {
+        store_stats(buf ^ 1, qt + 1);
+        dma_wait_all();
+        q_src.template clear_foreign<BQ>(next);
+        do_src.template clear_foreign<BQ>(next + L::TILE);
+        __syncthreads();
+        fetch_stats(qt + 2);
       }
-    if (more) store_tile(buf ^ 1);
-    }
-  } else {
-    // K and V fragments move to the accumulation registers, which the MFMAs below read them from
+      ring[(j + W - 1) % W] = load_frag(buf, j + W - 1);        // into the fragment of the slot before
+      if (ALIGNED && j < 2 * NCP) {
+        if (j < NCP) cq.one(j, q_src);
+        else cdo.one(j - NCP, do_src);
+      }
+      // the elements of block k, second half, beside the scores of k + 1; of block k + 1, first half, beside the gradients of k
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) asm volatile("" : "+a"(kf[kk]), "+a"(vf[kk]));
-    constexpr int NS = 2 * KK, NG = 4 * DT, PS = 2 * NS + 2 * NG, NSLOT = 2 * PS, W = 8;
-    constexpr int EPS = 16 / NS, EPG = 16 / NG;      // elements of a block per slot of the phase beside it
-    static_assert(16 % NS == 0 && 16 % NG == 0, "whole elements per slot");
-    // One tile: `masked` is a std::integral_constant (the tile on the diagonal: keys beyond the query get no weight)
-    // `fetch_row0` >= 0: the tile at that row is fetched on the way and stored to the other buffer (exact head
-    // dimensions): one 16-byte piece per thread and slot, the loads in the first score phase and the stores in the
-    // last gradient phase, whose slots have no exponentials beside their MFMAs.  Issued in one go, the loads of the
-    // four waves wait for the memory pipeline, and the stores for the LDS, with nothing to do meanwhile.
-    constexpr int NCH = TileRegs<BQ, D>::NCH, STORE_SLOT0 = NSLOT - 2 * NCH;
-    static_assert(2 * NCH <= NS && 2 * NCH <= NG, "a piece per slot of one phase");
-    auto tile_stream = [&](int q0, int buf, int fetch_row0, auto masked) {
-      constexpr bool MASKED = decltype(masked)::value;
-      const elem_t* sQ = sQ_[buf];
-      const elem_t* sdO = sdO_[buf];
-      const float* s_lse = s_lse_[buf];
-      const float* s_delta = s_delta_[buf];
-      floatx16 sacc[2], pacc[2];          // of the pair in flight
-      uint32_t pfw[2][8], dsw[2][8];      // P and dS of a block rounded to 16 bits, two per word: MFMA operands
-      floatx4 l4[2], d4[2];               // log-sum-exp and delta of the four queries of a group; two groups in flight
-      elemx8 ring[W];
-      auto load_stats = [&](int blk, int q4) {
-        l4[q4 & 1] = *reinterpret_cast<const floatx4*>(&s_lse[32 * blk + 8 * q4 + 4 * g]);
-        d4[q4 & 1] = *reinterpret_cast<const floatx4*>(&s_delta[32 * blk + 8 * q4 + 4 * g]);
-      };
-      // element r of block blk (half hf of its pair): P = exp(S - lse), dS = P (dP - delta), rounded once a pair of
-      // elements is complete
-      auto softmax_elem = [&](int blk, int r) {
-        const int hf = blk & 1, q4 = r >> 2;
-        float x = fmaf(sacc[hf][r], scale_log2, -l4[q4 & 1][r & 3]);
-        if (MASKED && kj > q0 + 32 * blk + 8 * q4 + 4 * g + (r & 3)) x = -INFINITY;
-        const float p = fast_exp2(x);
-        sacc[hf][r] = p;
-        pacc[hf][r] = p * (pacc[hf][r] - d4[q4 & 1][r & 3]);
-        if (r & 1) {
-          elemx2 pp, dd;
-          pp[0] = (elem_t)sacc[hf][r - 1]; pp[1] = (elem_t)sacc[hf][r];
-          dd[0] = (elem_t)pacc[hf][r - 1]; dd[1] = (elem_t)pacc[hf][r];
-          pfw[hf][r >> 1] = __builtin_bit_cast(uint32_t, pp);
-          dsw[hf][r >> 1] = __builtin_bit_cast(uint32_t, dd);
-        }
-        if ((r & 3) == 3 && q4 + 2 < 4) load_stats(blk, q4 + 2);     // the group after next, into the pair just used up
-      };
-      auto operand = [&](const uint32_t* w, int c) {
-        return __builtin_bit_cast(elemx8, make_uint4(w[4 * c], w[4 * c + 1], w[4 * c + 2], w[4 * c + 3]));
-      };
-      // slot j: pair j / PS; within the pair, score slots of its two blocks, then gradient slots of its two blocks
-      auto load_frag = [&](int j) -> elemx8 {
-        const int pair = j / PS, jj = j % PS;
-        if (jj < 2 * NS) {
-          const int blk = 2 * pair + jj / NS, i = jj % NS, kk = i >> 1;
-          return frag_kcontig(((i & 1) ? sdO : sQ) + (32 * blk) * LDQ + kk * 16, LDQ, lane);
-        }
-        const int blk = 2 * pair + (jj - 2 * NS) / NG, i = (jj - 2 * NS) % NG, c = i / (2 * DT), dt = (i % (2 * DT)) >> 1;
-        return frag_kstrided<true>(((i & 1) ? sQ : sdO) + (32 * blk + 16 * c) * LDQ + dt * 32, LDQ, lane);
-      };
-      auto slot_mfma = [&](int j, elemx8 f) {
-        const int jj = j % PS;
-        if (jj < 2 * NS) {
-          const int hf = jj / NS, i = jj % NS, kk = i >> 1;
-          if (i & 1) {
-            if (kk == 0) mfma32_vgpr_zero_ba(pacc[hf], f, vf[kk]);
-            else if (kk == KK - 1) mfma32_vgpr_settled_ba(pacc[hf], f, vf[kk]);     // the phase's last: its block's scores settle
-            else mfma32_vgpr_ba(pacc[hf], f, vf[kk]);
-          } else {
-            if (kk == 0) mfma32_vgpr_zero_ba(sacc[hf], f, kf[kk]); else mfma32_vgpr_ba(sacc[hf], f, kf[kk]);
-          }
-        } else {
-          const int hf = (jj - 2 * NS) / NG, i = (jj - 2 * NS) % NG, c = i / (2 * DT), dt = (i % (2 * DT)) >> 1;
-          if (i & 1) mfma32_agpr(dkacc[dt], f, operand(dsw[hf], c));
-          else mfma32_agpr(dvacc[dt], f, operand(pfw[hf], c));
-        }
-      };
-#pragma unroll
-      for (int j = 0; j < W - 1; ++j) ring[j] = load_frag(j);
+      for (int e = 0; e < 8; ++e) {
+        if (gi < 0 && i == e * NS / 8) softmax_elem(buf, k, 8 + e, MASKED, first);
+        if (gi >= 0 && gi == 3 + e * (NG - 3) / 8) softmax_elem(buf, k + 1, e, k + 1 < NB ? MASKED : NEXT_MASKED, first);
+      }
       __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int j = 0; j < NSLOT; ++j) {
-        const int pair = j / PS, jj = j % PS;
-        slot_mfma(j, ring[j % W]);
-        if (j + W - 1 < NSLOT) ring[(j + W - 1) % W] = load_frag(j + W - 1);   // into the fragment of the slot before
-        if (jj == NS - 1) { load_stats(2 * pair, 0); load_stats(2 * pair, 1); }
-        if (EXACT && fetch_row0 >= 0) {
-          if (j < 2 * NCH) {
-            const int k = j;
-            if (k < NCH) rq.load_buffer_one(k, q_rsrc, q_off0, q_row_bytes, fetch_row0);
-            else rdo.load_buffer_one(k - NCH, do_rsrc, do_off0, do_row_bytes, fetch_row0);
-          }
-          if (j >= STORE_SLOT0) {
-            const int k = j - STORE_SLOT0;
-            if (k < NCH) rq.template store_one<LDQ>(k, sQ_[buf ^ 1], tid);
-            else rdo.template store_one<LDQ>(k - NCH, sdO_[buf ^ 1], tid);
-          }
-        }
-        if (jj >= NS && jj < 2 * NS) {
-#pragma unroll
-          for (int e = 0; e < EPS; ++e) softmax_elem(2 * pair, (jj - NS) * EPS + e);
-          if (jj == 2 * NS - 1) { load_stats(2 * pair + 1, 0); load_stats(2 * pair + 1, 1); }
-        } else if (jj >= 2 * NS && jj < 2 * NS + NG) {
-#pragma unroll
-          for (int e = 0; e < EPG; ++e) softmax_elem(2 * pair + 1, (jj - 2 * NS) * EPG + e);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    // the tile on the diagonal, then the others in a loop of their own (so that the accumulators keep one place in
-    // the register files throughout it)
-    {
-      const bool more = qt_begin + 1 < n_qt;
-      __syncthreads();
-      if (more) { if (EXACT) prefetch_stats(qt_begin + 1); else prefetch(qt_begin + 1); }
-      tile_stream(qt_begin * BQ, 0, more ? (qt_begin + 1) * BQ : -1, std::true_type{});
-      if (more) { if (EXACT) store_stats(1); else store_tile(1); }
     }
-    for (int qt = qt_begin + 1; qt < n_qt; ++qt) {
-      const int buf = (qt - qt_begin) & 1;
-      const bool more = qt + 1 < n_qt;
-      __syncthreads();            // tile qt is in LDS; every wave has left tile qt - 1, whose buffer the next store takes
-      if (more) { if (EXACT) prefetch_stats(qt + 1); else prefetch(qt + 1); }
-      tile_stream(qt * BQ, buf, more ? (qt + 1) * BQ : -1, std::false_type{});
-      if (more) { if (EXACT) store_stats(buf ^ 1); else store_tile(buf ^ 1); }
-    }
+  };
+  // the scores of the first block, and the first half of its exponentials
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) mfma32_settle_agpr(dvacc[dt], dkacc[dt]);
+  for (int i = 0; i < W - 1; ++i) ring[i] = score_frag(0, 0, i);
+#pragma unroll
+  for (int i = 0; i < NS; ++i) {
+    score_mfma(0, i, ring[i % W]);
+    ring[(i + W - 1) % W] = i + W - 1 < NS ? score_frag(0, 0, i + W - 1) : load_frag(0, i + W - 1 - NS);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  if (EXACT) {
-    __syncthreads();              // the tiles in LDS are done with
-    elem_t* dk_rows = dqkv + ((int64_t)bi * s + kw0) * ld + h + hd * d;
-    store_rows_out<D>(&sQ_[0][0] + wave * (32 * (D + 8)), dkacc, scale, dk_rows, ld, s - kw0, lane);
-    store_rows_out<D>(&sdO_[0][0] + wave * (32 * (D + 8)), dvacc, 1.f, dk_rows + h, ld, s - kw0, lane);
-    return;
-  }
-  if (kj < s) {
-    elem_t* dk_row = dqkv + ((int64_t)bi * s + kj) * ld + h + hd * d;
-    elem_t* dv_row = dk_row + h;
+  load_stats(0, 0, 0);
+  load_stats(0, 0, 1);
+  mfma32_settle_vgpr(sacc[0], pacc[0]);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+  for (int r = 0; r < 8; ++r) softmax_elem(0, 0, r, true, kj - qt_begin * BQ - 4 * g);
+  __builtin_amdgcn_sched_barrier(0);
+  // the tiles on the diagonal, then the others in a loop of their own (so that the accumulators keep one place in
+  // the register files throughout it)
+  constexpr int DIAGONAL = 128 / BQ;
+  tile_stream(qt_begin, std::integral_constant<int, DIAGONAL>{});
+  if (DIAGONAL > 1 && qt_begin + 1 < n_qt) tile_stream(qt_begin + 1, std::integral_constant<int, 1>{});
+  for (int qt = qt_begin + DIAGONAL; qt < n_qt; ++qt) tile_stream(qt, std::integral_constant<int, 0>{});
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        elemx4 kv4, vv4;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          kv4[e] = (elem_t)(dkacc[dt][4 * q + e] * scale);
-          vv4[e] = (elem_t)dvacc[dt][4 * q + e];
-        }
-        if (dt * 32 + 8 * q + 4 * g < d) {
-          *reinterpret_cast<elemx4*>(dk_row + dt * 32 + 8 * q + 4 * g) = kv4;
-          *reinterpret_cast<elemx4*>(dv_row + dt * 32 + 8 * q + 4 * g) = vv4;
-        }
-      }
-  }
+  for (int dt = 0; dt < DT; ++dt) mfma32_settle_agpr(dvacc[dt], dkacc[dt]);
+  dma_wait_all();                 // copies of tiles beyond the last still write (zeros) to LDS
+  __syncthreads();                // the tiles in LDS are done with
+  constexpr int STAGED = 32 * (D + 8) * 2;
+  static_assert(8 * STAGED <= sizeof(lds.tiles), "the result rows fit the tile buffers");
+  elem_t* dk_rows = dqkv + ((int64_t)bi * s + kw0) * ld + h + hd * d;
+  store_rows_out<D>(lds.tiles + wave * STAGED, dkacc, scale, dk_rows, ld, s - kw0, cols, lane);
+  store_rows_out<D>(lds.tiles + (4 + wave) * STAGED, dvacc, 1.f, dk_rows + h, ld, s - kw0, cols, lane);
 }
 
-// dQ: grid (ceil(s/128), b*a); wave w owns queries q0 + 32w .. +31 and walks the key tiles up
-// to the diagonal (same traversal as the forward kernel).
-// The exact-size kernels also form delta (above) for their 128 queries, from the rows of dO they stage anyway and
-// the same rows of O, and leave it in `delta` for the dK / dV kernel, which then has to run behind this one: no
-// launch of its own for it, and dO is read once less.  The general kernels read `delta` and ignore `o`.
+// dQ: wave w owns queries q0 + 32w .. +31 and walks the key tiles up to the diagonal (same traversal as the forward kernel).
+// FORM_DELTA (d = D = 64 or 128): the kernel also forms delta (above) for its 128 queries, from the rows of dO and O, and
+// leaves it in `delta` for the dK / dV kernel, which then has to run behind this one: no launch of its own for it.  Else
+// `delta` is read and `o` ignored.  by_4: the sums in the order of the launch of its own, for sequences that take that launch
+// when they do not run with others.
+//
+// Two workgroups share a CU.  The fragments run a few MFMAs ahead through a ring, so that a wave waits for LDS only behind the
+// two barriers of a tile: one when everybody has left the tile before, whose buffer the memory pipeline then fills, one when
+// that has come.  40 heads of 128 x 2048 82 -> 74 us, 16 of 128 x 8192 418 -> 368, 8 x 24 of 188 x 512 100 -> 73.
 template <int D>
 struct DqLds {
-  static constexpr int BKV = 64, LDK = BothWaysStride<D>::LD;
-  __align__(16) elem_t tiles[2 * BKV * LDK];          // K and V tile; at the ends the staged Q, dO and dQ rows
+  static constexpr int BKV = 64, TILE = Tile<BKV, D>::BYTES, BUF = 2 * TILE;
+  // K and V tile, two of each; at the ends the staged Q, dO and dQ rows
+  __align__(1024) char tiles[2 * BUF];
   float delta[128];
 };
-// FORM_DELTA: delta is formed here, kept, and written out for a dK / dV launch behind this one; else it is read.  by_4: its
-// sums in the order of the launch of its own, for sequences that take that launch when they do not run with others.
-template <int D, bool EXACT, bool FORM_DELTA>
+template <int D, bool ALIGNED, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dq(
-    DqLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d_arg, const elem_t* __restrict__ qkv,
+    DqLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ o, const elem_t* __restrict__ dout, const float* __restrict__ lse, float* delta,
     elem_t* __restrict__ dqkv, int by_4) {
-  static_assert(EXACT || !FORM_DELTA, "the general kernels read delta");
-  constexpr int BKV = DqLds<D>::BKV, LDK = DqLds<D>::LDK, DT = D / 32, KK = D / 16;
-  elem_t* const smem = lds.tiles;
-  static_assert(2 * BKV * LDK >= 128 * (D + 8), "the workgroup's 128 rows fit the tile buffers");
-  elem_t* sK = smem;
-  elem_t* sV = smem + BKV * LDK;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5;
+  using L = DqLds<D>;
+  constexpr int BKV = L::BKV, DT = D / 32, KK = D / 16;
+  static_assert(Tile<128, D>::BYTES == L::BUF && 128 * (D + 8) * 2 <= 2 * L::BUF, "the workgroup's 128 rows fit the tile buffers");
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
   int rank, bh;
   attn_block(id, n_blocks, n_bh, rank, bh);
   const int qt = (s + 127) / 128 - 1 - rank;
   const int bi = bh / a, hd = bh % a;
-  const int d = EXACT ? D : d_arg;
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
-  const elem_t* kb = qb + h;
-  const elem_t* vb = qb + 2 * h;
   const elem_t* dob = dout + (int64_t)bi * s * h + hd * d;
   const int q0 = qt * 128, qw0 = q0 + 32 * wave, qi = qw0 + (lane & 31);
   const float scale = rsqrtf((float)d), scale_log2 = kLog2e * scale;
   const float lse_q = (qi < s) ? lse[((int64_t)bi * a + hd) * s + qi] * kLog2e : 0.f;
-  float delta_q;
-  float* const s_delta = lds.delta;
+  float delta_q = 0.f;
+  const HeadColumns cols(d, hd);
+  const FragLanes fl(lane);
+  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid),
+      do_src(dob, h, s, cols, tid);
+  const LdsBytes buf0(lds.tiles), buf1(lds.tiles + L::BUF);
 
   elemx8 qf[KK], dof[KK];
-  if (EXACT) {
-    // dO and O rows of the workgroup's queries, chunk for chunk in the same registers of the same threads: the
-    // D / 8 lanes that hold a row's chunks add up its products
-    using Rows = TileRegs<128, D>;
-    constexpr int LPR = D / 8, RSTEP = 256 / LPR;
-    const uint32_t o_bytes = (uint32_t)(((int64_t)(s - 1) * h + D) * 2), o_off0 = Rows::offset0((uint32_t)h * 2u, tid);
-    Rows r_q, r_do, r_o;         // all three requested at once; Q, needed first, in front
-    r_q.load_buffer(make_rsrc(qb, (uint32_t)(((int64_t)(s - 1) * ld + D) * 2)), Rows::offset0((uint32_t)ld * 2u, tid),
-                    (uint32_t)ld * 2u, q0);
-    r_do.load_buffer(make_rsrc(dob, o_bytes), o_off0, (uint32_t)h * 2u, q0);
-    if (FORM_DELTA) r_o.load_buffer(make_rsrc(o + (int64_t)bi * s * h + hd * d, o_bytes), o_off0, (uint32_t)h * 2u, q0);
-    r_q.template store<D + 8>(smem, tid);
-    __syncthreads();
+  q_src.template fill<128>(buf0, q0);
+  do_src.template fill<128>(buf1, q0);
+  if constexpr (FORM_DELTA) {
+    // O's rows and the same ones of dO: the D / 8 lanes that hold a row's chunks add up its products
+    constexpr int LPR = D / 8, RSTEP = 256 / LPR, N = 128 / RSTEP;
+    const elem_t* ob = o + (int64_t)bi * s * h + hd * d;
+    elemx8 ov[N], dv[N];
 #pragma unroll
-    for (int kk = 0; kk < KK; ++kk) qf[kk] = frag_kcontig(smem + (32 * wave) * (D + 8) + kk * 16, D + 8, lane);
-    __syncthreads();
-    r_do.template store<D + 8>(smem, tid);
+    for (int j = 0; j < N; ++j) {
+      const int row = min(q0 + tid / LPR + j * RSTEP, s - 1);
+      const int64_t at = (int64_t)row * h + (tid % LPR) * 8;
+      ov[j] = *reinterpret_cast<const elemx8*>(ob + at);
+      dv[j] = *reinterpret_cast<const elemx8*>(dob + at);
+    }
 #pragma unroll
-    for (int j = 0; FORM_DELTA && j < Rows::NCH; ++j) {
-      const elemx8 ov = __builtin_bit_cast(elemx8, r_o.r[j]), dv = __builtin_bit_cast(elemx8, r_do.r[j]);
+    for (int j = 0; j < N; ++j) {
       float p;
       if (by_4) {
         // the launch of its own's order: 4 elements of every 64 per lane, here in pairs of such lanes; at D = 128 the lanes
         // of the upper half go on from the sums of the lower half's
-        float lo = delta_add<4, true>(0.f, ov, dv, 0), hi = delta_add<4, true>(0.f, ov, dv, 4);
+        float lo = delta_add<4, true>(0.f, ov[j], dv[j], 0), hi = delta_add<4, true>(0.f, ov[j], dv[j], 4);
         if (LPR == 16) {
           const float lo0 = __shfl_xor(lo, 8, 64), hi0 = __shfl_xor(hi, 8, 64);
-          lo = delta_add<4, true>(lo0, ov, dv, 0);       // of the upper half's lanes; the lower half's are not used
-          hi = delta_add<4, true>(hi0, ov, dv, 4);
+          lo = delta_add<4, true>(lo0, ov[j], dv[j], 0);       // of the upper half's lanes; the lower half's are not used
+          hi = delta_add<4, true>(hi0, ov[j], dv[j], 4);
         }
 #pragma unroll
         for (int off = 4; off > 0; off >>= 1) { lo += __shfl_xor(lo, off, 64); hi += __shfl_xor(hi, off, 64); }
         p = lo + hi;
         if (LPR == 16) p = __shfl_xor(p, 8, 64);         // to the lane that keeps it
       } else {
-        p = delta_add<8, false>(0.f, ov, dv, 0);
+        p = delta_add<8, false>(0.f, ov[j], dv[j], 0);
 #pragma unroll
         for (int off = LPR / 2; off > 0; off >>= 1) p += __shfl_xor(p, off, 64);
       }
       const int row = tid / LPR + j * RSTEP;
       if (tid % LPR == 0) {
-        s_delta[row] = p;
+        lds.delta[row] = p;
         if (q0 + row < s) delta[((int64_t)bi * a + hd) * s + q0 + row] = p;
       }
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) dof[kk] = frag_kcontig(smem + (32 * wave) * (D + 8) + kk * 16, D + 8, lane);
-    delta_q = FORM_DELTA ? s_delta[32 * wave + (lane & 31)] : (qi < s) ? delta[((int64_t)bi * a + hd) * s + qi] : 0.f;
-  } else {
-    delta_q = (qi < s) ? delta[((int64_t)bi * a + hd) * s + qi] : 0.f;
-#pragma unroll
-    for (int kk = 0; kk < KK; ++kk) {
-      qf[kk] = global_frag<EXACT>(qb, ld, qi, s, kk * 16, lane, d);
-      dof[kk] = global_frag<EXACT>(dob, h, qi, s, kk * 16, lane, d);
-    }
   }
+  dma_wait_all();
+  q_src.template clear_foreign<128>(buf0);
+  do_src.template clear_foreign<128>(buf1);
+  __syncthreads();
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) qf[kk] = frag_rows<128, D>(buf0, fl, wave, kk);
+#pragma unroll
+  for (int kk = 0; kk < KK; ++kk) dof[kk] = frag_rows<128, D>(buf1, fl, wave, kk);
+  if constexpr (FORM_DELTA) delta_q = lds.delta[32 * wave + (lane & 31)];
+  else if (qi < s) delta_q = delta[((int64_t)bi * a + hd) * s + qi];
+  __syncthreads();                // the rows have been read
+  k_src.template fill<BKV>(buf0, 0);
+  v_src.template fill<BKV>(buf0 + L::TILE, 0);
   floatx16 dqacc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
@@ -858,47 +773,52 @@ __device__ __forceinline__ void attn_bwd_dq(
 
   const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
-  TileRegs<BKV, D> rk, rv;
-  const uint32_t row_bytes = (uint32_t)ld * 2u, tile_bytes = EXACT ? (uint32_t)(((int64_t)(s - 1) * ld + D) * 2) : 0u;
-  const __amdgpu_buffer_rsrc_t k_rsrc = make_rsrc(kb, tile_bytes), v_rsrc = make_rsrc(vb, tile_bytes);
-  const uint32_t off0 = TileRegs<BKV, D>::offset0(row_bytes, tid);
-  auto fetch = [&](int row0) {
-    if (EXACT) {
-      rk.load_buffer(k_rsrc, off0, row_bytes, row0);
-      rv.load_buffer(v_rsrc, off0, row_bytes, row0);
-    } else {
-      rk.template load<EXACT>(kb, ld, row0, s, d, tid);
-      rv.template load<EXACT>(vb, ld, row0, s, d, tid);
-    }
+  // Slots of a tile: per half of 32 keys NS score MFMAs (S and dP in turn), then NG for dQ; those beyond the last are the
+  // next tile's.
+  constexpr int NS = 2 * KK, NG = 2 * DT, HALF = NS + NG, NSLOT = 2 * HALF, W = D == 64 ? 4 : 8;
+  static_assert(NSLOT % W == 0 && NG >= W - 1, "ring position");
+  auto load_frag = [&](LdsBytes tile, LdsBytes next, int j) {
+    if (j >= NSLOT) { tile = next; j -= NSLOT; }
+    const int ks = j / HALF, i = j % HALF;
+    if (i < NS) return frag_rows<BKV, D>(i & 1 ? tile + L::TILE : tile, fl, ks, i >> 1);
+    return frag_cols<BKV, D>(tile, fl, 2 * ks + (i - NS) / DT, (i - NS) % DT);
   };
-  fetch(0);
+  elemx8 ring[W];
+  dma_wait_all();
+  k_src.template clear_foreign<BKV>(buf0);
+  v_src.template clear_foreign<BKV>(buf0 + L::TILE);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < W - 1; ++j) ring[j] = load_frag(buf0, buf0, j);
   for (int kt = 0; kt < n_kt; ++kt) {
     const int k0 = kt * BKV;
-    __syncthreads();
-    rk.template store<LDK>(sK, tid);
-    rv.template store<LDK>(sV, tid);
-    __syncthreads();
-    if (kt + 1 < n_kt) fetch(k0 + BKV);
-    if (k0 > qw0 + 31) continue;
+    const LdsBytes tile = buf0 + (kt & 1) * L::BUF, next = buf0 + (~kt & 1) * L::BUF;
+    // every wave has left the tile before
+    asm volatile("s_barrier" : : : "memory");
+    k_src.template fill<BKV>(next, k0 + BKV);
+    v_src.template fill<BKV>(next + L::TILE, k0 + BKV);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       floatx16 sacc, pacc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) sacc[r] = pacc[r] = 0.f;
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        sacc = mfma32(frag_kcontig(sK + (32 * ks) * LDK + kk * 16, LDK, lane), qf[kk], sacc);
-        pacc = mfma32(frag_kcontig(sV + (32 * ks) * LDK + kk * 16, LDK, lane), dof[kk], pacc);
+      for (int i = 0; i < NS; ++i) {
+        const int j = ks * HALF + i;
+        if (i & 1) pacc = mfma32(ring[j % W], dof[i >> 1], pacc);
+        else sacc = mfma32(ring[j % W], qf[i >> 1], sacc);
+        ring[(j + W - 1) % W] = load_frag(tile, next, j + W - 1);
+        __builtin_amdgcn_sched_barrier(0);
       }
       // lane = query qi; register r = key k0 + 32ks + 8*(r/4) + 4g + r%4
       // masking in the blocks that straddle the diagonal only (a wave-uniform branch, kept as one)
       if (k0 + 32 * ks + 31 > qw0) {
         asm volatile("" ::: "memory");
+        const int last = qi - k0 - 4 * g;       // the lane's last key, counted from its first one
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int key = k0 + 32 * ks + 8 * (r >> 2) + 4 * g + (r & 3);
-          if (key > qi) sacc[r] = -INFINITY;
-        }
+        for (int r = 0; r < 16; ++r)
+          if (32 * ks + 8 * (r >> 2) + (r & 3) > last) sacc[r] = -INFINITY;
       }
       const float neg_lse = -lse_q;
 #pragma unroll
@@ -906,78 +826,74 @@ __device__ __forceinline__ void attn_bwd_dq(
         const float p = fast_exp2(fmaf(sacc[r], scale_log2, neg_lse));
         pacc[r] = p * (pacc[r] - delta_q);
       }
+      elemx8 dsf[2];
 #pragma unroll
-      for (int c = 0; c < 2; ++c) {
-        const elemx8 dsf = pack8(pacc, 8 * c);
+      for (int c = 0; c < 2; ++c) dsf[c] = pack8(pacc, 8 * c);
+      if (ks == 1) {              // the next tile's first fragments are read below
+        dma_wait_all();
+        k_src.template clear_foreign<BKV>(next);
+        v_src.template clear_foreign<BKV>(next + L::TILE);
+        __syncthreads();
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
-          dqacc[dt] = mfma32(frag_kstrided<true>(sK + (32 * ks + 16 * c) * LDK + dt * 32, LDK, lane),
-                             dsf, dqacc[dt]);
+      for (int i = 0; i < NG; ++i) {
+        const int j = ks * HALF + NS + i;
+        dqacc[i % DT] = mfma32(ring[j % W], dsf[i / DT], dqacc[i % DT]);
+        ring[(j + W - 1) % W] = load_frag(tile, next, j + W - 1);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
-  if (EXACT) {
-    __syncthreads();              // the tiles in LDS are done with
-    store_rows_out<D>(smem + wave * (32 * (D + 8)), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, lane);
-    return;
-  }
-  if (qi < s) {
-    elem_t* dq_row = dqkv + ((int64_t)bi * s + qi) * ld + hd * d;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        elemx4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (elem_t)(dqacc[dt][4 * q + e] * scale);
-        if (EXACT || dt * 32 + 8 * q + 4 * g < d) *reinterpret_cast<elemx4*>(dq_row + dt * 32 + 8 * q + 4 * g) = v;
-      }
-  }
+  dma_wait_all();
+  __syncthreads();                // the tiles in LDS are done with
+  store_rows_out<D>(lds.tiles + wave * (32 * (D + 8) * 2), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, cols, lane);
 }
 
 // ------------------------------------------------------------------- backward kernels
-template <int D, bool EXACT>
+template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
     int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, const float* __restrict__ delta, elem_t* __restrict__ dqkv) {
   __shared__ DkdvLds<D> lds;
-  attn_bwd_dkdv<D, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
+  attn_bwd_dkdv<D, ALIGNED>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
 }
-template <int D, bool EXACT>
+template <int D, bool ALIGNED, bool FORM_DELTA = false>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
     elem_t* __restrict__ dqkv, int by_4) {
   __shared__ DqLds<D> lds;
-  attn_bwd_dq<D, EXACT, EXACT>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv, by_4);
+  attn_bwd_dq<D, ALIGNED, FORM_DELTA>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv, by_4);
 }
 // Both at once, for problems whose tiles do not fill the chip: the first half of the workgroups forms dK and dV, the second
 // dQ; delta is there already.  Each half alone is a chain of up to s / 128 (s / 64) tiles per workgroup on a part of the
 // CUs; side by side they take the longer of the two times.
-template <int D, bool EXACT>
+template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
     int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, float* delta, elem_t* __restrict__ dqkv) {
   __shared__ union { DkdvLds<D> dkdv; DqLds<D> dq; } lds;
   const int n = gridDim.x >> 1, id = blockIdx.x;
-  if (id < n) attn_bwd_dkdv<D, EXACT>(lds.dkdv, id, n, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
-  else attn_bwd_dq<D, EXACT, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
+  if (id < n) attn_bwd_dkdv<D, ALIGNED>(lds.dkdv, id, n, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
+  else attn_bwd_dq<D, ALIGNED, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
 }
 
 // ------------------------------------------------------------------------- launchers
-// d = 64 or 128: the kernels compiled for exactly that head dimension.  Any other multiple of 4 up to 192:
-// the next compiled size with the columns beyond d masked.
-// The exact-size kernels address the rows of a (batch, head) with 32-bit byte offsets (buffer loads): for sequences
-// too long for that (s * 3 * a * d * 2 bytes beyond 2^31) the general kernels take over.
-#define AXONN_ATTN_DISPATCH(KERNEL, ...)                                                              \
-  do {                                                                                                \
-    const bool off32 = ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);                       \
-    if (d == 64 && off32) hipLaunchKernelGGL((KERNEL<64, true>), grid, dim3(256), 0, st, __VA_ARGS__);         \
-    else if (d == 128 && off32) hipLaunchKernelGGL((KERNEL<128, true>), grid, dim3(256), 0, st, __VA_ARGS__);  \
-    else if (d <= 64) hipLaunchKernelGGL((KERNEL<64, false>), grid, dim3(256), 0, st, __VA_ARGS__);    \
-    else if (d <= 128) hipLaunchKernelGGL((KERNEL<128, false>), grid, dim3(256), 0, st, __VA_ARGS__); \
-    else hipLaunchKernelGGL((KERNEL<192, false>), grid, dim3(256), 0, st, __VA_ARGS__);               \
+// Head dimensions up to 64, 128 and 192 run in tiles of that many columns.  The copies into LDS want matrices that start at a
+// 16-byte boundary and take 32-bit byte offsets within 128 rows; others go through registers.
+#define AXONN_ATTN_DISPATCH(KERNEL, ...)                                                                  \
+  do {                                                                                                    \
+    if (d <= 64) { if (copies) hipLaunchKernelGGL((KERNEL<64, true>), grid, dim3(256), 0, st, __VA_ARGS__);       \
+                   else hipLaunchKernelGGL((KERNEL<64, false>), grid, dim3(256), 0, st, __VA_ARGS__); }           \
+    else if (d <= 128) { if (copies) hipLaunchKernelGGL((KERNEL<128, true>), grid, dim3(256), 0, st, __VA_ARGS__); \
+                         else hipLaunchKernelGGL((KERNEL<128, false>), grid, dim3(256), 0, st, __VA_ARGS__); }    \
+    else { if (copies) hipLaunchKernelGGL((KERNEL<192, true>), grid, dim3(256), 0, st, __VA_ARGS__);              \
+           else hipLaunchKernelGGL((KERNEL<192, false>), grid, dim3(256), 0, st, __VA_ARGS__); }                  \
   } while (0)
+static bool copies_fit(const void* qkv, const void* dout, int64_t h) {
+  return (((uintptr_t)qkv | (uintptr_t)dout) & 15) == 0 && 128 * 3 * h * 2 < (int64_t(1) << 31);
+}
 
 // dK / dV and dQ as one launch while the workgroups of both find a CU each (the dK / dV one leaves no room for a second in
 // registers and LDS).  delta then has a launch of its own, which the dQ kernel otherwise spares.  Measured, backward of 16
@@ -991,6 +907,7 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
                                 hipStream_t st) {
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(((s + 127) / 128) * b * a));
+  const bool copies = copies_fit(qkv, nullptr, (int64_t)a * d);
   AXONN_ATTN_DISPATCH(attn_fwd_kernel, s, a, b * a, d, (const elem_t*)qkv, (elem_t*)o, lse);
   return hipGetLastError();
 }
@@ -1001,14 +918,20 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
-  // the exact-size dQ kernel (the dispatch's condition for it) forms delta itself and runs first; sequences that run together
-  // get the sums in the order that rule_b of them have
-  const bool dq_forms_delta = !both && (d == 64 || d == 128) && ((int64_t)s + 256) * 3 * a * d * 2 < (int64_t(1) << 31);
+  const bool copies = copies_fit(qkv, dout, (int64_t)a * d);
+  // for d = 64 and 128 the dQ kernel forms delta itself and runs first; sequences that run together get the sums in the order
+  // that rule_b of them have
+  const bool dq_forms_delta = !both && (d == 64 || d == 128);
   const int by_4 = ((s + 127) / 128) * (rule_b > 0 ? rule_b : b) * a <= kBothMaxTiles;
   hipError_t e;
   dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
-    AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, by_4);
+#define AXONN_ATTN_DQ(D, COPIES)                                                                                                 \
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, COPIES, true>), grid, dim3(256), 0, st, s, a, b * a, d, (const elem_t*)qkv,          \
+                     (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, by_4)
+    if (d == 64) { if (copies) AXONN_ATTN_DQ(64, true); else AXONN_ATTN_DQ(64, false); }
+    else { if (copies) AXONN_ATTN_DQ(128, true); else AXONN_ATTN_DQ(128, false); }
+#undef AXONN_ATTN_DQ
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);

@@ -72,33 +72,62 @@ __device__ __forceinline__ void mfma16_acc(floatx4& c, elemx8 a, elemx8 b) {
 // accumulator themselves (volatile statements keep their order, and memory operations do not move across them): a
 // kernel with more than 256 registers per lane gets the accumulation-register form of the builtin for every MFMA, and
 // results that vector instructions consume next would be copied out one register at a time.
-//   mfma32_agpr:      c += a x b, c in the accumulation registers (long-lived accumulators)
-//   mfma32_vgpr_*_ba: c in ordinary registers, b in the accumulation registers; plain: c += a x b, _zero: c = a x b
-// The compiler does not know these are MFMAs and keeps none of their hazards, so the statements carry them:
-//   * two wait states ahead of every MFMA: the distance a register written by a vector instruction needs before an
-//     MFMA reads it, and the compiler may place such a write (a copy, an initialisation, the conversion that produces
-//     an operand) directly in front of the statement;
-//   * _settled: 20 wait states behind the MFMA, inside the statement, so that nothing can come between: more than
-//     the eight passes plus the distance the rules ask for before another kind of instruction reads (or the
-//     compiler copies) the result.  They pass while the MFMA executes.  A chain's last MFMA is issued this way, or
-//     one MFMA before such a one; mfma32_settle_agpr does the same for accumulators at the end of a kernel.
-#define AXONN_MFMA32_GAP "s_nop 1\n\t"
-#define AXONN_MFMA32_SETTLE "\n\ts_nop 7\n\ts_nop 7\n\ts_nop 3"
+//   mfma32_agpr:  c += a x b, c in the accumulation registers (long-lived accumulators)
+//   mfma32_vgpr:  c += a x b, c in ordinary registers; b in the accumulation registers (BA) or ordinary ones
+//   mfma32_vgpr_zero: c = a x b
+// The compiler does not know these are MFMAs and keeps none of their hazards.  Wait states in front of every statement would
+// (two instructions must lie between a vector instruction that writes a register and an MFMA that reads it), but they take
+// issue slots that a wave alone on its SIMD does not have: a slot of one MFMA, one LDS read and half an element's
+// exponential takes 45 clocks with `s_nop 1` and 40 without.  So the kernels place their operands' producers further
+// away, start to use a result three MFMAs later (mfma32_settle_* where nothing is in between), and
+// tests/test_library_abi.py checks both distances in the built libraries.
 __device__ __forceinline__ void mfma32_agpr(floatx16& c, elemx8 a, elemx8 b) {
-  asm volatile(AXONN_MFMA32_GAP AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma32_vgpr_ba(floatx16& c, elemx8 a, elemx8 b) {
-  asm volatile(AXONN_MFMA32_GAP AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
+template <bool BA>
+__device__ __forceinline__ void mfma32_vgpr(floatx16& c, elemx8 a, elemx8 b) {
+  if constexpr (BA) asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+v"(c) : "v"(a), "a"(b));
+  else asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma32_vgpr_zero_ba(floatx16& c, elemx8 a, elemx8 b) {
-  asm volatile(AXONN_MFMA32_GAP AXONN_MFMA_32X32X16_ASM " %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b));
+template <bool BA>
+__device__ __forceinline__ void mfma32_vgpr_zero(floatx16& c, elemx8 a, elemx8 b) {
+  if constexpr (BA) asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, 0" : "=&v"(c) : "v"(a), "a"(b));
+  else asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, 0" : "=&v"(c) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma32_vgpr_settled_ba(floatx16& c, elemx8 a, elemx8 b) {
-  asm volatile(AXONN_MFMA32_GAP AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" AXONN_MFMA32_SETTLE : "+v"(c) : "v"(a), "a"(b));
+__device__ __forceinline__ void mfma32_settle_vgpr(floatx16& c0, floatx16& c1) {
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+v"(c0), "+v"(c1));
 }
 __device__ __forceinline__ void mfma32_settle_agpr(floatx16& c0, floatx16& c1) {
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" : "+a"(c0), "+a"(c1));
 }
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // 16-byte chunk kept in registers; buffer descriptor
+
+// Workgroup barrier that orders LDS traffic only: global loads issued before it may still be in
+// flight after it (the prefetch of the next k-tile is).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+// Copy by the memory pipeline: the 64 chunks of 16 bytes that the lanes address (byte offset `voffset` from the
+// descriptor's base plus `soffset`) to 1 KB of LDS at `lds_addr`, in lane order.  The compiler does not see it: dma_wait_all.
+__device__ __forceinline__ void dma_chunk16(u32x4 rsrc, uint32_t voffset, uint32_t soffset, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
+               : "memory");
+}
+__device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// Buffer descriptor words of `bytes` bytes at p (raw buffer, offsets at or beyond `bytes` read zeros).
+__device__ __forceinline__ u32x4 rsrc_words(const void* p, uint32_t bytes) {
+  const uint64_t a = (uint64_t)p;
+  u32x4 r;
+  r[0] = (uint32_t)a; r[1] = (uint32_t)(a >> 32) & 0xffffu; r[2] = bytes; r[3] = 0x00020000u;
+  return r;
+}
+constexpr uint32_t kOutOfRange = 0x80000000u;   // an offset beyond any descriptor's range
 
 // Fragment of a 32(row) x 16(k) operand block from an LDS tile stored [row][k] (k
 // contiguous, `ld` elements per row).  `base` points at (row0, k0).

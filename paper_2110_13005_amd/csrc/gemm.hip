@@ -26,16 +26,6 @@ namespace axonn {
 // load is unconditional and nothing has to be patched after it arrives.
 __device__ __align__(16) uint32_t g_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));  // 16-byte chunk kept in registers
-
-// Workgroup barrier that orders LDS traffic only: global loads issued before it may still be in
-// flight after it (the prefetch of the next k-tile is).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Output tile (tm, tn) of this workgroup.  Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of
 // its own; the ids are remapped so that each XCD works on a contiguous run of tiles, and the tiles are ordered
 // in bands of 8 tiles across the SHORTER side of the tile grid, walked along the longer side: the ~32 tiles an
@@ -541,7 +531,6 @@ constexpr bool epilogue_sums_columns(bool a_kc, bool b_kc, int e) {
 // Tiles are fetched with buffer loads: an offset at or beyond the descriptor's size returns zeros
 // without touching memory, which covers rows outside the matrix, the k tail and the tiles past the
 // last one without branches or per-chunk pointers.
-constexpr uint32_t kOutOfRange = 0x80000000u;
 
 
 // Item idx of n items spread evenly over the MFMA slots [first, first + span), and its inverse (-1: no
@@ -789,12 +778,6 @@ __global__ __launch_bounds__(256) void gemm_big_kernel(const GemmArgs g) {
 // half a cache line: measured 3-6 % slower than whole lines behind one barrier.
 // The copies are inline assembly: the compiler neither sees them nor counts them in vmcnt, so the
 // waits on them are written out here, and the loop contains no other vector memory instruction.
-__device__ __forceinline__ void dma_chunk16(u32x4 rsrc, uint32_t voffset, uint32_t soffset, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
-               : "memory");
-}
 // One MFMA with a copy around it: M0 is written in front of the MFMA and consumed behind it (the MFMA is
 // the independent instruction the hardware wants between the two).  One statement, so that nothing the
 // compiler emits can come between the write of M0 and its use.
@@ -806,16 +789,6 @@ __device__ __forceinline__ void mfma16_acc_dma(floatx4& c, elemx8 a, elemx8 b, u
                : "v"(a), "v"(b), "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset)
                : "memory");
 }
-__device__ __forceinline__ void dma_wait_all() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Buffer descriptor words of `bytes` bytes at p (raw buffer, offsets at or beyond `bytes` read zeros).
-__device__ __forceinline__ u32x4 rsrc_words(const void* p, uint32_t bytes) {
-  const uint64_t a = (uint64_t)p;
-  u32x4 r;
-  r[0] = (uint32_t)a; r[1] = (uint32_t)(a >> 32) & 0xffffu; r[2] = bytes; r[3] = 0x00020000u;
-  return r;
-}
-
 // The copy instructions of a k-step in the order they are issued.  Phase 0: the first halves of the
 // k-strided operands and the "early" rows of a k-contiguous A.  Phase 1: the rest of the k-contiguous
 // operands, then the second halves of the k-strided ones.

@@ -453,6 +453,57 @@ def test_attention_around_the_one_launch_backward(b, s, a, d):
     test_attention_fwd_bwd(b, s, a, d)
 
 
+@pytest.mark.parametrize("b,s,a,d", [(1, 200, 2, 64), (2, 136, 33, 128), (1, 72, 4, 44), (1, 264, 2, 188), (1, 130, 66, 124)])
+def test_attention_of_matrices_that_are_not_16_byte_aligned(b, s, a, d):
+    """Such tiles go through registers instead of the memory pipeline's copies; the arithmetic is the same, so are the bits."""
+    import torch
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+    qkv, dout = (torch.randn(b * s, n, generator=g, device="cuda").to(dt) for n in (3 * h, h))
+
+    def shifted(t, by):
+        buf = torch.zeros(t.numel() + 8, dtype=dt, device="cuda")
+        buf[by:by + t.numel()] = t.flatten()
+        return buf[by:by + t.numel()].view(t.shape)
+
+    def run(by):
+        q, do = shifted(qkv, by), shifted(dout, by)
+        o, dq = torch.zeros(b * s, h, dtype=dt, device="cuda"), torch.zeros(b * s, 3 * h, dtype=dt, device="cuda")
+        lse, ws = (torch.zeros(b, a, s, device="cuda") for _ in range(2))
+        B.axonn_attention_fwd(b, s, a, d, q, o, lse)
+        B.axonn_attention_bwd(b, s, a, d, q, o, lse, do, dq, ws)
+        return o, lse, dq
+
+    for x, y in zip(run(0), run(4)):
+        assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("s,a,d", [(200, 4, 44), (130, 2, 188), (72, 4, 124), (72, 4, 60)])
+def test_attention_head_is_not_reached_by_its_neighbours(s, a, d):
+    """Heads of an odd multiple of 4 columns share 16-byte chunks: what the neighbours hold there, infinities and NaN included,
+    stays out of a head's results."""
+    import torch
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+    qkv, dout = (torch.randn(s, n, generator=g, device="cuda").to(dt) for n in (3 * h, h))
+
+    def run(q, do):
+        o, dq = torch.zeros(s, h, dtype=dt, device="cuda"), torch.zeros(s, 3 * h, dtype=dt, device="cuda")
+        lse, ws = (torch.zeros(1, a, s, device="cuda") for _ in range(2))
+        B.axonn_attention_fwd(1, s, a, d, q, o, lse)
+        B.axonn_attention_bwd(1, s, a, d, q, o, lse, do, dq, ws)
+        return torch.cat([o.view(s, 1, a, d), dq.view(s, 3, a, d)], 1)
+
+    clean = run(qkv, dout)
+    assert torch.isfinite(clean.float()).all()
+    for head in range(a):
+        others = [x for x in range(a) if x != head]
+        q, do = qkv.clone(), dout.clone()
+        q.view(s, 3, a, d)[:, :, others] = float("nan")
+        do.view(s, a, d)[:, others] = float("inf")
+        assert torch.equal(run(q, do)[:, :, head], clean[:, :, head])
+
+
 @pytest.mark.parametrize("b,s,a,d", [(2, 72, 66, 64), (4, 72, 33, 128)])
 def test_attention_delta_is_the_sum_of_products_in_element_order(b, s, a, d):
     """Where the dQ kernel forms delta = sum_d dO O itself (more than 128 tiles): 8 products per lane one after the other, then

@@ -107,13 +107,17 @@ def test_argument_validation_without_device():
     assert e.value.status == B.AXONN_EUNSUPPORTED
 
 
-def _kernel_scratch(lib_path, tmp_path):
-    """{mangled kernel name: bytes of scratch memory per lane} of a built library, from its own code objects' notes."""
-    readelf = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
-    if not os.path.exists(readelf):
-        pytest.skip("no llvm-readelf")
+def _llvm_tool(name):
+    path = shutil.which(name) or "/opt/rocm/llvm/bin/" + name
+    if not os.path.exists(path):
+        pytest.skip("no " + name)
+    return path
+
+
+def _code_objects(lib_path, tmp_path):
+    """The gfx950 code objects of a built library, as files."""
     blob = open(lib_path, "rb").read()
-    magic, out = b"__CLANG_OFFLOAD_BUNDLE__", {}
+    magic, out = b"__CLANG_OFFLOAD_BUNDLE__", []
     at = blob.find(magic)
     while at >= 0:
         (n,), p = struct.unpack_from("<Q", blob, at + len(magic)), at + len(magic) + 8
@@ -122,14 +126,21 @@ def _kernel_scratch(lib_path, tmp_path):
             triple = blob[p + 24:p + 24 + name_len]
             p += 24 + name_len
             if b"gfx950" in triple and size:
-                obj = tmp_path / "code_object"
-                obj.write_bytes(blob[at + off:at + off + size])
-                notes = subprocess.run([readelf, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
-                names = re.findall(r"^ +\.name: +(_Z\S+)$", notes, flags=re.M)
-                scratch = re.findall(r"^ +\.private_segment_fixed_size: +(\d+)$", notes, flags=re.M)
-                assert len(names) == len(scratch)
-                out.update(zip(names, map(int, scratch)))
+                out.append(tmp_path / ("code_object_%d" % len(out)))
+                out[-1].write_bytes(blob[at + off:at + off + size])
         at = blob.find(magic, at + 1)
+    return out
+
+
+def _kernel_scratch(lib_path, tmp_path):
+    """{mangled kernel name: bytes of scratch memory per lane} of a built library, from its own code objects' notes."""
+    readelf, out = _llvm_tool("llvm-readelf"), {}
+    for obj in _code_objects(lib_path, tmp_path):
+        notes = subprocess.run([readelf, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+        names = re.findall(r"^ +\.name: +(_Z\S+)$", notes, flags=re.M)
+        scratch = re.findall(r"^ +\.private_segment_fixed_size: +(\d+)$", notes, flags=re.M)
+        assert len(names) == len(scratch)
+        out.update(zip(names, map(int, scratch)))
     return out
 
 
@@ -141,3 +152,50 @@ def test_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
     scratch = {k: v for k, v in _kernel_scratch(BLD.VARIANTS[elem][0], tmp_path).items() if "gemm_" in k or "layernorm_" in k}
     assert len(scratch) > 50
     assert not {k: v for k, v in scratch.items() if v}
+
+
+def _registers(operand):
+    m = re.match(r"^[-|]*([va])(?:(\d+)|\[(\d+):(\d+)\])", operand)
+    if not m:
+        return set()
+    lo, hi = (int(m.group(2)),) * 2 if m.group(2) else (int(m.group(3)), int(m.group(4)))
+    return {(m.group(1), i) for i in range(lo, hi + 1)}
+
+
+@pytest.mark.parametrize("elem", ["bf16", "fp16"])
+def test_attention_mfmas_keep_their_distances(elem, tmp_path):
+    """The dK / dV kernels' MFMAs are inline assembly, for which the compiler keeps no distances.  In program order: two wait
+    states between a vector instruction's result and an MFMA that reads it; between an MFMA's result and another kind of
+    instruction that touches it two MFMAs or eleven wait states."""
+    from paper_2110_13005_amd import build as BLD
+    objdump, kernels, near = _llvm_tool("llvm-objdump"), 0, []
+    for obj in _code_objects(BLD.VARIANTS[elem][0], tmp_path):
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(obj)], capture_output=True, text=True, check=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\S*attn_bwd_(?:dkdv|both)\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, flags=re.M | re.S):
+            kernels += 1
+            pos = mfmas = 0
+            by_vector, by_mfma = {}, {}
+            for line in body.splitlines():
+                op, _, rest = line.split("//")[0].strip().partition(" ")
+                operands = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)]
+                if op == "s_nop":
+                    pos += int(operands[0], 0)
+                elif op.startswith("v_mfma"):
+                    used = set().union(*(_registers(x) for x in operands[1:]))
+                    near += [(name, line) for r in used if pos - by_vector.get(r, -9) - 1 < 2]
+                    for r in _registers(operands[0]):
+                        by_mfma[r] = (pos, mfmas)
+                        by_vector.pop(r, None)
+                    mfmas += 1
+                elif op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_")):
+                    for r in set().union(*(_registers(x) for x in operands)):
+                        at, n = by_mfma.get(r, (-99, -9))
+                        if pos - at - 1 < 11 and mfmas - n - 1 < 2:
+                            near.append((name, line))
+                    for r in _registers(operands[0]):
+                        by_mfma.pop(r, None)
+                        by_vector.pop(r, None)
+                        if op.startswith("v_"):
+                            by_vector[r] = pos
+                pos += 1
+    assert kernels >= 12 and not near, near[:4]
