@@ -1285,43 +1285,22 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
 
   uint32_t cur = 0, nxt = (NS - 1) * STAGE;            // stage to read next; stage to refill
   elemx8 fa[2][SLICES][TM], fb[2][SLICES][TN];
-  // Stage `cur` into fragment set F.  The wave's own copies of it have arrived behind the wait, everybody's behind
-  // the barrier, and nobody reads the stage of the step before any more: it may be refilled from here on.
-  auto read = [&](auto set) {
+  // Fragment f (B's, then A's, by slices) of stage `cur` into set F.
+  constexpr int NFR = SLICES * (TM + TN), NM = SLICES * TM * TN;
+  auto read_one = [&](auto set, int f) {
     constexpr int F = decltype(set)::value;
+    const int s = f / (TM + TN), i = f % (TM + TN);
+    if (i < TN) fb[F][s][i] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + i) * 16, grp * SLICES + s, lane);
+    else fa[F][s][i - TN] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i - TN) * 16, grp * SLICES + s, lane);
+  };
+  // The wave's own copies of stage `cur` have arrived behind the wait, everybody's behind the barrier, and nobody reads the
+  // stage of the step before any more: it may be refilled from here on.
+  auto enter = [&]() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"((NS - 2) * ND) : "memory");
     lds_barrier();
-#pragma unroll
-    for (int s = 0; s < SLICES; ++s) {
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        fb[F][s][j] = ring_fragment<B_KC, BN>(smem + cur + SA, (wn * TN + j) * 16, grp * SLICES + s, lane);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        fa[F][s][i] = ring_fragment<A_KC, BM>(smem + cur, (wm * TM + i) * 16, grp * SLICES + s, lane);
-    }
-    __builtin_amdgcn_sched_barrier(0);
   };
-  // The MFMAs of set F, and between them (COPY) the copies of the next k-tile into the stage read last but one.
-  auto multiply = [&](auto set, auto with_copies) {
+  auto column_sums = [&](auto set) {
     constexpr int F = decltype(set)::value;
-    constexpr bool COPY = decltype(with_copies)::value;
-    constexpr int NM = SLICES * TM * TN;
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
-      const int s = q / (TM * TN), i = q / TN % TM, j = q % TN;
-      acc[i][j] = mfma16(fb[F][s][j], fa[F][s][i], acc[i][j]);
-      if (COPY) {
-        const int c = item_at(q, ND, 0, NM);
-        if (c >= 0) {
-          copy(c, nxt);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-    }
-    if (COPY) copy_done();
-    nxt = cur;
-    cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
     if (CS && cs_on) {
 #pragma unroll
       for (int s = 0; s < SLICES; ++s)
@@ -1331,9 +1310,43 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
           for (int e = 0; e < 4; ++e) colsum_pair(cs[j], fb[F][s][j], e);
     }
   };
+  // The MFMAs of set F, and between them (MORE) the fragments of stage `cur` into the other set and the copies of the next
+  // k-tile into the stage read last but one.  Read in one go behind the barrier, the eight waves' fragments keep the LDS busy
+  // for as long as a third of the MFMAs, which wait for them.
+  auto multiply = [&](auto set, auto more) {
+    constexpr int F = decltype(set)::value;
+    constexpr bool MORE = decltype(more)::value;
+#pragma unroll
+    for (int q = 0; q < NM; ++q) {
+      const int s = q / (TM * TN), i = q / TN % TM, j = q % TN;
+      acc[i][j] = mfma16(fb[F][s][j], fa[F][s][i], acc[i][j]);
+      if (MORE) {
+        constexpr int SPAN = NM - NM / 4;
+        bool placed = false;
+#pragma unroll
+        for (int f = NFR * q / SPAN; f < NFR * (q + 1) / SPAN && f < NFR; ++f) {
+          read_one(std::integral_constant<int, F ^ 1>{}, f);
+          placed = true;
+        }
+        const int c = item_at(q, ND, 0, NM);
+        if (c >= 0) {
+          copy(c, nxt);
+          placed = true;
+        }
+        if (placed) __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (MORE) copy_done();
+    nxt = cur;
+    cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+    column_sums(set);
+  };
   using Set0 = std::integral_constant<int, 0>;
   using Set1 = std::integral_constant<int, 1>;
-  read(Set0{});
+  enter();
+#pragma unroll
+  for (int f = 0; f < NFR; ++f) read_one(Set0{}, f);
+  __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int c = 0; c < ND; ++c) copy(c, nxt);
   copy_done();
@@ -1341,12 +1354,17 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   cur += STAGE;
   int left = nk - 1;                                   // stages not read yet
   for (; left >= 2; left -= 2) {
-    read(Set1{});
+    enter();
     multiply(Set0{}, std::true_type{});
-    read(Set0{});
+    enter();
     multiply(Set1{}, std::true_type{});
   }
-  if (left) read(Set1{});
+  if (left) {
+    enter();
+#pragma unroll
+    for (int f = 0; f < NFR; ++f) read_one(Set1{}, f);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   multiply(Set0{}, std::false_type{});
   if (left) multiply(Set1{}, std::false_type{});
   dma_wait_all();                                      // copies of tiles past the end still write (zeros) to LDS
