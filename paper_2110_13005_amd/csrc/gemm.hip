@@ -254,12 +254,16 @@ __device__ __forceinline__ void gemm_epilogue_staged(const floatx4 (&acc)[8][TN]
   const int nl = 4 * (lane & 31);                 // column inside the wave tile
   const int n = n_base + nl;
   const bool col_ok = nl < 16 * TN && n < g.N;
+  const int nl_read = nl < 16 * TN ? nl : 0;
   float bv[4];
   if (col_ok) load_bias4<EPI>(bv, g, n);
-  // What the epilogue reads at its output positions (residual, stored derivative, accumulating C) is
-  // loaded in batches whose loads are all in flight together: the whole wave tile at once (64 row pairs,
-  // 2 registers each) for bf16 operands, 16 row pairs at a time for an fp32 C.
-  constexpr int OB = (EPI == EPI_ACC_F32) ? 16 : 64;
+  // What the epilogue reads at its output positions (residual, stored derivative, accumulating C) is requested ahead: the
+  // whole wave tile at once (64 row pairs, 2 registers each) for bf16 operands, 48 of the 64 row pairs for a C to add to (4
+  // registers each in fp32) and each of the others when a position's registers are free.  Sixteen at a time, and a branch in front of
+  // every load, made four trips to memory one behind the other: weight gradient 4096 x 4096 x 672 65.7 -> 49.0 us (47.1 in the
+  // copying kernel; 33 with a 16-bit result), 2560 x 7680 x 672 101.7 -> 64.8.  12B-shape batch, fp32 accumulators, one
+  // microbatch per contraction: 125.3 -> 113.7 ms.
+  constexpr int OB = EPI == EPI_ACC_F32 || EPI == EPI_ACC_BF16 ? 48 : 64;
   EpiOperand opnd[OB];
   const bool reads = epi_reads_operand<EPI>(g);
   // element offsets of this lane's position in row pair 0 and their step from one row pair to the next:
@@ -267,16 +271,21 @@ __device__ __forceinline__ void gemm_epilogue_staged(const floatx4 (&acc)[8][TN]
   const int64_t ld_side = epi_ld_side<EPI>(g);
   const int64_t off_c0 = (int64_t)(m_base + (lane >> 5)) * g.ldc + n, off_s0 = (int64_t)(m_base + (lane >> 5)) * ld_side + n;
   const int64_t step_c = 2 * g.ldc, step_s = 2 * ld_side;
-  if (OB == 64 && reads) {
-    int64_t oc = off_c0, os = off_s0;
+  // Position of the next load; rows and columns that do not exist are loaded from the last that does and not used: a
+  // branch in front of every load would keep them from being in flight together.
+  const int row0 = m_base + (lane >> 5), rows_left = g.M - 1 - row0;
+  const int64_t row_l = rows_left < 0 ? g.M - 1 : row0, n_l = col_ok ? n : 0;
+  int64_t oc_l = row_l * g.ldc + n_l, os_l = row_l * ld_side + n_l;
+  auto request = [&](int t) {
+    opnd[t % OB] = epi_load_operand<EPI>(g, oc_l, os_l);
+    const bool more = 2 * (t + 1) <= rows_left;
+    oc_l += more ? step_c : 0; os_l += more ? step_s : 0;
+  };
+  if (reads) {
 #pragma unroll
-    for (int t = 0; t < 64; ++t) {
-      const int m = m_base + 2 * t + (lane >> 5);
-      if (m < g.M && col_ok) opnd[t] = epi_load_operand<EPI>(g, oc, os);
-      oc += step_c; os += step_s;
-    }
+    for (int t = 0; t < OB; ++t) request(t);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  int64_t oc_l = off_c0, os_l = off_s0;       // positions of the loads of an fp32 C, 16 row pairs at a time
   int64_t oc = off_c0, os = off_s0;
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
@@ -286,26 +295,23 @@ __device__ __forceinline__ void gemm_epilogue_staged(const floatx4 (&acc)[8][TN]
       for (int j = 0; j < TN; ++j)
         *reinterpret_cast<floatx4*>(stage + (16 * ii + (lane & 15)) * LD + 16 * j + 4 * (lane >> 4)) =
             acc[4 * p + ii][j];
+    // A few positions' sums are fetched together, in front of the branches around the stores: 2048 x 51200 x 1024 222 -> 218 us.
+    constexpr int BATCH = 8;
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      if (OB == 16 && reads) {
+    for (int t0 = 0; t0 < 32; t0 += BATCH) {
+      floatx4 x[BATCH];
 #pragma unroll
-        for (int tt = 0; tt < 16; ++tt) {
-          const int m = m_base + 64 * p + 2 * (16 * hh + tt) + (lane >> 5);
-          if (m < g.M && col_ok) opnd[tt] = epi_load_operand<EPI>(g, oc_l, os_l);
-          oc_l += step_c; os_l += step_s;
-        }
-      }
+      for (int u = 0; u < BATCH; ++u) x[u] = *reinterpret_cast<const floatx4*>(stage + (2 * (t0 + u) + (lane >> 5)) * LD + nl_read);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int tt = 0; tt < 16; ++tt) {
-        const int r = 2 * (16 * hh + tt) + (lane >> 5);
-        const int m = m_base + 64 * p + r;
-        if (m < g.M && col_ok) {
-          const floatx4 x = *reinterpret_cast<const floatx4*>(stage + r * LD + nl);
-          float v[4] = {x[0], x[1], x[2], x[3]};
-          epi_finish<EPI>(v, bv, opnd[OB == 64 ? 32 * p + 16 * hh + tt : tt], g, oc, os);
+      for (int u = 0; u < BATCH; ++u) {
+        const int t = 32 * p + t0 + u;
+        if (m_base + 2 * t + (lane >> 5) < g.M && col_ok) {
+          float v[4] = {x[u][0], x[u][1], x[u][2], x[u][3]};
+          epi_finish<EPI>(v, bv, opnd[t % OB], g, oc, os);
         }
         oc += step_c; os += step_s;
+        if (t + OB < 64 && reads) request(t + OB);
       }
     }
   }
@@ -1549,16 +1555,15 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   g.tiles_m = (g.M + 255) / 256;
   g.tiles_n = (g.N + 32 * TN - 1) / (32 * TN);
   const dim3 grid(g.tiles_m * g.tiles_n), block(256);
-  // The kernel with copies by the memory pipeline is the faster one for every layout
-  // with a 16-bit result (single launches of the 12B-shape problems: forward +11 %, input gradients +4 %, weight
-  // gradients +8 % over the register-staged kernel; whole batches of the 12B / 24B / 100B stage shapes 3.4 / 3.3 /
-  // 4.3 % faster than with the previous choice); with an fp32 read-modify-write result the register-staged
-  // kernel stays ahead (110.3 vs 111.0 ms per 12B batch).
+  // The kernel with copies by the memory pipeline is the faster one everywhere: single launches of the 12B-shape problems
+  // forward +11 %, input gradients +4 %, weight gradients +8 % over the register-staged kernel; weight gradients with an fp32
+  // result 2 to 19 %, 9 % on average over 90 shapes of 40 to 420 tiles, and whole batches that accumulate in fp32 between 1 %
+  // slower (12B shape, three microbatches per contraction, beside another stream: 106.8 / 107.8 ms) and 3.3 % faster (h 3072).
   // axonn_tuning(AXONN_TUNE_GEMM_COPY_MASK, m) fixes the choice per class instead (bit 0 (kc,kc), bit 1 (kc,ks),
   // bit 2 (ks,ks) with a 16-bit result, bit 3 (ks,ks) with an fp32 result): the tests run every case through
   // both kernels with it.
   const int64_t mask_set = g_tune_copy_mask.load();
-  const int64_t dma_mask = mask_set >= 0 ? mask_set : 7;
+  const int64_t dma_mask = mask_set >= 0 ? mask_set : 15;
   const int dma_bit = A_KC ? (B_KC ? 0 : 1) : (epi == EPI_ACC_F32 ? 3 : 2);
   const bool use_dma = (dma_mask >> dma_bit) & 1;
 #define AXONN_GEMM_CASE(E)                                                                      \
