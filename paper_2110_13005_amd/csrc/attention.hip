@@ -372,12 +372,13 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
     for (int c = 0; c < 4; ++c) pf[c] = pack8(sacc[c >> 1], 8 * (c & 1));
 #pragma unroll
     for (int i = EARLY; i < NF; ++i) vfr[i] = v_frag(buf, i);
-    // The next tile is in LDS, and everybody has taken this one's fragments: its buffer is filled with the tile after next.
+    // The next tile is in LDS, and everybody has taken this one's fragments: its buffer is filled with the tile after next
+    // (behind the last tile too: the copies write, and other waves may still read its V).
     if (kt + 1 < n_kt) {
       dma_wait_all();
       k_src.template clear_foreign<BKV>(next);
-      __syncthreads();
     }
+    __syncthreads();
     if (!ALIGNED && kt + 2 < n_kt) {
       k_src.template fill<BKV>(buf, k0 + 2 * BKV);
       v_src.template fill<BKV>(buf + Tile<BKV, D>::BYTES, k0 + 2 * BKV);

@@ -504,6 +504,32 @@ def test_attention_head_is_not_reached_by_its_neighbours(s, a, d):
         assert torch.equal(run(q, do)[:, :, head], clean[:, :, head])
 
 
+@pytest.mark.parametrize("b,s,a,d", [(1, 2040, 24, 128), (4, 512, 16, 64), (1, 50, 8, 64), (2, 500, 24, 188)])
+def test_attention_beside_other_work_gives_the_same_bits(b, s, a, d):
+    """Waves of a workgroup fall behind each other when others share their CU: 100 passes on each of two streams at once, every
+    one the same bits."""
+    import torch
+    h, dt, n = a * d, B.torch_elem_dtype(), 100
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+    qkv, dout = (torch.randn(b * s, w, generator=g, device="cuda").to(dt) for w in (3 * h, h))
+    new = lambda: (torch.zeros(b * s, h, dtype=dt, device="cuda"), torch.zeros(b * s, 3 * h, dtype=dt, device="cuda"),
+                   torch.zeros(b * a * s, device="cuda"), torch.zeros(b * a * s, device="cuda"))
+    runs = [(torch.cuda.Stream(), new(), torch.zeros(2, dtype=torch.int64, device="cuda")) for _ in range(2)]
+    first = new()
+    B.axonn_attention_fwd(b, s, a, d, qkv, first[0], first[2])
+    B.axonn_attention_bwd(b, s, a, d, qkv, first[0], first[2], dout, first[1], first[3])
+    torch.cuda.synchronize()
+    for _ in range(n):
+        for stream, (o, dqkv, lse, ws), differ in runs:
+            with torch.cuda.stream(stream):
+                B.axonn_attention_fwd(b, s, a, d, qkv, o, lse, stream)
+                B.axonn_attention_bwd(b, s, a, d, qkv, o, lse, dout, dqkv, ws, stream)
+                differ[0] += (o.view(torch.int16) != first[0].view(torch.int16)).any()
+                differ[1] += (dqkv.view(torch.int16) != first[1].view(torch.int16)).any()
+    torch.cuda.synchronize()
+    assert [differ.tolist() for _, _, differ in runs] == [[0, 0]] * 2
+
+
 @pytest.mark.parametrize("b,s,a,d", [(2, 72, 66, 64), (4, 72, 33, 128)])
 def test_attention_delta_is_the_sum_of_products_in_element_order(b, s, a, d):
     """Where the dQ kernel forms delta = sum_d dO O itself (more than 128 tiles): 8 products per lane one after the other, then
