@@ -286,26 +286,22 @@ int ln_fwd(int64_t T, int64_t h, const void* x, const void* g, const void* b, fl
 }
 // LayerNorm backward of layer `layer` (which: 0 the first, 1 the second) for n microbatches.  The parameter gradients of a batch collect in
 // the LayerNorm's slices of st->ln_part (acc == 0: the batch's first microbatch) and are stored in the gradient
-// accumulators behind the batch's last one (and by store_ln_grads).
+// buffer by store_ln_grads.
 int ln_bwd(axonn_stage* st, int layer, int which, int n, const void* dout, const void* x, const float* stats,
            const void* res, void* dx, int acc, hipStream_t s) {
   const int64_t T = (int64_t)n * st->T, h = st->h;
   ProfScope ps(PC_LN_BWD, s);
-  const int which_g = which ? P_LN2G : P_LN1G, which_b = which ? P_LN2B : P_LN1B;
   float* const part = st->ln_part + (uint64_t)(2 * layer + which) * 2 * h * st->ln_slices;
-  AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, dout, x, stats, param_ptr(st, layer, which_g), res, dx, part,
-                                                   st->ln_slices, acc == 0, s), "layernorm_bwd"));
-  if (st->bwd_count + n < st->cfg.n_microbatches) return AXONN_OK;
-  return check_launch(launch_layernorm_param_grads(st->ln_slices, h, part, grad_ptr(st, layer, which_g), grad_ptr(st, layer, which_b),
-                                                   st->cfg.grad_accum_fp32 != 0, s), "layernorm parameter gradients");
+  return check_launch(launch_layernorm_bwd_partial(T, h, dout, x, stats, param_ptr(st, layer, which ? P_LN2G : P_LN1G), res, dx,
+                                                   part, st->ln_slices, acc == 0, s), "layernorm_bwd");
 }
-// Stores what all LayerNorms have collected so far in the 16-bit gradient buffer.
-int store_ln_grads(axonn_stage* st, hipStream_t s) {
+// Stores what the LayerNorms of n layers have collected so far in the 16-bit gradient buffer.
+int store_ln_grads(axonn_stage* st, int first, int n, hipStream_t s) {
   ProfScope ps(PC_LN_BWD, s);
   const uint64_t ln1 = st->tensors[P_LN1G].offset, ln2 = st->tensors[P_LN2G].offset;
   const uint64_t layer = st->cfg.n_layers > 1 ? st->tensors[kTensorsPerLayer + P_LN1G].offset - ln1 : 0;
-  return check_launch(launch_layernorm_param_grads_all(st->ln_slices, st->h, st->cfg.n_layers, st->ln_part, st->grads + ln1,
-                                                       (int64_t)layer, (int64_t)(ln2 - ln1), s),
+  return check_launch(launch_layernorm_param_grads_all(st->ln_slices, st->h, n, st->ln_part + (uint64_t)first * 4 * st->h * st->ln_slices,
+                                                       st->grads + ln1 + first * layer, (int64_t)layer, (int64_t)(ln2 - ln1), s),
                       "layernorm parameter gradients");
 }
 int attn_fwd(int b, int sq, int a, int d, const void* qkv, void* o, float* lse, hipStream_t s) {
@@ -504,8 +500,9 @@ int wgrad_layer(axonn_stage* st, int l, const LayerStash* const* rec, int n, int
   return check_launch(launch_wgrad_group(epi, grp, s), "gemm (weight gradients)");
 }
 
-// Rounds layer l's fp32 gradient accumulators into the bf16 gradient buffer (fp32 accumulation only) and
-// marks the layer's gradients final on `s`.
+// Rounds layer l's fp32 gradient accumulators into the bf16 gradient buffer (fp32 accumulation only), stores its LayerNorms'
+// gradients there and marks the layer's gradients final on `s`.  Both LayerNorms in one launch, behind the weight gradients; a
+// launch for each was in the chain (3 layers of 384 x 400 tokens on one stream: a batch 626 -> 608 us).
 int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
   if (st->cfg.grad_accum_fp32) {
     const uint64_t lo = st->tensors[l * kTensorsPerLayer].offset;
@@ -513,6 +510,7 @@ int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
     ProfScope ps(PC_GRAD_CONVERT, s);
     AX_TRY(check_launch(launch_f32_to_elem(hi - lo, st->grads32 + lo, st->grads + lo, s), "f32_to_bf16"));
   }
+  AX_TRY(store_ln_grads(st, l, 1, s));
   HIP_TRY(hipEventRecord(st->grads_final[l], s));
   return AXONN_OK;
 }
@@ -702,6 +700,8 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   // backward chains share the workspace and the bias / LayerNorm accumulators: keep them in order
   if (st->last_bwd) HIP_TRY(hipStreamWaitEvent(s, st->last_bwd, 0));
   const int acc = st->bwd_count > 0 ? 1 : 0;
+  // a batch's first one starts the LayerNorms' sums anew, which the last batch stored behind its weight gradients
+  if (!acc && st->last_wgrad) HIP_TRY(hipStreamWaitEvent(s, st->last_wgrad, 0));
   const bool ckpt = st->cfg.ckpt_stride > 0;
   const bool last = st->bwd_count + n == st->cfg.n_microbatches;
   // the embedding's pass reads the input gradient behind this chain, when the slots may be in use again: a buffer of its own
@@ -717,7 +717,7 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   for (int i = 0; i < n; ++i) complete = complete || w[i].complete;
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
-  if (!last && !st->cfg.grad_accum_fp32 && complete && pending == 0) AX_TRY(store_ln_grads(st, s));
+  if (!last && !st->cfg.grad_accum_fp32 && complete && pending == 0) AX_TRY(store_ln_grads(st, 0, st->cfg.n_layers, s));
   st->bwd_count += n;
   HIP_TRY(hipEventRecord(slot->own.dgrad_done, s));
   for (int i = 0; i < n; ++i) slot[i].dgrad_done = slot->own.dgrad_done;
