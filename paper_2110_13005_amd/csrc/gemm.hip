@@ -1253,7 +1253,10 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   asm volatile("" : : "s"(g.C), "s"(g.ldc), "s"(g.accumulate));
   if (EPI == EPI_BIAS_GELU) asm volatile("" : : "s"(g.aux));
 
-  // bias and what the epilogue reads at this thread's output positions are fetched beside the k loop
+  // Bias and what the epilogue reads at this thread's output positions are fetched beside the k loop, or behind it at once;
+  // rows and columns that do not exist are loaded from others and not used (a branch around every load keeps them apart).
+  // With the sums fetched in batches below, in tiles of 128 x 256, us: 8192 x 4096 x 1024 times a stored derivative 86.7 -> 81.8,
+  // 8192 x 1024 x 1024 with a residual 24.0 -> 22.7, with GeLU 102.1 -> 100.5.
   constexpr int NP = BM * BN / 4 / NT, CW = BN / 4;    // positions per thread (4 columns each), positions per row
   constexpr int NBV = NT % CW == 0 ? 1 : NP;           // one column for all positions of a thread, or one each
   const bool reads = epi_reads_operand<EPI>(g) && parts == 1;
@@ -1264,13 +1267,13 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
 #pragma unroll
     for (int p = 0; p < NBV; ++p) {
       const int n = n0 + 4 * ((tid + p * NT) % CW);
-      if (n < g.N) load_bias4<EPI>(bv[p], g, n);
+      load_bias4<EPI>(bv[p], g, n < g.N ? n : 0);
     }
     if (!reads) return;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
-      const int m = m0 + (tid + p * NT) / CW, n = n0 + 4 * ((tid + p * NT) % CW);
-      if (n < g.N && m < g.M) opnd[p] = epi_load_operand<EPI>(g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
+      const int m = min(m0 + (tid + p * NT) / CW, g.M - 1), nc = n0 + 4 * ((tid + p * NT) % CW), n = nc < g.N ? nc : 0;
+      opnd[p] = epi_load_operand<EPI>(g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
     }
   };
   constexpr bool EARLY = NP <= 8;                      // registers to hold them through the k loop
@@ -1374,13 +1377,16 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
   multiply(Set0{}, std::false_type{});
   if (left) multiply(Set1{}, std::false_type{});
   dma_wait_all();                                      // copies of tiles past the end still write (zeros) to LDS
+  if (!EARLY) {
+    load_operands();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   lds_barrier();                                       // and every wave is done with the tiles
 
   // The groups' partial results meet in LDS, and the result leaves in whole rows: lane owns 4 columns.
   float* const stage = reinterpret_cast<float*>(smem);
   float* const sums = stage + NPART * BM * LD;
   float* const mine = stage + (APART ? grp * (BM * LD) : 0) + (wm * 16 * TM + (lane & 15)) * LD + wn * 16 * TN + 4 * (lane >> 4);
-  if (!EARLY) load_operands();
   if (!APART) {
     if (grp == 1) {
 #pragma unroll
@@ -1414,19 +1420,32 @@ __device__ __forceinline__ void gemm_ring(const GemmArgs& g, const int tm, const
     }
   }
   lds_barrier();
+  // a few positions' sums are fetched together, in front of the branches around the stores
+  constexpr int BATCH = NP % 8 == 0 ? 8 : NP % 4 == 0 ? 4 : NP;
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    const int r = (tid + p * NT) / CW, ec = 4 * ((tid + p * NT) % CW), m = m0 + r, n = n0 + ec;
-    if (n < g.N && m < g.M) {
-      floatx4 x = *reinterpret_cast<const floatx4*>(stage + r * LD + ec);
+  for (int p0 = 0; p0 < NP; p0 += BATCH) {
+    floatx4 x[BATCH][NPART];
 #pragma unroll
-      for (int q = 1; q < NPART; ++q) x += *reinterpret_cast<const floatx4*>(stage + q * (BM * LD) + r * LD + ec);
-      if (parts > 1) {
-        *reinterpret_cast<floatx4*>(g.split_ws + ((int64_t)part * g.M + m) * g.N + n) = x;
-        continue;
+    for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+      for (int q = 0; q < NPART; ++q) {
+        const int at = tid + (p0 + u) * NT;
+        x[u][q] = *reinterpret_cast<const floatx4*>(stage + q * (BM * LD) + at / CW * LD + 4 * (at % CW));
       }
-      float v[4] = {x[0], x[1], x[2], x[3]};
-      epi_finish<EPI>(v, bv[NBV == 1 ? 0 : p], opnd[p], g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int p = p0 + u, m = m0 + (tid + p * NT) / CW, n = n0 + 4 * ((tid + p * NT) % CW);
+      if (n < g.N && m < g.M) {
+#pragma unroll
+        for (int q = 1; q < NPART; ++q) x[u][0] += x[u][q];
+        if (parts > 1) {
+          *reinterpret_cast<floatx4*>(g.split_ws + ((int64_t)part * g.M + m) * g.N + n) = x[u][0];
+          continue;
+        }
+        float v[4] = {x[u][0][0], x[u][0][1], x[u][0][2], x[u][0][3]};
+        epi_finish<EPI>(v, bv[NBV == 1 ? 0 : p], opnd[p], g, (int64_t)m * g.ldc + n, (int64_t)m * ld_side + n);
+      }
     }
   }
   if (cs_tile && tid < BN && n0 + tid < g.N) {
