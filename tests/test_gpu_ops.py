@@ -269,6 +269,22 @@ def _wide(rows, width, ld, offset=0):
     return vals.astype(np.float64), buf[offset:]
 
 
+@pytest.mark.parametrize("M,N,K", [(4000, 1544, 72), (8000, 1544, 72), (3976, 1800, 136), (1544, 4000, 72), (7944, 2312, 136)])
+def test_gemm_tiles_of_128_x_256_in_narrow_bands(M, N, K):
+    """More rows of these tiles than columns: the walk goes in bands of 4 tile columns, the last of 1 to 3 (and, the fourth,
+    fewer rows than columns)."""
+    import torch
+    rng = np.random.default_rng(M + N)
+    a, w = _rng_bf16(rng, (M, K)), _rng_bf16(rng, (K, N), 0.05)
+    try:
+        B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, 1 << 20)
+        out = torch.zeros(M, N, dtype=B.torch_elem_dtype(), device="cuda")
+        B.axonn_gemm_bf16(1, 0, B.EPI_BIAS, M, N, K, dev_bf16(a), K, dev_bf16(w), N, out, N)
+    finally:
+        B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, -1)
+    parity(host(out), a.astype(np.float64) @ w.astype(np.float64), TOL, C_ONE, label="gemm_tiles_of_128_x_256_in_narrow_bands")
+
+
 @pytest.mark.parametrize("min_tiles", [-1, 1])
 @pytest.mark.parametrize("M,N,K", [(8, 8, 8), (136, 264, 200), (264, 136, 72)])
 @pytest.mark.parametrize("wide", ["A", "B", "misaligned"])
