@@ -297,7 +297,6 @@ int ln_bwd(axonn_stage* st, int layer, int which, int n, const void* dout, const
 }
 // Stores what the LayerNorms of n layers have collected so far in the 16-bit gradient buffer.
 int store_ln_grads(axonn_stage* st, int first, int n, hipStream_t s) {
-  ProfScope ps(PC_LN_BWD, s);
   const uint64_t ln1 = st->tensors[P_LN1G].offset, ln2 = st->tensors[P_LN2G].offset;
   const uint64_t layer = st->cfg.n_layers > 1 ? st->tensors[kTensorsPerLayer + P_LN1G].offset - ln1 : 0;
   return check_launch(launch_layernorm_param_grads_all(st->ln_slices, st->h, n, st->ln_part + (uint64_t)first * 4 * st->h * st->ln_slices,
@@ -504,13 +503,15 @@ int wgrad_layer(axonn_stage* st, int l, const LayerStash* const* rec, int n, int
 // gradients there and marks the layer's gradients final on `s`.  Both LayerNorms in one launch, behind the weight gradients; a
 // launch for each was in the chain (3 layers of 384 x 400 tokens on one stream: a batch 626 -> 608 us).
 int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
-  if (st->cfg.grad_accum_fp32) {
-    const uint64_t lo = st->tensors[l * kTensorsPerLayer].offset;
-    const uint64_t hi = (l + 1 < st->cfg.n_layers) ? st->tensors[(l + 1) * kTensorsPerLayer].offset : st->n_params;
+  {
     ProfScope ps(PC_GRAD_CONVERT, s);
-    AX_TRY(check_launch(launch_f32_to_elem(hi - lo, st->grads32 + lo, st->grads + lo, s), "f32_to_bf16"));
+    if (st->cfg.grad_accum_fp32) {
+      const uint64_t lo = st->tensors[l * kTensorsPerLayer].offset;
+      const uint64_t hi = (l + 1 < st->cfg.n_layers) ? st->tensors[(l + 1) * kTensorsPerLayer].offset : st->n_params;
+      AX_TRY(check_launch(launch_f32_to_elem(hi - lo, st->grads32 + lo, st->grads + lo, s), "f32_to_bf16"));
+    }
+    AX_TRY(store_ln_grads(st, l, 1, s));
   }
-  AX_TRY(store_ln_grads(st, l, 1, s));
   HIP_TRY(hipEventRecord(st->grads_final[l], s));
   return AXONN_OK;
 }
@@ -717,7 +718,10 @@ int do_backward(axonn_stage* st, const Work* w, int n, hipStream_t s, hipStream_
   for (int i = 0; i < n; ++i) complete = complete || w[i].complete;
   // A batch may be cut short wherever no weight gradients are pending: the 16-bit buffer then holds every gradient of
   // the microbatches so far, the LayerNorms' too.
-  if (!last && !st->cfg.grad_accum_fp32 && complete && pending == 0) AX_TRY(store_ln_grads(st, 0, st->cfg.n_layers, s));
+  if (!last && !st->cfg.grad_accum_fp32 && complete && pending == 0) {
+    ProfScope ps(PC_LN_BWD, s);
+    AX_TRY(store_ln_grads(st, 0, st->cfg.n_layers, s));
+  }
   st->bwd_count += n;
   HIP_TRY(hipEventRecord(slot->own.dgrad_done, s));
   for (int i = 0; i < n; ++i) slot[i].dgrad_done = slot->own.dgrad_done;
