@@ -1575,6 +1575,12 @@ bool set_gemm_tuning(int knob, int64_t value) {
   }
 }
 
+static bool aligned16(const GemmArgs& g) {
+  uintptr_t bits = 0;
+  for (int i = 0; i < g.n_seg; ++i) bits |= (uintptr_t)g.A_seg[i] | (uintptr_t)g.B_seg[i];
+  return bits % 16 == 0;
+}
+
 template <bool A_KC, bool B_KC, int TN>
 static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   g.tiles_m = (g.M + 255) / 256;
@@ -1584,11 +1590,12 @@ static hipError_t launch_big(int epi, GemmArgs g, hipStream_t s) {
   // forward +11 %, input gradients +4 %, weight gradients +8 % over the register-staged kernel; weight gradients with an fp32
   // result 2 to 19 %, 9 % on average over 90 shapes of 40 to 420 tiles, and whole batches that accumulate in fp32 between 1 %
   // slower (12B shape, three microbatches per contraction, beside another stream: 106.8 / 107.8 ms) and 3.3 % faster (h 3072).
+  // Weight gradients with an fp32 result of operands that do not start at a multiple of 16 bytes stay on the register-staged one.
   // axonn_tuning(AXONN_TUNE_GEMM_COPY_MASK, m) fixes the choice per class instead (bit 0 (kc,kc), bit 1 (kc,ks),
   // bit 2 (ks,ks) with a 16-bit result, bit 3 (ks,ks) with an fp32 result): the tests run every case through
   // both kernels with it.
   const int64_t mask_set = g_tune_copy_mask.load();
-  const int64_t dma_mask = mask_set >= 0 ? mask_set : 15;
+  const int64_t dma_mask = mask_set >= 0 ? mask_set : aligned16(g) ? 15 : 7;
   const int dma_bit = A_KC ? (B_KC ? 0 : 1) : (epi == EPI_ACC_F32 ? 3 : 2);
   const bool use_dma = (dma_mask >> dma_bit) & 1;
 #define AXONN_GEMM_CASE(E)                                                                      \
@@ -1726,12 +1733,6 @@ static hipError_t launch_ring_group_tile(int tile, int epi, GemmGroup& grp, hipS
     case host::RING_128x192: return launch_ring_group<4, 6, 2, 1, 3>(epi, grp, s);
     default: return launch_ring_group<4, 8, 2, 1, 3>(epi, grp, s);
   }
-}
-
-static bool aligned16(const GemmArgs& g) {
-  uintptr_t bits = 0;
-  for (int i = 0; i < g.n_seg; ++i) bits |= (uintptr_t)g.A_seg[i] | (uintptr_t)g.B_seg[i];
-  return bits % 16 == 0;
 }
 
 template <bool A_KC, bool B_KC>

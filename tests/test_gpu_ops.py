@@ -195,8 +195,8 @@ def test_gemm_big_tile_strided_operands():
 
 @pytest.mark.parametrize("mask,min_tiles", [(15, 1), (0, 1), (15, -1)])
 def test_gemm_both_large_kernels_all_layouts_and_results(mask, min_tiles):
-    """The large-problem kernel whose tiles are copied by the memory pipeline serves three of the four (layout, result
-    type) classes by default and the register-staged one the fourth; axonn_tuning fixes the choice, so every GEMM
+    """The large-problem kernel whose tiles are copied by the memory pipeline serves all four (layout, result type) classes
+    by default, the register-staged one the fourth where operands are not aligned; axonn_tuning fixes the choice, so every GEMM
     case of this file runs again through the copying kernel (mask 15; its variant with a short last k-tile where K
     is no multiple of 64) and through the register-staged kernel everywhere (mask 0), with the threshold lowered so that the small ragged
     shapes reach the large-problem kernels too (all three block widths)."""
@@ -283,6 +283,21 @@ def test_gemm_tiles_of_128_x_256_in_narrow_bands(M, N, K):
     finally:
         B.axonn_tuning(B.TUNE_GEMM_BIG_MIN_TILES, -1)
     parity(host(out), a.astype(np.float64) @ w.astype(np.float64), TOL, C_ONE, label="gemm_tiles_of_128_x_256_in_narrow_bands")
+
+
+@pytest.mark.parametrize("off", [0, 4])
+def test_gemm_large_fp32_weight_gradient_by_alignment(off):
+    """Large weight gradients with an fp32 result: operands at a multiple of 16 bytes take the copying kernel, others the
+    register-staged one; stored and added."""
+    import torch
+    M, N, K = 4096, 4104, 72
+    am, a = _wide(K, M, M + 8, off)
+    bm, b = _wide(K, N, N + 8, off)
+    ref = am.T @ bm
+    out = torch.full((M, N), 7.0, device="cuda")
+    for acc in (0, 1):
+        B.axonn_gemm_bf16(0, 0, B.EPI_ACC_F32, M, N, K, a, M + 8, b, N + 8, out, N, accumulate=acc)
+        assert rel_fro(host(out), (1 + acc) * ref) <= 1e-5        # products are exact, 72 fp32 additions
 
 
 @pytest.mark.parametrize("min_tiles", [-1, 1])
