@@ -490,7 +490,8 @@ int axonn_profile_collect(double* total_ms, int64_t* launches, int32_t n_categor
  *   AXONN_TUNE_GEMM_COPY_MASK      which problem classes take the large-problem kernel whose tiles are copied
  *                                  into LDS by the memory pipeline (instead of the register-staged one), as a bit
  *                                  mask: 1 input gradients, 2 forward, 4 weight gradients with a 16-bit result,
- *                                  8 weight gradients with an fp32 result (built-in: 15)
+ *                                  8 weight gradients with an fp32 result (built-in: 15; 7 for
+ *                                  operands that do not start at a multiple of 16 bytes)
  *   AXONN_TUNE_GEMM_BIG_MIN_TILES  number of 256 x 256 tiles from which the large-problem kernels are used
  *                                  (built-in: 256, below that where they are modelled to be faster)
  *   AXONN_TUNE_GEMM_TILE_N         block width of the large-problem kernels: 160, 192 or 256 (0 or -1: chosen per
