@@ -535,6 +535,31 @@ def test_attention_head_is_not_reached_by_its_neighbours(s, a, d):
         assert torch.equal(run(q, do)[:, :, head], clean[:, :, head])
 
 
+@pytest.mark.parametrize("off", [0, 4])
+@pytest.mark.parametrize("s,a,d", [(200, 4, 44), (130, 2, 188), (72, 4, 124), (264, 2, 60)])
+def test_attention_head_does_not_depend_on_its_place(s, a, d, off):
+    """Heads of an odd multiple of 4 columns, the same numbers in each: a head that starts between two 16-byte boundaries gives the
+    bits of one that starts at one.  The matrices end with the last head's last column: nothing is read behind it."""
+    import torch
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+
+    def same(n):
+        buf = torch.full((off + s * n * h,), float("nan"), dtype=dt, device="cuda")
+        buf[off:] = torch.randn(s, n, 1, d, generator=g, device="cuda").to(dt).expand(s, n, a, d).reshape(-1)
+        return buf[off:].view(s, n * h)
+
+    qkv, dout = same(3), same(1)
+    o, dq = torch.zeros(s, h, dtype=dt, device="cuda"), torch.zeros(s, 3 * h, dtype=dt, device="cuda")
+    lse, ws = (torch.zeros(1, a, s, device="cuda") for _ in range(2))
+    B.axonn_attention_fwd(1, s, a, d, qkv, o, lse)
+    B.axonn_attention_bwd(1, s, a, d, qkv, o, lse, dout, dq, ws)
+    assert torch.isfinite(dq.float()).all() and o.any() and dq.any()
+    for x in (o.view(s, 1, a, d), dq.view(s, 3, a, d)):
+        assert torch.equal(x, x[:, :, :1].expand_as(x))
+    assert torch.equal(lse, lse[:, :1].expand_as(lse))
+
+
 @pytest.mark.parametrize("b,s,a,d", [(1, 2040, 24, 128), (4, 512, 16, 64), (1, 50, 8, 64), (2, 500, 24, 188)])
 def test_attention_beside_other_work_gives_the_same_bits(b, s, a, d):
     """Waves of a workgroup fall behind each other when others share their CU: 100 passes on each of two streams at once, every
