@@ -294,6 +294,8 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
 
   const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
+  // the wave's own: a last tile with every key in its future is left out (0 x Inf and 0 x NaN are not 0)
+  const int n_own = min(n_kt, (qw0 + 31) / BKV + 1);
   // Fragments of a tile in the order of the MFMAs that take them: K's alternate between the tile's two 32-key halves.
   auto k_frag = [&](LdsBytes buf, int i) { return frag_rows<BKV, D>(buf, fl, i & 1, i >> 1); };
   auto v_frag = [&](LdsBytes buf, int i) { return frag_cols<BKV, D>(buf + Tile<BKV, D>::BYTES, fl, i / DT, i % DT); };
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
     __syncthreads();                             // the Q rows have been read
     fill_second();
   }
-  for (int kt = 0; kt < n_kt; ++kt) {
+  for (int kt = 0; kt < n_own; ++kt) {
     const int k0 = kt * BKV;
     const LdsBytes buf = buf0 + (kt & 1) * BUF, next = buf0 + (~kt & 1) * BUF;
     floatx16 sacc[2];
@@ -394,6 +396,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
       __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if (n_own < n_kt) __syncthreads();
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   dma_wait_all();                 // copies of tiles beyond the last still write (zeros) to LDS
   __syncthreads();                // the tiles in LDS are done with
@@ -461,7 +464,8 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
 // W - 1 slots later needs (a ring of W fragments, also across tiles), and a share of the exponentials.  The MFMAs are
 // volatile assembly: they keep this order, and the reads stay between them where they are written.  The tile on the diagonal
 // takes the same path with the mask applied to every element (a block above the diagonal comes out as zeros; the wave with
-// the lowest keys needs all blocks anyway).
+// the lowest keys needs all blocks anyway).  Zeros times infinities are not zeros: above 128 columns the gradient MFMAs of a
+// block in front of the wave's keys are jumped over, so that what it holds does not reach their gradients.
 // What bounds a slot is what one wave issues: a vector instruction takes 5 clocks of its 32, an exponential 9, a conversion of
 // two elements 8; and the LDS, which gives a transposed fragment in 4.6 clocks without bank conflicts and in 8 with the two-way
 // ones of padded rows.  40 heads of 128 x 2048 117 -> 97 us, 16 of 128 x 8192 570 -> 472, 8 x 16 of 64 x 1024 64 -> 44 (two waves
@@ -611,6 +615,9 @@ __device__ __forceinline__ void attn_bwd_dkdv(
   // masked: 0 no, 1 this tile, 2 the next one too
   auto tile_stream = [&](int qt, auto masked) {
     constexpr bool MASKED = decltype(masked)::value > 0, NEXT_MASKED = decltype(masked)::value > 1;
+    // the gradients of block k are formed if its last query, 32 k + 31 in this tile, is not in front of the wave's keys
+    constexpr bool SKIPS = MASKED && D > 128;
+    const int past = SKIPS ? __builtin_amdgcn_readfirstlane(kw0 - qt * BQ - 31) : 0;
     const int buf = (qt - qt_begin) & 1, first = kj - qt * BQ - 4 * g;
     const LdsBytes next = tile0 + (buf ^ 1) * L::BUF;
     // every wave has left the tile before, whose buffer is filled again (what a wave has read of it it has used)
@@ -628,12 +635,17 @@ __device__ __forceinline__ void attn_bwd_dkdv(
         score_mfma(k + 1, i, ring[j % W]);
       } else {
         const int c = gi / (2 * DT), dt = (gi % (2 * DT)) >> 1;
-        if (gi & 1) mfma32_agpr(dkacc[dt], ring[j % W], operand(dsw[k & 1], c));
-        else mfma32_agpr(dvacc[dt], ring[j % W], operand(pfw[k & 1], c));
+        floatx16& acc = gi & 1 ? dkacc[dt] : dvacc[dt];
+        const elemx8 w = operand(gi & 1 ? dsw[k & 1] : pfw[k & 1], c);
+        if (SKIPS) mfma32_agpr_from(past - 32 * k, acc, ring[j % W], w);
+        else mfma32_agpr(acc, ring[j % W], w);
       }
       // The scores of block k + 1 have settled when the third MFMA behind their last one has been issued (one occupies the
       // pipe for nearly the distance asked for); nothing takes them from their registers before this statement.
-      if (gi == 2) asm volatile("" : "+v"(sacc[(k + 1) & 1]), "+v"(pacc[(k + 1) & 1]));
+      if (gi == 2) {
+        if (SKIPS) mfma32_settle_vgpr(sacc[(k + 1) & 1], pacc[(k + 1) & 1]);
+        else asm volatile("" : "+v"(sacc[(k + 1) & 1]), "+v"(pacc[(k + 1) & 1]));
+      }
       if (j == READY) {
         store_stats(buf ^ 1, qt + 1);
         dma_wait_all();
@@ -795,6 +807,8 @@ __device__ __forceinline__ void attn_bwd_dq(
 
   const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
+  // the wave's own: a last tile with every key in its future is left out (0 x Inf and 0 x NaN are not 0)
+  const int n_own = min(n_kt, (qw0 + 31) / BKV + 1);
   // Slots of a tile: per half of 32 keys NS score MFMAs (S and dP in turn), then NG for dQ; those beyond the last are the
   // next tile's.
   constexpr int NS = 2 * KK, NG = 2 * DT, HALF = NS + NG, NSLOT = 2 * HALF, W = D == 64 ? 4 : 8;
@@ -812,7 +826,7 @@ __device__ __forceinline__ void attn_bwd_dq(
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < W - 1; ++j) ring[j] = load_frag(buf0, buf0, j);
-  for (int kt = 0; kt < n_kt; ++kt) {
+  for (int kt = 0; kt < n_own; ++kt) {
     const int k0 = kt * BKV;
     const LdsBytes tile = buf0 + (kt & 1) * L::BUF, next = buf0 + (~kt & 1) * L::BUF;
     // every wave has left the tile before
@@ -866,6 +880,10 @@ __device__ __forceinline__ void attn_bwd_dq(
         __builtin_amdgcn_sched_barrier(0);
       }
     }
+  }
+  if (n_own < n_kt) {
+    asm volatile("s_barrier" : : : "memory");
+    __syncthreads();
   }
   dma_wait_all();
   __syncthreads();                // the tiles in LDS are done with

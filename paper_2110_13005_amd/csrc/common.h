@@ -72,7 +72,7 @@ __device__ __forceinline__ void mfma16_acc(floatx4& c, elemx8 a, elemx8 b) {
 // accumulator themselves (volatile statements keep their order, and memory operations do not move across them): a
 // kernel with more than 256 registers per lane gets the accumulation-register form of the builtin for every MFMA, and
 // results that vector instructions consume next would be copied out one register at a time.
-//   mfma32_agpr:  c += a x b, c in the accumulation registers (long-lived accumulators)
+//   mfma32_agpr:  c += a x b, c in the accumulation registers (long-lived accumulators); _from: from n <= 0 on
 //   mfma32_vgpr:  c += a x b, c in ordinary registers; b in the accumulation registers (BA) or ordinary ones
 //   mfma32_vgpr_zero: c = a x b
 // The compiler does not know these are MFMAs and keeps none of their hazards.  Wait states in front of every statement would
@@ -83,6 +83,13 @@ __device__ __forceinline__ void mfma16_acc(floatx4& c, elemx8 a, elemx8 b) {
 // tests/test_library_abi.py checks both distances in the built libraries.
 __device__ __forceinline__ void mfma32_agpr(floatx16& c, elemx8 a, elemx8 b) {
   asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// only if n <= 0 (the same in all lanes); the jump is part of the statement, so that nothing changes around it
+__device__ __forceinline__ void mfma32_agpr_from(int n, floatx16& c, elemx8 a, elemx8 b) {
+  asm volatile("s_cmp_gt_i32 %3, 0\n\ts_cbranch_scc1 .Lmfma_off%=\n\t" AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0\n.Lmfma_off%=:"
+               : "+a"(c)
+               : "v"(a), "v"(b), "s"(n)
+               : "scc");
 }
 template <bool BA>
 __device__ __forceinline__ void mfma32_vgpr(floatx16& c, elemx8 a, elemx8 b) {

@@ -560,6 +560,40 @@ def test_attention_head_does_not_depend_on_its_place(s, a, d, off):
     assert torch.equal(lse, lse[:, :1].expand_as(lse))
 
 
+@pytest.mark.parametrize("b,a", [(1, 2), (2, 24)])
+@pytest.mark.parametrize("d", [44, 64, 128, 188])
+def test_attention_is_not_reached_by_tiles_that_causality_leaves_out(d, b, a):
+    """A probability of zero times an infinity is no zero: a wave leaves out the tiles of 64 keys that lie in its queries' future
+    (forward, dQ) and, where heads have more than 128 columns, the blocks of 32 queries in front of its keys (dK / dV; tiles of 128
+    at fewer columns).  Infinities and NaN there do not reach its results; in one launch and in several."""
+    import torch
+    s, h, dt = 300, a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(d + a)
+    qkv, dout = (torch.randn(b * s, n, generator=g, device="cuda").to(dt) for n in (3 * h, h))
+
+    def run(q, do):
+        o, dq = torch.zeros(b * s, h, dtype=dt, device="cuda"), torch.zeros(b * s, 3 * h, dtype=dt, device="cuda")
+        lse, ws = (torch.zeros(b, a, s, device="cuda") for _ in range(2))
+        B.axonn_attention_fwd(b, s, a, d, q, o, lse)
+        B.axonn_attention_bwd(b, s, a, d, q, o, lse, do, dq, ws)
+        return o.view(b, s, h), lse, dq.view(b, s, 3, h)
+
+    o, lse, dq = run(qkv, dout)
+    assert all(torch.isfinite(x.float()).all() for x in (o, lse, dq))
+    for value in (float("inf"), float("nan")):
+        for p in range(64, s, 64):                      # keys and values from p on
+            q = qkv.clone(); q.view(b, s, 3, h)[:, p:, 1:] = value
+            po, plse, pdq = run(q, dout)
+            assert torch.equal(po[:, :p], o[:, :p]) and torch.equal(plse[..., :p], lse[..., :p])
+            assert torch.equal(pdq[:, :p, 0], dq[:, :p, 0])
+        step = 32 if d > 128 else 128
+        for p in range(step, s, step):                  # queries and their gradients up to p
+            q, do = qkv.clone(), dout.clone()
+            q.view(b, s, 3, h)[:, :p, 0] = value
+            do.view(b, s, h)[:, :p] = value
+            assert torch.equal(run(q, do)[2][:, p:, 1:], dq[:, p:, 1:])
+
+
 @pytest.mark.parametrize("b,s,a,d", [(1, 2040, 24, 128), (4, 512, 16, 64), (1, 50, 8, 64), (2, 500, 24, 188)])
 def test_attention_beside_other_work_gives_the_same_bits(b, s, a, d):
     """Waves of a workgroup fall behind each other when others share their CU: 100 passes on each of two streams at once, every
