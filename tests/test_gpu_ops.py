@@ -535,6 +535,59 @@ def test_attention_head_is_not_reached_by_its_neighbours(s, a, d):
         assert torch.equal(run(q, do)[:, :, head], clean[:, :, head])
 
 
+@pytest.mark.parametrize("by", [1, 2, 6])
+@pytest.mark.parametrize("b,s,a,d", [(1, 200, 2, 64), (2, 136, 33, 128), (1, 72, 4, 44), (1, 264, 2, 188), (1, 130, 66, 124)])
+def test_attention_of_matrices_at_any_element(b, s, a, d, by):
+    """Matrices that start at a multiple of 4 bytes are copied into LDS like others, those at an odd element go through registers;
+    the bits are the same."""
+    import torch
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+    data = [torch.randn(b * s * n, generator=g, device="cuda").to(dt) for n in (3 * h, h)]
+
+    def run(by):
+        q, do = (torch.full((x.numel() + by,), float("nan"), dtype=dt, device="cuda")[by:].copy_(x) for x in data)
+        o, dq = torch.zeros(b * s, h, dtype=dt, device="cuda"), torch.zeros(b * s, 3 * h, dtype=dt, device="cuda")
+        lse, ws = (torch.zeros(b, a, s, device="cuda") for _ in range(2))
+        B.axonn_attention_fwd(b, s, a, d, q, o, lse)
+        B.axonn_attention_bwd(b, s, a, d, q, o, lse, do, dq, ws)
+        return o, lse, dq
+
+    for x, y in zip(run(0), run(by)):
+        assert torch.equal(x, y)
+
+
+def test_attention_of_unaligned_matrices_takes_no_longer():
+    """16 heads of 128 x 2048 at a multiple of 8 bytes and at one of 16: the same time but for a half (through registers two to
+    three times as long)."""
+    import torch
+    s, a, d = 2048, 16, 128
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(1)
+    data = [torch.randn(s * n, generator=g, device="cuda").to(dt) for n in (3 * h, h)]
+    o, dq = torch.zeros(s, h, dtype=dt, device="cuda"), torch.zeros(s, 3 * h, dtype=dt, device="cuda")
+    lse, ws = (torch.zeros(1, a, s, device="cuda") for _ in range(2))
+
+    def times(by):
+        q, do = (torch.zeros(x.numel() + by, dtype=dt, device="cuda")[by:].copy_(x) for x in data)
+        calls = (lambda: B.axonn_attention_fwd(1, s, a, d, q, o, lse), lambda: B.axonn_attention_bwd(1, s, a, d, q, o, lse, do, dq, ws))
+        best = [float("inf")] * 2
+        for _ in range(5):
+            for i, call in enumerate(calls):
+                ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+                call()
+                ev[0].record()
+                for _ in range(20):
+                    call()
+                ev[1].record()
+                torch.cuda.synchronize()
+                best[i] = min(best[i], ev[0].elapsed_time(ev[1]))
+        return best
+
+    aligned, shifted = times(0), times(4)
+    assert shifted[0] < 1.5 * aligned[0] and shifted[1] < 1.5 * aligned[1], (aligned, shifted)
+
+
 @pytest.mark.parametrize("off", [0, 4])
 @pytest.mark.parametrize("s,a,d", [(200, 4, 44), (130, 2, 188), (72, 4, 124), (264, 2, 60)])
 def test_attention_head_does_not_depend_on_its_place(s, a, d, off):
