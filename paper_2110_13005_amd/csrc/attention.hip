@@ -262,7 +262,8 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   const float scale_log2 = kLog2e * rsqrtf((float)d);
   const HeadColumns cols{d};
   const FragLanes fl(lane);
-  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid);
+  const int kv_end = min(s, q0 + 128);         // keys behind the workgroup's last query are not fetched
+  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid);
 
   const LdsBytes buf0(smem);
   q_src.template fill<128>(buf0 + Q_AT, q0);
@@ -292,7 +293,6 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
     for (int r = 0; r < 16; ++r) oacc[dt][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
   // the wave's own: a last tile with every key in its future is left out (0 x Inf and 0 x NaN are not 0)
   const int n_own = min(n_kt, (qw0 + 31) / BKV + 1);
@@ -739,7 +739,8 @@ __device__ __forceinline__ void attn_bwd_dq(
   float delta_q = 0.f;
   const HeadColumns cols{d};
   const FragLanes fl(lane);
-  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid),
+  const int kv_end = min(s, q0 + 128);         // keys behind the workgroup's last query are not fetched
+  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid),
       do_src(dob, h, s, cols, tid);
   const LdsBytes buf0(lds.tiles), buf1(lds.tiles + L::BUF);
 
@@ -805,7 +806,6 @@ __device__ __forceinline__ void attn_bwd_dq(
 #pragma unroll
     for (int r = 0; r < 16; ++r) dqacc[dt][r] = 0.f;
 
-  const int kv_end = min(s, q0 + 128);
   const int n_kt = (kv_end + BKV - 1) / BKV;
   // the wave's own: a last tile with every key in its future is left out (0 x Inf and 0 x NaN are not 0)
   const int n_own = min(n_kt, (qw0 + 31) / BKV + 1);
