@@ -891,6 +891,9 @@ __device__ __forceinline__ void attn_bwd_dq(
 }
 
 // ------------------------------------------------------------------- backward kernels
+// At D = 64 two workgroups share a CU, with 160 ordinary and 96 accumulation registers per lane: at four more 8 x 16 heads of
+// 64 x 1024 take 55 us for dK / dV instead of 44.  (A second argument to __launch_bounds__ does not keep it so: it makes the compiler
+// halve the 256 between the two kinds and move accumulators about between the MFMAs, at distances that it does not know.)
 template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
     int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,

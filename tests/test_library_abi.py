@@ -154,6 +154,23 @@ def test_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
     assert not {k: v for k, v in scratch.items() if v}
 
 
+@pytest.mark.parametrize("elem", ["bf16", "fp16"])
+def test_attention_kernels_leave_room_for_their_second_workgroup(elem, tmp_path):
+    """Where two workgroups of four waves share a CU (the forward and dQ kernels up to 128 columns, the dK / dV ones up to 64),
+    each takes half of a SIMD's 512 registers per lane and of 160 KB of LDS at most."""
+    from paper_2110_13005_amd import build as BLD
+    readelf, seen = _llvm_tool("llvm-readelf"), 0
+    for obj in _code_objects(BLD.VARIANTS[elem][0], tmp_path):
+        notes = subprocess.run([readelf, "--notes", str(obj)], capture_output=True, text=True, check=True).stdout
+        for kernel in re.split(r"^ +- \.agpr_count:", notes, flags=re.M)[1:]:
+            name = re.search(r"\.name: +\S*?attn_(fwd|bwd_dq|bwd_dkdv|bwd_both)_kernelILi(\d+)E", kernel)
+            if name and int(name.group(2)) <= (128 if name.group(1) in ("fwd", "bwd_dq") else 64):
+                seen += 1
+                assert int(re.search(r"\.vgpr_count: +(\d+)", kernel).group(1)) <= 256, name.group(0)
+                assert int(re.search(r"\.group_segment_fixed_size: +(\d+)", kernel).group(1)) <= 80 * 1024, name.group(0)
+    assert seen >= 12
+
+
 def _registers(operand):
     m = re.match(r"^[-|]*([va])(?:(\d+)|\[(\d+):(\d+)\])", operand)
     if not m:
