@@ -200,11 +200,13 @@ __device__ __forceinline__ void attn_block(int id, int n_blocks, int n_bh, int& 
 // 32 dt + 8 q + 4 (lane / 32) ..) times `mul`, rounded, to rows of `ld` elements at `head`, through LDS: stored straight from
 // the MFMA layout every lane touches a row of its own, 8 bytes at a time, a memory instruction then covers 32 different
 // lines, and the last stores alone took a tenth of the dK / dV kernel's time.  `stage` is 32 x (D + 8) elements of LDS that
-// only this wave touches (no barrier: a wave's LDS operations keep their order).
-template <int D>
+// only this wave touches (no barrier: a wave's LDS operations keep their order).  Rows and columns that do not exist are stored out of
+// a descriptor's range instead of behind branches (ALIGNED; the same condition as for the copies).
+template <int D, bool ALIGNED>
 __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, float mul, elem_t* head, int64_t ld,
                                                int n_rows, HeadColumns cols, int lane) {
   constexpr int LDO = D + 8, DT = D / 32, CPR = D / 8;      // 16-byte chunks per row
+  asm volatile("" : "+v"(lane));      // places and offsets are computed here, not in front of the loop and kept through it
   elem_t* const stage = reinterpret_cast<elem_t*>(lds);
   const int g = lane >> 5;
 #pragma unroll
@@ -216,6 +218,22 @@ __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, f
       for (int e = 0; e < 4; ++e) v[e] = (elem_t)(acc[dt][4 * q + e] * mul);
       *reinterpret_cast<elemx4*>(stage + (lane & 31) * LDO + dt * 32 + 8 * q + 4 * g) = v;
     }
+  if (ALIGNED) {
+    const uint32_t row_bytes = (uint32_t)ld * 2u;
+    const int rows = min(n_rows, 32);
+    const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(head, rows > 0 ? (uint32_t)(rows - 1) * row_bytes + (uint32_t)cols.d * 2u : 0u);
+#pragma unroll
+    for (int j = 0; j < 32 * CPR / 64; ++j) {
+      const int idx = lane + 64 * j, row = idx / CPR, ch = idx % CPR;
+      const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * LDO + ch * 8);
+      __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, cols.has4(8 * ch + 4) ? row * row_bytes + ch * 16 : kOutOfRange, 0, 0);
+    }
+    if (cols.split()) {             // the half chunk in front of another head's
+      const u32x2 v = *reinterpret_cast<const u32x2*>(stage + (lane & 31) * LDO + cols.d - 4);
+      __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, g == 0 ? lane * row_bytes + (uint32_t)(cols.d - 4) * 2u : kOutOfRange, 0, 0);
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 32 * CPR / 64; ++j) {
     const int idx = lane + 64 * j, row = idx / CPR, ch = idx % CPR;
@@ -400,7 +418,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   dma_wait_all();                 // copies of tiles beyond the last still write (zeros) to LDS
   __syncthreads();                // the tiles in LDS are done with
-  store_rows_out<D>(smem + wave * (STAGED / 4), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, cols, lane);
+  store_rows_out<D, ALIGNED>(smem + wave * (STAGED / 4), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, cols, lane);
   if (g == 0 && qi < s) lse[((int64_t)bi * a + hd) * s + qi] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
@@ -696,8 +714,8 @@ __device__ __forceinline__ void attn_bwd_dkdv(
   constexpr int STAGED = 32 * (D + 8) * 2;
   static_assert(8 * STAGED <= sizeof(lds.tiles), "the result rows fit the tile buffers");
   elem_t* dk_rows = dqkv + ((int64_t)bi * s + kw0) * ld + h + hd * d;
-  store_rows_out<D>(lds.tiles + wave * STAGED, dkacc, scale, dk_rows, ld, s - kw0, cols, lane);
-  store_rows_out<D>(lds.tiles + (4 + wave) * STAGED, dvacc, 1.f, dk_rows + h, ld, s - kw0, cols, lane);
+  store_rows_out<D, ALIGNED>(lds.tiles + wave * STAGED, dkacc, scale, dk_rows, ld, s - kw0, cols, lane);
+  store_rows_out<D, ALIGNED>(lds.tiles + (4 + wave) * STAGED, dvacc, 1.f, dk_rows + h, ld, s - kw0, cols, lane);
 }
 
 // dQ: wave w owns queries q0 + 32w .. +31 and walks the key tiles up to the diagonal (same traversal as the forward kernel).
@@ -887,7 +905,7 @@ __device__ __forceinline__ void attn_bwd_dq(
   }
   dma_wait_all();
   __syncthreads();                // the tiles in LDS are done with
-  store_rows_out<D>(lds.tiles + wave * (32 * (D + 8) * 2), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, cols, lane);
+  store_rows_out<D, ALIGNED>(lds.tiles + wave * (32 * (D + 8) * 2), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, cols, lane);
 }
 
 // ------------------------------------------------------------------- backward kernels
@@ -936,8 +954,8 @@ __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
     else { if (copies) hipLaunchKernelGGL((KERNEL<192, true>), grid, dim3(256), 0, st, __VA_ARGS__);              \
            else hipLaunchKernelGGL((KERNEL<192, false>), grid, dim3(256), 0, st, __VA_ARGS__); }                  \
   } while (0)
-static bool copies_fit(const void* qkv, const void* dout, int64_t h) {
-  return (((uintptr_t)qkv | (uintptr_t)dout) & 3) == 0 && 128 * 3 * h * 2 < (int64_t(1) << 31);
+static bool copies_fit(const void* in, const void* dout, const void* out, int64_t h) {
+  return (((uintptr_t)in | (uintptr_t)dout | (uintptr_t)out) & 3) == 0 && 128 * 3 * h * 2 < (int64_t(1) << 31);
 }
 
 // dK / dV and dQ as one launch while the workgroups of both find a CU each (the dK / dV one leaves no room for a second in
@@ -952,7 +970,7 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
                                 hipStream_t st) {
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(((s + 127) / 128) * b * a));
-  const bool copies = copies_fit(qkv, nullptr, (int64_t)a * d);
+  const bool copies = copies_fit(qkv, nullptr, o, (int64_t)a * d);
   AXONN_ATTN_DISPATCH(attn_fwd_kernel, s, a, b * a, d, (const elem_t*)qkv, (elem_t*)o, lse);
   return hipGetLastError();
 }
@@ -963,7 +981,7 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
-  const bool copies = copies_fit(qkv, dout, (int64_t)a * d);
+  const bool copies = copies_fit(qkv, dout, dqkv, (int64_t)a * d);
   // for d = 64 and 128 the dQ kernel forms delta itself and runs first; sequences that run together get the sums in the order
   // that rule_b of them have
   const bool dq_forms_delta = !both && (d == 64 || d == 128);

@@ -155,6 +155,16 @@ def test_kernels_keep_their_loops_out_of_scratch_memory(elem, tmp_path):
 
 
 @pytest.mark.parametrize("elem", ["bf16", "fp16"])
+def test_attention_kernels_keep_out_of_scratch_memory(elem, tmp_path):
+    """A register spilled inside an attention kernel's loop waits for every copy in flight at its reload.  No such kernel uses
+    scratch memory."""
+    from paper_2110_13005_amd import build as BLD
+    scratch = {k: v for k, v in _kernel_scratch(BLD.VARIANTS[elem][0], tmp_path).items() if "attn_" in k}
+    assert len(scratch) > 20
+    assert not {k: v for k, v in scratch.items() if v}
+
+
+@pytest.mark.parametrize("elem", ["bf16", "fp16"])
 def test_attention_kernels_leave_room_for_their_second_workgroup(elem, tmp_path):
     """Where two workgroups of four waves share a CU (the forward and dQ kernels up to 128 columns, the dK / dV ones up to 64),
     each takes half of a SIMD's 512 registers per lane and of 160 KB of LDS at most."""
