@@ -79,8 +79,8 @@ __device__ __forceinline__ void mfma16_acc(floatx4& c, elemx8 a, elemx8 b) {
 // (two instructions must lie between a vector instruction that writes a register and an MFMA that reads it), but they take
 // issue slots that a wave alone on its SIMD does not have: a slot of one MFMA, one LDS read and half an element's
 // exponential takes 45 clocks with `s_nop 1` and 40 without.  So the kernels place their operands' producers further
-// away, start to use a result three MFMAs later (mfma32_settle_* where nothing is in between), and
-// tests/test_library_abi.py checks both distances in the built libraries.
+// away, start to use a result three MFMAs later (mfma32_settle_* where nothing is in between; twelve wait states are what the
+// compiler puts there), and tests/test_library_abi.py checks both distances in the built libraries, along every path.
 __device__ __forceinline__ void mfma32_agpr(floatx16& c, elemx8 a, elemx8 b) {
   asm volatile(AXONN_MFMA_32X32X16_ASM " %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }

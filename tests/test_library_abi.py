@@ -226,3 +226,113 @@ def test_attention_mfmas_keep_their_distances(elem, tmp_path):
                             by_vector[r] = pos
                 pos += 1
     assert kernels >= 12 and not near, near[:4]
+
+
+_SETTLED, _READABLE = 12, 2
+
+
+def _instructions(body):
+    """[(address, opcode, operands, target address or None)] of a function's listing."""
+    out = []
+    for text, at in re.findall(r"^\s+(\S[^\n]*?)\s*// ([0-9A-F]+):", body, flags=re.M):
+        op, _, rest = text.strip().partition(" ")
+        operands = [x.strip() for x in re.split(r",(?![^\[]*\])", rest)]
+        at, target = int(at, 16), None
+        if op.startswith(("s_branch", "s_cbranch")):
+            offset = int(operands[0].split()[0], 0)
+            target = at + 4 + 4 * (offset - 65536 if offset >= 32768 else offset)
+        assert not op.startswith(("s_setpc", "s_swappc", "s_call")), op
+        out.append((at, op, operands, target))
+    return out
+
+
+def _near_mfmas(body):
+    """The instructions of a function that stand too near to what they read, along any path (jumps taken and not, loops any
+    number of times): fewer than two wait states behind a vector instruction whose result an MFMA takes; fewer than twelve, and
+    fewer than two MFMAs, behind an MFMA whose result another kind of instruction touches or another MFMA multiplies."""
+    code = _instructions(body)
+    index = {at: i for i, (at, _, _, _) in enumerate(code)}
+    starts = {0} | {index[t] for _, _, _, t in code if t is not None}
+    starts |= {i + 1 for i, (_, op, _, t) in enumerate(code) if t is not None or op == "s_endpgm"}
+    known, todo, near = {0: ({}, {})}, [0], set()
+    while todo:
+        i = todo.pop()
+        vector, mfma = (dict(x) for x in known[i])      # register -> states since; register -> (states, MFMAs) since
+        while True:
+            _, op, operands, target = code[i]
+            regs = [_registers(x) for x in operands]
+            states, is_mfma = 1, op.startswith("v_mfma")
+            if op == "s_nop":
+                states += int(operands[0], 0)
+            elif is_mfma:
+                near |= {i for r in set().union(*regs[1:4]) if r in vector} | {i for r in regs[1] | regs[2] if r in mfma}
+            elif op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_")):
+                near |= {i for r in set().union(*regs) if r in mfma}
+            vector = {r: n + states for r, n in vector.items() if n + states < _READABLE}
+            mfma = {r: (n + states, m + is_mfma) for r, (n, m) in mfma.items() if n + states < _SETTLED and m + is_mfma < 2}
+            if is_mfma or op.startswith(("v_", "ds_", "buffer_", "global_", "scratch_")):
+                for r in regs[0]:
+                    vector.pop(r, None)
+                    mfma.pop(r, None)
+                    if is_mfma:
+                        mfma[r] = (0, 0)
+                    elif op.startswith("v_"):
+                        vector[r] = 0
+            nexts = ([] if op in ("s_branch", "s_endpgm") else [i + 1]) + ([index[target]] if target is not None else [])
+            if len(nexts) == 1 and nexts[0] == i + 1 and i + 1 not in starts:
+                i += 1
+                continue
+            for n in nexts:
+                old = known.get(n)
+                new = (vector, mfma)
+                if old:
+                    new = ({r: min(x.get(r, 99) for x in (old[0], vector)) for r in old[0].keys() | vector.keys()},
+                           {r: tuple(min(p) for p in zip(old[1].get(r, (99, 99)), mfma.get(r, (99, 99))))
+                            for r in old[1].keys() | mfma.keys()})
+                if new != old:
+                    known[n] = tuple(dict(x) for x in new)
+                    todo.append(n)
+            break
+    return [code[i] for i in sorted(near)]
+
+
+def _listing(lines):
+    return "".join("\t%s // %012X: 00000000\n" % (x, 4 * i) for i, x in enumerate(lines))
+
+
+def test_distances_are_counted_along_every_path():
+    """The scan below on listings in which the distance is one too short, or just enough: in a row, over a loop's back edge, over a
+    jump around what lies between."""
+    mfma, use = "v_mfma_f32_32x32x16_bf16 v[0:15], v[16:19], v[20:23], v[0:15]", "v_mul_f32_e32 v40, v15, v15"
+    def near(*lines):
+        return bool(_near_mfmas(_listing(list(lines) + ["s_endpgm"])))
+    assert near(mfma, "s_nop 10", use) and not near(mfma, "s_nop 11", use)
+    assert near(mfma, *["s_add_i32 s0, s0, 1"] * 11, use) and not near(mfma, *["s_add_i32 s0, s0, 1"] * 12, use)
+    other = "v_mfma_f32_32x32x16_bf16 a[0:15], v[16:19], v[20:23], a[0:15]"
+    assert near(mfma, other, use) and not near(mfma, other, other, use)
+    assert near("v_mov_b32_e32 v17, v50", "s_nop 0", mfma) and not near("v_mov_b32_e32 v17, v50", "s_nop 1", mfma)
+    assert near(mfma, "s_nop 10", "v_mfma_f32_32x32x16_bf16 a[0:15], v[0:3], v[20:23], a[0:15]")
+    # the loop's first instruction reads what its last MFMA left: 12 in the first round, 2 from the second on
+    assert near("s_nop 15", use, "s_nop 15", mfma, "s_nop 0", "s_cbranch_scc1 65531 <f+0x4>", "s_nop 15")
+    assert not near("s_nop 15", use, "s_nop 15", mfma, "s_nop 11", "s_cbranch_scc1 65531 <f+0x4>", "s_nop 15")
+    # the distance lies behind a jump around it
+    assert near(mfma, "s_cbranch_scc1 1 <f+0xc>", "s_nop 11", use)
+    assert not near(mfma, "s_cbranch_scc1 1 <f+0xc>", "s_nop 11", "s_nop 10", use)
+    # what lies behind an unconditional jump is not reached from in front of it
+    assert not near(mfma, "s_branch 1 <f+0xc>", use, "s_nop 11", use)
+
+
+@pytest.mark.parametrize("elem", ["bf16", "fp16"])
+def test_attention_mfma_distances_along_every_path(elem, tmp_path):
+    """The dK / dV kernels' MFMAs are inline assembly, for which the compiler keeps no distances: two wait states, and twelve or two
+    MFMAs (see _near_mfmas), whichever way the kernel takes.  Twelve are what the compiler itself puts between such an MFMA and
+    the use of its result."""
+    from paper_2110_13005_amd import build as BLD
+    objdump, kernels = _llvm_tool("llvm-objdump"), 0
+    for obj in _code_objects(BLD.VARIANTS[elem][0], tmp_path):
+        text = subprocess.run([objdump, "-d", "--no-show-raw-insn", str(obj)], capture_output=True, text=True, check=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\S*attn_bwd_(?:dkdv|both)\S*)>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", text, flags=re.M | re.S):
+            kernels += 1
+            near = _near_mfmas(body)
+            assert not near, (name, [(hex(at), op, operands) for at, op, operands, _ in near[:4]])
+    assert kernels >= 12
