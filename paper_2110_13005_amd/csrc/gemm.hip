@@ -57,7 +57,8 @@ __device__ __forceinline__ void tile_of_block(int tiles_m, int tiles_n, int& tm,
 // and the reciprocals come with the arguments (set_ring_walk).
 // Bands of 4 tiles across the longer side of a tile that is twice as long as wide, so that what an XCD works on covers about as
 // many rows as columns: 16384 x 2048 x 8192 448.7 -> 441.0 us, 8192 x 4096 x 1024 103.6 -> 102.1, batch of 2 layers of 2048, 16384
-// tokens 10.68 -> 10.53 ms.
+// tokens 10.68 -> 10.53 ms.  Tiles of 128 x 64: 1064 x 976 x 3224 24.4 -> 23.6 us, 1000 x 2000 x 512 6.8 -> 6.5, 1328 x 1328 x 1304 13.0 ->
+// 12.8, 720 x 1656 x 2024 15.7 -> 15.7.
 constexpr uint32_t ring_band(bool wide, int bm, int bn) { return (wide ? bm >= 2 * bn : bn >= 2 * bm) ? 4 : 8; }
 template <int BM, int BN>
 __device__ __forceinline__ void ring_walk(const GemmArgs& g, uint32_t pid, int& tm, int& tn) {
@@ -268,7 +269,9 @@ __device__ __forceinline__ void gemm_epilogue_staged(const floatx4 (&acc)[8][TN]
   // registers each in fp32) and each of the others when a position's registers are free.  Sixteen at a time, and a branch in front of
   // every load, made four trips to memory one behind the other: weight gradient 4096 x 4096 x 672 65.7 -> 49.0 us (47.1 in the
   // copying kernel; 33 with a 16-bit result), 2560 x 7680 x 672 101.7 -> 64.8.  12B-shape batch, fp32 accumulators, one
-  // microbatch per contraction: 125.3 -> 113.7 ms.
+  // microbatch per contraction: 125.3 -> 113.7 ms.  (A 16-bit C to add to would find registers for all 64 in the bf16 build, where it
+  // makes no difference: 4096 x 4096 x 672 33.3 us with 48, 32.7 with 64, 5120 x 5120 x 2048 108.8 and 108.6, 10240 x 10240 x 2048 386 and
+  // 383; in half precision one kernel spills.)
   constexpr int OB = EPI == EPI_ACC_F32 || EPI == EPI_ACC_BF16 ? 48 : 64;
   EpiOperand opnd[OB];
   const bool reads = epi_reads_operand<EPI>(g);
