@@ -445,8 +445,8 @@ __device__ __forceinline__ float delta_add(float p, V ov, V dv, int first) {
   return p;
 }
 // For any head dimension d that is a multiple of 4: 16 lanes per (row, head), 4 elements per lane and step.
-// (Launched in front of the general kernels and of the one-launch backward of either kind; the exact-size dQ kernel in a
-// launch of its own forms delta itself.)
+// (Launched in front of the one-launch backward and where d is not 64 or 128; at those the dQ kernel in a launch of its own forms
+// delta itself.)
 __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs, int s, int a, int d,
                                                                  const elem_t* __restrict__ o,
                                                                  const elem_t* __restrict__ dout,
@@ -958,10 +958,12 @@ static bool copies_fit(const void* in, const void* dout, const void* out, int64_
   return (((uintptr_t)in | (uintptr_t)dout | (uintptr_t)out) & 3) == 0 && 128 * 3 * h * 2 < (int64_t(1) << 31);
 }
 
-// dK / dV and dQ as one launch while the workgroups of both find a CU each (the dK / dV one leaves no room for a second in
-// registers and LDS).  delta then has a launch of its own, which the dQ kernel otherwise spares.  Measured, backward of 16
-// heads of 64 x 1024 (128 tiles): 44.3 -> 31.3 us with it; 3 heads of 128 x 200, 2 sequences: 26.0 -> 17.6; 4 heads of 64 x 128,
-// 2 sequences: 14.0 -> 10.2.
+// dK / dV and dQ as one launch while the workgroups of both find a CU each (above 64 columns the dK / dV one leaves no room for a
+// second in registers and LDS).  delta then has a launch of its own, which the dQ kernel spares at 64 and 128 columns.  Backward in
+// separate launches / in one, us: 16 heads of 64 x 1024 (128 tiles) 37.2 / 26.5, of 128 x 1024 53.5 / 34.4; 16 of 188 x 512 49.2 / 27.4; 3 of
+// 128 x 200, 2 sequences 22.8 / 14.0; 4 of 64 x 128, 2 sequences 12.7 / 9.0.  Beyond the line one launch is the faster one, too:
+// 24 heads of 64 x 1024 (192 tiles) 37.7 / 29.2, of 128 x 1024 55.4 / 40.9, of 188 x 1024 88.3 / 57.7; 16 of 64 x 2048 (256) 64.8 / 58.8.  The line
+// also says in which order delta is summed (by_4), which these shapes keep.
 constexpr int kBothMaxTiles = 128;
 
 static bool head_dim_supported(int d) { return d >= 4 && d <= 192 && d % 4 == 0; }

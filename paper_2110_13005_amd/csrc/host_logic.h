@@ -387,7 +387,8 @@ constexpr TileCost kRingCost[RING_TILES] = {{64, 64, 3.2, 0.20, 0.21}, {128, 64,
                                             {128, 256, 8.0, 0.65, 0.73}};
 // The large-problem kernels.  Weights for the comparison with the ring tiles and no rates: their scale is the one that
 // picks the faster kernel on 230 random shapes of 64 to 255 tiles of 256 x 256 (0.1 % slower than the better of the two on
-// average; weight gradients with an fp32 result 1 % on 90 shapes of 40 to 420 tiles, for any weight of theirs from 0.9 to 1.4).
+// average; weight gradients with an fp32 result 1 % on 90 shapes of 40 to 420 tiles, for any weight of theirs from 0.9 to 1.4:
+// 1.4 leaves their sums the order that they had when their large-problem kernel was the slower register-staged one).
 constexpr double kBigFp32 = 1.4;
 constexpr TileCost kBigCost[3] = {{256, 160, 12.0, 0.57, 0.80}, {256, 192, 12.0, 0.61, 0.84}, {256, 256, 12.0, 0.76, 1.06}};
 

@@ -500,8 +500,9 @@ int wgrad_layer(axonn_stage* st, int l, const LayerStash* const* rec, int n, int
 }
 
 // Rounds layer l's fp32 gradient accumulators into the bf16 gradient buffer (fp32 accumulation only), stores its LayerNorms'
-// gradients there and marks the layer's gradients final on `s`.  Both LayerNorms in one launch, behind the weight gradients; a
-// launch for each was in the chain (3 layers of 384 x 400 tokens on one stream: a batch 626 -> 608 us).
+// gradients there, whose place in the accumulators holds zeros, and marks the layer's gradients final on `s`.  Both LayerNorms
+// in one launch, behind the weight gradients; a launch for each was in the chain (3 layers of 384 x 400 tokens on one stream: a
+// batch 626 -> 608 us).
 int finish_layer_grads(axonn_stage* st, int l, hipStream_t s) {
   {
     ProfScope ps(PC_GRAD_CONVERT, s);
@@ -901,7 +902,7 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
     AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part,
                                                      layernorm_bwd_slices(T, h), !acc, s),
                         "layernorm_bwd (head)"));
-    AX_TRY(check_launch(launch_layernorm_param_grads(layernorm_bwd_slices(T, h), h, hd->ln_part, hd->grads, hd->grads + h, false, s),
+    AX_TRY(check_launch(launch_layernorm_param_grads(layernorm_bwd_slices(T, h), h, hd->ln_part, hd->grads, hd->grads + h, s),
                         "layernorm parameter gradients (head)"));
   }
   hd->count++;
