@@ -557,6 +557,35 @@ def test_attention_of_matrices_at_any_element(b, s, a, d, by):
         assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("by", [1, 2, 4])
+@pytest.mark.parametrize("b,s,a,d", [(2, 130, 2, 188), (2, 72, 4, 44), (3, 33, 2, 64), (2, 200, 34, 128)])
+def test_attention_results_at_any_element(b, s, a, d, by):
+    """Results go to any element, and nothing is written in front of them or behind: through descriptors that end with the last
+    row's last column at multiples of 4 bytes, row by row elsewhere; one sequence's rows end where the next one's begin."""
+    import torch
+    h, dt = a * d, B.torch_elem_dtype()
+    g = torch.Generator(device="cuda"); g.manual_seed(s + d)
+    qkv, dout = (torch.randn(b * s, n, generator=g, device="cuda").to(dt) for n in (3 * h, h))
+    lse, ws = (torch.zeros(b, a, s, device="cuda") for _ in range(2))
+
+    def run(by, guard=64):
+        bufs = [torch.full((guard + by + b * s * n + guard,), 7.0, dtype=dt, device="cuda") for n in (h, 3 * h)]
+        o, dq = (x[guard + by:guard + by + b * s * n] for x, n in zip(bufs, (h, 3 * h)))
+        B.axonn_attention_fwd(b, s, a, d, qkv, o, lse)
+        B.axonn_attention_bwd(b, s, a, d, qkv, o, lse, dout, dq, ws)
+        for x in bufs:
+            assert (x[:guard + by] == 7).all() and (x[-guard:] == 7).all()
+        return o, dq
+
+    whole = run(0)
+    for x, y in zip(whole, run(by)):
+        assert torch.equal(x, y)
+    for i in range(b):
+        o = torch.zeros(s * h, dtype=dt, device="cuda")
+        B.axonn_attention_fwd(1, s, a, d, qkv[i * s:(i + 1) * s], o, lse)
+        assert torch.equal(o, whole[0].view(b, -1)[i])
+
+
 def test_attention_of_unaligned_matrices_takes_no_longer():
     """16 heads of 128 x 2048 at a multiple of 8 bytes and at one of 16: the same time but for a half (through registers two to
     three times as long)."""
