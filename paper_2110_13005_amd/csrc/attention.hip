@@ -12,6 +12,7 @@
 // Operands whose contracted index is not contiguous in the [row][d] tiles (V, and Q / dO / K
 // in the backward kernels) are fetched with the transposing LDS read.
 #include "common.h"
+#include "host_logic.h"
 
 #include <type_traits>
 
@@ -185,15 +186,15 @@ __device__ __forceinline__ elemx8 pack8(const floatx16& t, int first) {
 // own, so XCD x gets ids x, x+8, ...: those are mapped to a contiguous range of (batch, head) pairs, so
 // that the K/V (or Q/dO) rows of a head are fetched into one L2 instead of all eight; inside the range
 // the tiles of rank 0 (the longest-running ones under causal masking) of every head come first.
-__device__ __forceinline__ void attn_block(int id, int n_blocks, int n_bh, int& rank, int& bh) {
-  if ((n_blocks & 7) == 0 && (n_bh & 7) == 0) {
-    const int per_xcd = n_bh >> 3, j = id >> 3;        // j-th block of XCD id % 8
-    rank = j / per_xcd;
-    bh = (id & 7) * per_xcd + j % per_xcd;
-  } else {
-    rank = id / n_bh;
-    bh = id % n_bh;
-  }
+// The divisions are by numbers whose reciprocals come with the arguments: of the instructions in front of the first copy, which
+// the smallest launches feel, they were half.  2 x 4 heads of 64 x 128 forward 5.20 -> 5.12 us, of 64 x 64 4.34 -> 4.14.
+struct AttnWalk { uint32_t xcds, block, heads; };   // blocks are dealt by XCD (1) or not (0); reciprocals of a block row's length and of a
+__device__ __forceinline__ void attn_block(uint32_t id, uint32_t n_bh, uint32_t a, AttnWalk w, int& rank, int& bi, int& hd) {
+  const uint32_t len = w.xcds ? n_bh >> 3 : n_bh, j = w.xcds ? id >> 3 : id;     // j-th block of XCD id % 8
+  rank = host::recip_div(j, len, w.block);
+  const uint32_t bh = j - rank * len + (w.xcds ? (id & 7) * len : 0);
+  bi = host::recip_div(bh, a, w.heads);
+  hd = bh - bi * a;
 }
 
 // One wave's 32 x D result (the MFMA result layout: lane = row lane % 32, registers 4q .. 4q+3 of tile dt = columns
@@ -256,7 +257,7 @@ __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, f
 // 128 x 2048 59.4 -> 53.3, 16 of 128 x 8192 296 -> 264 (1040 TFLOP/s), 8 x 24 of 188 x 512 (every lane on a row of its own,
 // 8 bytes at a time) 80 -> 59, 2 x 36 of 176 x 2048 255 -> 165.
 template <int D, bool ALIGNED>
-__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, int d,
+__global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, AttnWalk walk, int d,
                                                                         const elem_t* __restrict__ qkv,
                                                                         elem_t* __restrict__ o,
                                                                         float* __restrict__ lse) {
@@ -269,10 +270,9 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   __shared__ __align__(1024) char smem[Q_AT + Tile<128, D>::BYTES];
   static_assert(Tile<128, D>::BYTES == BUF && STAGED <= Q_AT + BUF, "rows staged in the tile buffers");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
-  int rank, bh;
-  attn_block(blockIdx.x, gridDim.x, n_bh, rank, bh);
+  int rank, bi, hd;
+  attn_block(blockIdx.x, n_bh, a, walk, rank, bi, hd);
   const int qt = (s + 127) / 128 - 1 - rank;  // longest rows first
-  const int bi = bh / a, hd = bh % a;
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
@@ -499,15 +499,14 @@ struct DkdvLds {
 };
 template <int D, bool ALIGNED>
 __device__ __forceinline__ void attn_bwd_dkdv(
-    DkdvLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv,
+    DkdvLds<D>& lds, int id, int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
     elem_t* __restrict__ dqkv) {
   using L = DkdvLds<D>;
   constexpr int BQ = L::BQ, DT = D / 32, KK = D / 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
-  int rank, bh;
-  attn_block(id, n_blocks, n_bh, rank, bh);    // key tile `rank` walks n_tiles - rank query tiles: longest first
-  const int bi = bh / a, hd = bh % a;
+  int rank, bi, hd;
+  attn_block(id, n_bh, a, walk, rank, bi, hd);    // key tile `rank` walks n_tiles - rank query tiles: longest first
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
@@ -736,17 +735,16 @@ struct DqLds {
 };
 template <int D, bool ALIGNED, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dq(
-    DqLds<D>& lds, int id, int n_blocks, int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv,
+    DqLds<D>& lds, int id, int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ o, const elem_t* __restrict__ dout, const float* __restrict__ lse, float* delta,
     elem_t* __restrict__ dqkv, int by_4) {
   using L = DqLds<D>;
   constexpr int BKV = L::BKV, DT = D / 32, KK = D / 16;
   static_assert(Tile<128, D>::BYTES == L::BUF && 128 * (D + 8) * 2 <= 2 * L::BUF, "the workgroup's 128 rows fit the tile buffers");
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), g = lane >> 5;
-  int rank, bh;
-  attn_block(id, n_blocks, n_bh, rank, bh);
+  int rank, bi, hd;
+  attn_block(id, n_bh, a, walk, rank, bi, hd);
   const int qt = (s + 127) / 128 - 1 - rank;
-  const int bi = bh / a, hd = bh % a;
   const int h = a * d;
   const int64_t ld = 3 * (int64_t)h;
   const elem_t* qb = qkv + (int64_t)bi * s * ld + hd * d;
@@ -914,30 +912,30 @@ __device__ __forceinline__ void attn_bwd_dq(
 // halve the 256 between the two kinds and move accumulators about between the MFMAs, at distances that it does not know.)
 template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
-    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
+    int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, const float* __restrict__ delta, elem_t* __restrict__ dqkv) {
   __shared__ DkdvLds<D> lds;
-  attn_bwd_dkdv<D, ALIGNED>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
+  attn_bwd_dkdv<D, ALIGNED>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
 }
 template <int D, bool ALIGNED, bool FORM_DELTA = false>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
-    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
+    int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
     elem_t* __restrict__ dqkv, int by_4) {
   __shared__ DqLds<D> lds;
-  attn_bwd_dq<D, ALIGNED, FORM_DELTA>(lds, blockIdx.x, gridDim.x, s, a, n_bh, d, qkv, o, dout, lse, delta, dqkv, by_4);
+  attn_bwd_dq<D, ALIGNED, FORM_DELTA>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, o, dout, lse, delta, dqkv, by_4);
 }
 // Both at once, for problems whose tiles do not fill the chip: the first half of the workgroups forms dK and dV, the second
 // dQ; delta is there already.  Each half alone is a chain of up to s / 128 (s / 64) tiles per workgroup on a part of the
 // CUs; side by side they take the longer of the two times.
 template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
-    int s, int a, int n_bh, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
+    int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, float* delta, elem_t* __restrict__ dqkv) {
   __shared__ union { DkdvLds<D> dkdv; DqLds<D> dq; } lds;
   const int n = gridDim.x >> 1, id = blockIdx.x;
-  if (id < n) attn_bwd_dkdv<D, ALIGNED>(lds.dkdv, id, n, s, a, n_bh, d, qkv, dout, lse, delta, dqkv);
-  else attn_bwd_dq<D, ALIGNED, false>(lds.dq, id - n, n, s, a, n_bh, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
+  if (id < n) attn_bwd_dkdv<D, ALIGNED>(lds.dkdv, id, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
+  else attn_bwd_dq<D, ALIGNED, false>(lds.dq, id - n, s, a, n_bh, walk, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
 }
 
 // ------------------------------------------------------------------------- launchers
@@ -966,6 +964,10 @@ static bool copies_fit(const void* in, const void* dout, const void* out, int64_
 // also says in which order delta is summed (by_4), which these shapes keep.
 constexpr int kBothMaxTiles = 128;
 
+static AttnWalk attn_walk(int n_bh, int a) {
+  const bool xcds = n_bh % 8 == 0;             // and with it the number of blocks
+  return {xcds ? 1u : 0u, host::recip_of(xcds ? n_bh / 8 : n_bh), host::recip_of(a)};
+}
 static bool head_dim_supported(int d) { return d >= 4 && d <= 192 && d % 4 == 0; }
 
 hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, void* o, float* lse,
@@ -973,7 +975,8 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(((s + 127) / 128) * b * a));
   const bool copies = copies_fit(qkv, nullptr, o, (int64_t)a * d);
-  AXONN_ATTN_DISPATCH(attn_fwd_kernel, s, a, b * a, d, (const elem_t*)qkv, (elem_t*)o, lse);
+  const AttnWalk walk = attn_walk(b * a, a);
+  AXONN_ATTN_DISPATCH(attn_fwd_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (elem_t*)o, lse);
   return hipGetLastError();
 }
 
@@ -984,6 +987,7 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
   const bool copies = copies_fit(qkv, dout, dqkv, (int64_t)a * d);
+  const AttnWalk walk = attn_walk(b * a, a);
   // for d = 64 and 128 the dQ kernel forms delta itself and runs first; sequences that run together get the sums in the order
   // that rule_b of them have
   const bool dq_forms_delta = !both && (d == 64 || d == 128);
@@ -992,14 +996,14 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
 #define AXONN_ATTN_DQ(D, COPIES)                                                                                                 \
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, COPIES, true>), grid, dim3(256), 0, st, s, a, b * a, d, (const elem_t*)qkv,          \
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, COPIES, true>), grid, dim3(256), 0, st, s, a, b * a, walk, d, (const elem_t*)qkv,          \
                      (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, by_4)
     if (d == 64) { if (copies) AXONN_ATTN_DQ(64, true); else AXONN_ATTN_DQ(64, false); }
     else { if (copies) AXONN_ATTN_DQ(128, true); else AXONN_ATTN_DQ(128, false); }
 #undef AXONN_ATTN_DQ
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
+    AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
     return hipGetLastError();
   }
   const int64_t n_pairs = (int64_t)b * s * a;
@@ -1009,13 +1013,13 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   if (e != hipSuccess) return e;
   if (both) {
     grid = dim3(2u * (unsigned)n_tiles);
-    AXONN_ATTN_DISPATCH(attn_bwd_both_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
+    AXONN_ATTN_DISPATCH(attn_bwd_both_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (const elem_t*)dout, lse, delta, (elem_t*)dqkv);
     return hipGetLastError();
   }
-  AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
+  AXONN_ATTN_DISPATCH(attn_bwd_dkdv_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (const elem_t*)dout, lse, (const float*)delta, (elem_t*)dqkv);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, 0);
+  AXONN_ATTN_DISPATCH(attn_bwd_dq_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, 0);
   return hipGetLastError();
 }
 #undef AXONN_ATTN_DISPATCH

@@ -267,8 +267,8 @@ __device__ __forceinline__ void gemm_epilogue_staged(const floatx4 (&acc)[8][TN]
   // What the epilogue reads at its output positions (residual, stored derivative, accumulating C) is requested ahead: the
   // whole wave tile at once (64 row pairs, 2 registers each) for bf16 operands, 48 of the 64 row pairs for a C to add to (4
   // registers each in fp32) and each of the others when a position's registers are free.  Sixteen at a time, and a branch in front of
-  // every load, made four trips to memory one behind the other: weight gradient 4096 x 4096 x 672 65.7 -> 49.0 us (47.1 in the
-  // copying kernel; 33 with a 16-bit result), 2560 x 7680 x 672 101.7 -> 64.8.  12B-shape batch, fp32 accumulators, one
+  // every load, made four trips to memory one behind the other: weight gradient 4096 x 4096 x 672 in the register-staged kernel
+  // 65.7 -> 49.0 us (47.1 in the copying kernel; 33 with a 16-bit result), 2560 x 7680 x 672 101.7 -> 64.8 (60.6).  12B-shape batch, fp32 accumulators, one
   // microbatch per contraction: 125.3 -> 113.7 ms.  (A 16-bit C to add to would find registers for all 64 in the bf16 build, where it
   // makes no difference: 4096 x 4096 x 672 33.3 us with 48, 32.7 with 64, 5120 x 5120 x 2048 108.8 and 108.6, 10240 x 10240 x 2048 386 and
   // 383; in half precision one kernel spills.)
