@@ -38,8 +38,8 @@ __device__ __forceinline__ float max_with_other_half(float v) {
 // 4, the last chunk is half the next head's (or the end of the matrix), and that half is cleared in LDS.  Zero columns add
 // nothing to a product over columns, and result columns outside the head are never stored.
 // Every other head then starts between two 16-byte boundaries, which costs the copies little (they take addresses that are multiples of
-// 4 bytes): 8 x 24 heads of 188 x 512 forward 54.7 us, dQ 69.1, dK / dV 79.5, against 55.6, 69.6 and 79.8 in
-// tiles that start at the boundary in front of such a head.
+// 4 bytes): 8 x 24 heads of 188 x 512 forward 54.7 us, dQ 69.1, dK / dV 79.5 where the same kernels with tiles that start at the
+// boundary in front of such a head took 55.6, 69.6 and 79.8.
 struct HeadColumns {
   int d;
   __device__ __forceinline__ int chunks() const { return (d + 7) >> 3; }
@@ -254,8 +254,8 @@ __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, f
 // beside the P V MFMAs, and the memory pipeline fills a tile's buffer a whole tile ahead.  K and V fragments being in
 // registers when the barrier of a tile is reached, its buffer is free behind it: two buffers and one barrier per tile.
 // Against tiles fetched into registers, stored between two barriers, and each tile's fragments read in one go, us: 40 heads of
-// 128 x 2048 59.4 -> 53.3, 16 of 128 x 8192 296 -> 264 (1040 TFLOP/s), 8 x 24 of 188 x 512 (every lane on a row of its own,
-// 8 bytes at a time) 80 -> 59, 2 x 36 of 176 x 2048 255 -> 165.
+// 128 x 2048 58.0 -> 52.0, 16 of 128 x 8192 311 -> 278 (990 TFLOP/s), 8 x 16 of 64 x 1024 28.4 -> 27.1, 8 x 24 of 188 x 512 (every
+// lane on a row of its own, 8 bytes at a time) 76 -> 50.6, 2 x 36 of 176 x 2048 256 -> 153.
 template <int D, bool ALIGNED>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, AttnWalk walk, int d,
                                                                         const elem_t* __restrict__ qkv,
@@ -486,9 +486,9 @@ __global__ __launch_bounds__(256) void attn_delta_general_kernel(int64_t n_pairs
 // block in front of the wave's keys are jumped over, so that what it holds does not reach their gradients.
 // What bounds a slot is what one wave issues: a vector instruction takes 5 clocks of its 32, an exponential 9, a conversion of
 // two elements 8; and the LDS, which gives a transposed fragment in 4.6 clocks without bank conflicts and in 8 with the two-way
-// ones of padded rows.  40 heads of 128 x 2048 117 -> 97 us, 16 of 128 x 8192 570 -> 472, 8 x 16 of 64 x 1024 64 -> 44 (two waves
+// ones of padded rows.  40 heads of 128 x 2048 125 -> 112 us, 16 of 128 x 8192 535 -> 477, 8 x 16 of 64 x 1024 60 -> 44 (two waves
 // per SIMD here, at 256 registers), against wait states in front of every MFMA, padded rows, tiles fetched into registers and
-// all of a block's exponentials beside 16 of its slots; 8 x 24 of 188 x 512 (block by block, tiles of 64) 140 -> 82.
+// all of a block's exponentials beside 16 of its slots; 8 x 24 of 188 x 512 (block by block, tiles of 64) 119 -> 75.
 template <int D>
 struct DkdvLds {
   static constexpr int BQ = D <= 128 ? 128 : 64, TILE = Tile<BQ, D>::BYTES, BUF = 2 * TILE, KEYS = Tile<128, D>::BYTES;
@@ -725,7 +725,8 @@ __device__ __forceinline__ void attn_bwd_dkdv(
 //
 // Two workgroups share a CU.  The fragments run a few MFMAs ahead through a ring, so that a wave waits for LDS only behind the
 // two barriers of a tile: one when everybody has left the tile before, whose buffer the memory pipeline then fills, one when
-// that has come.  40 heads of 128 x 2048 82 -> 74 us, 16 of 128 x 8192 418 -> 368, 8 x 24 of 188 x 512 100 -> 73.
+// that has come.  40 heads of 128 x 2048 86 -> 81 us, 16 of 128 x 8192 412 -> 372, 8 x 16 of 64 x 1024
+// 39.8 -> 37.8, 8 x 24 of 188 x 512 100 -> 65.
 template <int D>
 struct DqLds {
   static constexpr int BKV = 64, TILE = Tile<BKV, D>::BYTES, BUF = 2 * TILE;
@@ -941,8 +942,8 @@ __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
 // ------------------------------------------------------------------------- launchers
 // Head dimensions up to 64, 128 and 192 run in tiles of that many columns.  The copies into LDS want matrices that start at a
 // multiple of 4 bytes and take 32-bit byte offsets within 128 rows; others go through registers, a chunk after the other.  16 heads
-// of 128 x 2048 at a multiple of 8 bytes: forward 40.3 us (through registers 147; at a multiple of 16 bytes 38.5), dQ 50.4 (158), dK / dV
-// 53.8 (120).
+// of 128 x 2048 at a multiple of 8 bytes: forward 39.4 us (through registers 147; at a multiple of 16 bytes 39.0), dQ 49.2 (158),
+// dK / dV 52.3 (120).
 #define AXONN_ATTN_DISPATCH(KERNEL, ...)                                                                  \
   do {                                                                                                    \
     if (d <= 64) { if (copies) hipLaunchKernelGGL((KERNEL<64, true>), grid, dim3(256), 0, st, __VA_ARGS__);       \
