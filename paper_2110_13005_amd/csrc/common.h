@@ -301,12 +301,14 @@ hipError_t launch_layernorm_bwd(int64_t T, int64_t h, const void* dout, const vo
                                 float* ws, hipStream_t s);
 // dx and the parameter-gradient sums of one call, added to (`first`: stored in) the `slices` slices of 2 * h floats of
 // `partial`; layernorm_bwd_slices(T, h): as many as a call with T rows has use for, the same number in all calls that
-// collect in one `partial`.  launch_layernorm_param_grads stores what the slices have collected in 16-bit gradient vectors.
+// collect in one `partial`.  launch_layernorm_param_grads stores what the slices have collected in gradient vectors of
+// either type (the LM head's are 16-bit ones).
 int layernorm_bwd_slices(int64_t T, int64_t h);
 hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, const void* x, const float* stats,
                                         const void* gamma, const void* res_grad, void* dx, float* partial, int slices,
                                         bool first, hipStream_t s);
-hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta, hipStream_t s);
+hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta,
+                                        bool dst_fp32, hipStream_t s);
 // The same for both LayerNorms of n_layers layers (their slices lie behind one another) in one launch, into a 16-bit
 // gradient buffer: dgamma is the first layer's first one, each shift gradient follows its gain gradient.
 hipError_t launch_layernorm_param_grads_all(int slices, int64_t h, int n_layers, const float* partial, void* dgamma,

@@ -540,9 +540,10 @@ hipError_t launch_layernorm_bwd_partial(int64_t T, int64_t h, const void* dout, 
 #undef AXONN_LN
   return hipGetLastError();
 }
-hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta, hipStream_t s) {
+hipError_t launch_layernorm_param_grads(int slices, int64_t h, const float* partial, void* dgamma, void* dbeta,
+                                        bool dst_fp32, hipStream_t s) {
   hipLaunchKernelGGL(colsum_final_kernel<2>, dim3((unsigned)((h + 63) / 64)), dim3(256), 0, s, slices,
-                     (int)h, partial, dbeta, dgamma, 1, 0, 0, 0);
+                     (int)h, partial, dbeta, dgamma, 1, dst_fp32 ? 1 : 0, 0, 0);
   return hipGetLastError();
 }
 hipError_t launch_layernorm_param_grads_all(int slices, int64_t h, int n_layers, const float* partial, void* dgamma,

@@ -902,7 +902,7 @@ int head_forward_backward(axonn_head* hd, const void* x, const int32_t* targets,
     AX_TRY(check_launch(launch_layernorm_bwd_partial(T, h, hd->da, x, hd->stats, g, nullptr, dx, hd->ln_part,
                                                      layernorm_bwd_slices(T, h), !acc, s),
                         "layernorm_bwd (head)"));
-    AX_TRY(check_launch(launch_layernorm_param_grads(layernorm_bwd_slices(T, h), h, hd->ln_part, hd->grads, hd->grads + h, s),
+    AX_TRY(check_launch(launch_layernorm_param_grads(layernorm_bwd_slices(T, h), h, hd->ln_part, hd->grads, hd->grads + h, false, s),
                         "layernorm parameter gradients (head)"));
   }
   hd->count++;
