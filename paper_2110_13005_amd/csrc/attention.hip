@@ -37,9 +37,9 @@ __device__ __forceinline__ float max_with_other_half(float v) {
 // depend on where in the matrix the head lies.  Chunks behind the head's last column read as zeros; where d is an odd multiple of
 // 4, the last chunk is half the next head's (or the end of the matrix), and that half is cleared in LDS.  Zero columns add
 // nothing to a product over columns, and result columns outside the head are never stored.
-// Every other head then starts between two 16-byte boundaries, which costs the copies little (they take addresses that are multiples of
-// 4 bytes): 8 x 24 heads of 188 x 512 forward 54.7 us, dQ 69.1, dK / dV 79.5 where the same kernels with tiles that start at the
-// boundary in front of such a head took 55.6, 69.6 and 79.8.
+// Every other head then starts between two 16-byte boundaries, which costs the copies little (they take any address): 8 x 24 heads
+// of 188 x 512 forward 54.7 us, dQ 69.1, dK / dV 79.5 where the same kernels with tiles that start at the boundary in front of such
+// a head took 55.6, 69.6 and 79.8.
 struct HeadColumns {
   int d;
   __device__ __forceinline__ int chunks() const { return (d + 7) >> 3; }
@@ -103,7 +103,7 @@ __device__ __forceinline__ elemx8 frag_cols(LdsBytes tile, const FragLanes& f, i
 
 // Fills tiles with rows of one head of a [rows][ld] matrix; rows beyond the last one read as zeros.  The descriptor starts at
 // the tile's first row, so that offsets stay small for any sequence length.
-template <int D, bool ALIGNED>
+template <int D, bool FITS>
 struct TileSource {
   const elem_t* base;                  // row 0, the head's first column
   uint32_t row_bytes, row_end;         // row_end: bytes of a row up to the head's last column
@@ -125,7 +125,7 @@ struct TileSource {
   // the R rows from row0 on
   template <int R>
   __device__ __forceinline__ void fill(LdsBytes tile, int row0) const {
-    if (!ALIGNED) { fill_unaligned<R>(tile, row0); return; }
+    if (!FITS) { fill_long<R>(tile, row0); return; }
     const Copies<R> c = copies<R>(tile, row0);
 #pragma unroll
     for (int i = 0; i < Copies<R>::N; ++i) c.one(i, *this);
@@ -150,9 +150,9 @@ struct TileSource {
     c.lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)tile.p) + (uint32_t)wave * 1024u;
     return c;
   }
-  // Matrices that do not start at a multiple of 4 bytes: through registers.
+  // Rows too long for 32-bit offsets: through registers.
   template <int R>
-  __device__ __forceinline__ void fill_unaligned(LdsBytes tile, int row0) const {
+  __device__ __forceinline__ void fill_long(LdsBytes tile, int row0) const {
 #pragma unroll 1
     for (int i = 64 * wave + lane; i < R * (D / 8); i += 256) {
       const int r = i / (D / 8), ch = i % (D / 8), row = row0 + r;
@@ -202,8 +202,8 @@ __device__ __forceinline__ void attn_block(uint32_t id, uint32_t n_bh, uint32_t 
 // the MFMA layout every lane touches a row of its own, 8 bytes at a time, a memory instruction then covers 32 different
 // lines, and the last stores alone took a tenth of the dK / dV kernel's time.  `stage` is 32 x (D + 8) elements of LDS that
 // only this wave touches (no barrier: a wave's LDS operations keep their order).  Rows and columns that do not exist are stored out of
-// a descriptor's range instead of behind branches (ALIGNED; the same condition as for the copies).
-template <int D, bool ALIGNED>
+// a descriptor's range instead of behind branches.
+template <int D, bool FITS>
 __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, float mul, elem_t* head, int64_t ld,
                                                int n_rows, HeadColumns cols, int lane) {
   constexpr int LDO = D + 8, DT = D / 32, CPR = D / 8;      // 16-byte chunks per row
@@ -219,7 +219,7 @@ __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, f
       for (int e = 0; e < 4; ++e) v[e] = (elem_t)(acc[dt][4 * q + e] * mul);
       *reinterpret_cast<elemx4*>(stage + (lane & 31) * LDO + dt * 32 + 8 * q + 4 * g) = v;
     }
-  if (ALIGNED) {
+  if (FITS) {
     const uint32_t row_bytes = (uint32_t)ld * 2u;
     const int rows = min(n_rows, 32);
     const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(head, rows > 0 ? (uint32_t)(rows - 1) * row_bytes + (uint32_t)cols.d * 2u : 0u);
@@ -256,7 +256,7 @@ __device__ __forceinline__ void store_rows_out(char* lds, const floatx16* acc, f
 // Against tiles fetched into registers, stored between two barriers, and each tile's fragments read in one go, us: 40 heads of
 // 128 x 2048 58.0 -> 52.0, 16 of 128 x 8192 311 -> 278 (990 TFLOP/s), 8 x 16 of 64 x 1024 28.4 -> 27.1, 8 x 24 of 188 x 512 (every
 // lane on a row of its own, 8 bytes at a time) 76 -> 50.6, 2 x 36 of 176 x 2048 256 -> 153.
-template <int D, bool ALIGNED>
+template <int D, bool FITS>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, int a, int n_bh, AttnWalk walk, int d,
                                                                         const elem_t* __restrict__ qkv,
                                                                         elem_t* __restrict__ o,
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   const HeadColumns cols{d};
   const FragLanes fl(lane);
   const int kv_end = min(s, q0 + 128);         // keys behind the workgroup's last query are not fetched
-  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid);
+  const TileSource<D, FITS> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid);
 
   const LdsBytes buf0(smem);
   q_src.template fill<128>(buf0 + Q_AT, q0);
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   };
   if (OWN_Q) {
     fill_second();
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(ALIGNED ? 2 * TileSource<D, ALIGNED>::template Copies<BKV>::N : 0) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(FITS ? 2 * TileSource<D, FITS>::template Copies<BKV>::N : 0) : "memory");
   } else {
     dma_wait_all();
   }
@@ -397,20 +397,20 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
       k_src.template clear_foreign<BKV>(next);
     }
     __syncthreads();
-    if (!ALIGNED && kt + 2 < n_kt) {
+    if (!FITS && kt + 2 < n_kt) {
       k_src.template fill<BKV>(buf, k0 + 2 * BKV);
       v_src.template fill<BKV>(buf + Tile<BKV, D>::BYTES, k0 + 2 * BKV);
     }
     // one copy per two MFMAs: in one go in front of them they take as long as half of them
     const auto ck = k_src.template copies<BKV>(buf, k0 + 2 * BKV), cv = v_src.template copies<BKV>(buf + Tile<BKV, D>::BYTES, k0 + 2 * BKV);
-    static_assert(4 * TileSource<D, ALIGNED>::template Copies<BKV>::N == NF, "copies and MFMAs");
+    static_assert(4 * TileSource<D, FITS>::template Copies<BKV>::N == NF, "copies and MFMAs");
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
       oacc[i % DT] = mfma32(vfr[i], pf[i / DT], oacc[i % DT]);
       kfr[i] = k_frag(next, i);
-      if (ALIGNED && i % 4 == 0) ck.one(i / 4, k_src);
-      if (ALIGNED && i % 4 == 2) cv.one(i / 4, v_src);
+      if (FITS && i % 4 == 0) ck.one(i / 4, k_src);
+      if (FITS && i % 4 == 2) cv.one(i / 4, v_src);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_fwd_kernel(int s, i
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   dma_wait_all();                 // copies of tiles beyond the last still write (zeros) to LDS
   __syncthreads();                // the tiles in LDS are done with
-  store_rows_out<D, ALIGNED>(smem + wave * (STAGED / 4), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, cols, lane);
+  store_rows_out<D, FITS>(smem + wave * (STAGED / 4), oacc, 1.f / l_tot, o + ((int64_t)bi * s + qw0) * h + hd * d, h, s - qw0, cols, lane);
   if (g == 0 && qi < s) lse[((int64_t)bi * a + hd) * s + qi] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
@@ -497,7 +497,7 @@ struct DkdvLds {
   __align__(16) float lse[2][BQ];
   __align__(16) float delta[2][BQ];
 };
-template <int D, bool ALIGNED>
+template <int D, bool FITS>
 __device__ __forceinline__ void attn_bwd_dkdv(
     DkdvLds<D>& lds, int id, int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, const float* __restrict__ delta,
@@ -516,7 +516,7 @@ __device__ __forceinline__ void attn_bwd_dkdv(
   const float scale = rsqrtf((float)d), scale_log2 = kLog2e * scale;
   const HeadColumns cols{d};
   const FragLanes fl(lane);
-  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid),
+  const TileSource<D, FITS> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, s, cols, tid), v_src(qb + 2 * h, ld, s, cols, tid),
       do_src(dout + (int64_t)bi * s * h + hd * d, h, s, cols, tid);
   const int qt_begin = k0 / BQ, n_qt = (s + BQ - 1) / BQ;
   const LdsBytes keys(lds.tiles + L::BUF), tile0(lds.tiles);
@@ -627,7 +627,7 @@ __device__ __forceinline__ void attn_bwd_dkdv(
   // The next tile is copied into the other buffer during the first steps of a tile, one instruction per slot, and its first
   // block is read from slot READY on.  Rows beyond the sequence read as zeros, so a tile beyond the last one needs no case of
   // its own.
-  constexpr int READY = (NB - 1) * STEP - (W - 1), NCP = TileSource<D, ALIGNED>::template Copies<BQ>::N;
+  constexpr int READY = (NB - 1) * STEP - (W - 1), NCP = TileSource<D, FITS>::template Copies<BQ>::N;
   static_assert(2 * NCP < READY, "copies are issued in front of the wait for them");
   // masked: 0 no, 1 this tile, 2 the next one too
   auto tile_stream = [&](int qt, auto masked) {
@@ -639,7 +639,7 @@ __device__ __forceinline__ void attn_bwd_dkdv(
     const LdsBytes next = tile0 + (buf ^ 1) * L::BUF;
     // every wave has left the tile before, whose buffer is filled again (what a wave has read of it it has used)
     asm volatile("s_barrier" : : : "memory");
-    if (!ALIGNED) {
+    if (!FITS) {
       q_src.template fill<BQ>(next, (qt + 1) * BQ);
       do_src.template fill<BQ>(next + L::TILE, (qt + 1) * BQ);
     }
@@ -672,7 +672,7 @@ __device__ __forceinline__ void attn_bwd_dkdv(
         fetch_stats(qt + 2);
       }
       ring[(j + W - 1) % W] = load_frag(buf, j + W - 1);        // into the fragment of the slot before
-      if (ALIGNED && j < 2 * NCP) {
+      if (FITS && j < 2 * NCP) {
         if (j < NCP) cq.one(j, q_src);
         else cdo.one(j - NCP, do_src);
       }
@@ -713,8 +713,8 @@ __device__ __forceinline__ void attn_bwd_dkdv(
   constexpr int STAGED = 32 * (D + 8) * 2;
   static_assert(8 * STAGED <= sizeof(lds.tiles), "the result rows fit the tile buffers");
   elem_t* dk_rows = dqkv + ((int64_t)bi * s + kw0) * ld + h + hd * d;
-  store_rows_out<D, ALIGNED>(lds.tiles + wave * STAGED, dkacc, scale, dk_rows, ld, s - kw0, cols, lane);
-  store_rows_out<D, ALIGNED>(lds.tiles + (4 + wave) * STAGED, dvacc, 1.f, dk_rows + h, ld, s - kw0, cols, lane);
+  store_rows_out<D, FITS>(lds.tiles + wave * STAGED, dkacc, scale, dk_rows, ld, s - kw0, cols, lane);
+  store_rows_out<D, FITS>(lds.tiles + (4 + wave) * STAGED, dvacc, 1.f, dk_rows + h, ld, s - kw0, cols, lane);
 }
 
 // dQ: wave w owns queries q0 + 32w .. +31 and walks the key tiles up to the diagonal (same traversal as the forward kernel).
@@ -734,7 +734,7 @@ struct DqLds {
   __align__(1024) char tiles[2 * BUF];
   float delta[128];
 };
-template <int D, bool ALIGNED, bool FORM_DELTA>
+template <int D, bool FITS, bool FORM_DELTA>
 __device__ __forceinline__ void attn_bwd_dq(
     DqLds<D>& lds, int id, int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv,
     const elem_t* __restrict__ o, const elem_t* __restrict__ dout, const float* __restrict__ lse, float* delta,
@@ -757,7 +757,7 @@ __device__ __forceinline__ void attn_bwd_dq(
   const HeadColumns cols{d};
   const FragLanes fl(lane);
   const int kv_end = min(s, q0 + 128);         // keys behind the workgroup's last query are not fetched
-  const TileSource<D, ALIGNED> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid),
+  const TileSource<D, FITS> q_src(qb, ld, s, cols, tid), k_src(qb + h, ld, kv_end, cols, tid), v_src(qb + 2 * h, ld, kv_end, cols, tid),
       do_src(dob, h, s, cols, tid);
   const LdsBytes buf0(lds.tiles), buf1(lds.tiles + L::BUF);
 
@@ -904,58 +904,56 @@ __device__ __forceinline__ void attn_bwd_dq(
   }
   dma_wait_all();
   __syncthreads();                // the tiles in LDS are done with
-  store_rows_out<D, ALIGNED>(lds.tiles + wave * (32 * (D + 8) * 2), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, cols, lane);
+  store_rows_out<D, FITS>(lds.tiles + wave * (32 * (D + 8) * 2), dqacc, scale, dqkv + ((int64_t)bi * s + qw0) * ld + hd * d, ld, s - qw0, cols, lane);
 }
 
 // ------------------------------------------------------------------- backward kernels
 // At D = 64 two workgroups share a CU, with 160 ordinary and 96 accumulation registers per lane: at four more 8 x 16 heads of
 // 64 x 1024 take 55 us for dK / dV instead of 44.  (A second argument to __launch_bounds__ does not keep it so: it makes the compiler
 // halve the 256 between the two kinds and move accumulators about between the MFMAs, at distances that it does not know.)
-template <int D, bool ALIGNED>
+template <int D, bool FITS>
 __global__ __launch_bounds__(256) void attn_bwd_dkdv_kernel(
     int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, const float* __restrict__ delta, elem_t* __restrict__ dqkv) {
   __shared__ DkdvLds<D> lds;
-  attn_bwd_dkdv<D, ALIGNED>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
+  attn_bwd_dkdv<D, FITS>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
 }
-template <int D, bool ALIGNED, bool FORM_DELTA = false>
+template <int D, bool FITS, bool FORM_DELTA = false>
 __global__ __launch_bounds__(256, D > 128 ? 1 : 2) void attn_bwd_dq_kernel(
     int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ o,
     const elem_t* __restrict__ dout, const float* __restrict__ lse, float* __restrict__ delta,
     elem_t* __restrict__ dqkv, int by_4) {
   __shared__ DqLds<D> lds;
-  attn_bwd_dq<D, ALIGNED, FORM_DELTA>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, o, dout, lse, delta, dqkv, by_4);
+  attn_bwd_dq<D, FITS, FORM_DELTA>(lds, blockIdx.x, s, a, n_bh, walk, d, qkv, o, dout, lse, delta, dqkv, by_4);
 }
 // Both at once, for problems whose tiles do not fill the chip: the first half of the workgroups forms dK and dV, the second
 // dQ; delta is there already.  Each half alone is a chain of up to s / 128 (s / 64) tiles per workgroup on a part of the
 // CUs; side by side they take the longer of the two times.
-template <int D, bool ALIGNED>
+template <int D, bool FITS>
 __global__ __launch_bounds__(256) void attn_bwd_both_kernel(
     int s, int a, int n_bh, AttnWalk walk, int d, const elem_t* __restrict__ qkv, const elem_t* __restrict__ dout,
     const float* __restrict__ lse, float* delta, elem_t* __restrict__ dqkv) {
   __shared__ union { DkdvLds<D> dkdv; DqLds<D> dq; } lds;
   const int n = gridDim.x >> 1, id = blockIdx.x;
-  if (id < n) attn_bwd_dkdv<D, ALIGNED>(lds.dkdv, id, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
-  else attn_bwd_dq<D, ALIGNED, false>(lds.dq, id - n, s, a, n_bh, walk, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
+  if (id < n) attn_bwd_dkdv<D, FITS>(lds.dkdv, id, s, a, n_bh, walk, d, qkv, dout, lse, delta, dqkv);
+  else attn_bwd_dq<D, FITS, false>(lds.dq, id - n, s, a, n_bh, walk, d, qkv, nullptr, dout, lse, delta, dqkv, 0);
 }
 
 // ------------------------------------------------------------------------- launchers
-// Head dimensions up to 64, 128 and 192 run in tiles of that many columns.  The copies into LDS want matrices that start at a
-// multiple of 4 bytes and take 32-bit byte offsets within 128 rows; others go through registers, a chunk after the other.  16 heads
-// of 128 x 2048 at a multiple of 8 bytes: forward 39.4 us (through registers 147; at a multiple of 16 bytes 39.0), dQ 49.2 (158),
-// dK / dV 52.3 (120).
+// Head dimensions up to 64, 128 and 192 run in tiles of that many columns.  The copies into LDS and the stores take 32-bit byte
+// offsets within 128 rows (FITS); longer rows, of 2.8 million columns and more, go through registers, a chunk after the other.
+// Matrices start at any element.  16 heads of 128 x 2048 at a multiple of 16 bytes, 8 bytes behind one and 2 bytes behind one, us:
+// forward 39.4, 39.6 and 52.2, dQ 54.0, 49.8 and 60.8, dK / dV 57.1, 53.7 and 65.9 (through registers 147, 158 and 120).
 #define AXONN_ATTN_DISPATCH(KERNEL, ...)                                                                  \
   do {                                                                                                    \
-    if (d <= 64) { if (copies) hipLaunchKernelGGL((KERNEL<64, true>), grid, dim3(256), 0, st, __VA_ARGS__);       \
+    if (d <= 64) { if (fits) hipLaunchKernelGGL((KERNEL<64, true>), grid, dim3(256), 0, st, __VA_ARGS__);       \
                    else hipLaunchKernelGGL((KERNEL<64, false>), grid, dim3(256), 0, st, __VA_ARGS__); }           \
-    else if (d <= 128) { if (copies) hipLaunchKernelGGL((KERNEL<128, true>), grid, dim3(256), 0, st, __VA_ARGS__); \
+    else if (d <= 128) { if (fits) hipLaunchKernelGGL((KERNEL<128, true>), grid, dim3(256), 0, st, __VA_ARGS__); \
                          else hipLaunchKernelGGL((KERNEL<128, false>), grid, dim3(256), 0, st, __VA_ARGS__); }    \
-    else { if (copies) hipLaunchKernelGGL((KERNEL<192, true>), grid, dim3(256), 0, st, __VA_ARGS__);              \
+    else { if (fits) hipLaunchKernelGGL((KERNEL<192, true>), grid, dim3(256), 0, st, __VA_ARGS__);              \
            else hipLaunchKernelGGL((KERNEL<192, false>), grid, dim3(256), 0, st, __VA_ARGS__); }                  \
   } while (0)
-static bool copies_fit(const void* in, const void* dout, const void* out, int64_t h) {
-  return (((uintptr_t)in | (uintptr_t)dout | (uintptr_t)out) & 3) == 0 && 128 * 3 * h * 2 < (int64_t(1) << 31);
-}
+static bool offsets_fit(int64_t h) { return 128 * 3 * h * 2 < (int64_t(1) << 31); }
 
 // dK / dV and dQ as one launch while the workgroups of both find a CU each (above 64 columns the dK / dV one leaves no room for a
 // second in registers and LDS).  delta then has a launch of its own, which the dQ kernel spares at 64 and 128 columns.  Backward in
@@ -975,7 +973,7 @@ hipError_t launch_attention_fwd(int b, int s, int a, int d, const void* qkv, voi
                                 hipStream_t st) {
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)(((s + 127) / 128) * b * a));
-  const bool copies = copies_fit(qkv, nullptr, o, (int64_t)a * d);
+  const bool fits = offsets_fit((int64_t)a * d);
   const AttnWalk walk = attn_walk(b * a, a);
   AXONN_ATTN_DISPATCH(attn_fwd_kernel, s, a, b * a, walk, d, (const elem_t*)qkv, (elem_t*)o, lse);
   return hipGetLastError();
@@ -987,7 +985,7 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   if (!head_dim_supported(d)) return hipErrorInvalidValue;
   const int n_tiles = ((s + 127) / 128) * b * a;
   const bool both = n_tiles <= kBothMaxTiles;
-  const bool copies = copies_fit(qkv, dout, dqkv, (int64_t)a * d);
+  const bool fits = offsets_fit((int64_t)a * d);
   const AttnWalk walk = attn_walk(b * a, a);
   // for d = 64 and 128 the dQ kernel forms delta itself and runs first; sequences that run together get the sums in the order
   // that rule_b of them have
@@ -996,11 +994,11 @@ hipError_t launch_attention_bwd(int b, int s, int a, int d, const void* qkv, con
   hipError_t e;
   dim3 grid((unsigned)n_tiles);
   if (dq_forms_delta) {
-#define AXONN_ATTN_DQ(D, COPIES)                                                                                                 \
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, COPIES, true>), grid, dim3(256), 0, st, s, a, b * a, walk, d, (const elem_t*)qkv,          \
+#define AXONN_ATTN_DQ(D, FITS)                                                                                                 \
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, FITS, true>), grid, dim3(256), 0, st, s, a, b * a, walk, d, (const elem_t*)qkv,          \
                      (const elem_t*)o, (const elem_t*)dout, lse, delta, (elem_t*)dqkv, by_4)
-    if (d == 64) { if (copies) AXONN_ATTN_DQ(64, true); else AXONN_ATTN_DQ(64, false); }
-    else { if (copies) AXONN_ATTN_DQ(128, true); else AXONN_ATTN_DQ(128, false); }
+    if (d == 64) { if (fits) AXONN_ATTN_DQ(64, true); else AXONN_ATTN_DQ(64, false); }
+    else { if (fits) AXONN_ATTN_DQ(128, true); else AXONN_ATTN_DQ(128, false); }
 #undef AXONN_ATTN_DQ
     e = hipGetLastError();
     if (e != hipSuccess) return e;

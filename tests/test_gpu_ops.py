@@ -538,8 +538,7 @@ def test_attention_head_is_not_reached_by_its_neighbours(s, a, d):
 @pytest.mark.parametrize("by", [1, 2, 6])
 @pytest.mark.parametrize("b,s,a,d", [(1, 200, 2, 64), (2, 136, 33, 128), (1, 72, 4, 44), (1, 264, 2, 188), (1, 130, 66, 124)])
 def test_attention_of_matrices_at_any_element(b, s, a, d, by):
-    """Matrices that start at a multiple of 4 bytes are copied into LDS like others, those at an odd element go through registers;
-    the bits are the same."""
+    """Matrices start at any element: the copies into LDS take their addresses as they are.  The bits are the same."""
     import torch
     h, dt = a * d, B.torch_elem_dtype()
     g = torch.Generator(device="cuda"); g.manual_seed(s + d)
@@ -560,8 +559,8 @@ def test_attention_of_matrices_at_any_element(b, s, a, d, by):
 @pytest.mark.parametrize("by", [1, 2, 4])
 @pytest.mark.parametrize("b,s,a,d", [(2, 130, 2, 188), (2, 72, 4, 44), (3, 33, 2, 64), (2, 200, 34, 128)])
 def test_attention_results_at_any_element(b, s, a, d, by):
-    """Results go to any element, and nothing is written in front of them or behind: through descriptors that end with the last
-    row's last column at multiples of 4 bytes, row by row elsewhere; one sequence's rows end where the next one's begin."""
+    """Results go to any element, and nothing is written in front of them or behind: their descriptors end with the last row's last
+    column, and one sequence's rows end where the next one's begin."""
     import torch
     h, dt = a * d, B.torch_elem_dtype()
     g = torch.Generator(device="cuda"); g.manual_seed(s + d)
@@ -586,9 +585,40 @@ def test_attention_results_at_any_element(b, s, a, d, by):
         assert torch.equal(o, whole[0].view(b, -1)[i])
 
 
-def test_attention_of_unaligned_matrices_takes_no_longer():
-    """16 heads of 128 x 2048 at a multiple of 8 bytes and at one of 16: the same time but for a half (through registers two to
-    three times as long)."""
+@pytest.mark.parametrize("d", [188, 64])
+def test_attention_rows_beyond_32_bit_offsets(d):
+    """128 rows of q, k and v longer than 2^31 bytes go through registers: the bits of a few heads by themselves."""
+    import torch
+    s, dt = 37, B.torch_elem_dtype()
+    a = 2 * ((1 << 31) // (128 * 3 * 2 * 2 * d) + 1)
+    h = a * d
+    assert 128 * 3 * h * 2 >= 1 << 31
+    g = torch.Generator(device="cuda"); g.manual_seed(d)
+    pick = [0, 1, 77, a // 2, a - 2, a - 1]
+    few = [torch.randn(s, n, len(pick), d, generator=g, device="cuda").to(dt) for n in (3, 1)]
+    many = [torch.ones(s, n, a, d, dtype=dt, device="cuda") for n in (3, 1)]
+    for x, y in zip(many, few):
+        x[:, :, pick] = y
+
+    def run(q, do, a):
+        o, dq = torch.zeros(s, 1, a, d, dtype=dt, device="cuda"), torch.zeros(s, 3, a, d, dtype=dt, device="cuda")
+        lse, ws = (torch.zeros(a, s, device="cuda") for _ in range(2))
+        B.axonn_attention_fwd(1, s, a, d, q, o, lse)
+        B.axonn_attention_bwd(1, s, a, d, q, o, lse, do, dq, ws)
+        return o, lse, dq
+
+    o, lse, dq = run(*few, len(pick))
+    mo, mlse, mdq = run(*many, a)
+    assert torch.equal(mo[:, :, pick], o) and torch.equal(mlse[pick], lse)
+    # more than 128 tiles: where the dQ kernel forms delta (64 columns), its sums are in the other order
+    e = torch.linalg.norm((mdq[:, :, pick].float() - dq.float()).double()) / torch.linalg.norm(dq.double())
+    assert e <= (0 if d == 188 else 2.0 ** (-8 if dt == torch.bfloat16 else -11))
+
+
+@pytest.mark.parametrize("by", [4, 1])
+def test_attention_of_unaligned_matrices_takes_no_longer(by):
+    """16 heads of 128 x 2048 at a multiple of 16 bytes and elsewhere: the same time but for a half (through registers two to three
+    times as long)."""
     import torch
     s, a, d = 2048, 16, 128
     h, dt = a * d, B.torch_elem_dtype()
@@ -613,7 +643,7 @@ def test_attention_of_unaligned_matrices_takes_no_longer():
                 best[i] = min(best[i], ev[0].elapsed_time(ev[1]))
         return best
 
-    aligned, shifted = times(0), times(4)
+    aligned, shifted = times(0), times(by)
     assert shifted[0] < 1.5 * aligned[0] and shifted[1] < 1.5 * aligned[1], (aligned, shifted)
 
 
